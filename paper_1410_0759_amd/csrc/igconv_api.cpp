@@ -28,7 +28,7 @@ constexpr long long kMaxBytes = 1ll << 31;  // byte offsets must stay below this
 
 static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor, &kGroupF32Nopad, &kGroupF32Generic, &kGroupF32Swap,
                                             &kGroupBF16, &kGroupBF16Channels, &kGroupWgrad, &kGroupF64, &kGroupWgradBF16Channels, &kGroupBF16Pointwise, &kGroupF32Teams,
-                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct};
+                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap};
 
 int kernel_count() {
     int n = 0;
@@ -154,6 +154,7 @@ static long long direct_steps_per_wave(const KernelInfo &ki, const ConvKernelPar
 // 64 x 64 x 32 ones (unpadded forward, backward filter by tap: 112 registers) -, three or (tiles up to 64 x 128) four of those with steps
 // of 16.  More workgroups per compute unit cover more of each other's waits: Table-2 layer 3 gained 4 %.
 static int workgroups_per_cu(const KernelInfo &ki) {
+    if (ki.variant == 4) return std::min(2, (160 * 1024) / ki.ldsBytes);
     const bool small_tile = (ki.gmode == 2 || (ki.gmode == 8 && !ki.bf16)) && ki.BM * ki.BN <= 64 * 64 && ki.BK == 32;
     if (is_direct(ki.gmode)) return ki.variant == 1 ? 1 : (160 * 1024) / ki.ldsBytes;   // (64 or 80 KB of LDS each, 64 more with the filter rows staged)
     // (double precision, pipelined: 105 registers for the 64 x 64 tile, 169 for 128 x 64)
@@ -197,6 +198,17 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         const double st = ki.variant == 2 ? (double)((steps + 1) / 2 + 2) : (double)steps;
         return tile_times * st * 1000.0 *
                (2.75 * ki.BM + (ki.gmode == 5 ? 1.0 : 1.5) * ki.BN + ki.BM * ki.BN / 256.0);
+    }
+    if (ki.variant == 4) {
+        // Operands split into bfloat16 parts (igconv_kernel_f32s.hpp).  Per step the moving wavefronts' work - splitting
+        // and gathering, a row's and a column's share - costs more than the MFMAs; measured, in the units of the line
+        // below: 0.66 per row and 18 per column without a border (96x64x64 -> 128, 9x9, 128 images: 64 rows 4.5 ms,
+        // 128 rows 4.0 ms, fp32 instruction 6.1 ms), 0.70 and 25 with the window test (96x27x27 -> 256, 5x5: 775 and
+        // 637 us against 877).  Not offered where compute units would idle - the fp32 kernels' smaller tiles and
+        // teams win there (256x14x14 -> 256, 3x3, 32 images: 72 against 76 us) -, nor for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
+        // 11x11, stride 4: 112 against 117 us at best, slower with other tiles).
+        if (tiles < cus || (!ki.veca && steps < 16)) return 1e300;
+        return tile_times * (double)steps * (double)ki.BN * ki.BK * (ki.gmode == 14 ? 0.70 * ki.BM + 25.0 : 0.66 * ki.BM + 18.0);
     }
     const bool table = ki.gmode == 7 || ki.gmode == 11 || ki.gmode == 13;
     if (is_direct(ki.gmode)) {
@@ -260,6 +272,7 @@ static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool
     const int gmode = ki.gmode;
     if (gmode == 6 || gmode == 8 || gmode == 9 || gmode == 10) return false;  // backward-filter kernels are chosen by that pass itself
     if (gmode == 2) return k.pad_h == 0 && k.pad_w == 0;
+    if (gmode == 14 && ki.variant == 4) return true;
     if (gmode == 14) return k.RS <= 63;   // (one bit of a 64-bit mask per tap, the last one spare)
     if (is_direct(gmode))   // unpadded or at most 31 taps, and every index a wavefront can request has an entry in the offset table
         return (gmode == 16 ? k.RS <= 31 : k.pad_h == 0 && k.pad_w == 0) &&
@@ -304,6 +317,8 @@ static igcStatus choose(const igcContext *h, const Problem &pr, bool w_aligned, 
         const KernelInfo &ki = *kernel_info(id);
         if (ki.bf16 != pr.bf16 || ki.f64 != pr.f64 || (ki.veca && !can_vec) || !gather_mode_ok(ki, k, x_aligned)) continue;
         if (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u)) continue;
+        // (more than 63 taps under a border: the forward pass stays with tap-major order, whose filter copy callers lend room for)
+        if (ki.variant == 4 && ki.gmode == 14 && k.RS > 63 && pr.mode_mask == 0) continue;
         if (pr.no_teams && ((ki.variant == 2 && ki.gmode < 4) || is_direct(ki.gmode))) continue;
         double c = plan_cost(h, ki, k);
         if (ki.swap != want_swap) c *= 1.5;
@@ -353,7 +368,7 @@ static int forward_split(const igcContext *h, const KernelInfo &ki, const ConvKe
                          int *per_out) {
     const long long cus = h->computeUnits;
     *per_out = (k.ksteps + 1) & ~1;
-    if ((ki.gmode > 3 && ki.gmode != 14) || ki.variant == 2 || !packed_y) return 1;
+    if ((ki.gmode > 3 && ki.gmode != 14) || ki.variant == 2 || ki.variant == 4 || !packed_y) return 1;
     const long long tiles = (long long)k.tilesM * k.tilesN;
     const long long smax = std::min<long long>(std::min<long long>(64, k.ksteps / 8), max_parts);
     const double kFixed = 6.0, kSumPass = 12.0;

@@ -32,6 +32,7 @@ struct KernelInfo {
     int variant = 0;  // 1: (gather modes 15, 16) the filter rows staged in LDS;
                       // 2: `threads` / 256 teams of four wavefronts per workgroup, each on its share of the steps;
                       // 3: wavefronts that move tiles beside wavefronts that multiply (gather mode 5)
+                      // 4: float operands split into three bfloat16 parts, moving and multiplying wavefronts
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
     int patchPixels = 512;  // gather mode 5: pixels of the zero-extended image a tile's staged patch can hold
 };
@@ -43,7 +44,7 @@ struct KernelGroup {
 
 // One group per translation unit of kernel instantiations.
 extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGroupF32Generic, kGroupF32Swap, kGroupBF16,
-    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct;
+    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap;
 
 // Adds up `count` partial results (`stride` floats apart) into out = alpha*sum + beta*out;
 // returns the runtime's error code.

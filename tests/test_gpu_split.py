@@ -1,0 +1,85 @@
+"""The kernels that write float operands as sums of three bfloat16 numbers, outside the range where that is exact:
+infinities and NaN, values that round to infinity, values whose parts are bfloat16 denormals.  Inside it the parity tests
+(every kernel of the table, both backward passes) compare them with the oracle like any other kernel."""
+import numpy as np
+import pytest
+
+from oracle import conv_oracle as oc
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+def _planted(a, kind, rng):
+    """`a` with a few elements replaced, or scaled as a whole; the other operand's scale that keeps results in range."""
+    a = a.copy()
+    flat = a.reshape(-1)
+    at = rng.choice(flat.size, size=min(6, flat.size), replace=False)
+    if kind == "inf":
+        flat[at[:3]], flat[at[3:]] = np.inf, -np.inf
+    elif kind == "nan":
+        flat[at] = np.nan
+    elif kind == "huge":      # rounds to infinity in bfloat16, finite in float
+        flat[at] = np.float32(3.4e38)
+        return a, np.float32(2.0 ** -20)
+    elif kind == "tiny":      # the second and third parts are below bfloat16's smallest denormal
+        return a * np.float32(2.0 ** -115), np.float32(1.0)
+    return a, np.float32(1.0)
+
+
+def _same(got, want, kind):
+    """Infinities and NaN where the oracle has them; elsewhere the float bound, relative to the largest finite value."""
+    with np.errstate(over="ignore"):
+        want32 = want.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(want32)), kind
+    inf = np.isinf(want32)
+    assert np.array_equal(got[inf], want32[inf]), kind
+    fin = np.isfinite(want32)
+    big = np.abs(want[fin]).max()
+    # (results near the smallest normal float: one unit of the denormal grid)
+    assert np.abs(got[fin].astype(np.float64) - want[fin]).max() <= 2e-5 * big + 1.5e-45, kind
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny"])
+@pytest.mark.parametrize("swap", [False, True])
+def test_forward_outside_the_split_range(kind, swap):
+    import paper_1410_0759_amd as ig
+    gu = _gpu()
+    rng = np.random.default_rng(7)
+    for kid, name in enumerate(ig.kernel_names()):
+        if "split" not in name or "wgrad" in name or ("swap" in name) != swap:
+            continue
+        pad = (0, 0) if "nopad" in name else (1, 1)
+        C = 48 if "chunk" in name else 20
+        x, w = wl.random_problem(11, 2, C, 11, 13, 70, 3, 3)
+        x, ws = _planted(x, kind, rng)
+        w = w * ws
+        want = oc.conv_forward(x, w, pad=pad, mode=1)
+        print(kind, name, flush=True)
+        got, plan = gu.run(x, w, pad, (1, 1), 1, y_layout="NHWC" if swap else "NCHW", kernel=kid)
+        assert plan.kernelId == kid
+        _same(got, want, (kind, name))
+
+
+@pytest.mark.parametrize("kind", ["plain", "inf", "nan", "huge", "tiny"])
+@pytest.mark.parametrize("prob", [(16, 130, 32, 32, 24, 5, 5, 2), (20, 130, 24, 24, 24, 9, 9, 4)])
+def test_backward_data_outside_the_split_range(kind, prob):
+    """Sizes at which the general route runs on the split kernels (a compute unit's worth of tiles; more than 63 taps too)."""
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad = prob
+    rng = np.random.default_rng(8)
+    P, Q = H + 2 * pad - R + 1, W + 2 * pad - S + 1
+    dy = rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32)
+    w = (rng.standard_normal(size=(K, C, R, S)) * (K * R * S) ** -0.5).astype(np.float32)
+    dy, ws = _planted(dy, kind, rng)
+    w = w * ws
+    want = oc.conv_backward_data(dy, w, (H, W), pad=(pad, pad), mode=0)
+    print(kind, prob, flush=True)
+    _same(gu.run_backward_data(dy, w, (H, W), (pad, pad), (1, 1), 0, workspace="none"), want, kind)
