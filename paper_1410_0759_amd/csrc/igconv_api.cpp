@@ -28,7 +28,7 @@ constexpr long long kMaxBytes = 1ll << 31;  // byte offsets must stay below this
 
 static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor, &kGroupF32Nopad, &kGroupF32Generic, &kGroupF32Swap,
                                             &kGroupBF16, &kGroupBF16Channels, &kGroupWgrad, &kGroupF64, &kGroupWgradBF16Channels, &kGroupBF16Pointwise, &kGroupF32Teams,
-                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap};
+                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap, &kGroupWgradF32Split};
 
 int kernel_count() {
     int n = 0;

@@ -83,3 +83,21 @@ def test_backward_data_outside_the_split_range(kind, prob):
     want = oc.conv_backward_data(dy, w, (H, W), pad=(pad, pad), mode=0)
     print(kind, prob, flush=True)
     _same(gu.run_backward_data(dy, w, (H, W), (pad, pad), (1, 1), 0, workspace="none"), want, kind)
+
+
+@pytest.mark.parametrize("kind", ["plain", "inf", "nan", "huge", "tiny"])
+@pytest.mark.parametrize("prob", [(4, 100, 15, 14, 70, 3, 3, (1, 1), (1, 1)), (3, 70, 9, 17, 130, 5, 2, (2, 0), (2, 1)),
+                                  (2, 33, 8, 8, 33, 1, 1, (0, 0), (1, 1)), (2, 130, 6, 5, 140, 3, 3, (1, 1), (1, 2))])
+def test_backward_filter_outside_the_split_range(kind, prob):
+    """Every tile shape of the split kernels, with and without a cut reduction."""
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(9)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    x = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    dy, xs = _planted(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), kind, rng)
+    x = x * xs
+    want = oc.conv_backward_filter(x, dy, (R, S), pad=pad, stride=stride, mode=1)
+    for workspace in ("full", "none"):
+        print(kind, prob, workspace, flush=True)
+        _same(gu.run_backward_filter(x, dy, (R, S), pad, stride, 1, workspace=workspace)[0], want, kind)
