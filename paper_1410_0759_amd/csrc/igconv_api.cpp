@@ -28,7 +28,7 @@ constexpr long long kMaxBytes = 1ll << 31;  // byte offsets must stay below this
 
 static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor, &kGroupF32Nopad, &kGroupF32Generic, &kGroupF32Swap,
                                             &kGroupBF16, &kGroupBF16Channels, &kGroupWgrad, &kGroupF64, &kGroupWgradBF16Channels, &kGroupBF16Pointwise, &kGroupF32Teams,
-                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap, &kGroupWgradF32Split};
+                                            &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap, &kGroupWgradF32Split, &kGroupF32SplitPatch};
 
 int kernel_count() {
     int n = 0;
@@ -154,7 +154,7 @@ static long long direct_steps_per_wave(const KernelInfo &ki, const ConvKernelPar
 // 64 x 64 x 32 ones (unpadded forward, backward filter by tap: 112 registers) -, three or (tiles up to 64 x 128) four of those with steps
 // of 16.  More workgroups per compute unit cover more of each other's waits: Table-2 layer 3 gained 4 %.
 static int workgroups_per_cu(const KernelInfo &ki) {
-    if (ki.variant == 4) return std::min(2, (160 * 1024) / ki.ldsBytes);
+    if (ki.variant == 4 || ki.variant == 5) return std::min(2, (160 * 1024) / ki.ldsBytes);
     const bool small_tile = (ki.gmode == 2 || (ki.gmode == 8 && !ki.bf16)) && ki.BM * ki.BN <= 64 * 64 && ki.BK == 32;
     if (is_direct(ki.gmode)) return ki.variant == 1 ? 1 : (160 * 1024) / ki.ldsBytes;   // (64 or 80 KB of LDS each, 64 more with the filter rows staged)
     // (double precision, pipelined: 105 registers for the 64 x 64 tile, 169 for 128 x 64)
@@ -198,6 +198,16 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         const double st = ki.variant == 2 ? (double)((steps + 1) / 2 + 2) : (double)steps;
         return tile_times * st * 1000.0 *
                (2.75 * ki.BM + (ki.gmode == 5 ? 1.0 : 1.5) * ki.BN + ki.BM * ki.BN / 256.0);
+    }
+    if (ki.variant == 5) {
+        // The same with a staged patch (igconv_kernel_f32p.hpp), one workgroup per compute unit: bound by power, so that a
+        // partial round costs less than a full one (counted half way between); measured per step, in the units of
+        // the line below: 44 with 64 x 256 tiles, 92 with 128 x 128, 55 with 64 x 128, and 0.7 steps per tile for its epilogue.  Not offered
+        // where more than half of the compute units would idle (the kernels that cut the reduction win: 512x7x7 -> 512 at 4 images
+        // 31 against 79 us).
+        if (tiles * 2 < cus) return 1e300;
+        const double rounds = 0.5 * ((double)((tiles + cus - 1) / cus) + (double)tiles / (double)cus);
+        return rounds * ((double)steps + 0.7) * (double)ki.BN * ki.BK * (ki.BM == 128 ? 92.0 : (ki.BN == 256 ? 44.0 : 55.0));
     }
     if (ki.variant == 4) {
         // Operands split into bfloat16 parts (igconv_kernel_f32s.hpp).  Per step the moving wavefronts' work - splitting
@@ -285,6 +295,12 @@ static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool
         if (gmode == 13) return steps % 2 == 1 && steps >= 3;   // the skipped step: the one that rounds an odd count up
         return gmode == 7 || (steps % 2 == 0 && last <= ki.BK / 2);
     }
+    if (gmode == 3 && ki.variant == 5)
+        // nine contiguous taps per (row, channel), walked forwards or backwards; a tile's pixels fit the patch; the
+        // channel-fastest form reads four channels of a pixel at once
+        return k.RS == 9 && k.C % 16 == 0 && k.pad_h >= 0 && k.pad_w >= 0 && k.Wp == k.W + 2 * k.pad_w &&
+               ((k.wsTapS == 1 && k.wsTapR == k.S) || (k.wsTapS == -1 && k.wsTapR == -k.S)) && (!ki.swap || k.xsC == 1) &&
+               (long long)k.N * (k.H + 2 * k.pad_h) * k.Wp < (1ll << 31) && patch_pixels_bound(k, ki.BN) <= ki.patchPixels;
     if (gmode == 3) return k.RS == 9 && k.C % (ki.BK / 9) == 0;  // whole steps of BK/9 channels (16-byte filter loads: checked apart)
     if (gmode == 12)   // 1x1 filters, whole 16-byte channel vectors in x and in the filter rows
         return x_aligned && k.RS == 1 && k.C % 8 == 0 && k.xsC == 1 && k.xsN % 8 == 0 && k.xsH % 8 == 0 && k.xsW % 8 == 0;
@@ -322,7 +338,7 @@ static igcStatus choose(const igcContext *h, const Problem &pr, bool w_aligned, 
         if (pr.no_teams && ((ki.variant == 2 && ki.gmode < 4) || is_direct(ki.gmode))) continue;
         double c = plan_cost(h, ki, k);
         if (ki.swap != want_swap) c *= 1.5;
-        if (!ki.veca && can_vec && ki.gmode != 1) c *= 1.05;
+        if (!ki.veca && can_vec && ki.gmode != 1 && ki.variant != 5) c *= 1.05;
         if (best < 0 || c < best_cost) {
             best = id;
             best_cost = c;
@@ -368,7 +384,7 @@ static int forward_split(const igcContext *h, const KernelInfo &ki, const ConvKe
                          int *per_out) {
     const long long cus = h->computeUnits;
     *per_out = (k.ksteps + 1) & ~1;
-    if ((ki.gmode > 3 && ki.gmode != 14) || ki.variant == 2 || ki.variant == 4 || !packed_y) return 1;
+    if ((ki.gmode > 3 && ki.gmode != 14) || ki.variant == 2 || ki.variant >= 4 || !packed_y) return 1;
     const long long tiles = (long long)k.tilesM * k.tilesN;
     const long long smax = std::min<long long>(std::min<long long>(64, k.ksteps / 8), max_parts);
     const double kFixed = 6.0, kSumPass = 12.0;
@@ -530,8 +546,12 @@ static bool backward_data_phase(const BackwardDataProblem &b, int ph, int pw, Pr
     k.K = b.C; k.R = Rp; k.S = Sp; k.P = ah.count; k.Q = aw.count;
     k.pad_h = ah.pad; k.pad_w = aw.pad; k.u = 1; k.v = 1; k.flip = 0;
     k.RS = Rp * Sp; k.CRS = b.K * k.RS; k.PQ = ah.count * aw.count; k.NPQ = b.N * k.PQ;
-    k.Wp = 1; k.HpWp = 1;   // (patch staging is never used here)
-    magic_for(1, &k.mWp); magic_for(1, &k.mHpWp);
+    k.Wp = 1; k.HpWp = 1;
+    if (k.pad_h >= 0 && k.pad_w >= 0) {   // (patch staging: the zero-extended image of dy; never offered with a border cut off)
+        k.Wp = k.W + 2 * k.pad_w;
+        k.HpWp = (int)std::min<long long>((long long)(k.H + 2 * k.pad_h) * k.Wp, 0x7fffffff);
+    }
+    magic_for((uint32_t)k.Wp, &k.mWp); magic_for((uint32_t)k.HpWp, &k.mHpWp);
     magic_for((uint32_t)k.PQ, &k.mPQ); magic_for((uint32_t)k.Q, &k.mQ);
     magic_for((uint32_t)k.RS, &k.mRS); magic_for((uint32_t)k.S, &k.mS);
     k.wsRow = b.R * b.S; k.wsRed = b.C * b.R * b.S;

@@ -33,8 +33,9 @@ struct KernelInfo {
                       // 2: `threads` / 256 teams of four wavefronts per workgroup, each on its share of the steps;
                       // 3: wavefronts that move tiles beside wavefronts that multiply (gather mode 5)
                       // 4: float operands split into three bfloat16 parts, moving and multiplying wavefronts
+                      // 5: the same for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
-    int patchPixels = 512;  // gather mode 5: pixels of the zero-extended image a tile's staged patch can hold
+    int patchPixels = 512;  // gather mode 5, variant 5: pixels of the zero-extended image a tile's staged patch can hold
 };
 
 struct KernelGroup {
@@ -44,7 +45,7 @@ struct KernelGroup {
 
 // One group per translation unit of kernel instantiations.
 extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGroupF32Generic, kGroupF32Swap, kGroupBF16,
-    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split;
+    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch;
 
 // Adds up `count` partial results (`stride` floats apart) into out = alpha*sum + beta*out;
 // returns the runtime's error code.

@@ -57,10 +57,9 @@ def test_forward_outside_the_split_range(kind, swap):
         if "split" not in name or "wgrad" in name or ("swap" in name) != swap:
             continue
         pad = (0, 0) if "nopad" in name else (1, 1)
-        C = 48 if "chunk" in name else 20
-        x, w = wl.random_problem(11, 2, C, 11, 13, 70, 3, 3)
+        x, w = wl.random_problem(11, 2, 48 if "patch" in name else 20, 11, 13, 70, 3, 3)
         x, ws = _planted(x, kind, rng)
-        w = w * ws
+        x, w = wl.with_layout(x, "NHWC" if swap else "NCHW"), w * ws
         want = oc.conv_forward(x, w, pad=pad, mode=1)
         print(kind, name, flush=True)
         got, plan = gu.run(x, w, pad, (1, 1), 1, y_layout="NHWC" if swap else "NCHW", kernel=kid)
@@ -101,3 +100,23 @@ def test_backward_filter_outside_the_split_range(kind, prob):
     for workspace in ("full", "none"):
         print(kind, prob, workspace, flush=True)
         _same(gu.run_backward_filter(x, dy, (R, S), pad, stride, 1, workspace=workspace)[0], want, kind)
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("prob", [(40, 96, 14, 13, 32, 3, 3, (1, 1)), (20, 70, 28, 28, 16, 3, 3, (2, 1)), (24, 130, 12, 16, 48, 1, 9, (0, 3)),
+                                  (9, 64, 40, 40, 80, 3, 3, (0, 2))])
+def test_backward_data_from_a_staged_patch(prob, layout):
+    """Unit stride and nine taps at sizes where backward data runs from a staged patch of dy: both filter orders, ragged
+    tiles, one to five chunks of channels, borders on either side."""
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad = prob
+    rng = np.random.default_rng(10)
+    P, Q = H + 2 * pad[0] - R + 1, W + 2 * pad[1] - S + 1
+    dy = wl.with_layout(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), layout)
+    w = (rng.standard_normal(size=(K, C, R, S)) * (K * R * S) ** -0.5).astype(np.float32)
+    dx0 = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    for mode, alpha, beta in ((0, 1.0, 0.0), (1, 0.5, -1.5)):
+        print(prob, layout, mode, flush=True)
+        want = oc.conv_backward_data(dy, w, (H, W), pad=pad, mode=mode, alpha=alpha, beta=beta, dx_old=dx0 if beta else None)
+        got = gu.run_backward_data(dy, w, (H, W), pad, (1, 1), mode, alpha, beta, dx0 if beta else None, "f32", layout)
+        _same(got, want, (prob, layout, mode))
