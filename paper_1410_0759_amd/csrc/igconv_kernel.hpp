@@ -101,6 +101,31 @@ __device__ __forceinline__ void load_bias(const ConvKernelParams &p, int krow0, 
                                      : 0.f;
 }
 
+// The epilogue's activations.  e = exp(-|x|) lies in [0, 1], so the denominator 1 + e in [1, 2]: the hardware's reciprocal and
+// one Newton step give the division without the scaling that operands at the ends of the range need (the compiler's
+// division: ten instructions per element of every tile, while the matrix pipes wait: bias and tanh
+// added 80 us to 128x64x56x56 -> 64, now 18).
+// Infinities give the limits, NaN stays.
+__device__ __forceinline__ float reciprocal_1_2(float d) {
+    const float r = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
+}
+template <int ACT>
+__device__ __forceinline__ float activate(float x) {
+    if constexpr (ACT == 0) {                                        // sigmoid
+        const float e = __expf(-__builtin_fabsf(x)), r = reciprocal_1_2(1.f + e);
+        return x < 0.f ? e * r : r;
+    } else if constexpr (ACT == 1) {                                 // rectified linear
+        return fmaxf(x, 0.f);
+    } else {                                                         // tanh
+        const float e = __expf(-2.f * __builtin_fabsf(x));
+        return __builtin_copysignf((1.f - e) * reciprocal_1_2(1.f + e), x);
+    }
+}
+__device__ __forceinline__ float activate(int act, float x) {
+    return act == 0 ? activate<0>(x) : (act == 1 ? activate<1>(x) : (act == 2 ? activate<2>(x) : x));
+}
+
 template <bool SWAP, int MB, int NB, bool LINEAR = false>
 __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_buffer_rsrc_t ybuf,
                                            f32x16 (&acc)[MB][NB], const float (&bvec)[MB], int krow0, int col0, int half,
@@ -126,19 +151,43 @@ __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_b
         const uint32_t qq = rem - pp * (uint32_t)p.Q;
         return n * (uint32_t)p.ysN + pp * (uint32_t)p.ysP + qq * (uint32_t)p.ysQ;
     };
-    auto emit = [&](float a, uint32_t voff, uint32_t soff, float b) {
-        float out = p.alpha * a;
-        if (use_beta) {
-            const float old = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ybuf, voff, soff, 0));
-            out += p.beta * old;
-        }
-        if (fused) {
-            out += b;
-            if (p.act == 0) out = 1.f / (1.f + __expf(-out));                   // sigmoid
-            else if (p.act == 1) out = fmaxf(out, 0.f);                         // rectified linear
-            else if (p.act == 2) out = 1.f - 2.f / (__expf(2.f * out) + 1.f);   // tanh
-        }
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out), ybuf, voff, soff, 0);
+    // Half a 32x32 block at a time: every step over its 8 registers before the next one, so that the uniform questions (old
+    // values? bias? which activation?) are asked once per half block and old values are requested together.  (Asked per
+    // element, every old value was waited for by itself: accumulating onto y added 40 us to
+    // 128x64x56x56 -> 64, now 17; see also `activate`.  Sixteen at a time: more registers, fewer wavefronts per SIMD in the kernels with small tiles.)
+    auto block = [&](const f32x16 &a, auto voff, auto soff, auto bias) __attribute__((always_inline)) {
+        static_for<2>([&](auto hc) __attribute__((always_inline)) {
+            constexpr int h = decltype(hc)::value * 8;
+            float out[8];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) out[v] = p.alpha * a[h + v];
+            if (use_beta) {
+                float old[8];
+#pragma unroll
+                for (int v = 0; v < 8; ++v)
+                    old[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ybuf, voff(h + v), soff(h + v), 0));
+#pragma unroll
+                for (int v = 0; v < 8; ++v) out[v] += p.beta * old[v];
+            }
+            if (fused) {
+#pragma unroll
+                for (int v = 0; v < 8; ++v) out[v] += bias(h + v);
+                if (p.act == 0) {
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) out[v] = activate<0>(out[v]);
+                } else if (p.act == 1) {
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) out[v] = activate<1>(out[v]);
+                } else if (p.act == 2) {
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) out[v] = activate<2>(out[v]);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out[v]), ybuf, voff(h + v), soff(h + v), 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
     if constexpr (!SWAP) {
         const bool full = krow0 + MB * 32 <= p.K && col0 + NB * 32 <= p.NPQ;  // wavefront-uniform
@@ -152,17 +201,18 @@ __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_b
                 const uint32_t vo = (poff + (uint32_t)(4 * half) * (uint32_t)p.ysK) * 4u;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        emit(acc[mb][nb][v], vo, (uint32_t)(krow0 + mb * 32 + 8 * (v / 4) + (v % 4)) * (uint32_t)p.ysK * 4u, row_bias(mb, v));
+                    block(acc[mb][nb], [&](int) { return vo; },
+                          [&](int v) { return (uint32_t)(krow0 + mb * 32 + 8 * (v / 4) + (v % 4)) * (uint32_t)p.ysK * 4u; },
+                          [&](int v) { return row_bias(mb, v); });
             } else {
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int k = krow0 + mb * 32 + 8 * (v / 4) + 4 * half + (v % 4);
-                        emit(acc[mb][nb][v], pv && k < p.K ? (poff + (uint32_t)k * (uint32_t)p.ysK) * 4u : kOutOfRange, 0u, row_bias(mb, v));
-                    }
+                    block(acc[mb][nb],
+                          [&](int v) {
+                              const int k = krow0 + mb * 32 + 8 * (v / 4) + 4 * half + (v % 4);
+                              return pv && k < p.K ? (poff + (uint32_t)k * (uint32_t)p.ysK) * 4u : kOutOfRange;
+                          },
+                          [&](int) { return 0u; }, [&](int v) { return row_bias(mb, v); });
             }
         }
     } else {
@@ -180,12 +230,13 @@ __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_b
                 const int k = krow0 + mb * 32 + l32;
                 const bool kv = k < p.K;
                 const uint32_t koff = (uint32_t)k * (uint32_t)p.ysK * 4u;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int r0 = 8 * (v / 4) + (v % 4);
-                    const uint32_t d0 = __builtin_amdgcn_readlane(pd, r0), d1 = __builtin_amdgcn_readlane(pd, r0 + 4);
-                    emit(acc[mb][nb][v], kv ? koff + (half ? d1 : d0) : kOutOfRange, 0u, bvec[mb]);
-                }
+                block(acc[mb][nb],
+                      [&](int v) {
+                          const int r0 = 8 * (v / 4) + (v % 4);
+                          const uint32_t d0 = __builtin_amdgcn_readlane(pd, r0), d1 = __builtin_amdgcn_readlane(pd, r0 + 4);
+                          return kv ? koff + (half ? d1 : d0) : kOutOfRange;
+                      },
+                      [&](int) { return 0u; }, [&](int) { return bvec[mb]; });
             }
         }
     }
@@ -291,9 +342,9 @@ struct KernelConfig {
     static constexpr int TEAM_LDS_BYTES = 2 * (A_ELEMS + B_ELEMS) * ESIZE;
     static constexpr int LDS_BYTES = TEAMS_ * TEAM_LDS_BYTES + TABLE_BYTES;
     // Waves per SIMD the registers must allow: steps of 16 leave room (LDS, registers) for three workgroups per
-    // compute unit; where LDS lets two share it the registers must too - left alone, the kernels with the
+    // compute unit, four with tiles up to 64 x 128; where LDS lets two share it the registers must too - left alone, the kernels with the
     // largest tiles take more than half of a SIMD's 512 and run one wave per SIMD.
-    static constexpr int MIN_WAVES = TEAMS_ > 1 ? TEAMS_ : (BK_ == 16 ? 3 : (LDS_BYTES <= 80 * 1024 ? 2 : 1));
+    static constexpr int MIN_WAVES = TEAMS_ > 1 ? TEAMS_ : (BK_ == 16 ? (BM_ * BN_ <= 64 * 128 ? 4 : 3) : (LDS_BYTES <= 80 * 1024 ? 2 : 1));
     static constexpr int TM = BM / WM, TN = BN / WN; // per-wave output block
     static constexpr int MB = TM / 32, NB = TN / 32; // 32x32 MFMA blocks per wave
     static constexpr int CG = BN / 64;               // column groups of 64 lanes

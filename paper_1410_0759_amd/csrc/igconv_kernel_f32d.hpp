@@ -294,9 +294,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void igconv_f32d_kernel(const ConvKer
         if (p.beta != 0.f) out += p.beta * __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ybuf, off, 0, 0));
         if (fused) {
             if (p.bias != nullptr) out += p.bias[orow];
-            if (p.act == 0) out = 1.f / (1.f + __expf(-out));                   // sigmoid
-            else if (p.act == 1) out = fmaxf(out, 0.f);                         // rectified linear
-            else if (p.act == 2) out = 1.f - 2.f / (__expf(2.f * out) + 1.f);   // tanh
+            out = activate(p.act, out);
         }
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out), ybuf, off, 0, 0);
     }
