@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <algorithm>
+#include <cmath>
 #include <vector>
 #include <new>
 
@@ -30,15 +31,28 @@ static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor
                                             &kGroupBF16, &kGroupBF16Channels, &kGroupWgrad, &kGroupF64, &kGroupWgradBF16Channels, &kGroupBF16Pointwise, &kGroupF32Teams,
                                             &kGroupF32Masked, &kGroupF64Masked, &kGroupF32Direct, &kGroupF32SplitNopad, &kGroupF32SplitBorder, &kGroupF32SplitSwap, &kGroupWgradF32Split, &kGroupF32SplitPatch};
 
+// Kernels that only run on a filter the library has rewritten into a workspace: numbered after the others, so that they
+// cannot be named in igcSetKernelOverride.
+static const KernelGroup *const kInnerGroups[] = {&kGroupBF16Taps};
+
 int kernel_count() {
     int n = 0;
     for (const KernelGroup *g : kGroups) n += g->count;
+    return n;
+}
+static int kernel_count_all() {
+    int n = kernel_count();
+    for (const KernelGroup *g : kInnerGroups) n += g->count;
     return n;
 }
 
 const KernelInfo *kernel_info(int id) {
     if (id < 0) return nullptr;
     for (const KernelGroup *g : kGroups) {
+        if (id < g->count) return &g->kernels[id];
+        id -= g->count;
+    }
+    for (const KernelGroup *g : kInnerGroups) {
         if (id < g->count) return &g->kernels[id];
         id -= g->count;
     }
@@ -59,6 +73,7 @@ struct Problem {
     int vec;  // elements per 16 bytes of input
     unsigned mode_mask = 0;   // non-zero: bit g set when gather mode g can run this problem
     bool zero_steps = false;  // nothing to accumulate: the kernel only scales the old output
+    bool filter_inner = false;   // the filter will be read from a copy with the reduction's channel index innermost
     bool no_teams = false;    // leave the kernels that cut the reduction inside a workgroup (teams, gather mode 15) out of the
                               // choice: a workspace cuts it across compute units, which measured faster where both apply
 };
@@ -199,6 +214,8 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         return tile_times * st * 1000.0 *
                (2.75 * ki.BM + (ki.gmode == 5 ? 1.0 : 1.5) * ki.BN + ki.BM * ki.BN / 256.0);
     }
+    // (any filter over channel vectors: as the 1x1 kernel, a step of two units of 32 channels)
+    if (ki.variant == 6) return tile_times * (steps + 2.0) * 500.0 * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0);
     if (ki.variant == 5) {
         // The same with a staged patch (igconv_kernel_f32p.hpp), one workgroup per compute unit: bound by power, so that a
         // partial round costs less than a full one (counted half way between); measured per step, in the units of
@@ -282,6 +299,8 @@ static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool
     const int gmode = ki.gmode;
     if (gmode == 6 || gmode == 8 || gmode == 9 || gmode == 10) return false;  // backward-filter kernels are chosen by that pass itself
     if (gmode == 2) return k.pad_h == 0 && k.pad_w == 0;
+    if (gmode == 1 && ki.variant == 6)   // whole 16-byte channel vectors in x (the filter's copy has them by construction)
+        return x_aligned && k.C % 8 == 0 && k.xsC == 1 && k.xsN % 8 == 0 && k.xsH % 8 == 0 && k.xsW % 8 == 0;
     if (gmode == 14 && ki.variant == 4) return true;
     if (gmode == 14) return k.RS <= 63;   // (one bit of a 64-bit mask per tap, the last one spare)
     if (is_direct(gmode))   // unpadded or at most 31 taps, and every index a wavefront can request has an entry in the offset table
@@ -329,7 +348,8 @@ static igcStatus choose(const igcContext *h, const Problem &pr, bool w_aligned, 
     }
     int best = -1;
     double best_cost = 0;
-    for (int id = 0; id < kernel_count(); ++id) {
+    const int offered = pr.filter_inner ? kernel_count_all() : kernel_count();
+    for (int id = 0; id < offered; ++id) {
         const KernelInfo &ki = *kernel_info(id);
         if (ki.bf16 != pr.bf16 || ki.f64 != pr.f64 || (ki.veca && !can_vec) || !gather_mode_ok(ki, k, x_aligned)) continue;
         if (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u)) continue;
@@ -755,13 +775,17 @@ struct PhaseLaunch {
     long long dx_offset;   // elements of dx before the phase's first one
 };
 
-static igcStatus plan_backward_data_phases(const igcContext *handle, const BackwardDataProblem &b, std::vector<PhaseLaunch> *out) {
+// filter_inner: the filter will be read from its rewritten copy; dy_aligned: dy starts on a 16-byte boundary.
+static igcStatus plan_backward_data_phases(const igcContext *handle, const BackwardDataProblem &b, std::vector<PhaseLaunch> *out,
+                                           bool filter_inner = false, bool dy_aligned = false) {
     for (int ph = 0; ph < b.u; ++ph)
         for (int pw = 0; pw < b.v; ++pw) {
             PhaseLaunch l;
             l.dx_offset = 0;
             if (!backward_data_phase(b, ph, pw, &l.pr, &l.dx_offset)) continue;
-            igcStatus st = choose(handle, l.pr, /*w_aligned=*/false, /*x_aligned=*/false, &l.id);
+            l.pr.filter_inner = filter_inner;
+            if (filter_inner) l.pr.mode_mask = 1u << 1;
+            igcStatus st = choose(handle, l.pr, /*w_aligned=*/false, /*x_aligned=*/dy_aligned, &l.id);
             if (st != IGC_STATUS_SUCCESS) return st;
             igcConvolutionForwardPlan plan;
             st = fill_plan(handle, l.id, &l.pr, &plan);
@@ -1291,6 +1315,17 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     // instead of R*S apart (a 5x5 layer with 96 channels: 74 -> 129 TFLOP/s).  Same sums in the same order.
     if (splits <= 1 && kernel_info(id)->gmode == 1 && !pr.f64 && pr.kp.RS > 1 && workSpace &&
         (uintptr_t)workSpace % 16 == 0 && workSpaceSizeInBytes >= (size_t)pr.kp.w_bytes) {
+        // (bfloat16 with contiguous channels: the kernel that reads channel vectors of both operands)
+        Problem inner = pr;
+        int inner_id = -1;
+        inner.filter_inner = true;
+        inner.mode_mask = 1u << 1;
+        if (pr.bf16 && handle->kernelOverride < 0 && choose(handle, inner, true, ((uintptr_t)x % 16) == 0, &inner_id) == IGC_STATUS_SUCCESS &&
+            fill_plan(handle, inner_id, &inner, &plan) == IGC_STATUS_SUCCESS) {
+            pr = inner;
+            id = inner_id;
+            grid = plan.gridX;
+        }
         ConvKernelParams &k = pr.kp;
         Magic mC, mRS;
         if (magic_for((uint32_t)k.C, &mC) && magic_for((uint32_t)k.RS, &mRS)) {
@@ -1403,6 +1438,14 @@ per_phase:
     std::vector<PhaseLaunch> launches;
     st = plan_backward_data_phases(handle, b, &launches);
     if (st != IGC_STATUS_SUCCESS) return st;
+    // Float or bfloat16 phases that all run in tap-major order, and room for the filter: it is first rewritten as wt[c][t][k]
+    // (below); bfloat16 phases may then run on the kernel that reads channel vectors of both operands.
+    const bool rewrite = phases_want_filter_workspace(b, launches) && workSpace && (uintptr_t)workSpace % 16 == 0 &&
+                         workSpaceSizeInBytes >= (size_t)b.w_bytes;
+    if (rewrite && b.bf16) {
+        std::vector<PhaseLaunch> inner;
+        if (plan_backward_data_phases(handle, b, &inner, true, (uintptr_t)dy % 16 == 0) == IGC_STATUS_SUCCESS) launches.swap(inner);
+    }
     for (PhaseLaunch &l : launches) {
         l.pr.kp.x = dy;
         l.pr.kp.w = w;
@@ -1416,10 +1459,9 @@ per_phase:
             l.pr.kp.beta = *static_cast<const float *>(beta);
         }
     }
-    // Float phases that all run in tap-major order, and room for the filter: it is first rewritten as wt[c][t][k]
-    // (reduction index innermost) and read through those strides - a step's filter elements are then contiguous
-    // instead of C*R*S apart.  Same sums in the same order as without.
-    if (phases_want_filter_workspace(b, launches) && workSpace && (uintptr_t)workSpace % 16 == 0 && workSpaceSizeInBytes >= (size_t)b.w_bytes) {
+    // The rewritten filter (reduction index innermost) is read through its strides - a step's filter elements are then
+    // contiguous instead of C*R*S apart.  Same sums in the same order as without.
+    if (rewrite) {
         Magic mK, mRS;
         if (magic_for((uint32_t)b.K, &mK) && magic_for((uint32_t)(b.R * b.S), &mRS)) {
             if (launch_filter_taps_outer(w, workSpace, b.bf16 ? 2 : 4, b.K, b.C, b.R * b.S, true, mK, mRS, handle->stream) != 0)
@@ -1433,8 +1475,12 @@ per_phase:
             }
         }
     }
-    for (const PhaseLaunch &l : launches)
+    for (const PhaseLaunch &l : launches) {
+        // a phase that meets no tap would write dx = alpha * 0 + 1 * dx
+        if (l.pr.zero_steps && (b.f64 ? l.pr.kp.beta64 == 1.0 && std::isfinite(l.pr.kp.alpha64) : l.pr.kp.beta == 1.f && std::isfinite(l.pr.kp.alpha)))
+            continue;
         if (kernel_info(l.id)->launch(l.pr.kp, l.grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
+    }
     return IGC_STATUS_SUCCESS;
 }
 

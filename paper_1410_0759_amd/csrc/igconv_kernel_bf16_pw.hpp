@@ -33,7 +33,7 @@ struct Bf16PwConfig {
 };
 
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS) void igconv_fwd_bf16_pw_kernel(const ConvKernelParams p) {
+__global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_fwd_bf16_pw_kernel(const ConvKernelParams p) {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK;
     constexpr int MB = BM / 64, NB = BN / 64;
     constexpr int RB = kPwRowBytes;

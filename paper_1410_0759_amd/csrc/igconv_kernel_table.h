@@ -33,7 +33,8 @@ struct KernelInfo {
                       // 2: `threads` / 256 teams of four wavefronts per workgroup, each on its share of the steps;
                       // 3: wavefronts that move tiles beside wavefronts that multiply (gather mode 5)
                       // 4: float operands split into three bfloat16 parts, moving and multiplying wavefronts
-                      // 5: the same for nine taps, the gathered side from a staged image patch (gather mode 3)
+                      // 6: channel vectors of a filter rewritten with the channel index innermost (gather mode 1, bf16)
+                      // 5: the same as 4 for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
     int patchPixels = 512;  // gather mode 5, variant 5: pixels of the zero-extended image a tile's staged patch can hold
 };
@@ -45,7 +46,7 @@ struct KernelGroup {
 
 // One group per translation unit of kernel instantiations.
 extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGroupF32Generic, kGroupF32Swap, kGroupBF16,
-    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch;
+    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch, kGroupBF16Taps;
 
 // Adds up `count` partial results (`stride` floats apart) into out = alpha*sum + beta*out;
 // returns the runtime's error code.
@@ -84,7 +85,7 @@ int launch_sum_parts_f64(const double *parts, double *out, uint32_t n, int count
 // Compute units of the current device, 0 when the runtime finds none (igconv_probe.hip).
 int query_compute_units();
 
-int kernel_count();
+int kernel_count();   // (of those a caller may name)
 const KernelInfo *kernel_info(int id);  // nullptr when out of range
 
 }  // namespace igc

@@ -1,0 +1,30 @@
+// bf16 kernels for any filter over channel-contiguous tensors, reading a filter rewritten with the channel index
+// innermost (igconv_kernel_bf16_taps.hpp).
+#include "igconv_instantiate.hpp"
+#include "igconv_kernel_bf16_taps.hpp"
+
+namespace igc {
+
+template <class Cfg>
+static int launch_taps(const ConvKernelParams &p, int grid, void *stream) {
+    return launch_checked(&igconv_bf16_taps_kernel<Cfg>, "igconv_bf16_taps_kernel", p, grid, Cfg::THREADS, stream);
+}
+
+#define IGC_TAPS_LIST(X)                                        \
+    X("bf16 128x128x32 tapmajor vectors", 128, 128, false)      \
+    X("bf16 64x128x32 tapmajor vectors", 64, 128, false)        \
+    X("bf16 128x128x32 tapmajor vectors swap", 128, 128, true)  \
+    X("bf16 64x128x32 tapmajor vectors swap", 64, 128, true)
+
+#define IGC_TAPS_INSTANTIATE(NAME, BM, BN, SWAP) \
+    template __global__ void igconv_bf16_taps_kernel<Bf16TapsConfig<BM, BN, SWAP>>(const ConvKernelParams);
+IGC_TAPS_LIST(IGC_TAPS_INSTANTIATE)
+
+#if !defined(__HIP_DEVICE_COMPILE__)
+#define IGC_TAPS_ROW(NAME, BM, BN, SWAP) \
+    {NAME, true, BM, BN, 32, SWAP, false, 1, Bf16TapsConfig<BM, BN, SWAP>::THREADS, Bf16TapsConfig<BM, BN, SWAP>::LDS_BYTES, &launch_taps<Bf16TapsConfig<BM, BN, SWAP>>, 6},
+static const KernelInfo kRows[] = {IGC_TAPS_LIST(IGC_TAPS_ROW)};
+const KernelGroup kGroupBF16Taps = {kRows, sizeof(kRows) / sizeof(kRows[0])};
+#endif
+
+}  // namespace igc

@@ -1,0 +1,76 @@
+"""The bf16 kernels that read channel vectors of both operands, the filter rewritten with the channel index innermost:
+same bits as the element-wise kernels that read the filter in place (no workspace), both against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import conv_oracle as oc
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+def _rnd(rng, shape, scale=1.0):
+    return wl.round_to_bf16((rng.uniform(-1, 1, size=shape) * scale).astype(np.float32))
+
+
+@pytest.mark.parametrize("layout", ["NHWC", "NCHW"])     # of dx; dy has its channels innermost
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, S, pad, stride
+    (3, 70, 15, 18, 40, 3, 3, (1, 1), (2, 2)),        # phases of four, two, two and one taps, a ragged last unit of channels
+    (2, 130, 9, 10, 64, 1, 1, (0, 0), (2, 2)),        # phases without taps
+    (2, 33, 14, 13, 8, 5, 5, (2, 2), (1, 1)),         # one unit per tap, most of it past the channels
+    (1, 64, 12, 9, 136, 7, 2, (3, 0), (3, 1)),
+    (2, 64, 8, 8, 72, 5, 3, (4, 2), (1, 1)),          # "full" border
+])
+def test_backward_data(prob, layout):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(3)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    dy = wl.with_layout(_rnd(rng, (N, K, P, Q)), "NHWC")
+    w = _rnd(rng, (K, C, R, S), (K * R * S) ** -0.5)
+    dx0 = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    for mode, alpha, beta in ((0, 1.0, 0.0), (1, 0.5, -1.5), (0, 1.0, 1.0)):
+        print(prob, layout, mode, beta, flush=True)
+        old = dx0 if beta else None
+        want = oc.conv_backward_data(dy, w, (H, W), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dx_old=old)
+        got = gu.run_backward_data(dy, w, (H, W), pad, stride, mode, alpha, beta, old, "bf16", layout)
+        assert gu.rel_err(got, want) <= gu.BOUND["bf16"]
+        assert np.array_equal(got, gu.run_backward_data(dy, w, (H, W), pad, stride, mode, alpha, beta, old, "bf16", layout, workspace="none"))
+
+
+@pytest.mark.parametrize("layout", ["NHWC", "NCHW"])     # of y
+@pytest.mark.parametrize("prob", [
+    (16, 72, 20, 20, 150, 5, 5, (2, 2), (1, 1)),
+    (64, 64, 21, 19, 70, 7, 3, (3, 1), (2, 1)),
+])
+def test_forward(prob, layout):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(4)
+    x, w = wl.with_layout(_rnd(rng, (N, C, H, W)), "NHWC"), _rnd(rng, (K, C, R, S), (C * R * S) ** -0.5)
+    for mode in (0, 1):
+        want = oc.conv_forward(x, w, pad=pad, stride=stride, mode=mode)
+        g = gu.GpuConv(x, w, pad, stride, mode, dtype="bf16", y_layout=layout)
+        assert g.plan().gatherMode == 1
+        g.prefill(value=float("nan"))
+        g.launch(1.0, 0.0)
+        plain = g.result()
+        assert g.lend_workspace() == w.size * 2
+        print(prob, layout, mode, flush=True)
+        g.prefill(value=float("nan"))
+        g.launch(1.0, 0.0)
+        got = g.result()
+        g.ws.result()
+        assert gu.rel_err(got, want) <= gu.BOUND["bf16"] and np.array_equal(got, plain)
+        bias = rng.uniform(-1, 1, size=K).astype(np.float32)
+        g.prefill(value=float("nan"))
+        g.launch_fused(1.0, 0.0, bias, 1)
+        assert gu.rel_err(g.result(), np.maximum(want + bias[None, :, None, None], 0.0)) <= gu.BOUND["bf16"]
