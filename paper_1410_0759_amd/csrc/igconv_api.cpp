@@ -3,6 +3,7 @@
 // machine without a GPU.  See include/igconv.h for the contract of each entry point.
 #include "../../include/igconv.h"
 
+#include <limits.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -773,7 +774,53 @@ struct PhaseLaunch {
     Problem pr;
     int id, grid;
     long long dx_offset;   // elements of dx before the phase's first one
+    bool joint = false;    // runs in one launch with the others so marked (all of one kernel)
 };
+
+// One kernel for all phases that meet a tap, to run in one launch: -1 when there are not two to kMaxPhases of them or no kernel
+// with such a launch accepts them all.  One phase alone is short and often leaves most of the chip idle; together they
+// share it, the longest first so that the short ones fill the end, and the float ones can use the split kernels whose
+// tiles are too large for a phase alone.  Measured, separate and joint launches (us), no size found where separate ones are ahead:
+// float, 77x15x16 -> 101x29x31, 37 images 65 and 25; 512 -> 256x28x28, 32 images 257 and 156; 256 -> 128x28x28, one image
+// 78 and 43; 128 -> 64x112x112, 128 images 816 and 701; 24 -> 40x13x13, one image 28 and 9; bfloat16, 256 -> 128x56x56, 32
+// images 53 and 34; 1 image 128x28x28 36 and 15 (all 3x3 with stride 2).
+static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &launches, bool dy_aligned) {
+    long long live = 0;
+    for (const PhaseLaunch &l : launches) live += l.pr.zero_steps ? 0 : 1;
+    if (live < 2 || live > kMaxPhases) return -1;
+    int best = -1;
+    double best_cost = 0;
+    for (int id = 0; id < kernel_count_all(); ++id) {
+        const KernelInfo &ki = *kernel_info(id);
+        if (!ki.launchPhases || ki.veca) continue;
+        double work = 0, longest = 0;
+        long long tiles = 0;
+        bool ok = true;
+        for (const PhaseLaunch &l : launches) {
+            const ConvKernelParams &k = l.pr.kp;
+            if (l.pr.zero_steps) continue;
+            const bool want_swap = k.ysK == 1 && k.K > 1 && !(k.ysQ == 1 && k.Q > 1);
+            if (ki.bf16 != l.pr.bf16 || l.pr.f64 || (ki.variant == 6) != l.pr.filter_inner || ki.swap != want_swap || !gather_mode_ok(ki, k, dy_aligned)) {
+                ok = false;
+                break;
+            }
+            const long long t = (long long)((k.K + ki.BM - 1) / ki.BM) * ((k.NPQ + ki.BN - 1) / ki.BN);
+            const double steps = (double)kernel_steps(ki, k) + 2.0;
+            const double c = ki.variant == 6 ? steps * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0)
+                                             : steps * (0.70 * ki.BM + 25.0);
+            tiles += t;
+            work += (double)t * c;
+            longest = std::max(longest, c);
+        }
+        if (!ok) continue;
+        const double cost = work / (double)h->computeUnits + 0.5 * longest;
+        if (best < 0 || cost < best_cost) {
+            best = id;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
 
 // filter_inner: the filter will be read from its rewritten copy; dy_aligned: dy starts on a 16-byte boundary.
 static igcStatus plan_backward_data_phases(const igcContext *handle, const BackwardDataProblem &b, std::vector<PhaseLaunch> *out,
@@ -793,6 +840,19 @@ static igcStatus plan_backward_data_phases(const igcContext *handle, const Backw
             l.grid = plan.gridX;
             out->push_back(l);
         }
+    const int joint = joint_kernel(handle, *out, dy_aligned);
+    if (joint < 0) return IGC_STATUS_SUCCESS;
+    std::vector<PhaseLaunch> all = *out;
+    for (PhaseLaunch &l : all) {
+        if (l.pr.zero_steps) continue;
+        igcConvolutionForwardPlan plan;
+        if (fill_plan(handle, joint, &l.pr, &plan) != IGC_STATUS_SUCCESS) return IGC_STATUS_SUCCESS;
+        l.id = joint;
+        l.grid = plan.gridX;
+        l.joint = true;
+    }
+    std::stable_sort(all.begin(), all.end(), [](const PhaseLaunch &x, const PhaseLaunch &y) { return x.pr.kp.ksteps > y.pr.kp.ksteps; });
+    out->swap(all);
     return IGC_STATUS_SUCCESS;
 }
 
@@ -1475,7 +1535,21 @@ per_phase:
             }
         }
     }
+    ConvPhaseParams joint{};
+    int joined = 0, joint_grid = 0;
+    for (int &first : joint.start) first = INT_MAX;
+    for (const PhaseLaunch &l : launches)
+        if (l.joint) {
+            joint.p[joined] = l.pr.kp;
+            joint.start[joined++] = joint_grid;
+            joint_grid += l.grid;
+        }
     for (const PhaseLaunch &l : launches) {
+        if (l.joint) {
+            if (joint_grid != 0 && kernel_info(l.id)->launchPhases(joint, joint_grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
+            joint_grid = 0;   // (once)
+            continue;
+        }
         // a phase that meets no tap would write dx = alpha * 0 + 1 * dx
         if (l.pr.zero_steps && (b.f64 ? l.pr.kp.beta64 == 1.0 && std::isfinite(l.pr.kp.alpha64) : l.pr.kp.beta == 1.f && std::isfinite(l.pr.kp.alpha)))
             continue;

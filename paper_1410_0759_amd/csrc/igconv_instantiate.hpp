@@ -17,9 +17,9 @@ namespace igc {
 // launch call's own return value, not the thread's last-error state, which other users of
 // the runtime in the same thread may have left set.  With IGCONV_DEBUG set in the
 // environment a rejected launch is also described on stderr.
-template <class Kernel>
-int launch_checked(Kernel kernel, const char *what, const ConvKernelParams &p, int grid, int threads, void *stream) {
-    ConvKernelParams args = p;
+template <class Kernel, class Params>
+int launch_checked(Kernel kernel, const char *what, const Params &p, int grid, int threads, void *stream) {
+    Params args = p;
     void *argv[] = {&args};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(threads), argv, 0,
                                          static_cast<hipStream_t>(stream));

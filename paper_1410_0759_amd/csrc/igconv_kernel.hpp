@@ -365,6 +365,20 @@ struct KernelConfig {
     static_assert(GMODE != GATHER_TAPS9 || (BK % 9 == 0 && KPT % 9 == 0), "whole channels of nine taps per thread");
 };
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// The problem a workgroup of a joint launch belongs to, and its number there.  (Read from the argument segment itself: a
+// parameter indexed with a variable would be copied to scratch memory.)
+__device__ __forceinline__ ConvKernelParams phase_of_workgroup(uint32_t *block) {
+    const auto *args = (const ConvPhaseParams *)__builtin_amdgcn_kernarg_segment_ptr();
+    int i = 0;
+    for (int c = 1; c < kMaxPhases; ++c) i += (int)blockIdx.x >= args->start[c] ? 1 : 0;
+    *block = blockIdx.x - (uint32_t)args->start[i];
+    ConvKernelParams p;
+    __builtin_memcpy(&p, &args->p[i], sizeof(p));
+    return p;
+}
+#endif
+
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_WAVES) void igconv_fwd_kernel(const ConvKernelParams p) {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, LD = Cfg::LD;

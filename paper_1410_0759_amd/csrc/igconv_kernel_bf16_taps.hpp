@@ -29,8 +29,9 @@ struct Bf16TapsConfig {
     static_assert(BM % 64 == 0 && BN % 64 == 0, "2 x 2 wavefronts of whole 32 x 32 blocks");
 };
 
+// `block`: the workgroup's number within its problem
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_bf16_taps_kernel(const ConvKernelParams p) {
+__device__ __forceinline__ void bf16_taps_body(const ConvKernelParams &p, uint32_t block) {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, MB = BM / 64, NB = BN / 64, RB = Cfg::ROW;
     constexpr int NA = BM / 32, NBV = BN / 32;      // 16-byte loads per thread and step: rows tid/8 + 32 i
     __shared__ __attribute__((aligned(16))) uint8_t lds[Cfg::LDS_BYTES];
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_bf16_taps_kernel(const
     const int l32 = lane & 31, half = lane >> 5;
 
     const int tiles = p.tilesM * p.tilesN;
-    const int xcd = (int)(blockIdx.x % 8u), slot = (int)(blockIdx.x / 8u);
+    const int xcd = (int)(block % 8u), slot = (int)(block / 8u);
     const int range_end = (xcd + 1) * p.tilesPerXcd < tiles ? (xcd + 1) * p.tilesPerXcd : tiles;
     int tile = xcd * p.tilesPerXcd + slot;
     if (tile >= range_end) return;
@@ -185,6 +186,20 @@ __global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_bf16_taps_kernel(const
         // (the movers are already on the next tile's first steps)
         store_tile<Cfg::SWAP, MB, NB>(p, ybuf, acc, bias, m0 + wm * (BM / 2), n0 + wn * (BN / 2), half, l32);
     }
+}
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_bf16_taps_kernel(const ConvKernelParams p) {
+    bf16_taps_body<Cfg>(p, blockIdx.x);
+}
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 4) void igconv_bf16_taps_phases_kernel(const ConvPhaseParams) {
+#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass needs the kernel's name and signature only)
+    uint32_t block;
+    const ConvKernelParams p = phase_of_workgroup(&block);
+    bf16_taps_body<Cfg>(p, block);
+#endif
 }
 
 }  // namespace igc

@@ -264,9 +264,10 @@ struct SplitMultiplier {
     }
 };
 
+#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass needs the kernels' names and signatures only)
+// `block`: the workgroup's number within its problem
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_f32s_kernel(const ConvKernelParams p) {
-#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass needs the kernel's name and signature only)
+__device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t block) {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, MB = Cfg::MB, NB = Cfg::NB, KPT = Cfg::KPT;
     constexpr int ROW = Cfg::ROW, PART = Cfg::PART, STAGE = Cfg::STAGE;
 
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_f32s
     const int l32 = lane & 31;
 
     // persistent workgroups, tiles numbered in contiguous ranges per XCD (see igconv_kernel.hpp); the reduction is never cut
-    const int wg_xcd = (int)(blockIdx.x % 8u), wg_local = (int)(blockIdx.x / 8u);
+    const int wg_xcd = (int)(block % 8u), wg_local = (int)(block / 8u);
     const int tiles_total = p.tilesM * p.tilesN;
     auto tile_number = [&](int i) {
         const int local = wg_local + i * p.wgsPerXcd;
@@ -538,20 +539,53 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_f32s
         const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, kBufferWord3);
         store_tile<Cfg::SWAP, MB, NB>(p, ybuf, mult.acc, bvec, krow0, col0, half, l32);
     }
+}
+#endif
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_f32s_kernel(const ConvKernelParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    f32s_body<Cfg>(p, blockIdx.x);
+#endif
+}
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_f32s_phases_kernel(const ConvPhaseParams) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t block;
+    const ConvKernelParams p = phase_of_workgroup(&block);
+    f32s_body<Cfg>(p, block);
 #endif
 }
 
 // Instantiates the kernels of IGC_F32S_LIST and defines the group GROUP (variant 4: operands split).
 #define IGC_F32S_INSTANTIATE(NAME, BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS, GMODE) \
-    template __global__ void igconv_f32s_kernel<SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>>(const ConvKernelParams);
+    template __global__ void igconv_f32s_kernel<SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>>(const ConvKernelParams); \
+    IGC_F32S_PHASES_##VECA##_##PADDED(IGC_F32S_CONFIG(BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS))
+// (backward data only: filter through strides, window test)
+#define IGC_F32S_CONFIG(...) SplitConfig<__VA_ARGS__>
+#define IGC_F32S_PHASES_false_true(...) template __global__ void igconv_f32s_phases_kernel<__VA_ARGS__>(const ConvPhaseParams);
+#define IGC_F32S_PHASES_true_true(...)
+#define IGC_F32S_PHASES_false_false(...)
+#define IGC_F32S_PHASES_true_false(...)
 #define IGC_F32S_ROW(NAME, BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS, GMODE)                 \
     {NAME, false, BM, BN, BK, SWAP, VECA, GMODE,                                                  \
      SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>::THREADS,                        \
      SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>::LDS_BYTES,                      \
-     &launch_f32s<SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>>, 4},
+     &launch_f32s<SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>>, 4, false, 512,    \
+     f32s_phases_launcher<SplitConfig<BM, BN, BK, WM, WN, SWAP, VECA, PADDED, MOVERS>>()},
 template <class Cfg>
 inline int launch_f32s(const ConvKernelParams &p, int grid, void *stream) {
     return launch_checked(&igconv_f32s_kernel<Cfg>, "igconv_f32s_kernel", p, grid, Cfg::THREADS, stream);
+}
+template <class Cfg>
+inline int launch_f32s_phases(const ConvPhaseParams &p, int grid, void *stream) {
+    return launch_checked(&igconv_f32s_phases_kernel<Cfg>, "igconv_f32s_phases_kernel", p, grid, Cfg::THREADS, stream);
+}
+template <class Cfg>
+constexpr auto f32s_phases_launcher() -> int (*)(const ConvPhaseParams &, int, void *) {
+    if constexpr (!Cfg::VECA && Cfg::PADDED) return &launch_f32s_phases<Cfg>;
+    else return nullptr;
 }
 #if !defined(__HIP_DEVICE_COMPILE__)
 #define IGC_F32S_INSTANCES(GROUP)                                 \

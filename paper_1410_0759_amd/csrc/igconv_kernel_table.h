@@ -37,6 +37,8 @@ struct KernelInfo {
                       // 5: the same as 4 for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
     int patchPixels = 512;  // gather mode 5, variant 5: pixels of the zero-extended image a tile's staged patch can hold
+    // the same for several problems in one launch (null where the kernel has no such form); `grid`: workgroups in all
+    int (*launchPhases)(const ConvPhaseParams &, int grid, void *stream) = nullptr;
 };
 
 struct KernelGroup {

@@ -70,5 +70,13 @@ struct ConvKernelParams {
     Magic mWp, mHpWp;
 };
 
+// Several problems of one kernel in one launch (the stride phases of backward data): workgroup b belongs to problem i with
+// start[i] <= b < start[i+1].
+constexpr int kMaxPhases = 4;
+struct ConvPhaseParams {
+    ConvKernelParams p[kMaxPhases];
+    int32_t start[kMaxPhases + 1];
+};
+
 }  // namespace igc
 #endif

@@ -74,3 +74,26 @@ def test_forward(prob, layout):
         g.prefill(value=float("nan"))
         g.launch_fused(1.0, 0.0, bias, 1)
         assert gu.rel_err(g.result(), np.maximum(want + bias[None, :, None, None], 0.0)) <= gu.BOUND["bf16"]
+
+
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, S, pad, stride: a small gradient in more than eight ranges, summed by the kernel that cuts the ranges into runs
+    (24, 40, 28, 28, 72, 1, 1, (0, 0), (1, 1)),
+    (16, 136, 20, 20, 8, 2, 2, (1, 0), (1, 1)),
+    (40, 64, 30, 29, 24, 3, 1, (1, 0), (2, 1)),
+])
+def test_backward_filter_many_ranges(prob):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(5)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    x = wl.with_layout(_rnd(rng, (N, C, H, W)), "NHWC")
+    dy = wl.with_layout(_rnd(rng, (N, K, P, Q)), "NHWC")
+    dw0 = rng.uniform(-1, 1, size=(K, C, R, S)).astype(np.float32)
+    for mode, alpha, beta in ((0, 1.0, 0.0), (1, 0.5, -1.5)):
+        print(prob, mode, flush=True)
+        want = oc.conv_backward_filter(x, dy, (R, S), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dw_old=dw0 if beta else None)
+        got, ws_bytes = gu.run_backward_filter(x, dy, (R, S), pad, stride, mode, alpha, beta, dw0 if beta else None, "bf16")
+        assert ws_bytes > 8 * dw0.size * 4
+        # (products of bfloat16 numbers are exact; sums of N*P*Q of them in float)
+        assert gu.rel_err(got, want) <= gu.BOUND["bf16"]

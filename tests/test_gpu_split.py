@@ -120,3 +120,30 @@ def test_backward_data_from_a_staged_patch(prob, layout):
         want = oc.conv_backward_data(dy, w, (H, W), pad=pad, mode=mode, alpha=alpha, beta=beta, dx_old=dx0 if beta else None)
         got = gu.run_backward_data(dy, w, (H, W), pad, (1, 1), mode, alpha, beta, dx0 if beta else None, "f32", layout)
         _same(got, want, (prob, layout, mode))
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("kind", ["plain", "inf", "tiny"])
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, S, pad, stride: the phases that meet a tap run in one launch when there are two to four of them
+    (3, 33, 15, 18, 20, 3, 3, (1, 1), (2, 2)),        # four phases of one to four taps
+    (2, 140, 9, 11, 30, 1, 3, (0, 1), (2, 2)),        # two phases with taps, two without
+    (5, 101, 7, 23, 13, 2, 5, (1, 0), (1, 3)),        # three
+    (1, 65, 33, 6, 40, 4, 1, (3, 0), (4, 1)),         # four of one tap
+    (2, 129, 13, 12, 9, 5, 4, (2, 1), (3, 2)),        # six: one launch each
+])
+def test_strided_backward_data(prob, kind, layout):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(12)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    dy, ws = _planted(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), kind, rng)
+    dy = wl.with_layout(dy, layout)
+    w = (rng.standard_normal(size=(K, C, R, S)) * (K * R * S) ** -0.5).astype(np.float32) * ws
+    dx0 = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    for mode, alpha, beta in ((0, 1.0, 0.0), (1, 0.5, 1.0)) if kind == "plain" else ((0, 1.0, 0.0),):
+        for workspace in ("full", "none"):
+            print(prob, kind, layout, mode, workspace, flush=True)
+            old = dx0 if beta else None
+            want = oc.conv_backward_data(dy, w, (H, W), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dx_old=old)
+            _same(gu.run_backward_data(dy, w, (H, W), pad, stride, mode, alpha, beta, old, "f32", layout, workspace=workspace), want, kind)
