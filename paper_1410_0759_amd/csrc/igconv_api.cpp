@@ -465,6 +465,26 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
 }
 
 
+// At most four channels, 3x3 or 5x5 taps, up to 75 indices: the vector units (igconv_kernels_few_channels.hip).  A matrix kernel
+// runs such a reduction in one to three steps, mostly waiting, and pays for every output map its tile pads K with.
+// Measured, matrix kernels (with the border written out where that was ahead) and vector units, us:
+//   3x3 with a border: 1x3x32x32 -> 16 9.0 and 5.3; 8x3x224x224 -> 64 38.0 and 33.2; 32x3x224x224 -> 64 130 and 127;
+//     64x3x224x224 -> 96 367 and 382; 64x3x256x256 -> 3 269 and 66
+//   5x5 with a border: 128x3x32x32 -> 32 19.7 and 16.9; 128x3x32x32 -> 64 24.1 and 29.6; 32x3x128x128 -> 16 60 and 29
+//   without a border (the matrix kernels need no window test): 64x1x28x28 -> 20, 5x5 7.6 and 5.5; 32x3x224x224 -> 64, 3x3,
+//     stride 2 34.6 and 40.7
+//   four channels, 5x5, 1x4x32x32 -> 32: 6.0 and 8.2; eight channels, 3x3, 64x8x64x64 -> 64: 33 and 41
+//   y's maps next to each other, 32 bytes per thread's store: 1x3x64x64 -> 32 8.6 and 5.3; 32 images 21.9 and 26.3
+static bool few_channels(const igcContext *h, const Problem &pr) {
+    const ConvKernelParams &k = pr.kp;
+    if (pr.bf16 || pr.f64 || k.C > 4 || k.R != k.S || (k.R != 3 && k.R != 5) || k.CRS > 75 || k.K > 8 * 65535) return false;
+    const long long results = (long long)k.NPQ * k.K, cus = h->computeUnits;
+    if (k.ysK == 1 && k.K > 1) return results < cus * 2048;
+    if (k.pad_h == 0 && k.pad_w == 0) return results <= cus * 4096;
+    if (results <= cus * 20480 || k.K <= 16) return true;
+    return k.R == 3 && results <= cus * 524288;
+}
+
 // ---- backward data ------------------------------------------------------------------
 // dx[n,c,h,w] = sum over (k,p,q,r,s) whose forward read lands on (h,w) of w[k,c,r,s] * dy[n,k,p,q].
 // Per axis, with e the tap counted in reading direction (e = r for cross-correlation,
@@ -1343,6 +1363,11 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
             k.alpha = 1.f;
             k.beta = 0.f;
         }
+    }
+    // (a short reduction over few channels: the vector units)
+    if (splits <= 1 && handle->kernelOverride < 0 && few_channels(handle, pr)) {
+        if (launch_few_channels(pr.kp, handle->computeUnits, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
+        return IGC_STATUS_SUCCESS;
     }
     // Few channels, a zero border and room for x with the border written out: the copy is made and the pass runs
     // over it as a problem without a border (alpha, beta, bias and activation unchanged).
