@@ -396,7 +396,7 @@ static long long padded_copy_bytes(const KernelInfo &ki, const Problem &pr, igcT
 // ranges as in the backward-filter pass (partial results summed in order afterwards), which
 // puts idle compute units to work.  Returns the number of ranges (1: do not cut) and the
 // steps per range.  Only for kernels whose steps stand alone (modes 0-3 and 14), outputs packed
-// without gaps, and no fused epilogue; no range shorter than 8 steps.  The number of ranges
+// without gaps; no range shorter than 8 steps.  The number of ranges
 // minimises a small model of the run time in units of one reduction step: the busiest
 // compute unit holds ceil(tiles*s/256) workgroups, which share its MFMA pipes, each taking
 // its range plus a fixed start-up/epilogue share (about 6 steps); cutting adds the summing
@@ -1310,7 +1310,10 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     igcConvolutionForwardPlan plan;
     // With a workspace the reduction of a small problem is cut into ranges (below), finer than the team kernels
     // cut it: those are left out of the choice then, unless the cut does not pay for the kernel chosen instead.
-    const bool can_cut = workSpace && (uintptr_t)workSpace % 4 == 0 && !bias && activation == IGC_ACTIVATION_IDENTITY && !pr.f64;
+    // (The sum of the ranges applies bias and activation: 4x512x7x7 -> 512, 3x3, with both: 32.2 -> 17.8 us.)
+    Magic mPitch, mK;
+    const bool can_cut = workSpace && (uintptr_t)workSpace % 4 == 0 && !pr.f64 && 
+                         magic_for(pr.kp.K > 1 ? (uint32_t)pr.kp.ysK : 1u, &mPitch) && magic_for((uint32_t)pr.kp.K, &mK);
     bool cut_found = false;
     if (can_cut) {
         Problem trial = pr;
@@ -1362,6 +1365,8 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
             k.y = workSpace;
             k.alpha = 1.f;
             k.beta = 0.f;
+            k.bias = nullptr;
+            k.act = IGC_ACTIVATION_IDENTITY;
         }
     }
     // (a short reduction over few channels: the vector units)
@@ -1421,10 +1426,16 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
         }
     }
     if (kernel_info(id)->launch(pr.kp, grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
-    if (splits > 1 && launch_sum_parts(static_cast<const float *>(workSpace), static_cast<float *>(y), pr.kp.y_bytes / 4, splits,
-                                       pr.kp.y_bytes / 4, *static_cast<const float *>(alpha),
-                                       *static_cast<const float *>(beta), handle->stream) != 0)
-        return IGC_STATUS_EXECUTION_FAILED;
+    if (splits > 1) {
+        const float *const parts = static_cast<const float *>(workSpace);
+        const float a = *static_cast<const float *>(alpha), b = *static_cast<const float *>(beta);
+        const uint32_t n = pr.kp.y_bytes / 4;
+        const int rc = bias || activation != IGC_ACTIVATION_IDENTITY
+                           ? launch_sum_parts_fused(parts, static_cast<float *>(y), n, splits, n, a, b, static_cast<const float *>(bias), activation,
+                                                    pr.kp.K, mPitch, mK, handle->stream)
+                           : launch_sum_parts(parts, static_cast<float *>(y), n, splits, n, a, b, handle->stream);
+        if (rc != 0) return IGC_STATUS_EXECUTION_FAILED;
+    }
     return IGC_STATUS_SUCCESS;
 }
 

@@ -54,6 +54,9 @@ extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGro
 // returns the runtime's error code.
 int launch_sum_parts(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta,
                      void *stream);
+// The same with the forward pass's bias and activation: element e belongs to map (e / pitch) % K.
+int launch_sum_parts_fused(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta,
+                           const float *bias, int act, int K, Magic mPitch, Magic mK, void *stream);
 
 // wt[c][k][t] = w[k][c][t] for 2-byte elements, t < taps, taps 9 or 1 (the filter with its first two
 // dimensions exchanged, each pair's taps kept in order); returns the runtime's error code.

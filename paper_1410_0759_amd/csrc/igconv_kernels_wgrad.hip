@@ -55,8 +55,27 @@ namespace igc {
 // loads in flight), and the eight sums are added in order through LDS.  (One thread per element
 // adding all parts kept one load in flight per thread, on a fraction of the chip: 112 parts of
 // 147 KB took 28 us.)
+// FUSED: the forward pass's tail, out = f(... + bias[k]) with k = (e / pitch) % K.
+struct SumTail {
+    const float *bias;
+    int act, K;
+    Magic mPitch, mK;
+};
+template <bool FUSED>
+__device__ __forceinline__ float sum_tail(const SumTail &t, uint32_t e, float r) {
+    if constexpr (FUSED) {
+        if (t.bias != nullptr) {
+            const uint32_t row = magic_div(e, t.mPitch);
+            r += t.bias[row - magic_div(row, t.mK) * (uint32_t)t.K];
+        }
+        r = activate(t.act, r);
+    }
+    return r;
+}
+
+template <bool FUSED>
 __global__ __launch_bounds__(256) void igconv_sum_parts_kernel(const float *parts, float *out, uint32_t n, int count,
-                                                               uint32_t stride, float alpha, float beta) {
+                                                               uint32_t stride, float alpha, float beta, const SumTail tail) {
     __shared__ float runs[8][32];
     const uint32_t el = threadIdx.x & 31u, g = threadIdx.x >> 5;
     const uint32_t e = blockIdx.x * 32u + el;
@@ -83,14 +102,15 @@ __global__ __launch_bounds__(256) void igconv_sum_parts_kernel(const float *part
     for (int k = 1; k < 8; ++k) sum += runs[k][el];
     float r = alpha * sum;
     if (beta != 0.f) r += beta * out[e];
-    out[e] = r;
+    out[e] = sum_tail<FUSED>(tail, e, r);
 }
 
 // The same sums - the same additions in the same order, so the same bits - for at most 16 parts of whole 16-byte
 // vectors: a thread takes four consecutive elements and requests all its loads before it adds.  (With few parts the
 // kernel above leaves most of its threads without a load: 9 parts of 3.5 MB took 14.8 us.)
+template <bool FUSED>
 __global__ __launch_bounds__(256) void igconv_sum_few_parts_kernel(const float4 *parts, float4 *out, uint32_t n4, int count,
-                                                                   uint32_t stride4, float alpha, float beta) {
+                                                                   uint32_t stride4, float alpha, float beta, const SumTail tail) {
     const uint32_t e = blockIdx.x * 256u + threadIdx.x;
     if (e >= n4) return;
     float4 v[16];
@@ -126,20 +146,33 @@ __global__ __launch_bounds__(256) void igconv_sum_few_parts_kernel(const float4 
         r.z += beta * o.z;
         r.w += beta * o.w;
     }
+    if constexpr (FUSED)
+        r = {sum_tail<true>(tail, 4 * e, r.x), sum_tail<true>(tail, 4 * e + 1, r.y), sum_tail<true>(tail, 4 * e + 2, r.z), sum_tail<true>(tail, 4 * e + 3, r.w)};
     out[e] = r;
+}
+
+template <bool FUSED>
+static int launch_sum(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta, SumTail tail,
+                      void *stream) {
+    if (count <= 16 && n % 4 == 0 && stride % 4 == 0 && (uintptr_t)parts % 16 == 0 && (uintptr_t)out % 16 == 0) {
+        uint32_t n4 = n / 4, stride4 = stride / 4;
+        void *argv4[] = {&parts, &out, &n4, &count, &stride4, &alpha, &beta, &tail};
+        return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void *>(&igconv_sum_few_parts_kernel<FUSED>), dim3((n4 + 255u) / 256u),
+                                                dim3(256), argv4, 0, static_cast<hipStream_t>(stream)));
+    }
+    void *argv[] = {&parts, &out, &n, &count, &stride, &alpha, &beta, &tail};
+    return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void *>(&igconv_sum_parts_kernel<FUSED>), dim3((n + 31u) / 32u),
+                                            dim3(256), argv, 0, static_cast<hipStream_t>(stream)));
 }
 
 int launch_sum_parts(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta,
                      void *stream) {
-    if (count <= 16 && n % 4 == 0 && stride % 4 == 0 && (uintptr_t)parts % 16 == 0 && (uintptr_t)out % 16 == 0) {
-        uint32_t n4 = n / 4, stride4 = stride / 4;
-        void *argv4[] = {&parts, &out, &n4, &count, &stride4, &alpha, &beta};
-        return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void *>(&igconv_sum_few_parts_kernel), dim3((n4 + 255u) / 256u),
-                                                dim3(256), argv4, 0, static_cast<hipStream_t>(stream)));
-    }
-    void *argv[] = {&parts, &out, &n, &count, &stride, &alpha, &beta};
-    return static_cast<int>(hipLaunchKernel(reinterpret_cast<const void *>(&igconv_sum_parts_kernel), dim3((n + 31u) / 32u),
-                                            dim3(256), argv, 0, static_cast<hipStream_t>(stream)));
+    return launch_sum<false>(parts, out, n, count, stride, alpha, beta, SumTail{}, stream);
+}
+
+int launch_sum_parts_fused(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta,
+                           const float *bias, int act, int K, Magic mPitch, Magic mK, void *stream) {
+    return launch_sum<true>(parts, out, n, count, stride, alpha, beta, SumTail{bias, act, K, mPitch, mK}, stream);
 }
 
 // wt[k][t][c] = w[k][c][t] (float or bfloat16; t < RS): the filter with the channel index innermost, so that the tap-major
