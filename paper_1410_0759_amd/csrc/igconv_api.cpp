@@ -470,7 +470,7 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
 // Measured, matrix kernels (with the border written out where that was ahead) and vector units, us:
 //   3x3 with a border: 1x3x32x32 -> 16 9.0 and 5.3; 8x3x224x224 -> 64 38.0 and 33.2; 32x3x224x224 -> 64 130 and 127;
 //     64x3x224x224 -> 96 367 and 382; 64x3x256x256 -> 3 269 and 66
-//   5x5 with a border: 128x3x32x32 -> 32 19.7 and 16.9; 128x3x32x32 -> 64 24.1 and 29.6; 32x3x128x128 -> 16 60 and 29
+//   5x5 with a border: 128x3x32x32 -> 32 19.7 and 16.9; 128x3x32x32 -> 64 24.1 and 29.6; 256x1x28x28 -> 32 19.5 and 13.7; 32x3x128x128 -> 16 60 and 29
 //   without a border (the matrix kernels need no window test): 64x1x28x28 -> 20, 5x5 7.6 and 5.5; 32x3x224x224 -> 64, 3x3,
 //     stride 2 34.6 and 40.7
 //   four channels, 5x5, 1x4x32x32 -> 32: 6.0 and 8.2; eight channels, 3x3, 64x8x64x64 -> 64: 33 and 41
@@ -481,7 +481,7 @@ static bool few_channels(const igcContext *h, const Problem &pr) {
     const long long results = (long long)k.NPQ * k.K, cus = h->computeUnits;
     if (k.ysK == 1 && k.K > 1) return results < cus * 2048;
     if (k.pad_h == 0 && k.pad_w == 0) return results <= cus * 4096;
-    if (results <= cus * 20480 || k.K <= 16) return true;
+    if (results * k.CRS <= cus * 1536000 || k.K <= 16) return true;
     return k.R == 3 && results <= cus * 524288;
 }
 

@@ -8,7 +8,7 @@
 // (A first form walked any filter size with the tap arithmetic per element: 6.4, and 2.5 times the instructions.)
 // What bounds it: at small sizes the latency of that chain; at large ones the LDS reads of the filter (16 bytes for
 // 4 * PX multiply-adds, hence two pixels and sixteen maps per thread) and the stores of y.
-// Reduction order (c, r, s) in one chain of fused multiply-adds per output.
+// Reduction order (c, r, s), a chain of fused multiply-adds (3x3: per channel).
 #include "igconv_instantiate.hpp"
 #include "igconv_kernel.hpp"
 
@@ -69,18 +69,37 @@ __global__ __launch_bounds__(256, 4) void igconv_few_channels_kernel(const ConvK
 #pragma unroll
         for (int k = 0; k < KB; ++k) acc[px][k] = 0.f;
     auto multiply = [&](int c, const float (&v)[T][PX]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const f32x4 *row = reinterpret_cast<const f32x4 *>(&wl[(c * T + t) * KB]);
+        if constexpr (T == 9) {   // a channel's sum first, then added: shorter chains of roundings
 #pragma unroll
             for (int q = 0; q < KB / 4; ++q) {
-                const f32x4 f = row[q];
+                float sum[PX][4];
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const f32x4 f = *reinterpret_cast<const f32x4 *>(&wl[(c * T + t) * KB + 4 * q]);
+#pragma unroll
+                    for (int px = 0; px < PX; ++px)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[px][e] = t == 0 ? v[t][px] * f[e] : __builtin_fmaf(v[t][px], f[e], sum[px][e]);
+                }
 #pragma unroll
                 for (int px = 0; px < PX; ++px)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[px][4 * q + e] = __builtin_fmaf(v[t][px], f[e], acc[px][4 * q + e]);
+                    for (int e = 0; e < 4; ++e) acc[px][4 * q + e] += sum[px][e];
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
+        } else {                  // (no registers for that)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+#pragma unroll
+                for (int q = 0; q < KB / 4; ++q) {
+                    const f32x4 f = *reinterpret_cast<const f32x4 *>(&wl[(c * T + t) * KB + 4 * q]);
+#pragma unroll
+                    for (int px = 0; px < PX; ++px)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[px][4 * q + e] = __builtin_fmaf(v[t][px], f[e], acc[px][4 * q + e]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
     float v0[T][PX], v1[T][PX];
