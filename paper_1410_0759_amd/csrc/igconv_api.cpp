@@ -232,10 +232,13 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         // and gathering, a row's and a column's share - costs more than the MFMAs; measured, in the units of the line
         // below: 0.66 per row and 18 per column without a border (96x64x64 -> 128, 9x9, 128 images: 64 rows 4.5 ms,
         // 128 rows 4.0 ms, fp32 instruction 6.1 ms), 0.70 and 25 with the window test (96x27x27 -> 256, 5x5: 775 and
-        // 637 us against 877).  Not offered where compute units would idle - the fp32 kernels' smaller tiles and
-        // teams win there (256x14x14 -> 256, 3x3, 32 images: 72 against 76 us) -, nor for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
+        // 637 us against 877).  Not offered where more than a
+        // third of the compute units would idle (half with 128 rows, which make up for it per tile): the fp32 kernels' smaller
+        // tiles, teams and cut reductions win there.  96x27x27 -> 256, 5x5, 16 images: 128 rows on 184 units 94 us, 64 rows on
+        // all twice 116; 64x32x32 -> 128, 9x9, 24 images, 216 tiles of 64 rows: 125, fp32 teams 174; 144 tiles (128x32x32 ->
+        // 128, 16 images): 243, fp32 cut 213.  Not offered either for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
         // 11x11, stride 4: 112 against 117 us at best, slower with other tiles).
-        if (tiles < cus || (!ki.veca && steps < 16)) return 1e300;
+        if ((ki.BM == 128 ? tiles * 2 < cus : tiles * 3 < cus * 2) || (!ki.veca && steps < 16)) return 1e300;
         return tile_times * (double)steps * (double)ki.BN * ki.BK * (ki.gmode == 14 ? 0.70 * ki.BM + 25.0 : 0.66 * ki.BM + 18.0);
     }
     const bool table = ki.gmode == 7 || ki.gmode == 11 || ki.gmode == 13;
