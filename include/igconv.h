@@ -153,7 +153,8 @@ igcStatus igcGetConvolutionForwardWorkspaceSize(igcHandle_t handle,
  * most of the chip would idle (small mini-batches: Section 4 discusses them) can however be
  * run faster when the caller lends one: the reduction over (c,r,s) is then cut into ranges
  * computed side by side, each leaving a partial copy of y in the workspace, and a second
- * kernel adds the parts in a fixed order (deterministic) and applies alpha and beta.  This
+ * kernel adds the parts in a fixed order (deterministic) and applies alpha and beta (and bias and
+ * activation of igcConvolutionBiasActivationForward).  This
  * query reports the size that allows the finest cut the library would choose, 0 when
  * cutting would not help or does not apply (y with gaps between its elements, the bf16
  * channel-vector kernels).  Any smaller size passed to igcConvolutionForward is fine
@@ -167,7 +168,8 @@ igcStatus igcGetConvolutionForwardWorkspaceSize(igcHandle_t handle,
  * A third use, for float problems with a zero border and so few channels that the library would test
  * every gathered element against the window (the generic gather): the query reports the size of x
  * with its border written out, N*C*(H+2*pad_h)*(W+2*pad_w)*4 bytes; with such a workspace (16-byte
- * aligned) that copy is made first and the pass runs over it as a problem without a border. */
+ * aligned) that copy is made first and the pass runs over it as a problem without a border (most 3x3 and
+ * 5x5 filters over up to four channels need no copy: the workspace is then left alone). */
 igcStatus igcGetConvolutionForwardOptionalWorkspaceSize(igcHandle_t handle,
                                                         igcTensorDescriptor_t xDesc,
                                                         igcFilterDescriptor_t wDesc,

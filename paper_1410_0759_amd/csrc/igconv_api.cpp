@@ -496,7 +496,7 @@ static bool few_channels(const igcContext *h, const Problem &pr) {
 // e = a + u*t gives p = i + b - t with b = (ph + pad - a)/u.  That is a stride-1 gather over
 // dy with R' = ceil((R - a)/u) taps: with tap index g = R'-1-t it reads row i + g - (R'-1-b),
 // i.e. the forward kernel's own addressing with pad R'-1-b, taps walked backwards through
-// the filter, and the roles of k and c exchanged.  One launch per phase (ph, pw), each
+// the filter, and the roles of k and c exchanged.  One launch per phase (ph, pw) or one for all of them (joint_kernel), each
 // writing its own rows and columns of dx through strides multiplied by (u, v); for u = v = 1
 // there is a single phase.  A phase that meets no tap still runs, with zero reduction
 // steps, so that its part of dx becomes beta * dx.
@@ -792,7 +792,7 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
     return IGC_STATUS_SUCCESS;
 }
 
-// The general route of backward data: one launch per phase, each planned like a forward problem.
+// The general route of backward data: the phases, each planned like a forward problem; one launch each, or one for those marked `joint`.
 struct PhaseLaunch {
     Problem pr;
     int id, grid;
