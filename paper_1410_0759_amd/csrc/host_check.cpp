@@ -9,6 +9,7 @@
 #include <initializer_list>
 
 #include "../../include/igconv.h"
+#include "igconv_params.h"
 
 static unsigned long long state = 14100759ull;
 static int draw(int lo, int hi) {   // uniform in lo..hi
@@ -115,6 +116,20 @@ int main() {
         unsigned mul = 0, shift = 0;
         REQUIRE(igcMagicDivisor(d, &mul, &shift) == IGC_STATUS_SUCCESS);
         REQUIRE(igcMagicDivide(nn, mul, shift) == nn / d);
+    }
+    // offsets of the few-channel epilogue, by the hardware's rule (vector offset against "size - scalar offset", modulo
+    // 2^32): a map that exists is stored at its place, one that pads K to whole blocks of 8 or 16 nowhere
+    for (it = 0; it < 200000; ++it) {
+        const int K = draw(1, 70), block = it % 2 ? 8 : 16, N = draw(1, 3), PQ = draw(1, it % 5 ? 500 : 200000);
+        const bool nhwc = it % 3 == 0;
+        const unsigned ysK = nhwc ? 1u : (unsigned)PQ, ysN = (unsigned)K * (unsigned)PQ, size = ysN * (unsigned)N * 4u;
+        for (int map = 0; map < (K + block - 1) / block * block; ++map) {
+            const unsigned so = igc::few_channels_map_offset(map, K, ysK * 4u);
+            REQUIRE(so <= size);
+            REQUIRE(0x80000000u >= size - so);
+            const unsigned last = ((unsigned)(N - 1) * ysN + (unsigned)(PQ - 1) * (nhwc ? (unsigned)K : 1u)) * 4u;   // the last pixel
+            if (map < K) REQUIRE(last < size - so && so == (unsigned)map * ysK * 4u);
+        }
     }
     it = -3;
     REQUIRE(igcDestroyTensorDescriptor(x) == IGC_STATUS_SUCCESS && igcDestroyTensorDescriptor(y) == IGC_STATUS_SUCCESS &&

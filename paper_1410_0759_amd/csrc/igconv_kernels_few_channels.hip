@@ -118,17 +118,17 @@ __global__ __launch_bounds__(256, 4) void igconv_few_channels_kernel(const ConvK
 #pragma unroll
         for (int b = 0; b < KB; b += 8) {
             float out[8];
-            uint32_t off[8];
+            uint32_t off[8], row[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 out[k] = p.alpha * acc[px][b + k];
                 off[k] = m0 + b + k < p.K ? yoff[px] : kOutOfRange;
+                row[k] = few_channels_map_offset(m0 + b + k, p.K, (uint32_t)p.ysK * 4u);
             }
-            const uint32_t row = (uint32_t)(m0 + b) * (uint32_t)p.ysK * 4u, step = (uint32_t)p.ysK * 4u;
             if (use_beta) {
                 float old[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) old[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ybuf, off[k], row + (uint32_t)k * step, 0));
+                for (int k = 0; k < 8; ++k) old[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ybuf, off[k], row[k], 0));
 #pragma unroll
                 for (int k = 0; k < 8; ++k) out[k] += p.beta * old[k];
             }
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, 4) void igconv_few_channels_kernel(const ConvK
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out[k]), ybuf, off[k], row + (uint32_t)k * step, 0);
+            for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out[k]), ybuf, off[k], row[k], 0);
         }
 }
 

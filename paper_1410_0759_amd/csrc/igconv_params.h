@@ -27,6 +27,11 @@ inline bool magic_for(uint32_t d, Magic *m) {
     return true;
 }
 
+// Scalar offset of map `map`'s results (bytes) in the epilogue of igconv_kernels_few_channels.hip.  The hardware compares
+// a lane's vector offset with "size - scalar offset", so a scalar offset beyond the size would let kOutOfRange pass: the
+// maps that pad K to whole blocks, whose lanes rely on that marker, take none.
+constexpr uint32_t few_channels_map_offset(int map, int K, uint32_t map_bytes) { return map < K ? (uint32_t)map * map_bytes : 0u; }
+
 // The kernels that feed the MFMAs straight from global memory (igconv_kernel_f32d.hpp): entries of their LDS table of
 // tap offsets (one per reduction index), and how many steps ahead their requests run (as many register sets).
 constexpr int kDirectTableEntries = 16384;
