@@ -41,7 +41,8 @@ struct SplitPatchConfig {
     static constexpr int A_PART = BM * 32, A_TAP = 3 * A_PART, A_STAGE = 3 * A_TAP;
     static constexpr int B_PART = PIX * 32, B_STAGE = 3 * B_PART;
     static constexpr int B_BASE = 2 * A_STAGE;
-    static constexpr int LDS_BYTES = 2 * (A_STAGE + B_STAGE);
+    static constexpr int SEEN = 2 * (A_STAGE + B_STAGE);   // [parity of the tile][filter, patch][moving wavefront]
+    static constexpr int LDS_BYTES = SEEN + 2 * 2 * 4 * kSeenBytes;
     static constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
     static constexpr int CPT = BM / 16;                 // channels of a filter row per moving thread (of 256)
     static constexpr int NPASS = PIX / 128;             // passes of 256 (pixel, half) items over the patch
@@ -152,11 +153,16 @@ __global__ __launch_bounds__(512, 2) void igconv_f32p_kernel(const ConvKernelPar
                 b_reg[set][sl][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, b_voff[i], (c + (uint32_t)e) * (uint32_t)p.xsC * 4u, 0));
             }
         };
+        // The patch runs ahead of the filter, so that each has its own (SplitSeen; `operand` 0: filter, 1: patch); of tile number `it`.
+        SplitSeen seen[2];
+        auto publish = [&](int it, int operand) {
+            publish_seen(lds + Cfg::SEEN + (((it & 1) * 2 + operand) * 4 + mw) * kSeenBytes, seen[operand]);
+        };
         // split and write: filter, pair q of tap t (of the chunk in `set`) into stage `st`
         uint32_t ph[CPT / 2], pm[CPT / 2], pl[CPT / 2];
         auto convert_a = [&](auto set_c, int st, int t, int q) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
-            split_pair(a_reg[set][2 * q * 9 + t], a_reg[set][(2 * q + 1) * 9 + t], ph[q], pm[q], pl[q]);
+            split_pair(a_reg[set][2 * q * 9 + t], a_reg[set][(2 * q + 1) * 9 + t], ph[q], pm[q], pl[q], seen[0]);
             if (q == CPT / 2 - 1) {
                 uint8_t *const dst = lds + st * Cfg::A_STAGE + (t % 3) * Cfg::A_TAP + a_dst;
                 if constexpr (CPT == 8) {
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32p_kernel(const ConvKernelPar
         auto convert_b = [&](auto set_c, int st, int sl, int i, int q) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
             uint32_t h, m, l;
-            split_pair(b_reg[set][sl][2 * q], b_reg[set][sl][2 * q + 1], h, m, l);
+            split_pair(b_reg[set][sl][2 * q], b_reg[set][sl][2 * q + 1], h, m, l, seen[1]);
             bh[q] = h; bm[q] = m; bl[q] = l;
             if (q == 3) {
                 uint8_t *const dst = lds + st * Cfg::B_STAGE + b_dst[i];
@@ -185,7 +191,9 @@ __global__ __launch_bounds__(512, 2) void igconv_f32p_kernel(const ConvKernelPar
             }
         };
         uint32_t rc = 0;             // chunk of the tile whose operands are requested
-        // step j of chunk s (par: s & 1).  Third j of the patch: passes j and j + 3.
+        int it = 0;                  // its tile
+        // step j of chunk s (par: s & 1).  Third j of the patch: passes j and j + 3.  Where rc is 0, s is the last chunk of the
+        // tile before: all of its patch has been split after step 0, all of its filter rows after step 2.
         auto step = [&](auto par_c, auto j_c) __attribute__((always_inline)) {
             constexpr int par = decltype(par_c)::value, j = decltype(j_c)::value;
             constexpr int q = (par + j) & 1;                            // parity of 3s + j
@@ -209,9 +217,10 @@ __global__ __launch_bounds__(512, 2) void igconv_f32p_kernel(const ConvKernelPar
                 else convert_b(Got{}, stc, (i - NCA) / 4, jc + 3 * ((i - NCA) / 4), (i - NCA) % 4);
                 __builtin_amdgcn_sched_barrier(0);
             });
+            if (j != 1 && rc == 0 && it > 0) publish(it - 1, j == 0 ? 1 : 0);
             split_barrier();
         };
-        int it = 0, rem = 0;
+        int rem = 0;
         for (int i = 0; tile_number(i) < tiles_total; ++i) rem += nch;   // chunks of all tiles of this workgroup
         auto chunk = [&](auto par_c) __attribute__((always_inline)) {
             step(par_c, std::integral_constant<int, 0>{});
@@ -373,7 +382,8 @@ __global__ __launch_bounds__(512, 2) void igconv_f32p_kernel(const ConvKernelPar
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[mb][nb][v] += low[mb][nb][v];
-        if (__any(outside_split_range<MB, NB>(acc))) sums_in_fp32<Cfg::SWAP, MB, NB>(p, acc, krow0, col0, 0, p.CRS, half, l32);
+        const uint32_t inexact = inexact_below<8>(lds + Cfg::SEEN + (it & 1) * 8 * kSeenBytes, p.CRS);
+        if (__any(outside_split_range<MB, NB>(acc, inexact))) sums_in_fp32<Cfg::SWAP, MB, NB>(p, acc, krow0, col0, 0, p.CRS, half, l32);
         const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, kBufferWord3);
         store_tile<Cfg::SWAP, MB, NB>(p, ybuf, acc, bvec, krow0, col0, half, l32);
     }

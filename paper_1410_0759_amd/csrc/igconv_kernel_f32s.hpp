@@ -23,9 +23,14 @@
 // window test is the packed 16-bit comparison of igconv_kernel.hpp (any filter size, pad, stride).
 //
 // Values outside bfloat16's reach.  An infinite operand, or a finite one that rounds to infinity, has a NaN among its
-// parts, and operands below 2^-108 lose the parts that bfloat16's denormals cannot hold.  The epilogue looks at every
-// sum: where one is not finite, or where all of a lane's sums are below 2^-80, the wavefront multiplies its blocks
-// again with the fp32 instruction straight from global memory (slow, rare, no LDS, no barrier).
+// parts, which its sums show.  The parts of a small operand lose what bfloat16's denormals (multiples of 2^-133) cannot hold:
+// conversions and matrix instructions keep denormals, so that x - h - m is l, with at most eight significant bits, unless
+// it is itself a float denormal (some |x| < 2^-103).  l is therefore taken as its upper half, and a lower half that is not zero
+// says that something was lost, less than 2^-133; the movers gather those, and the largest magnitude (SplitSeen).  A sum of n
+// products of a tile that lost something is off by less than n * 2^-132 times the largest operand.  A wavefront some of whose
+// sums are smaller than 2^24 times that - half a unit of their last place - multiplies its blocks again with the fp32
+// instruction straight from global memory (slow, rare, no LDS, no barrier), as it does where a sum is not finite, or not zero
+// but below 2^-100.
 #ifndef IGCONV_KERNEL_F32S_HPP_
 #define IGCONV_KERNEL_F32S_HPP_
 
@@ -33,15 +38,64 @@
 
 namespace igc {
 
+// What a moving thread's operands were like: the bits their parts lost (low halves; see the head of the file), and the
+// largest magnitude.  Per pair of operands one `or` and one maximum beside eleven instructions of splitting: a layer's
+// forward and both backward passes, without and with them, 9x9, 128x96x64x64 -> 128 16.5 and 17.4 ms; 3x3, 128x64x56x56 -> 64
+// (staged patch) 694 and 702 us.  (Class tests of both remainders in place of the `or`, two vector and two scalar
+// instructions: 18.1 ms and 708 us.)
+struct SplitSeen {
+    uint32_t lost = 0;
+    float largest = 0.f;
+};
+constexpr int kSeenBytes = 8;   // of one wavefront and tile in LDS
+
 // x0, x1 as three pairs of bfloat16 numbers (x0's part in the low half)
-__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l, SplitSeen &seen) {
     using f32x2 = float __attribute__((ext_vector_type(2)));
     using bf16x2 = __bf16 __attribute__((ext_vector_type(2)));
     h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
     const float r0 = x0 - __builtin_bit_cast(float, h << 16), r1 = x1 - __builtin_bit_cast(float, h & 0xFFFF0000u);
     m = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
     const float s0 = r0 - __builtin_bit_cast(float, m << 16), s1 = r1 - __builtin_bit_cast(float, m & 0xFFFF0000u);
-    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{s0, s1}), bf16x2));
+    const uint32_t t0 = __builtin_bit_cast(uint32_t, s0), t1 = __builtin_bit_cast(uint32_t, s1);
+    l = __builtin_amdgcn_perm(t1, t0, 0x07060302u);   // the upper halves
+    seen.lost |= t0 | t1;
+    // (the compiler's maximum would quiet both operands first; a NaN shows in the sums)
+    asm("v_max3_f32 %0, %0, abs(%1), abs(%2)" : "+v"(seen.largest) : "v"(x0), "v"(x1));
+}
+
+// Leaves it in LDS for the multipliers (once per tile, before a barrier); the tile's operands have all been split.
+__device__ __forceinline__ void publish_seen(uint8_t *slot, SplitSeen &seen) {
+    uint32_t big = __builtin_bit_cast(uint32_t, seen.largest);   // (not negative: ordered like the integers)
+    auto reduce = [&](auto ctrl_c) __attribute__((always_inline)) {
+        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)big, decltype(ctrl_c)::value, 0xF, 0xF, true);
+        big = big > other ? big : other;
+    };
+    reduce(std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has the row's
+    reduce(std::integral_constant<int, 0x112>{});
+    reduce(std::integral_constant<int, 0x114>{});
+    reduce(std::integral_constant<int, 0x118>{});
+    reduce(std::integral_constant<int, 0x142>{});   // row_bcast 15 and 31: lane 63 has the wavefront's
+    reduce(std::integral_constant<int, 0x143>{});
+    const uint32_t inexact = __any((seen.lost & 0xFFFFu) != 0u) ? 1u : 0u;
+    if ((threadIdx.x & 63u) == 63u) *reinterpret_cast<u32x2 *>(slot) = u32x2{inexact, big};
+    seen.lost = 0;   // (the largest magnitude may only grow: that of the tiles before bounds this one's too)
+}
+
+// The multipliers' side: sums of `terms` products smaller than this in magnitude (its bits) may be off; 0 when the tile's
+// parts are exact.  `slots` of `count` wavefronts.
+template <int count>
+__device__ __forceinline__ uint32_t inexact_below(const uint8_t *slots, int terms) {
+    uint32_t inexact = 0, big = 0;
+#pragma unroll
+    for (int i = 0; i < count; ++i) {
+        const u32x2 s = *reinterpret_cast<const u32x2 *>(slots + i * kSeenBytes);
+        inexact |= s[0];
+        big = big > s[1] ? big : s[1];
+    }
+    if (__builtin_amdgcn_readfirstlane(inexact) == 0) return 0;
+    const float largest = __builtin_bit_cast(float, big < 0x7F800000u ? big : 0x7F800000u);
+    return __builtin_bit_cast(uint32_t, (float)terms * (largest * 0x1p-108f));
 }
 
 // BM x BN tile, WM x WN multiplying wavefronts.  VECA: the filter is read in its own order with 16-byte loads, else
@@ -55,7 +109,8 @@ struct SplitConfig {
     static constexpr int ROW = 3 * PART + 16;
     static constexpr int A_BYTES = BM * ROW, B_BYTES = BN * ROW, STAGE = A_BYTES + B_BYTES;
     static constexpr int RING = BK * 12;                // per moving wavefront: BK entries (offset, tap), BK filter offsets
-    static constexpr int LDS_USED = 2 * STAGE + MOVERS * RING;
+    static constexpr int SEEN = 2 * STAGE + MOVERS * RING;   // [parity of the tile][moving wavefront]
+    static constexpr int LDS_USED = SEEN + 2 * MOVERS * kSeenBytes;
     // workgroups per compute unit: one or two (three would leave a wavefront 85 registers); the allocation says so
     static constexpr int WGS = (160 * 1024) / LDS_USED >= 2 ? 2 : 1;
     static constexpr int LDS_BYTES = (160 * 1024) / LDS_USED >= 3 ? 64 * 1024 : LDS_USED;
@@ -140,20 +195,26 @@ __device__ __forceinline__ void sums_in_fp32(const ConvKernelParams &p, f32x16 (
 }
 
 // True when a lane's sums call for sums_in_fp32: one is infinite or NaN (times zero gives NaN, which every addition
-// keeps), or the largest is tiny but not zero.
+// keeps), or not zero but below 2^-100, or - zeros too - below what `inexact` (the bits of a magnitude) says.
 template <int MB, int NB>
-__device__ __forceinline__ bool outside_split_range(const f32x16 (&acc)[MB][NB]) {
-    float nan = 0.f, big = 0.f;
+__device__ __forceinline__ bool outside_split_range(const f32x16 (&acc)[MB][NB], uint32_t inexact) {
+    float nan = 0.f;
+    // twice the magnitude's bits; where the parts are exact one less, so that zero is the largest
+    const uint32_t zero_passes = inexact == 0 ? ~0u : 0u;
+    uint32_t small = ~0u;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                nan = __builtin_fmaf(acc[mb][nb][v], 0.f, nan);
-                big = __builtin_fmaxf(big, __builtin_fabsf(acc[mb][nb][v]));
+                const float a = acc[mb][nb][v];   // (a bit cast of the vector's element itself takes element 0)
+                nan = __builtin_fmaf(a, 0.f, nan);
+                const uint32_t u = (__builtin_bit_cast(uint32_t, a) << 1) + zero_passes;
+                small = small < u ? small : u;
             }
-    return nan != 0.f || (big > 0.f && big < 0x1p-80f);
+    const uint32_t limit = __builtin_bit_cast(uint32_t, 0x1p-100f) << 1, other = inexact << 1;
+    return nan != 0.f || small < (limit > other ? limit : other);
 }
 
 // Workgroup barrier after this wavefront's LDS reads and writes are done; global requests stay in flight.
@@ -435,6 +496,9 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
         // then pairs of the gathered run
         constexpr int NCV = A_PASSES + KPT / 2;
         u32x4 bh, bm, bl;
+        SplitSeen seen;
+        // of tile number `it` of this workgroup
+        auto publish = [&](int it) { publish_seen(lds + Cfg::SEEN + ((it & 1) * Cfg::MOVERS + mw) * kSeenBytes, seen); };
         auto convert = [&](auto set_c, int i) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
             uint8_t *const A = lds + set * STAGE, *const B = A + Cfg::A_BYTES;
@@ -444,8 +508,8 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
                 if constexpr (Cfg::VECA) {
                     const f32x4 v = __builtin_bit_cast(f32x4, a_vec[set][i]);
                     uint32_t h0, m0, l0, h1, m1, l1;
-                    split_pair(v[0], v[1], h0, m0, l0);
-                    split_pair(v[2], v[3], h1, m1, l1);
+                    split_pair(v[0], v[1], h0, m0, l0, seen);
+                    split_pair(v[2], v[3], h1, m1, l1, seen);
                     if (!A_PARTIAL || row < BM) {
                         *reinterpret_cast<u32x2 *>(dst) = u32x2{h0, h1};
                         *reinterpret_cast<u32x2 *>(dst + PART) = u32x2{m0, m1};
@@ -453,7 +517,7 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
                     }
                 } else {
                     uint32_t h, m, l;
-                    split_pair(a_sca[set][i][0], a_sca[set][i][1], h, m, l);
+                    split_pair(a_sca[set][i][0], a_sca[set][i][1], h, m, l, seen);
                     if (!A_PARTIAL || row < BM) {
                         *reinterpret_cast<uint32_t *>(dst) = h;
                         *reinterpret_cast<uint32_t *>(dst + PART) = m;
@@ -463,7 +527,7 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
             } else {
                 const int q = i - A_PASSES;
                 uint32_t h, m, l;
-                split_pair(b_val[set][2 * q], b_val[set][2 * q + 1], h, m, l);
+                split_pair(b_val[set][2 * q], b_val[set][2 * q + 1], h, m, l, seen);
                 bh[q % 4] = h; bm[q % 4] = m; bl[q % 4] = l;
                 if (q % 4 == 3) {
                     uint8_t *const dst = B + jl * ROW + kpart * (KPT * 2) + (q / 4) * 16;
@@ -478,7 +542,8 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
         // One interval: request a step into `set` (its offsets are in registers), bring the offsets of the one after
         // (`first`: the next tile's first step) to registers, write the step before (other set).  Requests and conversions
         // alternate, so that the address unit works beside the vector unit and every request has a whole interval to arrive.
-        auto interval = [&](auto set_c, auto other_c, int tau, bool first) __attribute__((always_inline)) {
+        // `done`: the step written is the last one of the tile of that number (-1: of none).
+        auto interval = [&](auto set_c, auto other_c, int tau, bool first, int done) __attribute__((always_inline)) {
             if constexpr (Cfg::VECA)
                 a_off[0] = (uint32_t)(tau * BK + a_kk) < n_live ? (uint32_t)(tau * BK) * 4u : kOutOfRange;
             advance(first);
@@ -492,6 +557,7 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
                 __builtin_amdgcn_sched_barrier(0);
             });
             get_offsets();
+            if (done >= 0) publish(done);
             split_barrier();
         };
         // (what the first interval writes lands in a stage that is not read before it is written again)
@@ -505,16 +571,18 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
         setup_tile(tile_number(0));
         put_offsets();
         get_offsets();
-        for (int it = 1;; ++it) {
+        int it = 1;
+        for (;; ++it) {
             const int next = tile_number(it);
             for (int t = 0; t < nsteps; t += 2) {
-                interval(S0{}, S1{}, t, false);
-                interval(S1{}, S0{}, t + 1, t + 2 >= nsteps);
+                interval(S0{}, S1{}, t, false, t == 0 ? it - 2 : -1);
+                interval(S1{}, S0{}, t + 1, t + 2 >= nsteps, -1);
             }
             if (next >= tiles_total) break;
             setup_tile(next);
         }
         static_for<NCV>([&](auto ic) { convert(S1{}, decltype(ic)::value); });
+        publish(it - 1);
         split_barrier();
         split_barrier();                       // (the multipliers' last step passes one more)
         return;
@@ -534,7 +602,9 @@ __device__ __forceinline__ void f32s_body(const ConvKernelParams &p, uint32_t bl
         load_bias<MB>(p, krow0, l32, bvec);
         mult.zero();
         mult.steps(nsteps);
-        if (__any(outside_split_range<MB, NB>(mult.acc)))
+        // (written two barriers ago or more, and not again for two tiles)
+        const uint32_t inexact = inexact_below<Cfg::MOVERS>(lds + Cfg::SEEN + (it & 1) * Cfg::MOVERS * kSeenBytes, p.CRS);
+        if (__any(outside_split_range<MB, NB>(mult.acc, inexact)))
             sums_in_fp32<Cfg::SWAP, MB, NB>(p, mult.acc, krow0, col0, 0, p.ksteps > 0 ? p.CRS : 0, half, l32);
         const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, kBufferWord3);
         store_tile<Cfg::SWAP, MB, NB>(p, ybuf, mult.acc, bvec, krow0, col0, half, l32);

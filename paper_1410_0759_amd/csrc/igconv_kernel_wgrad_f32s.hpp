@@ -26,7 +26,8 @@ struct WgradSplitConfig {
     static constexpr int PART = BK * 2, ROW = 3 * PART + 16;
     static constexpr int A_BYTES = BM * ROW, B_BYTES = BN * ROW, STAGE = A_BYTES + B_BYTES;
     static constexpr int RING = BK * 8;                 // per moving wavefront: BK entries (offset in x, offset in dy)
-    static constexpr int LDS_USED = 2 * STAGE + MOVERS * RING;
+    static constexpr int SEEN = 2 * STAGE + MOVERS * RING;   // [parity of the (tile, range)][moving wavefront]
+    static constexpr int LDS_USED = SEEN + 2 * MOVERS * kSeenBytes;
     static constexpr int WGS = (160 * 1024) / LDS_USED >= 2 ? 2 : 1;   // workgroups per compute unit: one or two
     static constexpr int LDS_BYTES = (160 * 1024) / LDS_USED >= 3 ? 64 * 1024 : LDS_USED;
     static constexpr int WAVES_PER_SIMD = WGS * THREADS / 256;
@@ -215,12 +216,14 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_wgra
                 b_val[set][ps - AP][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, b_off[e], sb[ps - AP], 0));
             }
         };
+        SplitSeen seen;
+        auto publish = [&](int it) { publish_seen(lds + Cfg::SEEN + ((it & 1) * Cfg::MOVERS + mw) * kSeenBytes, seen); };
         auto convert = [&](auto set_c, int ps) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
             uint8_t *const dst = lds + set * STAGE + (ps < AP ? ps * RPP * ROW : Cfg::A_BYTES + (ps - AP) * RPP * ROW) + lrow * ROW + kp * 4;
             uint32_t h, m, l;
-            if (ps < AP) split_pair(a_val[set][ps][0], a_val[set][ps][1], h, m, l);
-            else split_pair(b_val[set][ps - AP][0], b_val[set][ps - AP][1], h, m, l);
+            if (ps < AP) split_pair(a_val[set][ps][0], a_val[set][ps][1], h, m, l, seen);
+            else split_pair(b_val[set][ps - AP][0], b_val[set][ps - AP][1], h, m, l, seen);
             *reinterpret_cast<uint32_t *>(dst) = h;
             *reinterpret_cast<uint32_t *>(dst + PART) = m;
             *reinterpret_cast<uint32_t *>(dst + 2 * PART) = l;
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_wgra
         using S0 = std::integral_constant<int, 0>;
         using S1 = std::integral_constant<int, 1>;
         // one interval: see igconv_kernel_f32s.hpp
-        auto interval = [&](auto set_c, auto other_c) __attribute__((always_inline)) {
+        auto interval = [&](auto set_c, auto other_c, int done) __attribute__((always_inline)) {
             advance();
             put_offsets();
             __builtin_amdgcn_sched_barrier(0);
@@ -240,6 +243,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_wgra
                 __builtin_amdgcn_sched_barrier(0);
             });
             get_offsets();
+            if (done >= 0) publish(done);
             split_barrier();
         };
         // (what the first interval writes lands in a stage that is not read before it is written again)
@@ -248,16 +252,18 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_wgra
 #pragma unroll
         for (int ps = 0; ps < BP; ++ps) b_val[1][ps][0] = b_val[1][ps][1] = 0.f;
         setup_tile(tile_number(0));
-        for (int it = 1;; ++it) {
+        int it = 1;
+        for (;; ++it) {
             const int next = tile_number(it);
             for (int t = 0; t < nsteps; t += 2) {
-                interval(S0{}, S1{});
-                interval(S1{}, S0{});
+                interval(S0{}, S1{}, t == 0 ? it - 2 : -1);
+                interval(S1{}, S0{}, -1);
             }
             if (next >= tiles_total) break;
             setup_tile(next);
         }
         static_for<NCV>([&](auto ic) { convert(S1{}, decltype(ic)::value); });
+        publish(it - 1);
         split_barrier();
         split_barrier();                       // (the multipliers' last step passes one more)
         return;
@@ -278,7 +284,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::WAVES_PER_SIMD) void igconv_wgra
         const int krow0 = t.m0 + wm * Cfg::TM, col0 = t.n0 + wn * Cfg::TN;
         mult.zero();
         mult.steps(nsteps);
-        if (__any(outside_split_range<MB, NB>(mult.acc))) {
+        const uint32_t inexact = inexact_below<Cfg::MOVERS>(lds + Cfg::SEEN + (it & 1) * Cfg::MOVERS * kSeenBytes, nsteps * BK);
+        if (__any(outside_split_range<MB, NB>(mult.acc, inexact))) {
             const int kb = t.split * nsteps * BK, ke = kb + nsteps * BK;
             wgrad_sums_in_fp32<Cfg>(p, mult.acc, krow0, col0, t.tap_h, t.tap_w, kb < p.CRS ? kb : p.CRS, ke < p.CRS ? ke : p.CRS, half, l32);
         }

@@ -86,9 +86,11 @@ def test_backward_data_outside_the_split_range(kind, prob):
 
 @pytest.mark.parametrize("kind", ["plain", "inf", "nan", "huge", "tiny"])
 @pytest.mark.parametrize("prob", [(4, 100, 15, 14, 70, 3, 3, (1, 1), (1, 1)), (3, 70, 9, 17, 130, 5, 2, (2, 0), (2, 1)),
-                                  (2, 33, 8, 8, 33, 1, 1, (0, 0), (1, 1)), (2, 130, 6, 5, 140, 3, 3, (1, 1), (1, 2))])
+                                  (2, 33, 8, 8, 33, 1, 1, (0, 0), (1, 1)), (2, 130, 6, 5, 140, 3, 3, (1, 1), (1, 2)),
+                                  (4, 100, 15, 14, 64, 3, 3, (1, 1), (1, 1)), (3, 128, 8, 8, 120, 1, 1, (0, 0), (1, 1))])
 def test_backward_filter_outside_the_split_range(kind, prob):
-    """Every tile shape of the split kernels, with and without a cut reduction."""
+    """Every tile shape of the split kernels - by the least padding of K and C: 96 x 128 twice, (the fp32 kernel's 64 x 64),
+    96 x 64 run as 128 x 64, 64 x 128, 128 x 128 - with and without a cut reduction."""
     gu = _gpu()
     N, C, H, W, K, R, S, pad, stride = prob
     rng = np.random.default_rng(9)
@@ -147,3 +149,89 @@ def test_strided_backward_data(prob, kind, layout):
             old = dx0 if beta else None
             want = oc.conv_backward_data(dy, w, (H, W), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dx_old=old)
             _same(gu.run_backward_data(dy, w, (H, W), pad, stride, mode, alpha, beta, old, "f32", layout, workspace=workspace), want, kind)
+
+
+# Operands so small that the second and third parts leave bfloat16's range, where the results do not show it: multiplied
+# by large ones, or beside rows or columns of ordinary size.
+# kind -> (scale of all of one operand, of all of the other one, of some rows of the product, of some of its columns)
+SMALL = {
+    "116 and 40": (-116, 40, 0, 0), "120 and 50": (-120, 50, 0, 0), "125 and 60": (-125, 60, 0, 0),
+    "50 and 120": (50, -120, 0, 0), "denormal": (-140, 20, 0, 0), "denormal and large": (-146, 110, 0, 0),
+    "rows": (0, 0, -120, 0), "rows at the bottom": (0, 0, -125, 0), "columns": (0, 0, 0, -120), "columns at the bottom": (0, 0, 0, -125),
+    "rows and columns": (0, 0, -60, -62), "denormal rows": (0, 0, -140, 0),
+}
+
+
+def _scaled(a, exponent):
+    """a * 2^exponent, rounded once (float holds the powers down to 2^-149 only)."""
+    return np.ldexp(a.astype(np.float64), exponent).astype(np.float32)
+
+
+def _check(got, want, magnitude, terms, what):
+    """Sums of `terms` products: as many roundings of half a unit of the sum of magnitudes, or of the denormal grid."""
+    err = np.abs(got - want)
+    bad = err > (terms + 8) * 2.0 ** -24 * magnitude + terms * 2.0 ** -149
+    assert not bad.any(), (what, int(bad.sum()), float((err / np.maximum(magnitude, 2.0 ** -149)).max()))
+
+
+@pytest.mark.parametrize("kind", SMALL)
+@pytest.mark.parametrize("swap", [False, True])
+def test_forward_with_small_operands(kind, swap):
+    import paper_1410_0759_amd as ig
+    gu = _gpu()
+    sx, sw, rows, cols = SMALL[kind]
+    for kid, name in enumerate(ig.kernel_names()):
+        if "split" not in name or "wgrad" in name or ("swap" in name) != swap:
+            continue
+        pad = (0, 0) if "nopad" in name else (1, 1)
+        x, w = wl.random_problem(11, 2, 48 if "patch" in name else 20, 11, 13, 70, 3, 3)
+        x, w = _scaled(x, sx), _scaled(w, sw)
+        w[3::7] = _scaled(w[3::7], rows)              # maps
+        x[1, :, :5] = _scaled(x[1, :, :5], cols)      # pixels
+        x = wl.with_layout(x, "NHWC" if swap else "NCHW")
+        print(kind, name, flush=True)
+        got, plan = gu.run(x, w, pad, (1, 1), 1, y_layout="NHWC" if swap else "NCHW", kernel=kid)
+        assert plan.kernelId == kid
+        _check(got, oc.conv_forward(x, w, pad=pad, mode=1), oc.conv_forward(np.abs(x), np.abs(w), pad=pad, mode=1), w[0].size, (kind, name))
+
+
+@pytest.mark.parametrize("kind", SMALL)
+@pytest.mark.parametrize("prob", [(16, 130, 32, 32, 24, 5, 5, (2, 2), (1, 1)),     # the general route
+                                  (40, 96, 14, 13, 32, 3, 3, (1, 1), (1, 1)),      # a staged patch of dy
+                                  (5, 101, 15, 23, 13, 3, 3, (1, 1), (2, 2))])     # four phases in one launch
+def test_backward_data_with_small_operands(prob, kind):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    sy, sw, rows, cols = SMALL[kind]
+    rng = np.random.default_rng(13)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    dy = _scaled(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), sy)
+    w = _scaled((rng.standard_normal(size=(K, C, R, S)) * (K * R * S) ** -0.5).astype(np.float32), sw)
+    w[:, 3::7] = _scaled(w[:, 3::7], rows)
+    dy[1, :, :5] = _scaled(dy[1, :, :5], cols)
+    print(kind, prob, flush=True)
+    got = gu.run_backward_data(dy, w, (H, W), pad, stride, 0, workspace="none")
+    want, mag = (oc.conv_backward_data(a, b, (H, W), pad=pad, stride=stride, mode=0) for a, b in ((dy, w), (np.abs(dy), np.abs(w))))
+    _check(got, want, mag, K * R * S, (kind, prob))
+
+
+@pytest.mark.parametrize("kind", SMALL)
+@pytest.mark.parametrize("prob", [(4, 100, 15, 14, 64, 3, 3, (1, 1), (1, 1)),      # 64 x 128 tiles
+                                  (3, 70, 9, 17, 130, 5, 2, (2, 0), (2, 1)),       # 96 x 128
+                                  (2, 33, 6, 5, 128, 3, 3, (1, 1), (1, 2)),        # 128 x 64
+                                  (3, 128, 8, 8, 120, 1, 1, (0, 0), (1, 1))])      # 128 x 128
+def test_backward_filter_with_small_operands(prob, kind):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    sy, sx, rows, cols = SMALL[kind]
+    rng = np.random.default_rng(14)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    x = _scaled(rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32), sx)
+    dy = _scaled(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), sy)
+    dy[:, 3::7] = _scaled(dy[:, 3::7], rows)
+    x[:, 2::5] = _scaled(x[:, 2::5], cols)
+    want, mag = (oc.conv_backward_filter(a, b, (R, S), pad=pad, stride=stride, mode=1) for a, b in ((x, dy), (np.abs(x), np.abs(dy))))
+    for workspace in ("full", "none"):
+        print(kind, prob, workspace, flush=True)
+        got = gu.run_backward_filter(x, dy, (R, S), pad, stride, 1, workspace=workspace)[0]
+        _check(got, want, mag, N * P * Q, (kind, prob, workspace))
