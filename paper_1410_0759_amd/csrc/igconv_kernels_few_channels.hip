@@ -137,16 +137,9 @@ __global__ __launch_bounds__(256, 4) void igconv_few_channels_kernel(const ConvK
 #pragma unroll
                     for (int k = 0; k < 8; ++k) out[k] += p.bias[m0 + b + k < p.K ? m0 + b + k : p.K - 1];
                 }
-                if (p.act == 0) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) out[k] = activate<0>(out[k]);
-                } else if (p.act == 1) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) out[k] = activate<1>(out[k]);
-                } else if (p.act == 2) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) out[k] = activate<2>(out[k]);
-                }
+                if (p.act == 0) activate<0>(out);
+                else if (p.act == 1) activate<1>(out);
+                else if (p.act == 2) activate<2>(out);
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, out[k]), ybuf, off[k], row[k], 0);
