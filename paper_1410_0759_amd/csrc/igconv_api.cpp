@@ -67,6 +67,38 @@ static long long out_dim(long long H, long long R, long long u, long long pad) {
     return (num + u - 1) / u;
 }
 
+// The table's rows by what a pass looks for, in the table's order; found once.  (Walking all rows through kernel_info took
+// half or more of a call's time on the host: strided backward-data plan 6.3 us, now 2.7; forward plans 0.8 to 1.9, now 0.2 to 1.4.)
+struct KernelList {
+    static constexpr int kMost = 256;
+    int count = 0;
+    int id[kMost];
+    const KernelInfo *info[kMost];
+    template <class Wanted>
+    explicit KernelList(Wanted wanted) {
+        for (int i = 0; i < kernel_count_all() && count < kMost; ++i) {
+            const KernelInfo *ki = kernel_info(i);
+            if (!wanted(*ki)) continue;
+            id[count] = i;
+            info[count++] = ki;
+        }
+    }
+};
+static bool is_backward_filter(const KernelInfo &ki) { return ki.gmode == 6 || ki.gmode == 8 || ki.gmode == 9 || ki.gmode == 10; }
+// 0: float, 1: bfloat16, 2: double
+static int type_index(bool bf16, bool f64) { return f64 ? 2 : (bf16 ? 1 : 0); }
+static const KernelList &kernels_of(bool bf16, bool f64, bool backward_filter) {
+    static const auto of = [](int type, bool bwf) {
+        return KernelList([=](const KernelInfo &ki) { return type_index(ki.bf16, ki.f64) == type && is_backward_filter(ki) == bwf; });
+    };
+    static const KernelList lists[2][3] = {{of(0, false), of(1, false), of(2, false)}, {of(0, true), of(1, true), of(2, true)}};
+    return lists[backward_filter ? 1 : 0][type_index(bf16, f64)];
+}
+static const KernelList &kernels_with_phases() {
+    static const KernelList list([](const KernelInfo &ki) { return ki.launchPhases != nullptr; });
+    return list;
+}
+
 struct Problem {
     ConvKernelParams kp;
     bool bf16;
@@ -301,7 +333,7 @@ static long long patch_pixels_bound(const ConvKernelParams &k, int bn) {
 // wavefront can request, and pad 0 or - with a tap mask per column - at most 31 taps.
 static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool x_aligned) {
     const int gmode = ki.gmode;
-    if (gmode == 6 || gmode == 8 || gmode == 9 || gmode == 10) return false;  // backward-filter kernels are chosen by that pass itself
+    if (is_backward_filter(ki)) return false;  // (chosen by that pass itself)
     if (gmode == 2) return k.pad_h == 0 && k.pad_w == 0;
     if (gmode == 1 && ki.variant == 6)   // whole 16-byte channel vectors in x (the filter's copy has them by construction)
         return x_aligned && k.C % 8 == 0 && k.xsC == 1 && k.xsN % 8 == 0 && k.xsH % 8 == 0 && k.xsW % 8 == 0;
@@ -352,11 +384,13 @@ static igcStatus choose(const igcContext *h, const Problem &pr, bool w_aligned, 
     }
     int best = -1;
     double best_cost = 0;
-    const int offered = pr.filter_inner ? kernel_count_all() : kernel_count();
-    for (int id = 0; id < offered; ++id) {
-        const KernelInfo &ki = *kernel_info(id);
-        if (ki.bf16 != pr.bf16 || ki.f64 != pr.f64 || (ki.veca && !can_vec) || !gather_mode_ok(ki, k, x_aligned)) continue;
-        if (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u)) continue;
+    const int offered = pr.filter_inner ? INT_MAX : kernel_count();
+    const KernelList &list = kernels_of(pr.bf16, pr.f64, false);
+    for (int i = 0; i < list.count; ++i) {
+        const int id = list.id[i];
+        const KernelInfo &ki = *list.info[i];
+        if (id >= offered || (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u))) continue;
+        if ((ki.veca && !can_vec) || !gather_mode_ok(ki, k, x_aligned)) continue;
         // (more than 63 taps under a border: the forward pass stays with tap-major order, whose filter copy callers lend room for)
         if (ki.variant == 4 && ki.gmode == 14 && k.RS > 63 && pr.mode_mask == 0) continue;
         if (pr.no_teams && ((ki.variant == 2 && ki.gmode < 4) || is_direct(ki.gmode))) continue;
@@ -732,9 +766,10 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
         if (x->stride[d] % 8 != 0 || dy->stride[d] % 8 != 0) vectors = false;
     const bool unpadded = !by_tap && !f64 && cv->pad_h == 0 && cv->pad_w == 0;   // few channels, no padding: mode 9
     const int want_mode = vectors ? 10 : (by_tap ? 8 : (unpadded ? 9 : 6));
+    const KernelList &list = kernels_of(b16, f64, true);
     if (f64) {
-        for (int i = 0; i < kernel_count(); ++i)
-            if (kernel_info(i)->f64 && kernel_info(i)->gmode == 6) out->kernel_id = i;
+        for (int i = 0; i < list.count; ++i)
+            if (list.info[i]->gmode == 6) out->kernel_id = list.id[i];
         const KernelInfo &kf = *kernel_info(out->kernel_id);
         out->ksteps = (NPQ + kf.BK - 1) / kf.BK;
         out->tiles_n = (CRS + kf.BN - 1) / kf.BN;
@@ -752,9 +787,9 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
     const int want_bn = !by_tap ? 128 : ((dw->c - 1) % 128 < 64 ? 64 : 128);   // (least padding of C)
     int id = -1;
     for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
-        for (int i = 0; i < kernel_count(); ++i) {
-            const KernelInfo &ki = *kernel_info(i);
-            if (ki.gmode == want_mode && ki.bf16 == b16 && ki.BM == want_bm && ki.BN == want_bn) id = i;
+        for (int i = 0; i < list.count; ++i) {
+            const KernelInfo &ki = *list.info[i];
+            if (ki.gmode == want_mode && ki.BM == want_bm && ki.BN == want_bn) id = list.id[i];
         }
         if (id < 0) want_bm = 128;   // (not every tile shape exists with 96 rows)
     }
@@ -813,11 +848,12 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
     if (live < 2 || live > kMaxPhases) return -1;
     int best = -1;
     double best_cost = 0;
-    for (int id = 0; id < kernel_count_all(); ++id) {
-        const KernelInfo &ki = *kernel_info(id);
-        if (!ki.launchPhases || ki.veca) continue;
+    const KernelList &list = kernels_with_phases();
+    for (int i = 0; i < list.count; ++i) {
+        const int id = list.id[i];
+        const KernelInfo &ki = *list.info[i];
+        if (ki.veca) continue;
         double work = 0, longest = 0;
-        long long tiles = 0;
         bool ok = true;
         for (const PhaseLaunch &l : launches) {
             const ConvKernelParams &k = l.pr.kp;
@@ -831,7 +867,6 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
             const double steps = (double)kernel_steps(ki, k) + 2.0;
             const double c = ki.variant == 6 ? steps * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0)
                                              : steps * (0.70 * ki.BM + 25.0);
-            tiles += t;
             work += (double)t * c;
             longest = std::max(longest, c);
         }
