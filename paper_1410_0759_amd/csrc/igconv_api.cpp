@@ -1344,6 +1344,22 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     const int es = pr.bf16 ? 2 : (pr.f64 ? 8 : 4);
     if ((uintptr_t)x % es || (uintptr_t)w % es || (uintptr_t)y % (pr.f64 ? 8 : 4)) return IGC_STATUS_BAD_PARAM;
     if (pr.f64 && (bias || activation != IGC_ACTIVATION_IDENTITY)) return IGC_STATUS_NOT_SUPPORTED;
+    pr.kp.x = x;
+    pr.kp.w = w;
+    pr.kp.y = y;
+    if (pr.f64) {
+        pr.kp.alpha64 = *static_cast<const double *>(alpha);
+        pr.kp.beta64 = *static_cast<const double *>(beta);
+    } else {
+        pr.kp.alpha = *static_cast<const float *>(alpha);
+        pr.kp.beta = *static_cast<const float *>(beta);
+    }
+    pr.kp.bias = static_cast<const float *>(bias);
+    pr.kp.act = activation;
+    // A short reduction over few channels: the vector units, without a plan (never refused, at most 25 steps: never cut).  Planned
+    // all the same, twice with a workspace, a call that the GPU does in 5 us took 1.4 us more on the host.
+    if (handle->kernelOverride < 0 && few_channels(handle, pr))
+        return launch_few_channels(pr.kp, handle->computeUnits, handle->stream) == 0 ? IGC_STATUS_SUCCESS : IGC_STATUS_EXECUTION_FAILED;
     int id = -1;
     igcConvolutionForwardPlan plan;
     // With a workspace the reduction of a small problem is cut into ranges (below), finer than the team kernels
@@ -1373,18 +1389,6 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
         st = fill_plan(handle, id, &pr, &plan);
         if (st != IGC_STATUS_SUCCESS) return st;
     }
-    pr.kp.x = x;
-    pr.kp.w = w;
-    pr.kp.y = y;
-    if (pr.f64) {
-        pr.kp.alpha64 = *static_cast<const double *>(alpha);
-        pr.kp.beta64 = *static_cast<const double *>(beta);
-    } else {
-        pr.kp.alpha = *static_cast<const float *>(alpha);
-        pr.kp.beta = *static_cast<const float *>(beta);
-    }
-    pr.kp.bias = static_cast<const float *>(bias);
-    pr.kp.act = activation;
     // A small problem with a workspace: cut the reduction into ranges (see forward_split).
     int grid = plan.gridX;
     int splits = 1;
@@ -1406,11 +1410,6 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
             k.bias = nullptr;
             k.act = IGC_ACTIVATION_IDENTITY;
         }
-    }
-    // (a short reduction over few channels: the vector units)
-    if (splits <= 1 && handle->kernelOverride < 0 && few_channels(handle, pr)) {
-        if (launch_few_channels(pr.kp, handle->computeUnits, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
-        return IGC_STATUS_SUCCESS;
     }
     // Few channels, a zero border and room for x with the border written out: the copy is made and the pass runs
     // over it as a problem without a border (alpha, beta, bias and activation unchanged).
