@@ -789,7 +789,24 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
     for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
         for (int i = 0; i < list.count; ++i) {
             const KernelInfo &ki = *list.info[i];
-            if (ki.gmode == want_mode && ki.BM == want_bm && ki.BN == want_bn) id = list.id[i];
+    // Float tiles by tap of up to 96 x 128 come with split operands and with the fp32 instruction.  The split kernels' moving
+    // wavefronts set their pace, and each of their requests covers sixteen pairs of pixels.  Channels innermost, those are sixteen cache
+    // lines: the fp32 kernels are ahead unless the reduction is short.  In rows of pixels they lie apart under a horizontal
+    // stride, or in output rows of up to four: ahead with 64 filter maps per tile, and on short reductions with 128.  Measured, fp32
+    // and split, us.  Innermost: 40x75x75 -> 348, 3x3, stride 2, 41 images 371 and 506; 252x77x77 -> 68, 3x3, 8 images 234 and 336;
+    // 126x114x114 -> 33, 3x3 229 and 261; but 3 steps, 137 -> 272, 7x7 32 and 27.  Rows: stride 2, 249 -> 23, 5x5 79.5 and 92.5; 98 -> 290
+    // level; 128 maps, stride 3, 28 steps, 31 -> 80 20.2 and 23.3; stride 2, 2193 steps, 54 -> 98 104 and 93; rows of two, 30x6x6 -> 76,
+    // 5x5, 59 images 15.9 and 21.7.  Unit stride, longer rows: 91x58x58 -> 17, 5x5 79 and 66; 136 -> 68, 7x7 305 and 236.
+    const bool innermost = (x->stride[1] == 1 && x->stride[3] != 1) || (dy->stride[1] == 1 && dy->stride[3] != 1);
+    const long long steps32 = (NPQ + 31) / 32;
+    auto prefer_fp32 = [&](int bm, int bn) {
+        if (!by_tap || b16 || (bm == 128 && bn == 128)) return false;
+        if (innermost) return steps32 > 8;
+        return bm != 96 && (cv->v > 1 || (Q <= 4 && dw->r * dw->s > 1)) && (bm == 64 || steps32 < 64);
+    };
+            if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn) continue;
+            if (ki.variant == 4 && prefer_fp32(ki.BM, ki.BN)) continue;
+            id = list.id[i];   // (the split kernels come last)
         }
         if (id < 0) want_bm = 128;   // (not every tile shape exists with 96 rows)
     }

@@ -3,7 +3,8 @@
 #include "igconv_instantiate.hpp"
 #include "igconv_kernel_wgrad.hpp"
 
-// (float columns ordered (tap, channel): 64 x 64 tiles here, the larger ones in igconv_kernels_wgrad_f32_split.hip)
+// (float columns ordered (tap, channel): 128 x 128 tiles are in igconv_kernels_wgrad_f32_split.hip only; the others larger than
+// 64 x 64 there too, the rule between them in igconv_api.cpp)
 //    name, bf16, BM, BN, BK, WM, WN, gather mode
 #define IGC_WGRAD_LIST(X) \
     X("f32 64x128x32 wgrad", false, 64, 128, 32, 2, 2, GATHER_WGRAD) \
@@ -11,6 +12,9 @@
     X("bf16 64x128x32 wgrad", true, 64, 128, 32, 2, 2, GATHER_WGRAD) \
     X("bf16 128x128x32 wgrad", true, 128, 128, 32, 2, 2, GATHER_WGRAD) \
     X("f32 64x64x32 wgrad tap", false, 64, 64, 32, 2, 2, GATHER_WGRAD_TAP) \
+    X("f32 128x64x32 wgrad tap", false, 128, 64, 32, 2, 2, GATHER_WGRAD_TAP) \
+    X("f32 64x128x32 wgrad tap", false, 64, 128, 32, 2, 2, GATHER_WGRAD_TAP) \
+    X("f32 96x128x32 wgrad tap", false, 96, 128, 32, 1, 4, GATHER_WGRAD_TAP) \
     X("bf16 64x64x32 wgrad tap", true, 64, 64, 32, 2, 2, GATHER_WGRAD_TAP) \
     X("bf16 128x64x32 wgrad tap", true, 128, 64, 32, 2, 2, GATHER_WGRAD_TAP) \
     X("bf16 64x128x32 wgrad tap", true, 64, 128, 32, 2, 2, GATHER_WGRAD_TAP) \

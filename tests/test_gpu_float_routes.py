@@ -1,0 +1,48 @@
+"""Float passes on either side of the rules that choose between the fp32 instruction and operands in three bfloat16 parts:
+tiles of the backward filter, 32 and 33 output maps forward, phases together or apart in strided backward data, and a
+lent workspace beside a reduction of few steps."""
+import numpy as np
+import pytest
+
+from oracle import conv_oracle as oc
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, S, pad, stride, layout of x and dy                       tile, instruction
+    (2, 40, 11, 11, 100, 3, 3, (1, 1), (1, 1), "NHWC"),     # 242 pixels: 8 steps  128 x 64, parts
+    (3, 40, 11, 9, 100, 3, 3, (1, 1), (1, 1), "NHWC"),      # 297: 10 steps        128 x 64, fp32
+    (3, 100, 11, 9, 70, 3, 3, (1, 1), (1, 1), "NHWC"),      #                       96 x 128, fp32
+    (3, 100, 11, 9, 60, 1, 1, (0, 0), (1, 1), "NHWC"),      #                       64 x 128, fp32
+    (3, 128, 11, 9, 128, 1, 2, (0, 1), (1, 1), "NHWC"),     #                      128 x 128, parts
+    (5, 100, 13, 12, 40, 3, 3, (1, 1), (1, 2), "NCHW"),     # a stride along W      64 x 128, fp32
+    (5, 100, 13, 12, 40, 3, 3, (1, 1), (2, 1), "NCHW"),     # along H only          64 x 128, parts
+    (3, 40, 21, 63, 100, 1, 3, (0, 1), (1, 2), "NCHW"),     # 63 steps             128 x 64, fp32
+    (4, 40, 16, 63, 100, 1, 3, (0, 1), (1, 2), "NCHW"),     # 64 steps             128 x 64, parts
+    (9, 30, 6, 6, 76, 3, 3, (0, 0), (1, 1), "NCHW"),        # rows of four         128 x 64, fp32
+    (9, 30, 6, 4, 76, 1, 1, (0, 0), (1, 1), "NCHW"),        # (one tap)            128 x 64, parts
+    (9, 100, 6, 7, 76, 3, 3, (0, 0), (1, 2), "NCHW"),       #                       96 x 128, parts
+])
+def test_backward_filter(prob):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride, layout = prob
+    rng = np.random.default_rng(51)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    x, dy = (wl.with_layout(rng.uniform(-1, 1, size=s).astype(np.float32), layout) for s in ((N, C, H, W), (N, K, P, Q)))
+    dw0 = rng.uniform(-1, 1, size=(K, C, R, S)).astype(np.float32)
+    for mode, alpha, beta in ((0, 1.0, 0.0), (1, 0.5, -1.5)):
+        old = dw0 if beta else None
+        want = oc.conv_backward_filter(x, dy, (R, S), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dw_old=old)
+        for workspace in ("full", "none"):
+            print(prob, mode, workspace, flush=True)
+            got = gu.run_backward_filter(x, dy, (R, S), pad, stride, mode, alpha, beta, old, workspace=workspace)[0]
+            assert gu.rel_err(got, want) <= gu.BOUND["f32"]
