@@ -271,7 +271,11 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         // 128, 16 images): 243, fp32 cut 213.  Not offered either for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
         // 11x11, stride 4: 112 against 117 us at best, slower with other tiles).
         if ((ki.BM == 128 ? tiles * 2 < cus : tiles * 3 < cus * 2) || (!ki.veca && steps < 16)) return 1e300;
-        return tile_times * (double)steps * (double)ki.BN * ki.BK * (ki.gmode == 14 ? 0.70 * ki.BM + 25.0 : 0.66 * ki.BM + 18.0);
+        // At most 32 rows, where the fp32 kernels have a tile of 32: a seventh more, which prefers that tile and not the fp32 kernels
+        // with 64 rows.  Measured, split and fp32 kernel of 32 rows: 170x37x37 -> 9, 11x11 630 and 438; 290x120x120 -> 12, 3x3 83 and 62;
+        // 82x26x26 -> 10, 7x7, border 219 and 189; of 64 rows: 69x118x83 -> 22, 7x7, border 202 and 260.
+        return tile_times * (double)steps * (double)ki.BN * ki.BK * (ki.gmode == 14 ? 0.70 * ki.BM + 25.0 : 0.66 * ki.BM + 18.0) *
+               (k.K <= 32 ? 1.15 : 1.0);
     }
     const bool table = ki.gmode == 7 || ki.gmode == 11 || ki.gmode == 13;
     if (is_direct(ki.gmode)) {

@@ -46,3 +46,14 @@ def test_backward_filter(prob):
             print(prob, mode, workspace, flush=True)
             got = gu.run_backward_filter(x, dy, (R, S), pad, stride, mode, alpha, beta, old, workspace=workspace)[0]
             assert gu.rel_err(got, want) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("K", [9, 32, 33])
+@pytest.mark.parametrize("prob", [(24, 40, 37, 37, 5, (0, 0), "NCHW"), (24, 40, 33, 33, 5, (2, 2), "NCHW"), (24, 48, 37, 37, 3, (0, 0), "NHWC")])
+def test_forward_with_few_maps(prob, K):
+    gu = _gpu()
+    N, C, H, W, R, pad, layout = prob
+    x, w = wl.random_problem(52, N, C, H, W, K, R, R)
+    got, plan = gu.run(wl.with_layout(x, layout), w, pad, (1, 1), 1, y_layout=layout)
+    print(prob, K, plan.kernelId, flush=True)
+    assert gu.rel_err(got, oc.conv_forward(x, w, pad=pad, mode=1)) <= gu.BOUND["f32"]
