@@ -859,10 +859,14 @@ struct PhaseLaunch {
 // One kernel for all phases that meet a tap, to run in one launch: -1 when there are not two to kMaxPhases of them or no kernel
 // with such a launch accepts them all.  One phase alone is short and often leaves most of the chip idle; together they
 // share it, the longest first so that the short ones fill the end, and the float ones can use the split kernels whose
-// tiles are too large for a phase alone.  Measured, separate and joint launches (us), no size found where separate ones are ahead:
+// tiles are too large for a phase alone.  Measured, separate and joint launches (us):
 // float, 77x15x16 -> 101x29x31, 37 images 65 and 25; 512 -> 256x28x28, 32 images 257 and 156; 256 -> 128x28x28, one image
 // 78 and 43; 128 -> 64x112x112, 128 images 816 and 701; 24 -> 40x13x13, one image 28 and 9; bfloat16, 256 -> 128x56x56, 32
-// images 53 and 34; 1 image 128x28x28 36 and 15 (all 3x3 with stride 2).
+// images 53 and 34; 1 image 128x28x28 36 and 15 (all 3x3 with stride 2).  Separate ones are ahead only for float, up to 16 input
+// channels (a quarter of the rows of the smallest tile of a joint launch), many maps and the chip full several times over with one
+// phase's pixels along W: 307 -> 9x109x109, 57 images 358 and 490; 116 -> 2x53x53, 7x7, 126 images 363 and 492; with fewer
+// maps, 50 -> 14x74x74, 7x7 207 and 180, or tiles, 369 -> 9x59x59, 11x11, 17 images 1032 and 692, or channels innermost, 121 -> 4x35x35,
+// 11x11, 120 images 1023 and 616, they are not.
 static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &launches, bool dy_aligned) {
     long long live = 0;
     for (const PhaseLaunch &l : launches) live += l.pr.zero_steps ? 0 : 1;
@@ -875,6 +879,7 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
         const KernelInfo &ki = *list.info[i];
         if (ki.veca) continue;
         double work = 0, longest = 0;
+        long long tiles = 0;
         bool ok = true;
         for (const PhaseLaunch &l : launches) {
             const ConvKernelParams &k = l.pr.kp;
@@ -888,10 +893,13 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
             const double steps = (double)kernel_steps(ki, k) + 2.0;
             const double c = ki.variant == 6 ? steps * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0)
                                              : steps * (0.70 * ki.BM + 25.0);
+            tiles += t;
             work += (double)t * c;
             longest = std::max(longest, c);
         }
         if (!ok) continue;
+        const ConvKernelParams &first = launches.front().pr.kp;   // (the phases share rows and maps)
+        if (ki.variant == 4 && !ki.swap && first.K <= 16 && first.C >= 64 && tiles > 8ll * h->computeUnits) continue;
         const double cost = work / (double)h->computeUnits + 0.5 * longest;
         if (best < 0 || cost < best_cost) {
             best = id;

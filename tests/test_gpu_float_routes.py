@@ -57,3 +57,26 @@ def test_forward_with_few_maps(prob, K):
     got, plan = gu.run(wl.with_layout(x, layout), w, pad, (1, 1), 1, y_layout=layout)
     print(prob, K, plan.kernelId, flush=True)
     assert gu.rel_err(got, oc.conv_forward(x, w, pad=pad, mode=1)) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, layout: 3x3, stride 2; more than eight tiles per compute unit of 256
+    (9, 2, 172, 171, 64, "NCHW"),      # at most 16 rows, 64 maps: one launch per phase
+    (9, 2, 172, 171, 63, "NCHW"),      # together
+    (9, 2, 172, 171, 64, "NHWC"),      # together
+    (2, 17, 90, 91, 64, "NCHW"),       # together
+])
+def test_backward_data_phases(prob):
+    gu = _gpu()
+    N, C, H, W, K, layout = prob
+    rng = np.random.default_rng(53)
+    P, Q = oc.output_dim(H, 3, 2, 1), oc.output_dim(W, 3, 2, 1)
+    dy = wl.with_layout(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), layout)
+    w = (rng.standard_normal(size=(K, C, 3, 3)) * (K * 9) ** -0.5).astype(np.float32)
+    dx0 = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    for mode, beta in ((0, 0.0), (1, -1.5)):
+        print(prob, mode, flush=True)
+        old = dx0 if beta else None
+        want = oc.conv_backward_data(dy, w, (H, W), pad=(1, 1), stride=(2, 2), mode=mode, beta=beta, dx_old=old)
+        got = gu.run_backward_data(dy, w, (H, W), (1, 1), (2, 2), mode, 1.0, beta, old, "f32", layout, workspace="none")
+        assert gu.rel_err(got, want) <= gu.BOUND["f32"]
