@@ -1397,8 +1397,14 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     Magic mPitch, mK;
     const bool can_cut = workSpace && (uintptr_t)workSpace % 4 == 0 && !pr.f64 && 
                          magic_for(pr.kp.K > 1 ? (uint32_t)pr.kp.ysK : 1u, &mPitch) && magic_for((uint32_t)pr.kp.K, &mK);
+    st = choose(handle, pr, /*w_aligned=*/((uintptr_t)w % 16) == 0, /*x_aligned=*/((uintptr_t)x % 16) == 0, &id);
+    if (st != IGC_STATUS_SUCCESS) return st;
+    // Not where the 32 x 32 tiles of the kernels without LDS tiles need few steps per wavefront: the second launch costs more
+    // than the cut saves.  Uncut and cut, us: 16 steps, 816x3x4 -> 54, 1x1, 14 images 8.8 and 12.9; 16x50x30 -> 21, 7x7, 2 images 9.7 and 13.3;
+    // 24 steps 0.9 to 1.2 times, 48 and more up to 4 times as fast cut.
+    const bool short_direct = is_direct(kernel_info(id)->gmode) && direct_steps_per_wave(*kernel_info(id), pr.kp) <= 16;
     bool cut_found = false;
-    if (can_cut) {
+    if (can_cut && !short_direct) {
         Problem trial = pr;
         trial.no_teams = true;
         int tid_ = -1, per_ = 0;
@@ -1413,8 +1419,6 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
         }
     }
     if (!cut_found) {
-        st = choose(handle, pr, /*w_aligned=*/((uintptr_t)w % 16) == 0, /*x_aligned=*/((uintptr_t)x % 16) == 0, &id);
-        if (st != IGC_STATUS_SUCCESS) return st;
         st = fill_plan(handle, id, &pr, &plan);
         if (st != IGC_STATUS_SUCCESS) return st;
     }

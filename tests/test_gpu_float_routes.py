@@ -80,3 +80,22 @@ def test_backward_data_phases(prob):
         want = oc.conv_backward_data(dy, w, (H, W), pad=(1, 1), stride=(2, 2), mode=mode, beta=beta, dx_old=old)
         got = gu.run_backward_data(dy, w, (H, W), (1, 1), (2, 2), mode, 1.0, beta, old, "f32", layout, workspace="none")
         assert gu.rel_err(got, want) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("C", [756, 1200])      # 16 and 24 steps per wavefront
+def test_short_reduction_with_a_workspace(C, layout):
+    gu = _gpu()
+    x, w = wl.random_problem(54, 5, C, 8, 8, 12, 1, 1)
+    want = oc.conv_forward(x, w, mode=1)
+    g = gu.GpuConv(wl.with_layout(x, layout), w, (0, 0), (1, 1), 1, y_layout=layout)
+    g.lend_workspace(8 * want.size * 4)
+    g.prefill(value=float("nan"))
+    g.launch(1.0, 0.0)
+    print(C, layout, flush=True)
+    assert gu.rel_err(g.result(), want) <= gu.BOUND["f32"]
+    g.ws.result()
+    bias = np.linspace(-1, 1, 12).astype(np.float32)
+    g.prefill(value=float("nan"))
+    g.launch_fused(1.0, 0.0, bias, 1)
+    assert gu.rel_err(g.result(), np.maximum(want + bias[None, :, None, None], 0)) <= gu.BOUND["f32"]
