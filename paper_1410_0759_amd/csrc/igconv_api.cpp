@@ -789,10 +789,6 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
         if (pad_new <= pad_old) want_bm = bm;
     }
     const int want_bn = !by_tap ? 128 : ((dw->c - 1) % 128 < 64 ? 64 : 128);   // (least padding of C)
-    int id = -1;
-    for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
-        for (int i = 0; i < list.count; ++i) {
-            const KernelInfo &ki = *list.info[i];
     // Float tiles by tap of up to 96 x 128 come with split operands and with the fp32 instruction.  The split kernels' moving
     // wavefronts set their pace, and each of their requests covers sixteen pairs of pixels.  Channels innermost, those are sixteen cache
     // lines: the fp32 kernels are ahead unless the reduction is short.  In rows of pixels they lie apart under a horizontal
@@ -808,6 +804,10 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
         if (innermost) return steps32 > 8;
         return bm != 96 && (cv->v > 1 || (Q <= 4 && dw->r * dw->s > 1)) && (bm == 64 || steps32 < 64);
     };
+    int id = -1;
+    for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
+        for (int i = 0; i < list.count; ++i) {
+            const KernelInfo &ki = *list.info[i];
             if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn) continue;
             if (ki.variant == 4 && prefer_fp32(ki.BM, ki.BN)) continue;
             id = list.id[i];   // (the split kernels come last)
