@@ -516,12 +516,15 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
 //     stride 2 34.6 and 40.7
 //   four channels, 5x5, 1x4x32x32 -> 32: 6.0 and 8.2; eight channels, 3x3, 64x8x64x64 -> 64: 33 and 41
 //   y's maps next to each other, 32 bytes per thread's store: 1x3x64x64 -> 32 8.6 and 5.3; 32 images 21.9 and 26.3
-static bool few_channels(const igcContext *h, const Problem &pr) {
+//   5x5 with a border and room to write it out (`room`), maps that fill the matrix kernels' tiles: 16x3x32x32 -> 64 9.1 and 8.4, 32 images
+//     10.8 and 12.2; 32x3x32x32 -> 128 14.9 and 16.6; 48 maps 10.7 and 9.6; one channel, 64 images -> 128 20.4 and 15.8
+static bool few_channels(const igcContext *h, const Problem &pr, bool room) {
     const ConvKernelParams &k = pr.kp;
     if (pr.bf16 || pr.f64 || k.C > 4 || k.R != k.S || (k.R != 3 && k.R != 5) || k.CRS > 75 || k.K > 8 * 65535) return false;
     const long long results = (long long)k.NPQ * k.K, cus = h->computeUnits;
     if (k.ysK == 1 && k.K > 1) return results < cus * 2048;
     if (k.pad_h == 0 && k.pad_w == 0) return results <= cus * 4096;
+    if (room && k.R == 5 && k.C > 1 && k.K > 48 && results * k.CRS > cus * 600000) return false;
     if (results * k.CRS <= cus * 1536000 || k.K <= 16) return true;
     return k.R == 3 && results <= cus * 524288;
 }
@@ -1387,7 +1390,9 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     pr.kp.act = activation;
     // A short reduction over few channels: the vector units, without a plan (never refused, at most 25 steps: never cut).  Planned
     // all the same, twice with a workspace, a call that the GPU does in 5 us took 1.4 us more on the host.
-    if (handle->kernelOverride < 0 && few_channels(handle, pr))
+    const bool room = workSpace && (uintptr_t)workSpace % 16 == 0 &&
+                      workSpaceSizeInBytes / 4 >= (size_t)pr.kp.N * pr.kp.C * (pr.kp.H + 2 * pr.kp.pad_h) * (pr.kp.W + 2 * pr.kp.pad_w);
+    if (handle->kernelOverride < 0 && few_channels(handle, pr, room))
         return launch_few_channels(pr.kp, handle->computeUnits, handle->stream) == 0 ? IGC_STATUS_SUCCESS : IGC_STATUS_EXECUTION_FAILED;
     int id = -1;
     igcConvolutionForwardPlan plan;

@@ -99,3 +99,31 @@ def test_short_reduction_with_a_workspace(C, layout):
     g.prefill(value=float("nan"))
     g.launch_fused(1.0, 0.0, bias, 1)
     assert gu.rel_err(g.result(), np.maximum(want + bias[None, :, None, None], 0)) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, pad: few channels, on the vector units or with the border written out in the lent workspace
+    (31, 3, 33, 32, 64, 5, 2), (33, 3, 33, 32, 64, 5, 2),       # limit of 5x5 layers with more than 48 maps
+    (150, 3, 33, 32, 48, 5, 2),                                 # ... with 48: the general limit, above and below
+    (90, 3, 33, 32, 48, 5, 2),
+    (7, 4, 225, 100, 96, 3, 1), (24, 3, 225, 100, 256, 3, 1),   # 3x3, by the number of results
+    (11, 2, 100, 101, 41, 3, 0),                                # unpadded
+])
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+def test_few_channels_with_and_without_a_workspace(prob, layout):
+    gu = _gpu()
+    N, C, H, W, K, R, pad = prob
+    x, w = wl.random_problem(55, N, C, H, W, K, R, R)
+    images = sorted({0, N // 2, N - 1})   # (the oracle takes these; the others go through the same kernels)
+    want = oc.conv_forward(np.ascontiguousarray(x[images]), w, pad=(pad, pad), mode=1)
+    g = gu.GpuConv(wl.with_layout(x, layout), w, (pad, pad), (1, 1), 1, y_layout=layout)
+    for lent in (False, True):
+        if lent:
+            g.lend_workspace(N * C * (H + 2 * pad) * (W + 2 * pad) * 4)
+        g.prefill(value=float("nan"))
+        print(prob, layout, lent, flush=True)
+        g.launch(1.0, 0.0)
+        got = g.result()
+        assert np.isfinite(got).all() and gu.rel_err(got[images], want) <= gu.BOUND["f32"]
+        if lent:
+            g.ws.result()
