@@ -1,11 +1,12 @@
 """Benchmark: convolution forward effective TFLOP/s and fraction of the MI355X matrix peak.
 
 A step is one igcConvolutionForward call (the whole hot path) on one batch of seeded
-synthetic input already resident in HBM.  Prints ONE JSON line.  The headline workload
+synthetic input already resident in HBM.  Prints ONE JSON line, of a few kilobytes (`brief`);
+``--report FILE`` writes every section with all its fields.  The headline workload
 is the second entry of the workload list (large-kernel strided first layer, fp32); all five
-workloads are timed and reported inside "roofline" ("per_config": mean, median and minimum
-per launch, TFLOP/s, fraction of the matrix peak of the data type, parity error, kernel),
-with the measured rate of a register-only MFMA loop ("achievable_peak") beside the datasheet
+workloads are timed and reported inside "roofline" ("per_config": mean time per launch,
+TFLOP/s, fraction of the matrix peak of the data type, parity error; in the report also median, minimum
+and kernel), with the measured rate of a register-only MFMA loop ("achievable_peak") beside the datasheet
 peaks.  The CPU oracle is timed beside it on a bounded sample of the same workload as a
 stated baseline.
 """
@@ -548,6 +549,48 @@ def measured_traffic(workload, kernel):
     return entry.get("bytes_per_launch")
 
 
+def rounded(v):
+    """Floats to five significant digits, in nested lists and dictionaries."""
+    if isinstance(v, float):
+        return float("%.5g" % v)
+    if isinstance(v, dict):
+        return {k: rounded(e) for k, e in v.items()}
+    return [rounded(e) for e in v] if isinstance(v, list) else v
+
+
+def brief(out):
+    """The printed line: the headline result whole, of every other section one short row per entry (the whole report of
+    24 KB is more than tools that read a run's last line keep; ``--report FILE`` has it)."""
+    def rates(e, *keys):
+        return [e[k]["tflops"] for k in keys if k in e and isinstance(e[k], dict)]
+    line = {k: v for k, v in out.items() if not isinstance(v, (list, dict))}
+    line.pop("paper_context")
+    line["config"] = {k: out["config"][k] for k in ("workload", "kernel", "grid", "parallelism", "workspace_bytes")}
+    roof = out["roofline"]
+    line["roofline"] = {k: roof[k] for k in ("bound", "achieved", "peak", "unit", "frac", "traffic", "algorithmic_bytes", "ms_median", "ms_min",
+                                             "target_met", "achievable_peak", "achievable_peak_random_operands")}
+    line["roofline"]["per_config"] = [{k: r[k] for k in ("workload", "dtype", "ms", "tflops", "frac", "rel_err", "tolerance")} for r in roof["per_config"]]
+    line["cpu_baseline"] = out["cpu_baseline"]
+    line["device"] = out["device"]
+    if out["table2_layers"]:
+        line["table2_tflops"] = [r["tflops"] for r in out["table2_layers"]]
+    if out["table2_batch_sweep"]:
+        line["table2_mini_batch_tflops"] = dict(zip(map(str, out["table2_batch_sweep"]["mini_batches"]), out["table2_batch_sweep"]["mean_tflops"]))
+    if out["backward"]:
+        line["backward_data_filter_tflops"] = {r["workload"]: rates(r, "backward_data", "backward_filter") for r in out["backward"]}
+    if out["padded_filter_layers"]:
+        line["padded_forward_data_tflops"] = {r["shape"]: rates(r, "forward", "backward_data") for r in out["padded_filter_layers"]}
+    if out["small_mini_batch_layers"]:
+        line["small_mini_batch_us"] = {r["shape"]: r["ms"] * 1e3 for r in out["small_mini_batch_layers"]}
+    if out["other_functions"]:
+        line["other_functions_gb_per_s"] = {r["function"]: r["gb_per_s"] for r in out["other_functions"] if "gb_per_s" in r}
+    if out["double_precision"]:
+        line["double_forward_data_filter_tflops"] = [rates(r, "forward", "backward_data", "backward_filter") for r in out["double_precision"]]
+    line = rounded(line)
+    line["value"], line["ms_per_step"] = out["value"], out["ms_per_step"]
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -555,6 +598,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=100)
     ap.add_argument("--config", type=int, default=2, help="headline workload (1-5)")
     ap.add_argument("--only", action="store_true", help="time the headline workload only")
+    ap.add_argument("--report", default=None, help="file for the whole report, every section with all its fields")
     ap.add_argument("--no-batch-sweep", action="store_true", help="skip the mini-batch sweep over the Table-2 layers")
     ap.add_argument("--batch-sweep-only", action="store_true", help="time only that sweep")
     ap.add_argument("--no-table2", action="store_true", help="skip the paper's Table-2 layer collection")
@@ -734,7 +778,10 @@ def main():
         "paper_context": "paper Table 3: 0.99-1.52 TFLOP/s (23-35% of 4.29) on Tesla K40, 1.46-2.49 (30-51% of 4.95) "
                          "on GTX 980, fp32, its own Table-2 layers",
     }
-    print(json.dumps(out))
+    if args.report:
+        with open(args.report, "w") as fh:
+            json.dump(out, fh)
+    print(json.dumps(brief(out)))
 
 
 if __name__ == "__main__":
