@@ -455,6 +455,9 @@ typedef struct {
                         7 unpadded with tap offsets tabulated in LDS (short reductions) */
 } igcConvolutionForwardPlan;
 
+/* The plan is that of the kernel table.  Float 3x3 and 5x5 layers of up to four channels mostly run on a kernel outside the table
+ * (igcConvolutionForward without an override; see igcGetConvolutionForwardOptionalWorkspaceSize), and a lent workspace can
+ * change the route: the plan then names the kernel that an override or a larger layer of the kind would use. */
 igcStatus igcGetConvolutionForwardPlan(igcHandle_t handle,
                                        igcTensorDescriptor_t xDesc,
                                        igcFilterDescriptor_t wDesc,

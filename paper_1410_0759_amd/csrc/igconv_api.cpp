@@ -262,14 +262,14 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
     if (ki.variant == 4) {
         // Operands split into bfloat16 parts (igconv_kernel_f32s.hpp).  Per step the moving wavefronts' work - splitting
         // and gathering, a row's and a column's share - costs more than the MFMAs; measured, in the units of the line
-        // below: 0.66 per row and 18 per column without a border (96x64x64 -> 128, 9x9, 128 images: 64 rows 4.5 ms,
-        // 128 rows 4.0 ms, fp32 instruction 6.1 ms), 0.70 and 25 with the window test (96x27x27 -> 256, 5x5: 775 and
-        // 637 us against 877).  Not offered where more than a
+        // below: 0.66 per row and 18 per column without a border (96x64x64 -> 128, 9x9, 128 images: 64 rows 4.65 ms,
+        // 128 rows 4.15 ms, fp32 instruction 6.0 ms), 0.70 and 25 with the window test (96x27x27 -> 256, 5x5: 802 and
+        // 654 us against 880).  Not offered where more than a
         // third of the compute units would idle (half with 128 rows, which make up for it per tile): the fp32 kernels' smaller
-        // tiles, teams and cut reductions win there.  96x27x27 -> 256, 5x5, 16 images: 128 rows on 184 units 94 us, 64 rows on
-        // all twice 116; 64x32x32 -> 128, 9x9, 24 images, 216 tiles of 64 rows: 125, fp32 teams 174; 144 tiles (128x32x32 ->
-        // 128, 16 images): 243, fp32 cut 213.  Not offered either for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
-        // 11x11, stride 4: 112 against 117 us at best, slower with other tiles).
+        // tiles, teams and cut reductions win there.  96x27x27 -> 256, 5x5, 16 images: 128 rows on 184 units 101 us, 64 rows on
+        // all twice 124; 64x32x32 -> 128, 9x9, 24 images, 216 tiles of 64 rows: 138, fp32 teams 191; 144 tiles (128x32x32 ->
+        // 128, 16 images): 271, fp32 cut 213.  Not offered either for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
+        // 11x11, stride 4, 64 images: 107 us at best against 112, with other tiles 125 and 175).
         if ((ki.BM == 128 ? tiles * 2 < cus : tiles * 3 < cus * 2) || (!ki.veca && steps < 16)) return 1e300;
         // At most 32 rows, where the fp32 kernels have a tile of 32: a seventh more, which prefers that tile and not the fp32 kernels
         // with 64 rows.  Measured, split and fp32 kernel of 32 rows: 170x37x37 -> 9, 11x11 630 and 438; 290x120x120 -> 12, 3x3 83 and 62;
@@ -863,8 +863,8 @@ struct PhaseLaunch {
 // with such a launch accepts them all.  One phase alone is short and often leaves most of the chip idle; together they
 // share it, the longest first so that the short ones fill the end, and the float ones can use the split kernels whose
 // tiles are too large for a phase alone.  Measured, separate and joint launches (us):
-// float, 77x15x16 -> 101x29x31, 37 images 65 and 25; 512 -> 256x28x28, 32 images 257 and 156; 256 -> 128x28x28, one image
-// 78 and 43; 128 -> 64x112x112, 128 images 816 and 701; 24 -> 40x13x13, one image 28 and 9; bfloat16, 256 -> 128x56x56, 32
+// float, 77x15x16 -> 101x29x31, 37 images 65 and 26; 512 -> 256x28x28, 32 images 217 and 160; 256 -> 128x28x28, one image
+// 77 and 44; 128 -> 64x112x112, 128 images 820 and 715; 24 -> 40x13x13, one image 29 and 10; bfloat16, 256 -> 128x56x56, 32
 // images 53 and 34; 1 image 128x28x28 36 and 15 (all 3x3 with stride 2).  Separate ones are ahead only for float, up to 16 input
 // channels (a quarter of the rows of the smallest tile of a joint launch), many maps and the chip full several times over with one
 // phase's pixels along W: 307 -> 9x109x109, 57 images 358 and 490; 116 -> 2x53x53, 7x7, 126 images 363 and 492; with fewer

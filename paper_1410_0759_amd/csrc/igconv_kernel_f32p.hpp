@@ -10,10 +10,10 @@
 // channel k, the taps walked backwards); they are loaded once per 16 channels - 16 + 16 + 4 bytes - and handed out tap by
 // tap from registers.  (A forward row's 72 floats of eight channels as eighteen aligned 16-byte loads: 2 to 9 % slower.)
 //
-// Measured, fp32 instruction -> this kernel: 128x64x56x56 -> 64 229 -> 163 us, 128x384x13x13 -> 256 298 -> 199, 64x128x28x28 -> 128
-// 122 -> 78, 128x512x7x7 -> 512 262 -> 139, 32x256x14x14 -> 256 72 -> 48; 64x64x56x56 -> 64 channel-fastest 236 -> 96; error against 64
-// bits 3.4e-7 -> 1.3e-7 on the first.  What bounds it: power.  On zeros the first takes 122 us (the clocks stay up), and 115
-// with the movers requesting and splitting nothing; 17 us are the tiles' epilogues.
+// Measured, best kernel with the fp32 instruction -> this one: 128x64x56x56 -> 64 223 -> 149 us, 128x384x13x13 -> 256 293 -> 198,
+// 64x128x28x28 -> 128 120 -> 74, 128x512x7x7 -> 512 261 -> 140, 32x256x14x14 -> 256 69 -> 49; 64x64x56x56 -> 64 channel-fastest 236 -> 89; error
+// against 64 bits 3.4e-7 -> 1.3e-7 on the first.  What bounds it: power.  On zeros the first took 122 us where it took 163 on data
+// (the clocks stay up), and 115 with the movers requesting and splitting nothing; 17 us were the tiles' epilogues.
 //
 // Four multiplying and four moving wavefronts, one workgroup per compute unit (LDS), persistent.  A step is three taps of
 // 16 channels, one barrier each:

@@ -9,8 +9,9 @@
 // beside it), v_mfma_f32_32x32x16_bf16 gives 2517: six of the latter do the work of eight of the former in 192 cycles
 // instead of 512, and the vector unit stays free for the gather and for the splitting.  Error against 64-bit results:
 // smaller than the fp32 instruction's, because the large sums are rounded once per 16 reduction indices.  Measured, 128
-// images, fp32 instruction -> this kernel: 384x13x13 -> 256, 3x3 298 -> 263 us, error 7.9e-7 -> 2.7e-7; 96x27x27 -> 256, 5x5 881 ->
-// 640 us, 6.6e-7 -> 2.2e-7; 96x64x64 -> 128, 9x9 6.1 -> 4.1 ms, 1.2e-6 -> 4.2e-7.
+// images, fp32 instruction -> this kernel: 384x13x13 -> 256, 3x3 293 -> 268 us, error 7.9e-7 -> 2.7e-7; 96x27x27 -> 256, 5x5 880 ->
+// 654 us, 6.6e-7 -> 2.2e-7; 96x64x64 -> 128, 9x9 6.0 -> 4.15 ms, 1.2e-6 -> 4.2e-7.  (Published: Henry, Tang, Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019.)
 //
 // Division of labour, as in igconv_kernel_bf16s.hpp: four multiplying wavefronts (operand fragments from LDS, MFMAs,
 // epilogue) and MOVERS moving ones (gather, splitting, LDS writes), one barrier per step of BK reduction indices.
@@ -29,8 +30,9 @@
 // says that something was lost, less than 2^-133; the movers gather those, and the largest magnitude (SplitSeen).  A sum of n
 // products of a tile that lost something is off by less than n * 2^-132 times the largest operand.  A wavefront some of whose
 // sums are smaller than 2^24 times that - half a unit of their last place - multiplies its blocks again with the fp32
-// instruction straight from global memory (slow, rare, no LDS, no barrier), as it does where a sum is not finite, or not zero
-// but below 2^-100.
+// instruction straight from global memory (no LDS, no barrier), as it does where a sum is not finite, or not zero but below
+// 2^-100.  Slow where it happens: with every sum NaN, 96x64x64 -> 128, 9x9, 32 images 1.2 -> 5.5 ms, backward filter 1.4 -> 8.1 ms;
+// 128x384x13x13 -> 256, 3x3 0.20 -> 1.18 ms.
 #ifndef IGCONV_KERNEL_F32S_HPP_
 #define IGCONV_KERNEL_F32S_HPP_
 
@@ -111,7 +113,8 @@ struct SplitConfig {
     static constexpr int RING = BK * 12;                // per moving wavefront: BK entries (offset, tap), BK filter offsets
     static constexpr int SEEN = 2 * STAGE + MOVERS * RING;   // [parity of the tile][moving wavefront]
     static constexpr int LDS_USED = SEEN + 2 * MOVERS * kSeenBytes;
-    // workgroups per compute unit: one or two (three would leave a wavefront 85 registers); the allocation says so
+    // workgroups per compute unit: one or two (three would leave a wavefront 85 registers); the allocation says so.  (Two, the
+    // 64 x 128 tiles: 128 registers, a dozen of the multiplying wavefronts' values spill to scratch around the epilogue.)
     static constexpr int WGS = (160 * 1024) / LDS_USED >= 2 ? 2 : 1;
     static constexpr int LDS_BYTES = (160 * 1024) / LDS_USED >= 3 ? 64 * 1024 : LDS_USED;
     static constexpr int WAVES_PER_SIMD = WGS * THREADS / 256;

@@ -67,10 +67,10 @@ int launch_filter_exchange(const void *w, void *wt, int K, int C, int taps, void
 int launch_filter_taps_outer(const void *w, void *wt, int elem_bytes, int K, int C, int RS, bool exchange, Magic mInner, Magic mRS,
                              void *stream);
 
-// xp = x with its zero border written out, packed N,C,H+2pad_h,W+2pad_w (float; x read through the strides xs).
 // A forward pass with a short reduction on the vector units (igconv_kernels_few_channels.hip): float, 3x3 or 5x5,
 // at most four channels.
 int launch_few_channels(const ConvKernelParams &p, int computeUnits, void *stream);
+// xp = x with its zero border written out, packed N,C,H+2pad_h,W+2pad_w (float; x read through the strides xs).
 int launch_pad_image(const float *x, float *xp, int N, int C, int H, int W, int pad_h, int pad_w, const long long xs[4], Magic mWp,
                      Magic mHp, Magic mC, void *stream);
 

@@ -2,9 +2,10 @@
 // bfloat16 parts (why, and what it does to the error: igconv_kernel_f32s.hpp, whose multiplying half this kernel uses as
 // it is).  Rows are feature maps k of dy, columns (tap, channel) with one tap per column tile (gather mode 8), the reduction runs over
 // output pixels (n,p,q) and is cut into ranges, one (tile, range) after another per workgroup (igconv_kernel_wgrad.hpp).
-// Measured, 128 images, fp32 instruction -> this kernel: 384x13x13 -> 256, 3x3 320 -> 235 us; 96x27x27 -> 256, 5x5 1151 -> 822;
-// 96x64x64 -> 128, 9x9 8.0 -> 5.6 ms; error against 64 bits 1.0e-6 -> 5.0e-7, 1.7e-6 -> 8.7e-7, 2.5e-6 -> 1.2e-6.  64 x 64 tiles
-// (64 maps and channels) are level (250 us) and few channels (11x11, stride 4, columns (c,r,s)) slower (127 -> 142): not built.
+// Measured, 128 images, fp32 instruction -> this kernel: 384x13x13 -> 256, 3x3 320 -> 240 us; 96x27x27 -> 256, 5x5 1151 -> 837;
+// 96x64x64 -> 128, 9x9 8.0 -> 5.9 ms; error against 64 bits 1.0e-6 -> 5.0e-7, 1.7e-6 -> 8.7e-7, 2.5e-6 -> 1.2e-6.  64 x 64 tiles
+// (64 maps and channels) were level (250 us) and few channels (11x11, stride 4, columns (c,r,s)) slower (127 -> 142): not built.
+// Where the fp32 kernels stay ahead (channels innermost, strides, narrow rows): see validate_backward_filter in igconv_api.cpp.
 //
 // Movers: 16 lanes stand for a step's 32 reduction indices, two consecutive ones each, so that a pair becomes one dword
 // of each part; four rows (columns) per request.  The two indices' offsets in dy and in x (tap shift and window test

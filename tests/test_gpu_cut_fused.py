@@ -47,3 +47,31 @@ def test_bias_and_activation(prob, layout):
     g.prefill(y0)
     g.launch_fused(0.5, -1.5, None, 1)
     assert np.abs(g.result() - np.maximum(0.5 * want - 1.5 * y0, 0)).max() <= gu.BOUND["f32"] * np.abs(want).max() + 2.0 ** -20
+
+
+@pytest.mark.parametrize("order", ["nkpq", "npqk", "knpq", "kpqn", "pqnk", "pkqn"])
+@pytest.mark.parametrize("prob", [(2, 512, 5, 7, 36, 3, (1, 1)), (3, 300, 5, 5, 33, 3, (0, 1))])
+def test_packed_orders_of_y(prob, order):
+    """The map of an element follows from its place in y, whatever the order of the dimensions."""
+    gu = _gpu()
+    N, C, H, W, K, R, pad = prob
+    x, w = wl.random_problem(33, N, C, H, W, K, R, R)
+    rng = np.random.default_rng(34)
+    bias = rng.uniform(-1, 1, size=K).astype(np.float32)
+    want = oc.conv_forward(x, w, pad=pad, mode=1)
+    y0 = rng.uniform(-1, 1, size=want.shape).astype(np.float32)
+    sizes, strides, step = dict(zip("nkpq", want.shape)), {}, 1
+    for d in reversed(order):
+        strides[d], step = step, step * sizes[d]
+    g = gu.GpuConv(x, w, pad, (1, 1), 1, y_strides=tuple(strides[d] for d in "nkpq"))
+    print(prob, order, flush=True)
+    plain = np.empty(0)
+    for lent in (0, 4 * want.size * 4):
+        if lent:
+            g.lend_workspace(lent)
+        g.prefill(y0)
+        g.launch_fused(0.5, -1.5, bias, 2)
+        got = g.result()
+        assert np.abs(got - np.tanh(0.5 * want - 1.5 * y0 + bias[None, :, None, None])).max() <= gu.BOUND["f32"] * np.abs(want).max() + 2.0 ** -20
+        plain = got if not lent else plain
+    assert plain.size and not np.array_equal(got, plain)   # (the sums of the ranges round otherwise: the cut took place)
