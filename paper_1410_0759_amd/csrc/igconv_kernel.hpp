@@ -223,7 +223,8 @@ __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_b
             } else {
                 // the row of register 0 (none beyond NPQ) and its offset; the others add scalars.  (Row times stride per register
                 // kept 16 products per block row alive over all columns: 146 -> 185 registers in the bf16 64 x 128 kernels, whose
-                // loops the compiler then schedules for two wavefronts per SIMD instead of three: 120x28x28 -> 296, 5x5, 3 images 89 -> 121 us.)
+                // loops the compiler then schedules for two wavefronts per SIMD instead of three: 120x28x28 -> 296, 5x5, 3 images 89 -> 121 us.
+                // The register's number is added to the row: taken off K it is a scalar per register: 53 spilled in the table-driven 96 x 128 kernel, 6 now.)
                 const int row = pv ? krow0 + 4 * half : p.K;
                 const uint32_t first = (poff + (uint32_t)row * (uint32_t)p.ysK) * 4u;
 #pragma unroll
@@ -231,7 +232,7 @@ __device__ __forceinline__ void store_tile(const ConvKernelParams &p, __amdgpu_b
                     block(acc[mb][nb],
                           [&](int v) {
                               const int r0 = mb * 32 + 8 * (v / 4) + (v % 4);
-                              return row < p.K - r0 ? first + (uint32_t)r0 * ((uint32_t)p.ysK * 4u) : kOutOfRange;
+                              return row + r0 < p.K ? first + (uint32_t)r0 * ((uint32_t)p.ysK * 4u) : kOutOfRange;
                           },
                           [&](int) { return 0u; }, [&](int v) { return row_bias(mb, v); });
             }
