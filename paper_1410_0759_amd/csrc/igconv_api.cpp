@@ -442,8 +442,12 @@ static long long padded_copy_bytes(const KernelInfo &ki, const Problem &pr, igcT
 // compute unit holds ceil(tiles*s/256) workgroups, which share its MFMA pipes, each taking
 // its range plus a fixed start-up/epilogue share (about 6 steps); cutting adds the summing
 // pass (about 12).  Cutting must win by a tenth, or it is not done.
+// With `rewritten` the uncut pass would read a rewritten filter and the ranges would not: a step of it takes 0.4 to 0.9 of the time,
+// and on reductions that are not short cutting must win by 0.3.  (120 tap-major layers, both forced.  Model up to 0.7: cut faster in all
+// float layers and all but three of bfloat16; 528x56x35 -> 124, 9x9, 2 images 1544 us cut, 2297 uncut.  Above: uncut faster or level in all
+// but one, of 24 steps (15 and 25); 129x16x16 -> 377, 7x7, stride 2, 32 images 308 and 211; 165x29x29 -> 510, 11x11, 30 images 3993 and 1479.)
 static int forward_split(const igcContext *h, const KernelInfo &ki, const ConvKernelParams &k, bool packed_y, long long max_parts,
-                         int *per_out) {
+                         int *per_out, bool rewritten = false) {
     const long long cus = h->computeUnits;
     *per_out = (k.ksteps + 1) & ~1;
     if ((ki.gmode > 3 && ki.gmode != 14) || ki.variant == 2 || ki.variant >= 4 || !packed_y) return 1;
@@ -457,7 +461,7 @@ static int forward_split(const igcContext *h, const KernelInfo &ki, const ConvKe
     long long best = 1;
     for (long long s = 2; s <= smax; ++s)
         if (cost(s) < cost(best)) best = s;
-    if (best == 1 || cost(best) > 0.9 * cost(1)) return 1;
+    if (best == 1 || cost(best) > (rewritten && k.ksteps >= 48 ? 0.7 : 0.9) * cost(1)) return 1;
     long long per = (k.ksteps + best - 1) / best;
     per += per & 1;
     *per_out = (int)per;
@@ -1408,46 +1412,46 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     // than the cut saves.  Uncut and cut, us: 16 steps, 816x3x4 -> 54, 1x1, 14 images 8.8 and 12.9; 16x50x30 -> 21, 7x7, 2 images 9.7 and 13.3;
     // 24 steps 0.9 to 1.2 times, 48 and more up to 4 times as fast cut.
     const bool short_direct = is_direct(kernel_info(id)->gmode) && direct_steps_per_wave(*kernel_info(id), pr.kp) <= 16;
-    bool cut_found = false;
+    // Uncut, tap-major order with a lent workspace of the filter's size: see below.
+    auto rewrites_filter = [&]() {
+        return kernel_info(id)->gmode == 1 && !pr.f64 && pr.kp.RS > 1 && workSpace && (uintptr_t)workSpace % 16 == 0 &&
+               workSpaceSizeInBytes >= (size_t)pr.kp.w_bytes;
+    };
+    int splits = 1, per = 0;
     if (can_cut && !short_direct) {
         Problem trial = pr;
         trial.no_teams = true;
-        int tid_ = -1, per_ = 0;
+        int tid_ = -1;
         if (choose(handle, trial, ((uintptr_t)w % 16) == 0, ((uintptr_t)x % 16) == 0, &tid_) == IGC_STATUS_SUCCESS &&
             fill_plan(handle, tid_, &trial, &plan) == IGC_STATUS_SUCCESS) {
             const bool packed = extent(yDesc->dim, yDesc->stride) == (long long)trial.kp.K * trial.kp.NPQ;
-            if (forward_split(handle, *kernel_info(tid_), trial.kp, packed, (long long)(workSpaceSizeInBytes / trial.kp.y_bytes), &per_) > 1) {
+            splits = forward_split(handle, *kernel_info(tid_), trial.kp, packed, (long long)(workSpaceSizeInBytes / trial.kp.y_bytes), &per,
+                                   rewrites_filter());
+            if (splits > 1) {
                 pr = trial;
                 id = tid_;
-                cut_found = true;
             }
         }
     }
-    if (!cut_found) {
+    if (splits <= 1) {
         st = fill_plan(handle, id, &pr, &plan);
         if (st != IGC_STATUS_SUCCESS) return st;
     }
     // A small problem with a workspace: cut the reduction into ranges (see forward_split).
     int grid = plan.gridX;
-    int splits = 1;
-    if (can_cut) {
+    if (splits > 1) {
         ConvKernelParams &k = pr.kp;
-        const bool packed = extent(yDesc->dim, yDesc->stride) == (long long)k.K * k.NPQ;
-        int per;
-        splits = forward_split(handle, *kernel_info(id), k, packed, (long long)(workSpaceSizeInBytes / k.y_bytes), &per);
-        if (splits > 1) {
-            k.splits = splits;
-            k.stepsPerSplit = per;
-            k.ySplitBytes = k.y_bytes;
-            k.tilesPerXcd = (int)(((long long)k.tilesM * k.tilesN * splits + kXcds - 1) / kXcds);
-            k.wgsPerXcd = workgroups_per_xcd(handle, *kernel_info(id), k.tilesPerXcd);
-            grid = kXcds * k.wgsPerXcd;
-            k.y = workSpace;
-            k.alpha = 1.f;
-            k.beta = 0.f;
-            k.bias = nullptr;
-            k.act = IGC_ACTIVATION_IDENTITY;
-        }
+        k.splits = splits;
+        k.stepsPerSplit = per;
+        k.ySplitBytes = k.y_bytes;
+        k.tilesPerXcd = (int)(((long long)k.tilesM * k.tilesN * splits + kXcds - 1) / kXcds);
+        k.wgsPerXcd = workgroups_per_xcd(handle, *kernel_info(id), k.tilesPerXcd);
+        grid = kXcds * k.wgsPerXcd;
+        k.y = workSpace;
+        k.alpha = 1.f;
+        k.beta = 0.f;
+        k.bias = nullptr;
+        k.act = IGC_ACTIVATION_IDENTITY;
     }
     // Few channels, a zero border and room for x with the border written out: the copy is made and the pass runs
     // over it as a problem without a border (alpha, beta, bias and activation unchanged).
@@ -1478,8 +1482,7 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     // Tap-major order with a lent workspace of the filter's size: the filter is first rewritten with the channel
     // index innermost (wt[k][t][c]) and read through those strides - a step's filter elements are then contiguous
     // instead of R*S apart (a 5x5 layer with 96 channels: 74 -> 129 TFLOP/s).  Same sums in the same order.
-    if (splits <= 1 && kernel_info(id)->gmode == 1 && !pr.f64 && pr.kp.RS > 1 && workSpace &&
-        (uintptr_t)workSpace % 16 == 0 && workSpaceSizeInBytes >= (size_t)pr.kp.w_bytes) {
+    if (splits <= 1 && rewrites_filter()) {
         // (bfloat16 with contiguous channels: the kernel that reads channel vectors of both operands)
         Problem inner = pr;
         int inner_id = -1;

@@ -1,6 +1,6 @@
 """Float passes on either side of the rules that choose between the fp32 instruction and operands in three bfloat16 parts:
 tiles of the backward filter, 32 and 33 output maps forward, phases together or apart in strided backward data, and a
-lent workspace beside a reduction of few steps."""
+lent workspace beside a reduction of few steps or in tap-major order."""
 import numpy as np
 import pytest
 
@@ -99,6 +99,33 @@ def test_short_reduction_with_a_workspace(C, layout):
     g.prefill(value=float("nan"))
     g.launch_fused(1.0, 0.0, bias, 1)
     assert gu.rel_err(g.result(), np.maximum(want + bias[None, :, None, None], 0)) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, pad, stride, layout; is the reduction cut?
+    (5, 52, 44, 44, 53, 7, 3, 1, "NCHW", False),    # 152 tiles: the rewritten filter gains more
+    (40, 45, 37, 37, 174, 11, 5, 4, "NCHW", False),   # 192
+    (2, 73, 14, 14, 159, 9, 4, 1, "NCHW", True),    # 20 tiles
+])
+def test_tap_major_with_a_workspace(prob):
+    gu = _gpu()
+    N, C, H, W, K, R, pad, stride, layout, cut = prob
+    x, w = wl.random_problem(56, N, C, H, W, K, R, R)
+    images = sorted({0, N - 1})
+    want = oc.conv_forward(np.ascontiguousarray(x[images]), w, pad=(pad, pad), stride=(stride, stride), mode=1)
+    bias = np.linspace(-1, 1, K).astype(np.float32)
+    g = gu.GpuConv(wl.with_layout(x, layout), w, (pad, pad), (stride, stride), 1, y_layout=layout)
+    results = []
+    for lent in (False, True):
+        if lent:
+            g.lend_workspace(max(64 * N * K * want.shape[2] * want.shape[3] * 4, w.size * 4))
+        g.prefill(value=float("nan"))
+        print(prob, lent, flush=True)
+        g.launch_fused(1.0, 0.0, bias, 1)
+        results.append(g.result())
+        assert gu.rel_err(results[-1][images], np.maximum(want + bias[None, :, None, None], 0)) <= gu.BOUND["f32"]
+    g.ws.result()
+    assert np.array_equal(*results) == (not cut)     # (uncut: the same sums in the same order)
 
 
 @pytest.mark.parametrize("prob", [
