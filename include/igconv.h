@@ -169,7 +169,11 @@ igcStatus igcGetConvolutionForwardWorkspaceSize(igcHandle_t handle,
  * every gathered element against the window (the generic gather): the query reports the size of x
  * with its border written out, N*C*(H+2*pad_h)*(W+2*pad_w)*4 bytes; with such a workspace (16-byte
  * aligned) that copy is made first and the pass runs over it as a problem without a border (most 3x3 and
- * 5x5 filters over up to four channels need no copy: the workspace is then left alone). */
+ * 5x5 filters over up to four channels need no copy: the workspace is then left alone).
+ * A fourth use, which the query does not report: float problems with nine taps or more, C*R*S >= 432 and enough tiles run up
+ * to several times faster with any workspace (16-byte aligned) that holds the filter written as pairs of 16-bit numbers,
+ * ceil(K/64) * ceil(C/16) * ceil(R*S/9) * 36872 bytes, for instance the one lent to the same layer's backward filter pass; the sums
+ * then round otherwise (no further from the exact ones).  Backward data with unit strides: the same with C and K exchanged. */
 igcStatus igcGetConvolutionForwardOptionalWorkspaceSize(igcHandle_t handle,
                                                         igcTensorDescriptor_t xDesc,
                                                         igcFilterDescriptor_t wDesc,

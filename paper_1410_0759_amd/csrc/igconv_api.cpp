@@ -34,7 +34,7 @@ static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor
 
 // Kernels that only run on a filter the library has rewritten into a workspace: numbered after the others, so that they
 // cannot be named in igcSetKernelOverride.
-static const KernelGroup *const kInnerGroups[] = {&kGroupBF16Taps};
+static const KernelGroup *const kInnerGroups[] = {&kGroupBF16Taps, &kGroupF32HalvesPatch};
 
 int kernel_count() {
     int n = 0;
@@ -107,6 +107,7 @@ struct Problem {
     unsigned mode_mask = 0;   // non-zero: bit g set when gather mode g can run this problem
     bool zero_steps = false;  // nothing to accumulate: the kernel only scales the old output
     bool filter_inner = false;   // the filter will be read from a copy with the reduction's channel index innermost
+    size_t halves_room = 0;   // bytes lent for the split filter of the kernels of variants 7 and 8 (the queries keep to the plan without)
     bool no_teams = false;    // leave the kernels that cut the reduction inside a workgroup (teams, gather mode 15) out of the
                               // choice: a workspace cuts it across compute units, which measured faster where both apply
 };
@@ -172,10 +173,13 @@ static igcStatus validate(igcTensorDescriptor_t x, igcFilterDescriptor_t w,
     return IGC_STATUS_SUCCESS;
 }
 
+static bool is_halves(const KernelInfo &ki) { return ki.variant == 7 || ki.variant == 8; }   // (igconv_kernel_f32h.hpp)
+
 // Reduction steps a kernel needs: its order is either the filter's (c,r,s), cut into
 // chunks of BK, or tap-major: per tap, the channels in chunks of BK.
 static long long kernel_steps(const KernelInfo &ki, const ConvKernelParams &k) {
     if (ki.gmode == 1) return (long long)k.RS * ((k.C + ki.BK - 1) / ki.BK);
+    if (is_halves(ki)) return (long long)((k.C + 15) / 16) * ((k.RS + 8) / 9);
     if (ki.gmode == 3 || ki.gmode == 4 || ki.gmode == 5) return k.C / (ki.BK / 9);
     if (ki.gmode == 12) return (k.C + ki.BK - 1) / ki.BK;
     return (k.CRS + ki.BK - 1) / ki.BK;
@@ -202,7 +206,7 @@ static long long direct_steps_per_wave(const KernelInfo &ki, const ConvKernelPar
 // 64 x 64 x 32 ones (unpadded forward, backward filter by tap: 112 registers) -, three or (tiles up to 64 x 128) four of those with steps
 // of 16.  More workgroups per compute unit cover more of each other's waits: Table-2 layer 3 gained 4 %.
 static int workgroups_per_cu(const KernelInfo &ki) {
-    if (ki.variant == 4 || ki.variant == 5) return std::min(2, (160 * 1024) / ki.ldsBytes);
+    if (ki.variant == 4 || ki.variant == 5 || is_halves(ki)) return std::min(2, (160 * 1024) / ki.ldsBytes);
     const bool small_tile = (ki.gmode == 2 || (ki.gmode == 8 && !ki.bf16)) && ki.BM * ki.BN <= 64 * 64 && ki.BK == 32;
     if (is_direct(ki.gmode)) return ki.variant == 1 ? 1 : (160 * 1024) / ki.ldsBytes;   // (64 or 80 KB of LDS each, 64 more with the filter rows staged)
     // (double precision, pipelined: 105 registers for the 64 x 64 tile, 169 for 128 x 64)
@@ -211,10 +215,39 @@ static int workgroups_per_cu(const KernelInfo &ki) {
     return std::max(1, std::min(by_regs, (160 * 1024) / ki.ldsBytes));
 }
 
+// Largest number of pixels of the zero-extended images (flat index over all images) between
+// the first pixel of a tile's first column window and the last pixel of its last column's,
+// for tiles of bn consecutive columns: an upper bound.  Going from one column to the next
+// advances the window start by v, by a row wrap or by an image wrap; within bn-1 such
+// moves at most `rows` are wraps and at most `imgs` of those image wraps.  (`whole`: no tile spans two images.)
+static long long patch_pixels_bound(const ConvKernelParams &k, int bn, bool whole = false) {
+    const long long d = (whole ? std::min(bn, k.PQ) : bn) - 1;
+    const long long rows = (d + k.Q - 1) / k.Q, imgs = whole ? 0 : (d + k.PQ - 1) / k.PQ;
+    const long long row_wrap = std::max<long long>((long long)k.u * k.Wp - (long long)(k.Q - 1) * k.v, k.v);
+    const long long img_wrap =
+        std::max<long long>((long long)k.HpWp - (long long)(k.P - 1) * k.u * k.Wp - (long long)(k.Q - 1) * k.v, row_wrap);
+    return (d - rows) * k.v + (rows - imgs) * row_wrap + imgs * img_wrap + (long long)(k.R - 1) * k.Wp + k.S;
+}
+
+// Column tiles of each image where the patch of a tile that spans two images would not fit (variants 7 and 8); 0: tiles run on.
+static int image_tiles(const KernelInfo &ki, const ConvKernelParams &k) {
+    if (!is_halves(ki) || patch_pixels_bound(k, ki.BN) <= ki.patchPixels) return 0;
+    return (k.PQ + ki.BN - 1) / ki.BN;
+}
+static long long column_tiles(const KernelInfo &ki, const ConvKernelParams &k) {
+    const long long per_image = image_tiles(ki, k);
+    return per_image ? per_image * k.N : (k.NPQ + ki.BN - 1) / ki.BN;
+}
+
+// Workspace of variants 7 and 8: the split filter and its table.
+static size_t halves_bytes(const KernelInfo &ki, const ConvKernelParams &k) {
+    return (size_t)((k.K + ki.BM - 1) / ki.BM) * (size_t)kernel_steps(ki, k) * ((size_t)(9 * ki.BM * 64) + 8);
+}
+
 static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKernelParams &k) {
     const long long cus = h->computeUnits;
     const long long tm = (k.K + ki.BM - 1) / ki.BM;
-    const long long tn = (k.NPQ + ki.BN - 1) / ki.BN;
+    const long long tn = column_tiles(ki, k);
     const long long steps = kernel_steps(ki, k);
     const long long tiles = tm * tn;
     const long long occ = workgroups_per_cu(ki);
@@ -249,6 +282,16 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
     }
     // (any filter over channel vectors: as the 1x1 kernel, a step of two units of 32 channels)
     if (ki.variant == 6) return tile_times * (steps + 2.0) * 500.0 * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0);
+    if (is_halves(ki)) {
+        // Operands as two binary16 parts (igconv_kernel_f32h.hpp), counted like variant 5, and about 6 us for splitting the filter.
+        // Measured per step in the units of the line below: 29 with nine taps, 39 where its patch is wide, 24 with more taps.
+        // Not below 432 reduction indices: there the operands' own rounding (7e-8 of a result) is no longer hidden by what the
+        // longer chains of sums of the other kernels lose (three parts, 288 indices: 9e-8; two parts: 1.1e-7).
+        if (k.CRS < 432 || tiles * 2 < cus) return 1e300;
+        const double rounds = 0.5 * ((double)((tiles + cus - 1) / cus) + (double)tiles / (double)cus);
+        const double unit = ki.variant == 8 ? 24.0 : (ki.patchPixels > 640 ? 39.0 : 29.0);
+        return rounds * ((double)steps + 0.7) * (double)ki.BN * ki.BK * unit + 2.0e6;
+    }
     if (ki.variant == 5) {
         // The same with a staged patch (igconv_kernel_f32p.hpp), one workgroup per compute unit: bound by power, so that a
         // partial round costs less than a full one (counted half way between); measured per step, in the units of
@@ -312,20 +355,6 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
     return tile_times * eff_steps * (double)ki.BN * ki.BK * (ki.BM + gather) * (ki.BK == 16 ? 0.975 : 1.0);
 }
 
-// Largest number of pixels of the zero-extended images (flat index over all images) between
-// the first pixel of a tile's first column window and the last pixel of its last column's,
-// for tiles of bn consecutive columns: an upper bound.  Going from one column to the next
-// advances the window start by v, by a row wrap or by an image wrap; within bn-1 such
-// moves at most `rows` are wraps and at most `imgs` of those image wraps.
-static long long patch_pixels_bound(const ConvKernelParams &k, int bn) {
-    const long long d = bn - 1;
-    const long long rows = (d + k.Q - 1) / k.Q, imgs = (d + k.PQ - 1) / k.PQ;
-    const long long row_wrap = std::max<long long>((long long)k.u * k.Wp - (long long)(k.Q - 1) * k.v, k.v);
-    const long long img_wrap =
-        std::max<long long>((long long)k.HpWp - (long long)(k.P - 1) * k.u * k.Wp - (long long)(k.Q - 1) * k.v, row_wrap);
-    return (d - rows) * k.v + (rows - imgs) * row_wrap + imgs * img_wrap + (long long)(k.R - 1) * k.Wp + k.S;
-}
-
 // Gather modes a kernel may use for this problem (see the kernel sources): the unpadded
 // mode needs pad 0, the nine-tap table R*S = 9 and whole steps of four channels; the
 // generic and the tap-major modes always work.  The channel-vector modes (bf16) read 8
@@ -354,6 +383,10 @@ static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool
         if (gmode == 13) return steps % 2 == 1 && steps >= 3;   // the skipped step: the one that rounds an odd count up
         return gmode == 7 || (steps % 2 == 0 && last <= ki.BK / 2);
     }
+    if (is_halves(ki))   // R*S contiguous taps per (row, channel), nine or (variant 8) more; else as below, but with any number of channels
+        return (ki.variant == 8 ? k.RS > 9 : k.RS == 9) && (!ki.swap || k.C % 4 == 0) && k.pad_h >= 0 && k.pad_w >= 0 && k.Wp == k.W + 2 * k.pad_w &&
+               ((k.wsTapS == 1 && k.wsTapR == k.S) || (k.wsTapS == -1 && k.wsTapR == -k.S)) && (!ki.swap || k.xsC == 1) &&
+               (long long)k.N * (k.H + 2 * k.pad_h) * k.Wp < (1ll << 31) && patch_pixels_bound(k, ki.BN, image_tiles(ki, k) != 0) <= ki.patchPixels;
     if (gmode == 3 && ki.variant == 5)
         // nine contiguous taps per (row, channel), walked forwards or backwards; a tile's pixels fit the patch; the
         // channel-fastest form reads four channels of a pixel at once
@@ -393,14 +426,14 @@ static igcStatus choose(const igcContext *h, const Problem &pr, bool w_aligned, 
     for (int i = 0; i < list.count; ++i) {
         const int id = list.id[i];
         const KernelInfo &ki = *list.info[i];
-        if (id >= offered || (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u))) continue;
-        if ((ki.veca && !can_vec) || !gather_mode_ok(ki, k, x_aligned)) continue;
+        if ((id >= offered && !is_halves(ki)) || (pr.mode_mask != 0 && !((pr.mode_mask >> ki.gmode) & 1u))) continue;
+        if ((ki.veca && !can_vec) || (is_halves(ki) && halves_bytes(ki, k) > pr.halves_room) || !gather_mode_ok(ki, k, x_aligned)) continue;
         // (more than 63 taps under a border: the forward pass stays with tap-major order, whose filter copy callers lend room for)
         if (ki.variant == 4 && ki.gmode == 14 && k.RS > 63 && pr.mode_mask == 0) continue;
         if (pr.no_teams && ((ki.variant == 2 && ki.gmode < 4) || is_direct(ki.gmode))) continue;
         double c = plan_cost(h, ki, k);
         if (ki.swap != want_swap) c *= 1.5;
-        if (!ki.veca && can_vec && ki.gmode != 1 && ki.variant != 5) c *= 1.05;
+        if (!ki.veca && can_vec && ki.gmode != 1 && ki.variant != 5 && !is_halves(ki)) c *= 1.05;
         if (best < 0 || c < best_cost) {
             best = id;
             best_cost = c;
@@ -472,7 +505,11 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
     const KernelInfo &ki = *kernel_info(id);
     ConvKernelParams &k = pr->kp;
     k.tilesM = (k.K + ki.BM - 1) / ki.BM;
-    k.tilesN = (k.NPQ + ki.BN - 1) / ki.BN;
+    k.imageTiles = image_tiles(ki, k);
+    // one workgroup per tile; the runtime limits a launch to fewer than 2^32 threads
+    const long long tiles_n = column_tiles(ki, k);
+    if ((long long)k.tilesM * tiles_n >= (1ll << 24)) return IGC_STATUS_NOT_SUPPORTED;
+    k.tilesN = (int)tiles_n;
     k.tilesPerXcd = (int)(((long long)k.tilesM * k.tilesN + kXcds - 1) / kXcds);
     const long long steps = pr->zero_steps ? 0 : kernel_steps(ki, k);
     if (steps >= (1ll << 30)) return IGC_STATUS_NOT_SUPPORTED;
@@ -483,8 +520,6 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
     if (ki.gmode == 1 && k.C % ki.BK != 0) k.tail_step = (int)((long long)(k.C / ki.BK) * k.RS);
     if ((ki.gmode == 0 || ki.gmode == 2 || ki.gmode == 7 || ki.gmode == 11 || ki.gmode == 13 || ki.gmode == 14) && k.CRS % ki.BK != 0)
         k.tail_step = k.ksteps - 1;
-    // one workgroup per tile; the runtime limits a launch to fewer than 2^32 threads
-    if ((long long)k.tilesM * k.tilesN >= (1ll << 24)) return IGC_STATUS_NOT_SUPPORTED;
     k.wgsPerXcd = workgroups_per_xcd(h, ki, k.tilesPerXcd);
     k.splits = 1;
     k.stepsPerSplit = (k.ksteps + 1) & ~1;
@@ -918,13 +953,14 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
 
 // filter_inner: the filter will be read from its rewritten copy; dy_aligned: dy starts on a 16-byte boundary.
 static igcStatus plan_backward_data_phases(const igcContext *handle, const BackwardDataProblem &b, std::vector<PhaseLaunch> *out,
-                                           bool filter_inner = false, bool dy_aligned = false) {
+                                           bool filter_inner = false, bool dy_aligned = false, size_t halves_room = 0) {
     for (int ph = 0; ph < b.u; ++ph)
         for (int pw = 0; pw < b.v; ++pw) {
             PhaseLaunch l;
             l.dx_offset = 0;
             if (!backward_data_phase(b, ph, pw, &l.pr, &l.dx_offset)) continue;
             l.pr.filter_inner = filter_inner;
+            l.pr.halves_room = halves_room;
             if (filter_inner) l.pr.mode_mask = 1u << 1;
             igcStatus st = choose(handle, l.pr, /*w_aligned=*/false, /*x_aligned=*/dy_aligned, &l.id);
             if (st != IGC_STATUS_SUCCESS) return st;
@@ -1398,6 +1434,7 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
                       workSpaceSizeInBytes / 4 >= (size_t)pr.kp.N * pr.kp.C * (pr.kp.H + 2 * pr.kp.pad_h) * (pr.kp.W + 2 * pr.kp.pad_w);
     if (handle->kernelOverride < 0 && few_channels(handle, pr, room))
         return launch_few_channels(pr.kp, handle->computeUnits, handle->stream) == 0 ? IGC_STATUS_SUCCESS : IGC_STATUS_EXECUTION_FAILED;
+    pr.halves_room = workSpace && (uintptr_t)workSpace % 16 == 0 ? workSpaceSizeInBytes : 0;
     int id = -1;
     igcConvolutionForwardPlan plan;
     // With a workspace the reduction of a small problem is cut into ranges (below), finer than the team kernels
@@ -1502,6 +1539,10 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
             k.w = workSpace;
             k.wsRow = k.CRS; k.wsRed = 1; k.wTap0 = 0; k.wsTapR = k.S * k.C; k.wsTapS = k.C;
         }
+    }
+    if (is_halves(*kernel_info(id))) {
+        pr.kp.halves = workSpace;
+        if (launch_split_filter(pr.kp, workSpace, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
     }
     if (kernel_info(id)->launch(pr.kp, grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
     if (splits > 1) {
@@ -1610,7 +1651,7 @@ igcStatus igcConvolutionBackwardData(igcHandle_t handle, const void *alpha, igcF
 per_phase:
     // plan every phase before the first launch, so that a rejected problem launches nothing
     std::vector<PhaseLaunch> launches;
-    st = plan_backward_data_phases(handle, b, &launches);
+    st = plan_backward_data_phases(handle, b, &launches, false, false, workSpace && (uintptr_t)workSpace % 16 == 0 ? workSpaceSizeInBytes : 0);
     if (st != IGC_STATUS_SUCCESS) return st;
     // Float or bfloat16 phases that all run in tap-major order, and room for the filter: it is first rewritten as wt[c][t][k]
     // (below); bfloat16 phases may then run on the kernel that reads channel vectors of both operands.
@@ -1667,7 +1708,12 @@ per_phase:
         // a phase that meets no tap would write dx = alpha * 0 + 1 * dx
         if (l.pr.zero_steps && (b.f64 ? l.pr.kp.beta64 == 1.0 && std::isfinite(l.pr.kp.alpha64) : l.pr.kp.beta == 1.f && std::isfinite(l.pr.kp.alpha)))
             continue;
-        if (kernel_info(l.id)->launch(l.pr.kp, l.grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
+        ConvKernelParams kp = l.pr.kp;
+        if (is_halves(*kernel_info(l.id))) {   // (unit strides: the only launch)
+            kp.halves = workSpace;
+            if (launch_split_filter(kp, workSpace, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
+        }
+        if (kernel_info(l.id)->launch(kp, l.grid, handle->stream) != 0) return IGC_STATUS_EXECUTION_FAILED;
     }
     return IGC_STATUS_SUCCESS;
 }

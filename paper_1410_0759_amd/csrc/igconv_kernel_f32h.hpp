@@ -1,0 +1,672 @@
+// fp32 convolution (forward; backward data with unit stride) on the 16-bit matrix pipes, every operand as two binary16
+// numbers, with the gathered operand read from a staged patch of the zero-extended image.
+//
+//     x * 2^e = h + m / 2^11,   h = f16(x * 2^e), m = f16((x * 2^e - h) * 2^11)
+// (11 + 11 significant bits and m's sign: x itself for three operands out of four, else one unit of its last place off),
+// and a product as h*h' + (h*m' + m*h') / 2^11; the product left out is below 2^-22 of it, and as often above zero as below.
+// Where three bfloat16 parts (igconv_kernel_f32s.hpp) need six products, this takes three.  What the operands lose is made up
+// for in the sums: those of a chunk of 144 indices (16 channels, nine taps) are formed in accumulators of their own, h*h' apart
+// from the two small products, and added up in a third one - fewer roundings at the full sum's size.
+//
+// The exponent e is that of the chunk: the movers take the largest magnitude of the patch (of the filter rows) once it has
+// arrived, before any of it is written, and scale it to [2^14, 2^15); the factor 2^-(e + e') goes into the addition to
+// the third accumulator.  No range is assumed and none is kept from chunk to chunk.  What leaves it: an operand below 2^-13 after scaling
+// (below 2^-28 of its chunk's largest) loses up to 2^-36; the movers look for the smallest one that is not zero and, where
+// there are such operands, count them.  A sum of a tile with n of them is off by less than n * 2^-36 * 2^15 * 2^-(e + e'); a
+// wavefront with a sum below 2^24 times that, or that is not finite, or not zero but below 2^-100, multiplies its blocks
+// again with the fp32 instruction (sums_in_fp32).
+//
+// The reduction is ordered (16 channels, group of nine taps, tap, channel).  A tile's whole range of pixels of the
+// zero-extended image goes to LDS once per 16 channels, and all R*S taps read their operands from it at shifted
+// pixels.  The nine floats of a (row, channel, group) of the filter are contiguous in either pass (forward: row k, channel c;
+// backward data: row c, channel k, the taps walked backwards).  Where R*S is no multiple of nine the last group begins at
+// R*S - 9 and the taps it shares with the one before are zero.
+//
+// The filter is split once per call, into the caller's workspace, in the order in which the tiles read it (split_filter below:
+// [row block][chunk][tap][part][half of the channels][row][8 channels], and each chunk's exponent and count).
+//
+// Measured, us and error against 64 bits, 128 images unless said, three bfloat16 parts -> this with the filter's split: 64x56x56 -> 64, 3x3
+// 151 -> 106, 1.3e-7 -> 1.1e-7 (backward data 147 -> 107); 384x13x13 -> 256, 3x3 200 -> 144, 3.4e-7 -> 1.6e-7 (168 -> 117); 96x64x64 -> 128,
+// 9x9, 32 images 1228 -> 566, 5.5e-7 -> 2.1e-7 (1670 -> 720); 96x27x27 -> 256, 5x5 653 -> 318 (765 -> 384); 64x224x224 -> 64, 3x3, 4
+// images 118 -> 80.  What bounds it: with many taps the matrix pipes at the clocks that power leaves (350 TFLOP/s); with nine the
+// requests and the splitting of the patch (the first layer without them 87 us, with neither MFMAs nor their waits 77) and 17 us of epilogues.
+// (The filter split by the movers as well, in each tile, from registers: 137 us where this took 121, the 9x9 layer 1230; a barrier per
+// step instead of per chunk: 121 instead of 110; 128 x 128 tiles level.)
+//
+// Four multiplying wavefronts, one that copies the split filter to LDS (loads straight into LDS, 16 bytes per lane) and three that
+// move the patch; one workgroup per compute unit (LDS), persistent.  A step is three taps, a chunk three steps, one barrier each (WHOLE: one per chunk,
+// with two stages of a chunk's filter):
+//   filter, step q: request step q + 1 (three stages), wait for step q;
+//   patch, in a 16-channel block's last chunk: the next block's - largest and smallest magnitude (end of step 0), split and write
+//     every other item (steps 1 and 2), requesting the same item of the block after (nine taps: of the one after that, so
+//     that its loads have four steps to arrive);
+//   multipliers run one step behind: they pass the barrier that ends step q + 1 in the middle of step q's last tap.
+// LDS: filter [stage][tap of 3][part][half][row][8 channels], patch [stage][part][half][pixel][8 channels]: a fragment is
+// 32 neighbouring 16-byte pieces per half wavefront, and a tap a distance the same for all lanes.
+#ifndef IGCONV_KERNEL_F32H_HPP_
+#define IGCONV_KERNEL_F32H_HPP_
+
+#include "igconv_kernel_f32s.hpp"
+
+namespace igc {
+
+using f16x8 = _Float16 __attribute__((ext_vector_type(8)));
+
+// Scale of a chunk of one operand, from its largest magnitude (bits).
+struct HalvesScale {
+    int e;           // operands times 2^e
+    float s, t;      // 2^e, 2^(e + 11)
+    uint32_t below;  // bits of the magnitude under which an operand loses something
+};
+__device__ __forceinline__ HalvesScale halves_scale(uint32_t largest) {
+    HalvesScale r;
+    const int e = 141 - (int)(largest >> 23);   // the largest to [2^14, 2^15); within 2^60 either way the factors stay normal
+    r.e = e < -60 ? -60 : (e > 60 ? 60 : e);
+    r.s = __builtin_bit_cast(float, (uint32_t)(127 + r.e) << 23);
+    r.t = __builtin_bit_cast(float, (uint32_t)(138 + r.e) << 23);
+    r.below = (uint32_t)(114 - r.e) << 23;
+    return r;
+}
+
+// x0, x1 as two pairs of binary16 numbers (x0's part in the low half): six instructions.
+__device__ __forceinline__ void halves_pair(float x0, float x1, const HalvesScale &sc, uint32_t &h, uint32_t &m) {
+    const float t0 = x0 * sc.t, t1 = x1 * sc.t;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(x0), "s"(sc.s));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(h) : "v"(x1), "s"(sc.s));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(m) : "v"(h), "s"(-2048.f), "v"(t0));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(m) : "v"(h), "s"(-2048.f), "v"(t1));
+}
+
+// Largest magnitude and, of those that are not zero, smallest one (twice its bits, less one) of a thread's operands.
+struct HalvesSeen {
+    float largest = 0.f;
+    uint32_t smallest = ~0u;
+};
+__device__ __forceinline__ void look_at(HalvesSeen &seen, float x0, float x1) {
+    // (the compiler's maximum would quiet both operands first; a NaN shows in the sums)
+    asm("v_max3_f32 %0, %0, abs(%1), abs(%2)" : "+v"(seen.largest) : "v"(x0), "v"(x1));
+    const uint32_t u0 = (__builtin_bit_cast(uint32_t, x0) << 1) - 1u, u1 = (__builtin_bit_cast(uint32_t, x1) << 1) - 1u;
+    const uint32_t u = u0 < u1 ? u0 : u1;
+    seen.smallest = seen.smallest < u ? seen.smallest : u;
+}
+__device__ __forceinline__ uint32_t wave_largest(uint32_t v) {
+    auto reduce = [&](auto ctrl_c) __attribute__((always_inline)) {
+        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl_c)::value, 0xF, 0xF, true);
+        v = v > other ? v : other;
+    };
+    reduce(std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has the row's
+    reduce(std::integral_constant<int, 0x112>{});
+    reduce(std::integral_constant<int, 0x114>{});
+    reduce(std::integral_constant<int, 0x118>{});
+    reduce(std::integral_constant<int, 0x142>{});   // row_bcast 15 and 31: lane 63 has the wavefront's
+    reduce(std::integral_constant<int, 0x143>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// The wavefront's largest magnitude to LDS for the other moving wavefronts; returns its smallest (as in HalvesSeen).
+__device__ __forceinline__ uint32_t publish_largest(uint8_t *slot, const HalvesSeen &seen, int lane) {
+    const uint32_t big = wave_largest(__builtin_bit_cast(uint32_t, seen.largest));
+    const uint32_t small = ~wave_largest(~seen.smallest);
+    if (lane == 0) *reinterpret_cast<uint32_t *>(slot) = big;
+    return small;
+}
+__device__ __forceinline__ HalvesScale read_scale(const uint8_t *slots) {   // of the four moving wavefronts
+    const u32x4 b = *reinterpret_cast<const u32x4 *>(slots);
+    const uint32_t b0 = b[0] > b[1] ? b[0] : b[1], b1 = b[2] > b[3] ? b[2] : b[3];
+    return halves_scale((uint32_t)__builtin_amdgcn_readfirstlane((int)(b0 > b1 ? b0 : b1)));
+}
+__device__ __forceinline__ uint32_t count_lossy(float x, uint32_t below) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x) & 0x7FFFFFFFu;
+    return (uint32_t)__popcll(__ballot(u != 0u && u < below));
+}
+
+// First tap of group g: the last group ends with the filter.
+__host__ __device__ __forceinline__ int halves_first_tap(int g, int taps) { return 9 * g < taps - 9 ? 9 * g : taps - 9; }
+
+// Chunk of a row block of the split filter: exponent, operands that lost something.
+struct HalvesChunk {
+    int e;
+    uint32_t lossy;
+};
+
+// NHWC: channel-fastest x (16-byte loads of channels) and y (lanes along output channels in the epilogue).
+// SETS: patches in registers, 2 (nine taps: a chunk is a block) or 1 (more).  WHOLE: one barrier per chunk, where two stages of
+// a chunk's filter fit (nine taps).
+template <int BM_, int BN_, int WM_, int WN_, int PIX_, bool NHWC_, int SETS_, bool WHOLE_>
+struct HalvesPatchConfig {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, PIX = PIX_, SETS = SETS_;
+    static constexpr bool NHWC = NHWC_, SWAP = NHWC_, WHOLE = WHOLE_;
+    static constexpr int THREADS = 512, BK = 144, MOVERS = 3;
+    static constexpr int A_PLANE = BM * 16, A_PART = 2 * A_PLANE, A_TAP = 2 * A_PART, A_STAGE = (WHOLE ? 9 : 3) * A_TAP;
+    static constexpr int B_PLANE = PIX * 16, B_PART = 2 * B_PLANE, B_STAGE = 2 * B_PART;
+    static constexpr int B_BASE = (WHOLE ? 2 : 3) * A_STAGE;
+    static constexpr int SLOT_B = B_BASE + 2 * B_STAGE;   // largest magnitudes of the patch [parity of the block][wavefront]
+    static constexpr int SLOT_C = SLOT_B + 32;            // 2^-(e + e') [parity of the chunk]
+    static constexpr int SLOT_N = SLOT_C + 16;            // operands that lost something [parity of the tile][wavefront]
+    static constexpr int LDS_BYTES = SLOT_N + 32;
+    static constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
+    static constexpr int COPIES = A_STAGE / 1024;         // loads into LDS per step
+    static constexpr int BLOCKS = PIX / 64;               // of 64 pixels
+    static constexpr int ITEMS = (2 * BLOCKS + MOVERS - 1) / MOVERS;   // (block, half of the channels) per moving wavefront
+    static_assert(WM * WN == 4 && BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "four wavefronts of 32x32 blocks");
+    static_assert((BM == 64 || BM == 128) && PIX % 64 == 0 && COPIES < 64 && !(WHOLE && SETS == 1), "shares of the moving wavefronts");
+    static_assert(LDS_BYTES <= 160 * 1024 && B_PART < 65536, "LDS budget, offsets of the LDS instructions");
+};
+
+template <class Cfg>
+__global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass needs the kernel's name and signature only)
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, MB = Cfg::MB, NB = Cfg::NB, ITEMS = Cfg::ITEMS, SETS = Cfg::SETS;
+
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[Cfg::LDS_BYTES];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5;
+    const int l32 = lane & 31;
+
+    // persistent workgroups, tiles numbered in contiguous ranges per XCD (see igconv_kernel.hpp)
+    const int wg_xcd = (int)(blockIdx.x % 8u), wg_local = (int)(blockIdx.x / 8u);
+    const int tiles_total = p.tilesM * p.tilesN;
+    auto tile_number = [&](int i) {
+        const int local = wg_local + i * p.wgsPerXcd;
+        const int t = wg_xcd * p.tilesPerXcd + local;
+        return local < p.tilesPerXcd && t < tiles_total ? t : tiles_total;
+    };
+    if (tile_number(0) >= tiles_total) return;
+    const int groups = (p.RS + 8) / 9;            // of nine taps
+    const int nch = (p.C + 15) / 16;              // blocks of 16 channels; the split filter is zero beyond the last channel
+    auto first_tap = [&](int g) { return halves_first_tap(g, p.RS); };
+    // columns of a tile: [first, end); where an image's pixels are tiled by themselves its last tile is cut short
+    auto tile_columns = [&](int tile, int *first, int *end) {
+        const int tn = tile / p.tilesM;
+        if (p.imageTiles == 0) {
+            *first = tn * BN;
+            *end = p.NPQ;
+        } else {
+            const int image = tn / p.imageTiles;
+            *first = image * p.PQ + (tn - image * p.imageTiles) * BN;
+            *end = (image + 1) * p.PQ;
+        }
+    };
+    // first pixel of column j's window as a flat index into the zero-extended images
+    auto window_start = [&](uint32_t j) {
+        const uint32_t n = magic_div(j, p.mPQ);
+        const uint32_t rem = j - n * (uint32_t)p.PQ;
+        const uint32_t pp = magic_div(rem, p.mQ);
+        const uint32_t qq = rem - pp * (uint32_t)p.Q;
+        return n * (uint32_t)p.HpWp + pp * (uint32_t)(p.u * p.Wp) + qq * (uint32_t)p.v;
+    };
+
+    const int chunks = nch * groups;
+    int rem = 0;
+    for (int i = 0; tile_number(i) < tiles_total; ++i) rem += chunks;   // chunks of all tiles of this workgroup
+
+    if (wave == 4) {
+        // ================================ filter ================================
+        const uint32_t block_bytes = (uint32_t)(chunks * 9 * Cfg::A_TAP);   // of a row block
+        const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.halves), 0, (uint32_t)p.tilesM * block_bytes, kBufferWord3);
+        const uint32_t voff = (uint32_t)lane * 16u;
+        constexpr int STEPS = Cfg::WHOLE ? 1 : 3;
+        int it = 0, left = chunks * STEPS;   // of the step to be requested: tile, steps of it that are left
+        uint32_t from = (uint32_t)(tile_number(0) % p.tilesM) * block_bytes;
+        auto request = [&](auto stage_c) __attribute__((always_inline)) {
+            uint8_t *const dst = lds + decltype(stage_c)::value * Cfg::A_STAGE;
+#pragma unroll
+            for (int i = 0; i < Cfg::COPIES; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (__attribute__((address_space(3))) void *)(dst + i * 1024), 16, voff, from + i * 1024u, 0, 0);
+            from += Cfg::A_STAGE;
+            if (--left == 0) {   // (past the last tile: its first steps again; nothing of them is multiplied)
+                left = chunks * STEPS;
+                const int next = tile_number(++it);
+                from = next < tiles_total ? (uint32_t)(next % p.tilesM) * block_bytes : 0u;
+            }
+        };
+        if constexpr (Cfg::WHOLE) {
+            split_barrier();
+            auto chunk = [&](auto stage_c) __attribute__((always_inline)) {
+                request(stage_c);
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                split_barrier();
+            };
+            for (;;) {
+                chunk(std::integral_constant<int, 0>{});
+                if (--rem <= 0) break;
+                chunk(std::integral_constant<int, 1>{});
+                if (--rem <= 0) break;
+            }
+            split_barrier();
+            return;
+        }
+        request(std::integral_constant<int, 0>{});
+        split_barrier();
+        for (int s = rem; s > 0; --s)
+            static_for<3>([&](auto jc) __attribute__((always_inline)) {
+                request(std::integral_constant<int, (decltype(jc)::value + 1) % 3>{});
+                constexpr int later = Cfg::COPIES;   // (the step requested just now may stay in flight)
+                __builtin_amdgcn_s_waitcnt(0x0F70 | (later & 15) | ((later >> 4) << 14));
+                split_barrier();
+            });
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // no request may still be on its way into LDS when it is given away
+        split_barrier();                       // (the multipliers' last step passes one more)
+        return;
+    }
+    if (wave > 4) {
+        // ================================ patch ================================
+        const int mw = wave - 5;
+        const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
+        using ConstantChunk = const __attribute__((address_space(4))) uint64_t;   // (written by the kernel before: read through scalar loads)
+        ConstantChunk *const table = (ConstantChunk *)(uintptr_t)(static_cast<const char *>(p.halves) + (size_t)p.tilesM * (size_t)chunks * (9 * Cfg::A_TAP));
+        // item i of this wavefront: 64 pixels (block n / 2) and one half (n % 2) of the 16 channels, n = 3 i + mw
+        uint32_t b_voff[ITEMS];
+        float b_reg[SETS][ITEMS][8];
+        int items = 0, held[SETS];   // items of the block to be requested, of those in registers, next one first
+
+        auto setup_patch = [&](int tile) {
+            int n0, n_end;
+            tile_columns(tile, &n0, &n_end);
+            const uint32_t g_first = __builtin_amdgcn_readfirstlane(window_start((uint32_t)n0));
+            const int j_last = n0 + BN - 1 < n_end ? n0 + BN - 1 : n_end - 1;
+            const uint32_t g_end = __builtin_amdgcn_readfirstlane(window_start((uint32_t)j_last)) +
+                                   (uint32_t)((p.R - 1) * p.Wp + p.S);   // one past the tile's last pixel
+            items = (int)(g_end - g_first + 63u) / 64 * 2;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const uint32_t g = g_first + (uint32_t)((3 * i + mw) / 2 * 64 + lane);
+                const uint32_t n = magic_div(g, p.mHpWp);
+                const uint32_t rem_ = g - n * (uint32_t)p.HpWp;
+                const uint32_t hp = magic_div(rem_, p.mWp);
+                const uint32_t wp = rem_ - hp * (uint32_t)p.Wp;
+                const uint32_t h = hp - (uint32_t)p.pad_h, w = wp - (uint32_t)p.pad_w;   // wrap below 0 -> huge
+                const bool ok = g < g_end && h < (uint32_t)p.H && w < (uint32_t)p.W;    // (g < g_end implies n < N)
+                b_voff[i] = ok ? (n * (uint32_t)p.xsN + h * (uint32_t)p.xsH + w * (uint32_t)p.xsW) * 4u : kOutOfRange;
+            }
+        };
+        // request item i of the patch of block cb
+        auto request_b = [&](auto set_c, int i, uint32_t cb) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            const uint32_t c = cb * 16u + (uint32_t)((3 * i + mw) % 2 * 8);
+            // (beyond the last channel, where the filter is zero, the last one again - channel-fastest: the last four)
+            auto channel = [&](uint32_t k, uint32_t last) { return k < last ? k : last; };
+            if constexpr (Cfg::NHWC) {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xbuf, b_voff[i], channel(c + (uint32_t)e * 4u, (uint32_t)p.C - 4u) * 4u, 0));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) b_reg[set][i][e * 4 + q] = v[q];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    b_reg[set][i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, b_voff[i], channel(c + (uint32_t)e, (uint32_t)p.C - 1u) * (uint32_t)p.xsC * 4u, 0));
+            }
+        };
+        // split item i and write it into the stage at byte offset `stage`
+        HalvesScale sb;
+        auto convert_b = [&](auto set_c, int i, int stage) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            u32x4 bh, bm;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t h, m;
+                halves_pair(b_reg[set][i][2 * q], b_reg[set][i][2 * q + 1], sb, h, m);
+                bh[q] = h; bm[q] = m;
+            }
+            const int n = 3 * i + mw;
+            uint8_t *const dst = lds + Cfg::B_BASE + stage + n % 2 * Cfg::B_PLANE + n / 2 * 1024 + lane * 16;
+            *reinterpret_cast<u32x4 *>(dst) = bh;
+            *reinterpret_cast<u32x4 *>(dst + Cfg::B_PART) = bm;
+        };
+        uint32_t small_b = 0;   // smallest magnitude of what is in registers (this wavefront's)
+        uint32_t lossy_a = 0, lossy_b = 0;   // operands of the tile that lose something: all of the filter's, this wavefront's
+        auto look_at_patch = [&](auto set_c, int parity) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            HalvesSeen seen;
+            static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                if (3 * i + mw < held[0])
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) look_at(seen, b_reg[set][i][e], b_reg[set][i][e + 1]);
+            });
+            small_b = publish_largest(lds + Cfg::SLOT_B + parity * 16 + mw * 4, seen, lane);
+        };
+        auto scale_patch = [&](auto set_c, int parity) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            sb = read_scale(lds + Cfg::SLOT_B + parity * 16);
+            if (small_b < 2u * sb.below - 1u)
+                static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value;
+                    if (3 * i + mw < held[0])
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) lossy_b += count_lossy(b_reg[set][i][e], sb.below);
+                });
+        };
+
+        // where the chunk being written and the block being requested are
+        int it = 0, cb = 0, g = 0;
+        int b_it = 0, b_cb = 0;
+        // (past the last tile the last one's operands are requested again; nothing of them is multiplied)
+        auto next_block = [&]() {
+            if (++b_cb == nch) {
+                b_cb = 0;
+                if (tile_number(++b_it) < tiles_total) setup_patch(tile_number(b_it));
+            }
+        };
+        int e_patch;                 // exponent of the block being multiplied
+        int stage = 0;               // byte offset of its patch's stage
+        uint32_t n_chunk = 0;        // chunks so far
+        int n_block = 0;             // blocks so far
+        uint32_t entry = (uint32_t)(tile_number(0) % p.tilesM) * (uint32_t)chunks;   // this chunk's in the table
+        auto publish_scale = [&](bool tile_begins) __attribute__((always_inline)) {   // the chunk's, for the multipliers
+            if (mw == 0) {
+                const uint64_t t = table[entry];   // HalvesChunk
+                lossy_a = (tile_begins ? 0u : lossy_a) + (uint32_t)(t >> 32);
+                if (lane == 0)
+                    *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_C + (n_chunk & 1u) * 4u) = (uint32_t)(127 - (int)(uint32_t)t - e_patch) << 23;
+            }
+        };
+        auto publish_lossy = [&]() __attribute__((always_inline)) {   // the tile's
+            if (lane == 0) *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + ((it & 1) * 4 + mw) * 4) = lossy_a + lossy_b;
+        };
+        auto next_chunk = [&]() __attribute__((always_inline)) {
+            ++n_chunk;
+            ++entry;
+            if (++g == groups) {
+                g = 0;
+                if (++cb == nch) {
+                    cb = 0;
+                    const int next = tile_number(++it);
+                    entry = next < tiles_total ? (uint32_t)(next % p.tilesM) * (uint32_t)chunks : 0u;
+                }
+            }
+        };
+        // (Requests stand under no condition but the compile-time ones: with any other the compiler, which counts the loads in
+        // flight, would wait for those just requested as well.  `block_end`: the block's last chunk.)
+        auto chunk = [&](auto par_c, auto end_c) __attribute__((always_inline)) {
+            constexpr int par = decltype(par_c)::value;
+            constexpr bool block_end = decltype(end_c)::value;
+            using Blk = std::integral_constant<int, SETS == 2 ? par ^ 1 : 0>;   // the next block's patch
+            static_for<3>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                if constexpr (j == 0) {
+                    publish_scale(cb == 0 && g == 0);
+                    if (block_end && cb == nch - 1) publish_lossy();
+                }
+                if constexpr (j == 1 && block_end) {
+                    if (cb == nch - 1) lossy_b = 0;   // (from here on the next tile's)
+                    scale_patch(Blk{}, (n_block + 1) & 1);
+                }
+                if constexpr (j > 0 && block_end)
+                    static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
+                        constexpr int i = decltype(ic)::value;
+                        if constexpr (i % 2 == j - 1) {
+                            if (3 * i + mw < held[0]) convert_b(Blk{}, i, Cfg::B_STAGE - stage);
+                            request_b(Blk{}, i, (uint32_t)b_cb);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    });
+                if constexpr (j == 0 && block_end) look_at_patch(Blk{}, (n_block + 1) & 1);
+                split_barrier();
+            });
+            if constexpr (block_end) {
+                e_patch = sb.e;
+                stage = Cfg::B_STAGE - stage;
+                ++n_block;
+                if constexpr (SETS == 2) held[0] = held[1];
+                held[SETS - 1] = items;
+                next_block();
+            }
+            next_chunk();
+        };
+        // One barrier per chunk: the chunk's own patch is split and written, the same registers requested for the block
+        // after the next, the next one's magnitudes taken.
+        auto whole_chunk = [&](auto par_c) __attribute__((always_inline)) {
+            constexpr int par = decltype(par_c)::value;
+            if (cb == 0) lossy_b = 0;
+            scale_patch(par_c, par);
+            e_patch = sb.e;
+            publish_scale(cb == 0);
+            if (cb == nch - 1) publish_lossy();
+            static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                if (3 * i + mw < held[0]) convert_b(par_c, i, par * Cfg::B_STAGE);
+                request_b(par_c, i, (uint32_t)b_cb);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            held[0] = held[SETS - 1];
+            held[SETS - 1] = items;
+            next_block();
+            look_at_patch(std::integral_constant<int, par ^ 1>{}, par ^ 1);
+            split_barrier();
+            next_chunk();
+        };
+        // the first block's patch
+        using S0 = std::integral_constant<int, 0>;
+        auto request_patch = [&](auto set_c, int h) __attribute__((always_inline)) {
+            held[h] = items;
+            static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) { request_b(set_c, decltype(ic)::value, (uint32_t)b_cb); });
+            next_block();
+        };
+        if (lane == 0 && mw == 0)   // (the unused fourth wavefront's)
+            for (int i = 0; i < 2; ++i)
+                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_B + i * 16 + 12) = *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + i * 16 + 12) = 0u;
+        setup_patch(tile_number(0));
+        request_patch(S0{}, 0);
+        if constexpr (SETS == 2) request_patch(std::integral_constant<int, 1>{}, 1);
+        look_at_patch(S0{}, 0);
+        split_barrier();
+        if constexpr (Cfg::WHOLE) {
+            for (;;) {
+                whole_chunk(S0{});
+                if (--rem <= 0) break;
+                whole_chunk(std::integral_constant<int, 1>{});
+                if (--rem <= 0) break;
+            }
+            split_barrier();
+            return;
+        }
+        scale_patch(S0{}, 0);
+        e_patch = sb.e;
+        static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) { if (3 * decltype(ic)::value + mw < held[0]) convert_b(S0{}, decltype(ic)::value, 0); });
+        if constexpr (SETS == 2) held[0] = held[1];
+        request_patch(S0{}, SETS - 1);
+        auto any_chunk = [&](auto par_c) __attribute__((always_inline)) {
+            if constexpr (SETS == 2) chunk(par_c, std::true_type{});   // (nine taps: every one)
+            else if (g == groups - 1) chunk(par_c, std::true_type{});
+            else chunk(par_c, std::false_type{});
+        };
+        for (;;) {
+            any_chunk(std::integral_constant<int, 0>{});
+            if (--rem <= 0) break;
+            any_chunk(std::integral_constant<int, 1>{});
+            if (--rem <= 0) break;
+        }
+        split_barrier();                       // (the multipliers' last step passes one more)
+        return;
+    }
+
+    // ================================ multipliers ================================
+    const int wm = wave % Cfg::WM, wn = wave / Cfg::WM;
+    constexpr int M = MB * NB;
+    u32x4 ah[2][MB], am[MB], bh[NB], bm[NB];
+    f32x16 total[MB][NB], acc[MB][NB], low[MB][NB];
+    // filter operands of the chunk's first tap (step j of a chunk has stage j; WHOLE: the chunks alternate)
+    int fa = half * Cfg::A_PLANE + (wm * Cfg::TM + l32) * 16;
+    int a_other = Cfg::WHOLE ? Cfg::A_STAGE : 0;
+    int fb[NB], fb_next[NB];                                    // patch operands of tap offset 0: this chunk, the next one
+    int b_other = Cfg::B_STAGE;                                 // distance to the patch's other stage
+    // the storage order of the taps is that of the filter; where in the window one reads: reversed for eq. 2, and for
+    // the exchanged filter of backward data, whose gather walks the taps backwards
+    const bool rev = (p.flip != 0) != (p.wsTapS < 0);
+    const int in_row = rev ? -16 : 16, to_row = (rev ? -1 : 1) * (p.Wp - p.S + 1) * 16;   // from tap to tap, bytes
+    auto tap_position = [&](int g, int *s) {   // column and offset of group g's first tap
+        const uint32_t tap = (uint32_t)first_tap(g);
+        const uint32_t r = magic_div(tap, p.mS);
+        *s = (int)(tap - r * (uint32_t)p.S);
+        const int o = (int)r * p.Wp + *s;
+        return (rev ? (p.R - 1) * p.Wp + p.S - 1 - o : o) * 16;
+    };
+    auto columns = [&](int tile, int stage_offset, int (&f)[NB]) {
+        int n0, n_end;
+        tile_columns(tile, &n0, &n_end);
+        const uint32_t g_first = __builtin_amdgcn_readfirstlane(window_start((uint32_t)n0));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int j = n0 + wn * Cfg::TN + nb * 32 + l32;
+            // columns past the end are never stored; let them read the last column's window
+            const uint32_t rel = window_start((uint32_t)(j < n_end ? j : n_end - 1)) - g_first;
+            f[nb] = Cfg::B_BASE + stage_offset + half * Cfg::B_PLANE + (int)rel * 16;
+        }
+    };
+    auto read = [&](int at) __attribute__((always_inline)) { return *reinterpret_cast<const u32x4 *>(lds + at); };
+    // product 0: h*m', 1: m*h', 2: h*h'; block j: column block first
+    auto mfma = [&](int prod, int set, int j, bool fresh) __attribute__((always_inline)) {
+        const int mb = j % MB, nb = j / MB;
+        const f16x8 a = __builtin_bit_cast(f16x8, prod == 1 ? am[mb] : ah[set][mb]);
+        const f16x8 b = __builtin_bit_cast(f16x8, prod == 0 ? bm[nb] : bh[nb]);
+        f32x16 &sum = prod == 2 ? acc[mb][nb] : low[mb][nb];
+        const f32x16 zero = {};
+        if constexpr (Cfg::SWAP) sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a, fresh ? zero : sum, 0, 0, 0);
+        else sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, fresh ? zero : sum, 0, 0, 0);
+    };
+    float c_cur = 0.f, c_before = 0.f;   // 2^-(e + e') of this chunk, of the one before
+    uint32_t c_largest = 0, n_chunk = 0;
+    // The nine taps of a chunk.  The h*h' sums of the chunk before join the total during the first two products of
+    // the first tap, this chunk's small ones during the last product of the last tap; each accumulator then starts from zero.
+    auto chunk = [&](int off, int s, int off_next) __attribute__((always_inline)) {
+        uint32_t c_bits = 0;
+        static_for<9>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value, set = t & 1;
+            constexpr bool last = t % 3 == 2;
+            const int a_next = fa + (t == 8 ? a_other : (t + 1) * Cfg::A_TAP);
+            const bool wrap = s + 1 == p.S;
+            const int off_after = t == 8 ? off_next : off + (wrap ? to_row : in_row);
+            s = wrap ? 0 : s + 1;
+            const int (&f)[NB] = t == 8 ? fb_next : fb;
+            if constexpr (t == 1) c_bits = *reinterpret_cast<const uint32_t *>(lds + Cfg::SLOT_C + (n_chunk & 1u) * 4u);
+            static_for<3 * M>([&](auto sc) __attribute__((always_inline)) {
+                constexpr int i = decltype(sc)::value;
+                if constexpr (i == 0) bh[NB - 1] = read(fb[NB - 1] + off);
+                if constexpr ((Cfg::WHOLE ? t == 8 : last) && i == M) split_barrier();
+                // the next tap's fragments: bm after product 0, ah any time, am after product 1, bh after its blocks of product 2
+                if constexpr (i >= M && i < 2 * M) {
+                    constexpr int r0 = (i - M) * (NB + MB) / M, r1 = (i - M + 1) * (NB + MB) / M;
+                    static_for<r1 - r0>([&](auto rc) __attribute__((always_inline)) {
+                        constexpr int r = r0 + decltype(rc)::value;
+                        if constexpr (r < NB) bm[r] = read(f[r] + off_after + Cfg::B_PART);
+                        else ah[set ^ 1][r - NB] = read(a_next + (r - NB) * 512);
+                    });
+                }
+                if constexpr (i >= 2 * M) {
+                    constexpr int r0 = (i - 2 * M) * MB / M, r1 = (i - 2 * M + 1) * MB / M;
+                    static_for<r1 - r0>([&](auto rc) __attribute__((always_inline)) {
+                        constexpr int r = r0 + decltype(rc)::value;
+                        am[r] = read(a_next + r * 512 + Cfg::A_PART);
+                    });
+                    if constexpr ((i - 2 * M) % MB == 0 && i > 2 * M) bh[(i - 2 * M) / MB - 1] = read(f[(i - 2 * M) / MB - 1] + off_after);
+                }
+                mfma(i / M, set, i % M, t == 0 && i < 3 * M && (i < M || i >= 2 * M));
+                if constexpr (t == 0 && i < 2 * M) {
+                    constexpr int mb = (i / 2) % MB, nb = (i / 2) / MB;
+#pragma unroll
+                    for (int v = 0; v < 8; ++v)
+                        total[mb][nb][(i % 2) * 8 + v] = __builtin_fmaf(acc[mb][nb][(i % 2) * 8 + v], c_before, total[mb][nb][(i % 2) * 8 + v]);
+                }
+                if constexpr (t == 8 && i >= 2 * M) {
+                    constexpr int mb = (i - 2 * M) % MB, nb = (i - 2 * M) / MB;
+                    const float c_low = c_cur * 0x1p-11f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) total[mb][nb][v] = __builtin_fmaf(low[mb][nb][v], c_low, total[mb][nb][v]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (t == 4) {
+                c_bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)c_bits);
+                c_cur = __builtin_bit_cast(float, c_bits);
+                c_largest = c_largest > c_bits ? c_largest : c_bits;
+            }
+            off = off_after;
+        });
+        fa += a_other;
+        a_other = -a_other;
+        // (the next chunk's first fragments sit in set 1)
+        c_before = c_cur;
+        ++n_chunk;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) ah[0][mb] = ah[1][mb];
+    };
+    __builtin_amdgcn_s_setprio(2);   // the MFMA stream goes first where both kinds of wavefront want to issue
+    split_barrier();
+    split_barrier();
+    columns(tile_number(0), 0, fb);
+    int s0;
+    int off0 = tap_position(0, &s0);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        ah[0][mb] = read(fa + mb * 512);
+        am[mb] = read(fa + mb * 512 + Cfg::A_PART);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        bm[nb] = read(fb[nb] + off0 + Cfg::B_PART);
+        if (nb < NB - 1) bh[nb] = read(fb[nb] + off0);
+    }
+    for (int it = 0;; ++it) {
+        const int tile = tile_number(it);
+        if (tile >= tiles_total) break;
+        int n0, n_end;
+        tile_columns(tile, &n0, &n_end);
+        const int krow0 = (tile % p.tilesM) * BM + wm * Cfg::TM, col0 = n0 + wn * Cfg::TN;
+        float bvec[MB];
+        load_bias<MB>(p, krow0, l32, bvec);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mb][nb][v] = total[mb][nb][v] = 0.f;
+        c_largest = 0;
+        const int next = tile_number(it + 1);
+        for (int c = 0; c < nch; ++c)
+            for (int g = 0; g < groups; ++g) {
+                int s_next;
+                const int off_next = tap_position(g + 1 < groups ? g + 1 : 0, &s_next);
+                if (g + 1 < groups) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb];
+                } else {
+                    if (c + 1 < nch) {
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb] + b_other;
+                    } else {
+                        columns(next < tiles_total ? next : tile, b_other < 0 ? 0 : Cfg::B_STAGE, fb_next);
+                    }
+                    b_other = -b_other;
+                }
+                chunk(off0, s0, off_next);
+                off0 = off_next;
+                s0 = s_next;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) fb[nb] = fb_next[nb];
+            }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) total[mb][nb][v] = __builtin_fmaf(acc[mb][nb][v], c_before, total[mb][nb][v]);
+        const u32x4 lossy = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
+        const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lossy[0] + lossy[1] + lossy[2] + lossy[3]));
+        const float off_by = (float)count * 8.f * __builtin_bit_cast(float, c_largest);   // count * 2^-36 * 2^15 * 2^24 * c
+        ConvKernelParams pt = p;
+        pt.NPQ = n_end;
+        if (__any(outside_split_range<MB, NB>(total, count != 0 ? __builtin_bit_cast(uint32_t, off_by) : 0u)))
+            sums_in_fp32<Cfg::SWAP, MB, NB>(pt, total, krow0, col0, 0, p.CRS, half, l32);
+        const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, kBufferWord3);
+        store_tile<Cfg::SWAP, MB, NB>(pt, ybuf, total, bvec, krow0, col0, half, l32);
+    }
+#endif
+}
+
+}  // namespace igc
+#endif

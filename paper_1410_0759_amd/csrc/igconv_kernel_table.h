@@ -34,9 +34,10 @@ struct KernelInfo {
                       // 3: wavefronts that move tiles beside wavefronts that multiply (gather mode 5)
                       // 4: float operands split into three bfloat16 parts, moving and multiplying wavefronts
                       // 6: channel vectors of a filter rewritten with the channel index innermost (gather mode 1, bf16)
+                      // 7: float operands as two binary16 parts, the gathered side from a staged image patch, nine taps (gather mode 3); 8: more taps
                       // 5: the same as 4 for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
-    int patchPixels = 512;  // gather mode 5, variant 5: pixels of the zero-extended image a tile's staged patch can hold
+    int patchPixels = 512;  // gather mode 5, variants 5, 7 and 8: pixels of the zero-extended image a tile's staged patch can hold
     // the same for several problems in one launch (null where the kernel has no such form); `grid`: workgroups in all
     int (*launchPhases)(const ConvPhaseParams &, int grid, void *stream) = nullptr;
 };
@@ -48,7 +49,7 @@ struct KernelGroup {
 
 // One group per translation unit of kernel instantiations.
 extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGroupF32Generic, kGroupF32Swap, kGroupBF16,
-    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch, kGroupBF16Taps;
+    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch, kGroupF32HalvesPatch, kGroupBF16Taps;
 
 // Adds up `count` partial results (`stride` floats apart) into out = alpha*sum + beta*out;
 // returns the runtime's error code.
@@ -67,6 +68,8 @@ int launch_filter_exchange(const void *w, void *wt, int K, int C, int taps, void
 int launch_filter_taps_outer(const void *w, void *wt, int elem_bytes, int K, int C, int RS, bool exchange, Magic mInner, Magic mRS,
                              void *stream);
 
+// The filter split for the kernels of variants 7 and 8 (igconv_kernel_f32h.hpp) with row blocks of 64; `p` as the kernel will get it.
+int launch_split_filter(const ConvKernelParams &p, void *out, void *stream);
 // A forward pass with a short reduction on the vector units (igconv_kernels_few_channels.hip): float, 3x3 or 5x5,
 // at most four channels.
 int launch_few_channels(const ConvKernelParams &p, int computeUnits, void *stream);

@@ -73,6 +73,8 @@ struct ConvKernelParams {
     // zero-extended image: Wp = W + 2 pad_w pixels per row, HpWp = (H + 2 pad_h) * Wp per image
     int32_t Wp, HpWp;
     Magic mWp, mHpWp;
+    const void *halves = nullptr;   // (variants 7 and 8) the split filter, then its table (igconv_kernel_f32h.hpp)
+    int32_t imageTiles = 0;   // (variants 7 and 8) column tiles of each image where no tile spans two; 0: columns cut regardless of images
 };
 
 // Several problems of one kernel in one launch (the stride phases of backward data): workgroup b belongs to problem i with
