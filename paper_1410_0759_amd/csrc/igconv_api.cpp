@@ -34,7 +34,7 @@ static const KernelGroup *const kGroups[] = {&kGroupF32Taps9, &kGroupF32TapMajor
 
 // Kernels that only run on a filter the library has rewritten into a workspace: numbered after the others, so that they
 // cannot be named in igcSetKernelOverride.
-static const KernelGroup *const kInnerGroups[] = {&kGroupBF16Taps, &kGroupF32HalvesPatch};
+static const KernelGroup *const kInnerGroups[] = {&kGroupBF16Taps, &kGroupF32HalvesPatch, &kGroupWgradF32Halves};
 
 int kernel_count() {
     int n = 0;
@@ -850,7 +850,7 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
     for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
         for (int i = 0; i < list.count; ++i) {
             const KernelInfo &ki = *list.info[i];
-            if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn) continue;
+            if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn || ki.variant == 9) continue;   // (variant 9: halves_backward_filter)
             if (ki.variant == 4 && prefer_fp32(ki.BM, ki.BN)) continue;
             id = list.id[i];   // (the split kernels come last)
         }
@@ -1033,7 +1033,7 @@ static void backward_filter_split(const igcContext *h, const BackwardFilterProbl
     const KernelInfo *ki = kernel_info(b.kernel_id);
     const long long per_cu = ki && ki->f64 ? 4 : (ki && ki->gmode != 10 ? workgroups_per_cu(*ki) : 2);
     long long want = std::max<long long>(1, (per_cu * cus) / b.tiles);
-    want = std::min(want, std::max<long long>(1, b.ksteps / 8));
+    want = std::min(want, std::max<long long>(1, b.ksteps / (ki && ki->variant == 9 ? 2 : 8)));
     want = std::min(want, std::max<long long>(1, max_parts));
     if (ki && (ki->f64 || ki->gmode == 10)) {
         // These kernels run one workgroup per (tile, range), handed to the compute units as they come free.  With few
@@ -1066,6 +1066,56 @@ static void backward_filter_split(const igcContext *h, const BackwardFilterProbl
     per += per & 1;
     *steps_per_split = (int)per;
     *splits = (int)((b.ksteps + per - 1) / per);
+}
+
+// Float operands as two binary16 parts (igconv_kernel_wgrad_f32h.hpp), where that kernel can run, is the faster one and loses
+// no precision: `b`, whose workspace the query has reported, becomes its problem.  max_parts: ranges there is room for.
+static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b, long long max_parts) {
+    const KernelInfo &old = *kernel_info(b->kernel_id);
+    const ConvKernelParams &k = b->pr.kp;
+    if (old.gmode != 8 || old.bf16 || old.f64) return;
+    const int C = k.NPQ, S = k.Q, Q = k.S, P = k.RS / k.S;   // (renamed: see validate_backward_filter)
+    // Rows of three taps and more at unit horizontal stride; eight maps and channels and more (the last eight stand in for a
+    // ragged end); output rows of nine and more: the patch of a chunk of 128 pixels, two more for each row it
+    // meets, has 160.  Either both tensors have channels innermost or none.
+    if (S < 3 || k.redMulW != 1 || k.K < 8 || C < 8 || Q < 9 || (k.xsN == 1) != (k.wsRow == 1)) return;
+    const bool innermost = k.xsN == 1;
+    const KernelList &list = kernels_of(false, false, true);
+    BackwardFilterProblem n = *b;
+    n.kernel_id = -1;
+    for (int i = 0; i < list.count; ++i)
+        if (list.info[i]->variant == 9 && list.info[i]->swap == innermost) n.kernel_id = list.id[i];
+    if (n.kernel_id < 0) return;
+    const KernelInfo &ki = *kernel_info(n.kernel_id);
+    ConvKernelParams &kn = n.pr.kp;
+    kn.PQ = (C + 31) / 32;
+    kn.Wp = Q + 2;
+    kn.HpWp = P;
+    if (!magic_for((uint32_t)kn.PQ, &kn.mPQ) || !magic_for((uint32_t)kn.Wp, &kn.mWp) || !magic_for((uint32_t)kn.HpWp, &kn.mHpWp)) return;
+    n.ksteps = (k.CRS + ki.BK - 1) / ki.BK;
+    n.tiles_n = ((long long)k.R * ((S + 2) / 3) * kn.PQ + 1) / 2;
+    n.tiles = (long long)((k.K + ki.BM - 1) / ki.BM) * n.tiles_n;
+    int splits, per, splits_old, per_old;
+    backward_filter_split(h, n, max_parts, &splits, &per);
+    backward_filter_split(h, *b, max_parts, &splits_old, &per_old);
+    // Precision.  Errors against 64 bits over 140 drawn layers: 5.9e-9 of a result times the root of the pixels a sum adds up before
+    // ranges meet with three bfloat16 parts, 1.8e-8 with the fp32 instruction; with two binary16 parts 6.2e-9, and 1.5e-7 of the operands'
+    // and small products' own.  Short reductions therefore stay (2x320x27x27 -> 112, 3x3: 1.1e-7, here 1.3e-7).
+    const bool split = old.variant == 4;
+    const double chain_old = 32.0 * per_old, chain = 64.0 * per;   // (two halves of a chunk's pixels apart)
+    if ((split ? 34.8 : 317.0) * chain_old < 22500.0 + 38.4 * chain) return;
+    // Time, us.  Here 3.0 per chunk, NCHW or channels innermost, and 21 for start, end and the parts' sum.  The others: steps at
+    // 195 to 143 TFLOP/s of the chip in tiles of split operands, 110 of fp32 ones, half of that or less with channels innermost.  Model and measured
+    // times of those layers (others -> here): 28x32x64x64 -> 112, 3x3 128 -> 69, measured 137 -> 80; 20x384x15x15 -> 160, 5x5 179 -> 129,
+    // measured 173 -> 139; 8x455x22x22 -> 230, 5x5 141 -> 153, measured 137 -> 166; 8x32x44x44 -> 32, 5x5 30 -> 33, measured 28 -> 33.
+    const double cus = h->computeUnits;
+    const double wgs_old = (double)b->tiles * splits_old;
+    const double resident = std::min((double)workgroups_per_cu(old), std::ceil(wgs_old / cus));
+    double rate = split ? (old.BM * old.BN >= 96 * 128 ? 6.6e5 : 5.6e5) : 4.3e5;   // flop per us and compute unit
+    if (innermost) rate *= 0.5;
+    const double us_old = 6.0 + std::ceil(wgs_old / (cus * resident)) * (per_old + 3.0) * resident * old.BM * old.BN * 64.0 / rate;
+    const double us = 21.0 + std::ceil((double)n.tiles * splits / cus) * per * 3.0;
+    if (us < us_old) *b = n;
 }
 
 }  // namespace igc
@@ -1746,6 +1796,7 @@ igcStatus igcConvolutionBackwardFilter(igcHandle_t handle, const void *alpha, ig
     const size_t part_bytes = (size_t)b.part_elems() * out_es;
     int splits, per;
     const long long room = workSpace ? (long long)(workSpaceSizeInBytes / part_bytes) : 0;
+    halves_backward_filter(handle, &b, std::max<long long>(1, room));
     backward_filter_split(handle, b, room, &splits, &per);
     // Channel-vector kernels: with room for at least one part the results go to the workspace in accumulator
     // order (coalesced) and the summing kernel moves them to dw; writing dw's layout from the tile is slow.

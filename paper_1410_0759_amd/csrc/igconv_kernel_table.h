@@ -35,6 +35,7 @@ struct KernelInfo {
                       // 4: float operands split into three bfloat16 parts, moving and multiplying wavefronts
                       // 6: channel vectors of a filter rewritten with the channel index innermost (gather mode 1, bf16)
                       // 7: float operands as two binary16 parts, the gathered side from a staged image patch, nine taps (gather mode 3); 8: more taps
+                      // 9: backward filter, float operands as two binary16 parts, three taps of a filter row per tile (gather mode 8)
                       // 5: the same as 4 for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
     int patchPixels = 512;  // gather mode 5, variants 5, 7 and 8: pixels of the zero-extended image a tile's staged patch can hold
@@ -49,7 +50,7 @@ struct KernelGroup {
 
 // One group per translation unit of kernel instantiations.
 extern const KernelGroup kGroupF32Taps9, kGroupF32TapMajor, kGroupF32Nopad, kGroupF32Generic, kGroupF32Swap, kGroupBF16,
-    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch, kGroupF32HalvesPatch, kGroupBF16Taps;
+    kGroupBF16Channels, kGroupWgrad, kGroupF64, kGroupWgradBF16Channels, kGroupBF16Pointwise, kGroupF32Teams, kGroupF32Masked, kGroupF64Masked, kGroupF32Direct, kGroupF32SplitNopad, kGroupF32SplitBorder, kGroupF32SplitSwap, kGroupWgradF32Split, kGroupF32SplitPatch, kGroupF32HalvesPatch, kGroupWgradF32Halves, kGroupBF16Taps;
 
 // Adds up `count` partial results (`stride` floats apart) into out = alpha*sum + beta*out;
 // returns the runtime's error code.

@@ -1,0 +1,133 @@
+"""The backward-filter kernel that writes float operands as two binary16 numbers.  On a handle told of eight compute units small
+problems take that route, several (tile, range) pairs to a workgroup."""
+import numpy as np
+import pytest
+
+import paper_1410_0759_amd as ig
+from oracle import conv_oracle as oc
+import workloads as wl
+from tests.test_gpu_split import SMALL, _check, _planted, _same, _scaled
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from tests import gpu_util
+    return gpu_util
+
+
+def _problem(seed, N, C, H, W, K, R, S, pad, stride):
+    rng = np.random.default_rng(seed)
+    P, Q = (H + 2 * pad[0] - R) // stride[0] + 1, (W + 2 * pad[1] - S) // stride[1] + 1
+    x = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    return x, (0.1 * rng.standard_normal(size=(N, K, P, Q))).astype(np.float32)
+
+
+@pytest.fixture
+def run(monkeypatch, capfd):
+    def call(gu, x, dy, rs, pad, stride, mode=1, layout="NCHW", workspace="full", alpha=1.0, beta=0.0, old=None, units=8):
+        g = gu.GpuBackwardFilter(wl.with_layout(x, layout), wl.with_layout(dy, layout), rs, pad, stride, mode, "f32", workspace)
+        if units:
+            ig.set_compute_units(g.handle, units)
+        if old is not None:
+            g.out.prefill(old=old)
+        else:
+            g.out.prefill(value=float("nan"))
+        monkeypatch.setenv("IGCONV_DEBUG", "1")
+        capfd.readouterr()
+        g.launch(alpha, beta)
+        assert "wgrad halves" in capfd.readouterr().err, "the route under test did not run"
+        g.ws.result()   # (guard bands)
+        return g.out.result()
+    return call
+
+
+PROBLEMS = [
+    # N, C, H, W, K, R, S, pad, stride
+    (12, 48, 14, 13, 70, 3, 3, (1, 1), (1, 1)),      # ragged rows; the last pair of units is half empty
+    (40, 32, 11, 9, 64, 3, 3, (1, 1), (1, 1)),       # shortest output rows: the longest patch
+    (9, 33, 40, 31, 45, 5, 4, (2, 1), (2, 1)),       # four taps in a row: the second three share two; vertical stride
+    (6, 96, 20, 24, 8, 3, 7, (1, 3), (1, 1)),        # eight maps
+    (5, 40, 30, 40, 130, 1, 5, (0, 2), (1, 1)),      # one filter row
+    (3, 25, 40, 60, 72, 9, 9, (0, 0), (1, 1)),       # channels: the last block has the last eight again
+    (1, 32, 30, 300, 64, 3, 3, (1, 1), (1, 1)),      # rows longer than two chunks
+]
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("prob", PROBLEMS)
+def test_backward_filter(prob, layout, run):
+    gu = _gpu()
+    *dims, pad, stride = prob
+    rs = dims[5:]
+    x, dy = _problem(51, *prob)
+    rng = np.random.default_rng(52)
+    for mode, alpha, beta, workspace in ((1, 1.0, 0.0, "full"), (0, 0.5, -1.5, "full"), (0, 1.0, 0.0, "none"), (1, 0.5, -1.5, "none")):
+        print(prob, layout, mode, workspace, flush=True)
+        old = rng.uniform(-1, 1, size=(dims[4], dims[1], *rs)).astype(np.float32) if beta else None
+        want = oc.conv_backward_filter(x, dy, rs, pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dw_old=old)
+        got = run(gu, x, dy, rs, pad, stride, mode, layout, workspace, alpha, beta, old)
+        assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
+        if beta == 0.0:   # (1.3e-7 and twice the chains' roundings: see halves_backward_filter in igconv_api.cpp)
+            assert np.linalg.norm(got - want) <= (1.5e-7 + 1.3e-8 * (dy.size / dims[4]) ** 0.5) * np.linalg.norm(want)
+
+
+def test_every_compute_unit(run):
+    """All of the chip: ranges of a few chunks, hundreds of parts."""
+    gu = _gpu()
+    x, dy = _problem(53, 24, 32, 40, 41, 64, 5, 5, (2, 2), (1, 1))
+    want = oc.conv_backward_filter(x, dy, (5, 5), pad=(2, 2), stride=(1, 1), mode=1)
+    got = run(gu, x, dy, (5, 5), (2, 2), (1, 1), units=0)
+    assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
+
+
+PLANTED = [(12, 48, 14, 13, 70, 3, 3, (1, 1), (1, 1)), (9, 33, 40, 31, 45, 5, 4, (2, 1), (2, 1))]
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny"])
+@pytest.mark.parametrize("prob", PLANTED)
+def test_values_outside_the_range(prob, kind, run):
+    gu = _gpu()
+    *dims, pad, stride = prob
+    rng = np.random.default_rng(54)
+    x, dy = _problem(55, *prob)
+    for operand in (0, 1):
+        a = [x, dy]
+        a[operand], other = _planted(a[operand], kind, rng)
+        a[1 - operand] = a[1 - operand] * other
+        print(prob, kind, operand, flush=True)
+        got = run(gu, a[0], a[1], dims[5:], pad, stride)
+        _same(got, oc.conv_backward_filter(a[0], a[1], dims[5:], pad=pad, stride=stride, mode=1), (prob, kind, operand))
+
+
+@pytest.mark.parametrize("kind", [*SMALL, "images", "drift", "wide range", "mostly zero"])
+@pytest.mark.parametrize("prob", PLANTED)
+def test_operands_of_unequal_size(prob, kind, run):
+    """Maps, channels, images or single operands far below the largest of their chunk, or of another chunk of the range."""
+    gu = _gpu()
+    *dims, pad, stride = prob
+    rng = np.random.default_rng(56)
+    x, dy = _problem(57, *prob)
+    if kind in SMALL:
+        sx, sy, rows, cols = SMALL[kind]
+        x, dy = _scaled(x, sx), _scaled(dy, sy)
+        dy[:, 3::7] = _scaled(dy[:, 3::7], rows)
+        x[:, :5] = _scaled(x[:, :5], cols)
+    elif kind == "images":      # exponents that leave what a range may span, up and down
+        for n in range(dims[0]):
+            x[n], dy[n] = _scaled(x[n], 60 - 30 * (n % 5)), _scaled(dy[n], 10 * (n % 3) - 60)
+    elif kind == "drift":       # sums scaled again from image to image
+        for n in range(dims[0]):
+            x[n] = _scaled(x[n], (n * 5) % 17)
+    elif kind == "wide range":
+        x, dy = (np.ldexp(a.astype(np.float64), rng.integers(-60, 1, size=a.shape)).astype(np.float32) for a in (x, dy))
+    else:
+        x *= rng.random(size=x.shape) < 0.02
+        x[0], dy[-1] = 0, 0
+    print(prob, kind, flush=True)
+    got = run(gu, x, dy, dims[5:], pad, stride)
+    want = oc.conv_backward_filter(x, dy, dims[5:], pad=pad, stride=stride, mode=1)
+    magnitude = oc.conv_backward_filter(np.abs(x), np.abs(dy), dims[5:], pad=pad, stride=stride, mode=1)
+    _check(got, want, magnitude, dy.size // dims[4], (prob, kind))
