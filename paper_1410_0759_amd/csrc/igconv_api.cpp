@@ -1569,21 +1569,31 @@ igcStatus igcConvolutionBiasActivationForward(igcHandle_t handle, const void *al
     // Tap-major order with a lent workspace of the filter's size: the filter is first rewritten with the channel
     // index innermost (wt[k][t][c]) and read through those strides - a step's filter elements are then contiguous
     // instead of R*S apart (a 5x5 layer with 96 channels: 74 -> 129 TFLOP/s).  Same sums in the same order.
-    if (splits <= 1 && rewrites_filter()) {
+    // bfloat16, nine taps whose window no staged patch holds (strides above all): the kernel that gathers channel vectors
+    // for every tap anew gives way to the one that reads them of both operands, rewritten filter included, with more tiles than
+    // compute units.  Gathered and rewritten, us: 32x128x56x56 -> 256, stride 2, 392 tiles 43 and 35 (accumulating 50 and 38); 64x32x56x56 ->
+    // 64, stride 2, 392 tiles 16.0 and 13.2; 32x64x200x200 -> 64 364 and 229; 128x16x64x64 -> 32, stride 2 26 and 19; but 32x256x28x28 ->
+    // 512, stride 2, 196 tiles 36.1 and 38.7; 100x160x20x20 -> 320, 237 tiles 24.9 and 27.9; 4x256x28x28 -> 512 22 and 28.
+    const bool gathered = pr.bf16 && kernel_info(id)->gmode == 4 && handle->kernelOverride < 0 && workSpace && (uintptr_t)workSpace % 16 == 0 &&
+                          workSpaceSizeInBytes >= (size_t)pr.kp.w_bytes;
+    auto more_tiles_than_units = [&](const KernelInfo &ki, const ConvKernelParams &k) {
+        return (long long)((k.K + ki.BM - 1) / ki.BM) * ((k.NPQ + ki.BN - 1) / ki.BN) > handle->computeUnits;
+    };
+    if (splits <= 1 && (rewrites_filter() || gathered)) {
         // (bfloat16 with contiguous channels: the kernel that reads channel vectors of both operands)
         Problem inner = pr;
         int inner_id = -1;
         inner.filter_inner = true;
         inner.mode_mask = 1u << 1;
         if (pr.bf16 && handle->kernelOverride < 0 && choose(handle, inner, true, ((uintptr_t)x % 16) == 0, &inner_id) == IGC_STATUS_SUCCESS &&
-            fill_plan(handle, inner_id, &inner, &plan) == IGC_STATUS_SUCCESS) {
+            (!gathered || more_tiles_than_units(*kernel_info(inner_id), inner.kp)) && fill_plan(handle, inner_id, &inner, &plan) == IGC_STATUS_SUCCESS) {
             pr = inner;
             id = inner_id;
             grid = plan.gridX;
         }
         ConvKernelParams &k = pr.kp;
         Magic mC, mRS;
-        if (magic_for((uint32_t)k.C, &mC) && magic_for((uint32_t)k.RS, &mRS)) {
+        if (kernel_info(id)->gmode == 1 && magic_for((uint32_t)k.C, &mC) && magic_for((uint32_t)k.RS, &mRS)) {
             if (launch_filter_taps_outer(w, workSpace, pr.bf16 ? 2 : 4, k.K, k.C, k.RS, false, mC, mRS, handle->stream) != 0)
                 return IGC_STATUS_EXECUTION_FAILED;
             k.w = workSpace;

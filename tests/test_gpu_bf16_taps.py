@@ -97,3 +97,37 @@ def test_backward_filter_many_ranges(prob):
         assert ws_bytes > 8 * dw0.size * 4
         # (products of bfloat16 numbers are exact; sums of N*P*Q of them in float)
         assert gu.rel_err(got, want) <= gu.BOUND["bf16"]
+
+
+@pytest.mark.parametrize("layout", ["NHWC", "NCHW"])     # of y
+@pytest.mark.parametrize("prob", [
+    # nine taps that no staged patch holds, more tiles than compute units (of which the handle is told 8)
+    (16, 48, 32, 45, 70, 3, 3, (1, 1), (2, 2)),       # ragged rows and columns, half a unit of channels
+    (40, 64, 29, 30, 136, 3, 3, (0, 1), (2, 2)),
+    (24, 96, 40, 33, 24, 9, 1, (4, 0), (3, 2)),
+])
+def test_forward_nine_taps(prob, layout):
+    import paper_1410_0759_amd as ig
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(6)
+    x, w = wl.with_layout(_rnd(rng, (N, C, H, W)), "NHWC"), _rnd(rng, (K, C, R, S), (C * R * S) ** -0.5)
+    bias = rng.uniform(-1, 1, size=K).astype(np.float32)
+    for mode in (0, 1):
+        print(prob, layout, mode, flush=True)
+        want = oc.conv_forward(x, w, pad=pad, stride=stride, mode=mode)
+        y0 = rng.uniform(-1, 1, size=want.shape).astype(np.float32)
+        res = []
+        for lent in (0, w.size * 2 - 2, w.size * 2):
+            g = gu.GpuConv(x, w, pad, stride, mode, dtype="bf16", y_layout=layout)
+            ig.set_compute_units(g.handle, 8)
+            assert g.plan().gatherMode == 4
+            if lent:
+                g.lend_workspace(lent)
+            g.prefill(y0, float("nan"))
+            g.launch_fused(0.5, -1.5, bias, 1)
+            res.append(g.result())
+            if lent:
+                g.ws.result()   # (guard bands)
+            assert gu.rel_err(res[-1], np.maximum(0.5 * want - 1.5 * y0 + bias[None, :, None, None], 0.0)) <= gu.BOUND["bf16"]
+        assert np.array_equal(res[0], res[1]) and not np.array_equal(res[0], res[2]), "the route under test did not run"
