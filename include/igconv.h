@@ -289,6 +289,7 @@ igcStatus igcConvolutionBackwardData(igcHandle_t handle, const void *alpha,
  *    a single range, because that kernel keeps its results in another order than dw's),
  *    down to a single range that writes dw directly - same result up to summation order,
  *    less parallelism.
+ *    Float layers whose filter rows have three taps and more, at unit horizontal stride, may be cut finer with more than the query reports.
  *  - dw and workSpace must not overlap x, dy or each other.
  *  - NOT_SUPPORTED also when H + 2*pad_h or W + 2*pad_w exceeds 2^14.
  *  - Other errors as for igcConvolutionForward; igcSetKernelOverride does not apply. */

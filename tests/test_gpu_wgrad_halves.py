@@ -28,7 +28,7 @@ def _problem(seed, N, C, H, W, K, R, S, pad, stride):
 @pytest.fixture
 def run(monkeypatch, capfd):
     def call(gu, x, dy, rs, pad, stride, mode=1, layout="NCHW", workspace="full", alpha=1.0, beta=0.0, old=None, units=8):
-        g = gu.GpuBackwardFilter(wl.with_layout(x, layout), wl.with_layout(dy, layout), rs, pad, stride, mode, "f32", workspace)
+        g = gu.GpuBackwardFilter(wl.with_layout(x, layout) if layout else x, wl.with_layout(dy, layout) if layout else dy, rs, pad, stride, mode, "f32", workspace)
         if units:
             ig.set_compute_units(g.handle, units)
         if old is not None:
@@ -131,3 +131,19 @@ def test_operands_of_unequal_size(prob, kind, run):
     want = oc.conv_backward_filter(x, dy, dims[5:], pad=pad, stride=stride, mode=1)
     magnitude = oc.conv_backward_filter(np.abs(x), np.abs(dy), dims[5:], pad=pad, stride=stride, mode=1)
     _check(got, want, magnitude, dy.size // dims[4], (prob, kind))
+
+
+@pytest.mark.parametrize("order", ["cnhw", "chwn", "whcn", "hnwc"])
+def test_tensors_of_any_order(order, run):
+    """Both operands in other orders than the two usual ones, x cut out of a larger tensor: the same sums as packed."""
+    gu = _gpu()
+    prob = (12, 48, 14, 13, 70, 3, 3, (1, 1), (1, 1))
+    x, dy = _problem(60, *prob)
+    where = {d: i for i, d in enumerate("nchw")}
+    placed = lambda a: np.ascontiguousarray(a.transpose([where[d] for d in order])).transpose([order.index(d) for d in "nchw"])
+    larger = np.zeros((13, 51, 15, 16), np.float32)
+    larger[:12, 2:50, :14, 1:14] = x
+    cut = placed(larger)[:12, 2:50, :14, 1:14]
+    print(order, flush=True)
+    want = run(gu, x, dy, (3, 3), (1, 1), (1, 1), layout="NHWC" if order[-1] == "c" else "NCHW")
+    assert np.array_equal(run(gu, cut, placed(dy), (3, 3), (1, 1), (1, 1), layout=None), want)
