@@ -8,8 +8,7 @@
 #include <cstdlib>
 #include <initializer_list>
 
-#include "../../include/igconv.h"
-#include "igconv_params.h"
+#include "igconv_api.cpp"   // (with what is internal to it: the choice of a kernel for lent space cannot be queried)
 
 static unsigned long long state = 14100759ull;
 static int draw(int lo, int hi) {   // uniform in lo..hi
@@ -130,6 +129,30 @@ int main() {
             const unsigned last = ((unsigned)(N - 1) * ysN + (unsigned)(PQ - 1) * (nhwc ? (unsigned)K : 1u)) * 4u;   // the last pixel
             if (map < K) REQUIRE(last < size - so && so == (unsigned)map * ysK * 4u);
         }
+    }
+    // The split filter of the two-part float kernels is addressed with 32 bits and may be many times the filter: lent any room,
+    // layers whose split filter is too large run elsewhere, those below it as before
+    REQUIRE(igcSetComputeUnits(h, 256) == IGC_STATUS_SUCCESS);
+    struct { int N, C, H, W, K, R, S, pad_h, pad_w; bool taken; } const rooms[] = {
+        {359, 103570, 1, 1, 513, 2, 5, 1, 4, false},     // 2.1 GB of filter, 4.3 GB split
+        {448, 116600, 1, 1, 449, 2, 5, 1, 4, false},
+        {280, 1870000, 1, 1, 8, 3, 3, 2, 2, false},      // 0.5 GB, 4.3 GB
+        {359, 52000, 1, 1, 513, 2, 5, 1, 4, false},      // 2.16 GB split: more than 2 GiB, less than 4
+        {359, 50000, 1, 1, 513, 2, 5, 1, 4, true},       // 2.07 GB: less than 2 GiB
+        {128, 64, 56, 56, 64, 3, 3, 1, 1, true}};
+    for (it = 0; it < 6; ++it) {
+        const auto &r = rooms[it];
+        const int P = r.H + 2 * r.pad_h - r.R + 1, Q = r.W + 2 * r.pad_w - r.S + 1;
+        REQUIRE(igcSetTensor4dDescriptor(x, IGC_DATA_FLOAT, r.N, r.C, r.H, r.W, (long long)r.C * r.H * r.W, r.H * r.W, r.W, 1) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetFilter4dDescriptor(w, IGC_DATA_FLOAT, r.K, r.C, r.R, r.S) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetConvolution2dDescriptor(c, r.pad_h, r.pad_w, 1, 1, IGC_CROSS_CORRELATION) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetTensor4dDescriptor(y, IGC_DATA_FLOAT, r.N, r.K, P, Q, (long long)r.K * P * Q, P * Q, Q, 1) == IGC_STATUS_SUCCESS);
+        igc::Problem pr;
+        REQUIRE(igc::validate(x, w, c, y, &pr) == IGC_STATUS_SUCCESS);
+        pr.halves_room = (size_t)1 << 40;
+        int id = -1;
+        REQUIRE(igc::choose(h, pr, true, true, &id) == IGC_STATUS_SUCCESS);
+        REQUIRE(igc::is_halves(*igc::kernel_info(id)) == r.taken);
     }
     it = -3;
     REQUIRE(igcDestroyTensorDescriptor(x) == IGC_STATUS_SUCCESS && igcDestroyTensorDescriptor(y) == IGC_STATUS_SUCCESS &&

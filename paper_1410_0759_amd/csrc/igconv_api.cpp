@@ -239,7 +239,8 @@ static long long column_tiles(const KernelInfo &ki, const ConvKernelParams &k) {
     return per_image ? per_image * k.N : (k.NPQ + ki.BN - 1) / ki.BN;
 }
 
-// Workspace of variants 7 and 8: the split filter and its table.
+// Workspace of variants 7 and 8: the split filter and its table.  (The kernels address the split filter with 32 bits, and its padding - K to 64,
+// C to 16, taps to nine - can make it many times the filter: see gather_mode_ok.)
 static size_t halves_bytes(const KernelInfo &ki, const ConvKernelParams &k) {
     return (size_t)((k.K + ki.BM - 1) / ki.BM) * (size_t)kernel_steps(ki, k) * ((size_t)(9 * ki.BM * 64) + 8);
 }
@@ -386,7 +387,8 @@ static bool gather_mode_ok(const KernelInfo &ki, const ConvKernelParams &k, bool
     if (is_halves(ki))   // R*S contiguous taps per (row, channel), nine or (variant 8) more; else as below, but with any number of channels
         return (ki.variant == 8 ? k.RS > 9 : k.RS == 9) && (!ki.swap || k.C % 4 == 0) && k.pad_h >= 0 && k.pad_w >= 0 && k.Wp == k.W + 2 * k.pad_w &&
                ((k.wsTapS == 1 && k.wsTapR == k.S) || (k.wsTapS == -1 && k.wsTapR == -k.S)) && (!ki.swap || k.xsC == 1) &&
-               (long long)k.N * (k.H + 2 * k.pad_h) * k.Wp < (1ll << 31) && patch_pixels_bound(k, ki.BN, image_tiles(ki, k) != 0) <= ki.patchPixels;
+               (long long)k.N * (k.H + 2 * k.pad_h) * k.Wp < (1ll << 31) && patch_pixels_bound(k, ki.BN, image_tiles(ki, k) != 0) <= ki.patchPixels &&
+               halves_bytes(ki, k) < (size_t)kMaxBytes;
     if (gmode == 3 && ki.variant == 5)
         // nine contiguous taps per (row, channel), walked forwards or backwards; a tile's pixels fit the patch; the
         // channel-fastest form reads four channels of a pixel at once
