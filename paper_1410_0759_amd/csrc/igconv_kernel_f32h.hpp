@@ -11,10 +11,14 @@
 // The exponent e is that of the chunk: the movers take the largest magnitude of the patch (of the filter rows) once it has
 // arrived, before any of it is written, and scale it to [2^14, 2^15); the factor 2^-(e + e') goes into the addition to
 // the third accumulator.  No range is assumed and none is kept from chunk to chunk.  What leaves it: an operand below 2^-13 after scaling
-// (below 2^-28 of its chunk's largest) loses up to 2^-36; the movers look for the smallest one that is not zero and, where
-// there are such operands, count them.  A sum of a tile with n of them is off by less than n * 2^-36 * 2^15 * 2^-(e + e'); a
-// wavefront with a sum below 2^24 times that, or that is not finite, or not zero but below 2^-100, multiplies its blocks
-// again with the fp32 instruction (sums_in_fp32).
+// (below 2^-28 of its chunk's largest) loses up to 2^-36.  The movers note each lane's smallest operand that is not zero; from the lanes that have such
+// operands, and from the largest sum of magnitudes of a filter row, follows what a sum of the tile may be off by (off_by).  Results below 2^22 times that,
+// not finite, or not zero but below 2^-100 are multiplied again with fp32 multiply-adds, one by one or - more than 96 of a wavefront's 4096 -
+// together (halves_mend).  Zeros are asked about only where an operand was below 2^-19, and pass where their whole filter row or window is zero.
+// us, 128x64x56x56 -> 64, 3x3, backward data (every tile with such an operand multiplied again -> this): log-normal gradients, sigma 2 130 -> 128, 2.5
+// 291 -> 137, 3 733 -> 150, with maps of zeros 739 -> 150; normal ones 134 -> 131.  -> 70 maps, one weight of 1e-12: 1152 -> 195, without it 207 -> 193.
+// What still costs: tiles over images whose gradients differ by 10^6 and more (384x13x13 -> 256: 868 -> 789, 123 where they are alike), windows of
+// zeros beside an operand far below the others (1286 -> 415, 150 without it).
 //
 // The reduction is ordered (16 channels, group of nine taps, tap, channel).  A tile's whole range of pixels of the
 // zero-extended image goes to LDS once per 16 channels, and all R*S taps read their operands from it at shifted
@@ -102,13 +106,17 @@ __device__ __forceinline__ uint32_t wave_largest(uint32_t v) {
     reduce(std::integral_constant<int, 0x143>{});
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
-// The wavefront's largest magnitude to LDS for the other moving wavefronts; returns its smallest (as in HalvesSeen).
-__device__ __forceinline__ uint32_t publish_largest(uint8_t *slot, const HalvesSeen &seen, int lane) {
+// The wavefront's largest magnitude to LDS for the other moving wavefronts.
+__device__ __forceinline__ void publish_largest(uint8_t *slot, const HalvesSeen &seen, int lane) {
     const uint32_t big = wave_largest(__builtin_bit_cast(uint32_t, seen.largest));
-    const uint32_t small = ~wave_largest(~seen.smallest);
     if (lane == 0) *reinterpret_cast<uint32_t *>(slot) = big;
-    return small;
 }
+// Beside a count of operands that lost something: one of them was below 2^-19 after scaling.  Then sums of zero are asked about too: else each
+// operand has 17 bits and more, and a sum of zero has no products but zeros, or some that cancel.
+constexpr uint32_t kFarBelow = 1u << 31;
+__device__ __forceinline__ uint32_t far_below(uint32_t below) { return below - (6u << 23); }
+// Lanes whose smallest operand (as in HalvesSeen) is under a magnitude.
+__device__ __forceinline__ uint64_t lanes_under(uint32_t smallest, uint32_t magnitude) { return __ballot(smallest < 2u * magnitude - 1u); }
 __device__ __forceinline__ HalvesScale read_scale(const uint8_t *slots) {   // of the four moving wavefronts
     const u32x4 b = *reinterpret_cast<const u32x4 *>(slots);
     const uint32_t b0 = b[0] > b[1] ? b[0] : b[1], b1 = b[2] > b[3] ? b[2] : b[3];
@@ -119,15 +127,130 @@ __device__ __forceinline__ uint32_t count_lossy(float x, uint32_t below) {
     return (uint32_t)__popcll(__ballot(u != 0u && u < below));
 }
 
+// True when a lane's sums call for a second look: one is infinite or NaN, or below 2^-100 or `limit` - zeros only where they are asked about.
+template <int MB, int NB>
+__device__ __forceinline__ bool outside_halves_range(const f32x16 (&sums)[MB][NB], float limit, bool zeros_too) {
+    float nan = 0.f;   // (as outside_split_range of igconv_kernel_f32s.hpp)
+    const uint32_t zero_passes = zeros_too ? 0u : ~0u;
+    uint32_t small = ~0u;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float a = sums[mb][nb][v];
+                nan = __builtin_fmaf(a, 0.f, nan);
+                const uint32_t u = (__builtin_bit_cast(uint32_t, a) << 1) + zero_passes;
+                small = small < u ? small : u;
+            }
+    const uint32_t least = __builtin_bit_cast(uint32_t, 0x1p-100f) << 1, other = __builtin_bit_cast(uint32_t, limit) << 1;
+    return nan != 0.f || small < (least > other ? least : other);
+}
+// A sum over the wavefront, the same in every lane.
+template <class T>
+__device__ __forceinline__ T wave_sum(T s) {
+    auto add = [&](auto ctrl_c) __attribute__((always_inline)) {
+        s += __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), decltype(ctrl_c)::value, 0xF, 0xF, true));
+    };
+    add(std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8: see wave_largest
+    add(std::integral_constant<int, 0x112>{});
+    add(std::integral_constant<int, 0x114>{});
+    add(std::integral_constant<int, 0x118>{});
+    add(std::integral_constant<int, 0x142>{});
+    add(std::integral_constant<int, 0x143>{});
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, s), 63));
+}
+
 // First tap of group g: the last group ends with the filter.
 __host__ __device__ __forceinline__ int halves_first_tap(int g, int taps) { return 9 * g < taps - 9 ? 9 * g : taps - 9; }
 
-// Chunk of a row block of the split filter: exponent, operands that lost something.
+// Chunk of a row block of the split filter: exponent, operands that lost something (144 at most: no result meets more; kFarBelow) and, from bit 8 on, the
+// largest sum of a row's magnitudes, scaled (at most 144 * 2^15).
 struct HalvesChunk {
     int e;
-    uint32_t lossy;
+    uint32_t lossy_sum;
 };
 
+// The results that operands with something lost could have touched, multiplied again one by one: four at a time, the wavefront's lanes along
+// their reduction.  get(g, v), set(g, v, s): result v of the lane's block g; counts(g, v): whether it is stored;
+// sums(which, from, s): the sums of result which[i] (16 g + v) of lane from[i].  limit: see the callers.  Results that are zero are, where
+// they are asked about, handed to zeros(bits) first, which strikes out those whose zero is right.  False, and nothing done, when there
+// are more than kMendMost left (then the blocks are cheaper as a whole).
+constexpr int kMendMost = 96;
+template <int G, class Get, class Set, class Counts, class Zeros, class Sums>
+__device__ __forceinline__ bool mend_results(float limit, bool zeros_too, int lane, Get get, Set set, Counts counts, Zeros zeros, Sums sums) {
+    const float least = limit > 0x1p-100f ? limit : 0x1p-100f;
+    uint32_t bad[G], zero[G];   // one bit per result
+    uint32_t any_zero = 0;
+    int left = 0;
+    auto count = [&](const uint32_t (&bits)[G]) __attribute__((always_inline)) {
+        int n = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) n += __builtin_popcount(bits[g]);
+        return wave_sum(n);
+    };
+    static_for<G>([&](auto gc) __attribute__((always_inline)) {
+        constexpr int g = decltype(gc)::value;
+        bad[g] = zero[g] = 0u;
+        static_for<16>([&](auto vc) __attribute__((always_inline)) {
+            constexpr int v = decltype(vc)::value;
+            const float a = __builtin_fabsf(get(gc, vc));
+            const uint32_t bit = counts(gc, vc) ? 1u << v : 0u;
+            zero[g] |= a == 0.f ? bit : 0u;
+            bad[g] |= a >= least && a < __builtin_inff() ? 0u : bit;   // (NaN: bad)
+        });
+        bad[g] &= ~zero[g];
+        if (zeros_too) any_zero |= zero[g];
+    });
+    left = count(bad);
+    if (left > kMendMost) return false;
+    if (__any(any_zero != 0u)) {
+        zeros(zero);
+        left += count(zero);
+        if (left > kMendMost) return false;
+#pragma unroll
+        for (int g = 0; g < G; ++g) bad[g] |= zero[g];
+    }
+#pragma clang loop unroll(disable)
+    while (left > 0) {
+        int first = -1;   // this lane's next one
+#pragma unroll
+        for (int g = G - 1; g >= 0; --g)
+            if (bad[g] != 0u) first = g * 16 + __builtin_ctz(bad[g]);
+        uint64_t lanes = __ballot(first >= 0);
+        int which[4], from[4];
+        float s[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // (fewer than four left: the first again)
+            from[i] = lanes != 0u ? __builtin_ctzll(lanes) : from[0];
+            which[i] = __builtin_amdgcn_readlane(first, from[i]);
+            left -= lanes != 0u ? 1 : 0;
+            lanes &= lanes - 1u;
+        }
+        sums(which, from, s);
+        float mended = 0.f;
+        bool mine = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            mended = lane == from[i] ? s[i] : mended;
+            mine = mine || lane == from[i];
+        }
+        const int at = mine ? first : -1;
+        static_for<G>([&](auto gc) __attribute__((always_inline)) {
+            constexpr int g = decltype(gc)::value;
+            static_for<16>([&](auto vc) __attribute__((always_inline)) {
+                constexpr int v = decltype(vc)::value;
+                set(gc, vc, at == g * 16 + v ? mended : get(gc, vc));
+            });
+            bad[g] = at >= 0 && at / 16 == g ? bad[g] & (bad[g] - 1u) : bad[g];
+        });
+    }
+    return true;
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
+}
 // NHWC: channel-fastest x (16-byte loads of channels) and y (lanes along output channels in the epilogue).
 // SETS: patches in registers, 2 (nine taps: a chunk is a block) or 1 (more).  WHOLE: one barrier per chunk, where two stages of
 // a chunk's filter fit (nine taps).
@@ -141,8 +264,9 @@ struct HalvesPatchConfig {
     static constexpr int B_BASE = (WHOLE ? 2 : 3) * A_STAGE;
     static constexpr int SLOT_B = B_BASE + 2 * B_STAGE;   // largest magnitudes of the patch [parity of the block][wavefront]
     static constexpr int SLOT_C = SLOT_B + 32;            // 2^-(e + e') [parity of the chunk]
-    static constexpr int SLOT_N = SLOT_C + 16;            // operands that lost something [parity of the tile][wavefront]
-    static constexpr int LDS_BYTES = SLOT_N + 32;
+    // [parity of the tile]: patch operands of each moving wavefront that lost something, what a sum may be off by for all the patch's, for the filter's
+    static constexpr int SLOT_N = SLOT_C + 16;
+    static constexpr int LDS_BYTES = SLOT_N + 64;
     static constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
     static constexpr int COPIES = A_STAGE / 1024;         // loads into LDS per step
     static constexpr int BLOCKS = PIX / 64;               // of 64 pixels
@@ -151,6 +275,299 @@ struct HalvesPatchConfig {
     static_assert((BM == 64 || BM == 128) && PIX % 64 == 0 && COPIES < 64 && !(WHOLE && SETS == 1), "shares of the moving wavefronts");
     static_assert(LDS_BYTES <= 160 * 1024 && B_PART < 65536, "LDS budget, offsets of the LDS instructions");
 };
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// All sums of a wavefront's blocks with v_mfma_f32_32x32x2_f32 straight from global memory: four taps as the filter stores them (they are next to each other:
+// see gather_mode_ok) of four channels at a time, the next ones requested meanwhile.  Half wavefronts have channels of their own.
+// (Index by index as sums_in_fp32 goes, a division for each and the filter element by element, a tile of 64x56x56 -> 64 took 100 us.)
+template <bool SWAP, int MB, int NB>
+__device__ __forceinline__ void halves_in_fp32(const ConvKernelParams &p, f32x16 (&acc)[MB][NB], int krow0, int col0, int half, int l32) {
+    constexpr int CH = 2;   // channels of a half wavefront per round
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.w), 0, p.w_bytes, kBufferWord3);
+    const bool rev = (p.flip != 0) != (p.wsTapS < 0);   // (see the kernel)
+    uint32_t rowoff[MB], colbase[NB];
+    int h0[NB], w0[NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int row = krow0 + mb * 32 + l32;
+        rowoff[mb] = row < p.K ? (uint32_t)row * (uint32_t)p.wsRow * 4u : kOutOfRange;
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int j = col0 + nb * 32 + l32;
+        const uint32_t jj = j < p.NPQ ? (uint32_t)j : 0u, n = magic_div(jj, p.mPQ), rem = jj - n * (uint32_t)p.PQ, pp = magic_div(rem, p.mQ), qq = rem - pp * (uint32_t)p.Q;
+        h0[nb] = j < p.NPQ ? (int)pp * p.u - p.pad_h : -(1 << 20);
+        w0[nb] = (int)qq * p.v - p.pad_w;
+        colbase[nb] = (n * (uint32_t)p.xsN + (uint32_t)((int)pp * p.u - p.pad_h) * (uint32_t)p.xsH + (uint32_t)w0[nb] * (uint32_t)p.xsW) * 4u;
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+    struct Operands { f32x4 a[CH][MB]; float b[CH][NB][4]; };
+    int tap0 = 0, c0 = 0;   // of the round to be requested
+    auto request = [&](Operands &o) __attribute__((always_inline)) {
+        uint32_t xo[NB][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int at = rev ? p.RS - 1 - (tap0 + t) : tap0 + t;   // (past the last tap: outside every window)
+            const uint32_t tr = magic_div((uint32_t)(at < 0 ? 0 : at), p.mS), ts = (uint32_t)at - tr * (uint32_t)p.S;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const bool ok = tap0 + t < p.RS && (uint32_t)(h0[nb] + (int)tr) < (uint32_t)p.H && (uint32_t)(w0[nb] + (int)ts) < (uint32_t)p.W;
+                xo[nb][t] = ok ? colbase[nb] + (tr * (uint32_t)p.xsH + ts * (uint32_t)p.xsW) * 4u : kOutOfRange;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < CH; ++e) {
+            const int c = c0 + e * 2 + half;
+            const bool live = c < p.C;
+            const uint32_t wc = ((uint32_t)c * (uint32_t)p.wsRed + (uint32_t)tap0) * 4u, xc = (uint32_t)c * (uint32_t)p.xsC * 4u;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {   // (taps past the last one: multiplied by zero below)
+                const uint32_t at = live && rowoff[mb] != kOutOfRange ? rowoff[mb] + wc : kOutOfRange;
+                o.a[e][mb] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, at, 0, 0));
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint32_t at = live && xo[nb][t] != kOutOfRange ? xo[nb][t] + xc : kOutOfRange;
+                    o.b[e][nb][t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, at, 0, 0));
+                }
+        }
+        if ((c0 += 2 * CH) >= p.C) {
+            c0 = 0;
+            tap0 += 4;
+        }
+    };
+    int tap_now = 0, c_now = 0;   // of the round being multiplied
+    auto multiply = [&](const Operands &o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (tap_now + t >= p.RS) break;   // (what was read in their place may be another row's infinity)
+#pragma unroll
+            for (int e = 0; e < CH; ++e)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const float a = o.a[e][mb][t], b = o.b[e][nb][t];
+                        if constexpr (SWAP) acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, acc[mb][nb], 0, 0, 0);
+                        else acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc[mb][nb], 0, 0, 0);
+                    }
+        }
+        if ((c_now += 2 * CH) >= p.C) {
+            c_now = 0;
+            tap_now += 4;
+        }
+    };
+    Operands o0, o1;
+    request(o0);
+#pragma clang loop unroll(disable)
+    for (int left = (p.RS + 3) / 4 * ((p.C + 2 * CH - 1) / (2 * CH)); left > 0; left -= 2) {
+        request(o1);
+        multiply(o0);
+        request(o0);
+        multiply(o1);
+    }
+}
+
+// The sums of a tile's results that are out of range or that something lost could have touched, with fp32 multiply-adds, one by one or - many of them -
+// all blocks of the wavefront.  limit: 2^22 times what a sum may be off by.  A sum of zero is right where its whole row or window of operands is zero.
+// n_end: first column beyond the tile's.  A call: inlined, its registers spilled in the tiles that need none of it (64x56x56 -> 64, channels innermost 120 -> 131 us).
+using KernelArguments = const __attribute__((address_space(4))) ConvKernelParams;
+template <bool SWAP, int MB, int NB>
+__device__ __attribute__((noinline)) void halves_mend(uint64_t arguments, f32x16 *blocks, float limit, bool zeros_too, int n_end, int krow0, int col0) {
+    ConvKernelParams p = *(KernelArguments *)(uintptr_t)uniform64(arguments);
+    p.NPQ = __builtin_amdgcn_readfirstlane(n_end);
+    krow0 = __builtin_amdgcn_readfirstlane(krow0);
+    col0 = __builtin_amdgcn_readfirstlane(col0);
+    limit = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, limit)));
+    zeros_too = __builtin_amdgcn_readfirstlane((int)zeros_too) != 0;
+    f32x16 total[MB][NB];
+#pragma unroll
+    for (int g = 0; g < MB * NB; ++g) total[g / NB][g % NB] = blocks[g];
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.w), 0, p.w_bytes, kBufferWord3);
+    auto get = [&](auto gc, auto vc) __attribute__((always_inline)) {
+        const float a = total[decltype(gc)::value / NB][decltype(gc)::value % NB][decltype(vc)::value];
+        return a;
+    };
+    auto set = [&](auto gc, auto vc, float a) __attribute__((always_inline)) { total[decltype(gc)::value / NB][decltype(gc)::value % NB][decltype(vc)::value] = a; };
+    auto in_block = [](int v, int h) { return v / 4 * 8 + v % 4 + h * 4; };   // row (SWAP: column) of a block
+    auto counts = [&](auto gc, auto vc) __attribute__((always_inline)) {
+        constexpr int mb = decltype(gc)::value / NB, nb = decltype(gc)::value % NB, v = decltype(vc)::value;
+        return krow0 + mb * 32 + (SWAP ? l32 : in_block(v, half)) < p.K && col0 + nb * 32 + (SWAP ? in_block(v, half) : l32) < p.NPQ;
+    };
+    // reduction index k: offsets of its filter element and of its tap's pixel, the tap
+    struct Index { uint32_t ao, so; int tr, ts; };
+    auto decode = [&](uint32_t k) __attribute__((always_inline)) {
+        const uint32_t c = magic_div(k, p.mRS), rs = k - c * (uint32_t)p.RS, r = magic_div(rs, p.mS), sx = rs - r * (uint32_t)p.S;
+        Index x;
+        x.tr = (int)(p.flip ? (uint32_t)p.R - 1u - r : r);
+        x.ts = (int)(p.flip ? (uint32_t)p.S - 1u - sx : sx);
+        x.ao = (c * (uint32_t)p.wsRed + (uint32_t)p.wTap0 + r * (uint32_t)p.wsTapR + sx * (uint32_t)p.wsTapS) * 4u;
+        x.so = (c * (uint32_t)p.xsC + (uint32_t)x.tr * (uint32_t)p.xsH + (uint32_t)x.ts * (uint32_t)p.xsW) * 4u;
+        return x;
+    };
+    struct Window { int h0, w0; uint32_t base; };
+    auto window = [&](int j) __attribute__((always_inline)) {
+        const uint32_t n = magic_div((uint32_t)j, p.mPQ), rem = (uint32_t)j - n * (uint32_t)p.PQ, pp = magic_div(rem, p.mQ), qq = rem - pp * (uint32_t)p.Q;
+        Window w;
+        w.h0 = (int)pp * p.u - p.pad_h;
+        w.w0 = (int)qq * p.v - p.pad_w;
+        w.base = (n * (uint32_t)p.xsN + (uint32_t)w.h0 * (uint32_t)p.xsH + (uint32_t)w.w0 * (uint32_t)p.xsW) * 4u;
+        return w;
+    };
+    auto load_w = [&](bool ok, uint32_t rowoff, const Index &x) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wbuf, ok ? rowoff + x.ao : kOutOfRange, 0, 0));
+    };
+    auto load_x = [&](bool ok, const Window &w, const Index &x) __attribute__((always_inline)) {
+        ok = ok && (uint32_t)(w.h0 + x.tr) < (uint32_t)p.H && (uint32_t)(w.w0 + x.ts) < (uint32_t)p.W;
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, ok ? w.base + x.so : kOutOfRange, 0, 0));
+    };
+    // Rows of zeros: the lanes along a row, as far as the first operand that is not zero.  Then windows of zeros: a lane on each.
+    auto zeros = [&](uint32_t (&zero)[MB * NB]) __attribute__((always_inline)) {
+        // (row or column) r of block i of 32: its results' bits
+        auto strike_lanes = [&](int i, uint32_t which, bool rows) __attribute__((always_inline)) {   // along the lanes: a bit per lane
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g)
+                if ((rows ? g / NB : g % NB) == i && ((which >> l32) & 1u) != 0u) zero[g] = 0u;
+        };
+        auto strike_results = [&](int i, uint32_t which, bool rows) __attribute__((always_inline)) {   // along the results of a lane
+            uint32_t bits = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bits |= ((which >> in_block(v, half)) & 1u) << v;
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g)
+                if ((rows ? g / NB : g % NB) == i) zero[g] &= ~bits;
+        };
+        // which rows (columns) of block i have such results
+        auto present_lanes = [&](int i, bool rows) __attribute__((always_inline)) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g)
+                if ((rows ? g / NB : g % NB) == i) bits |= zero[g];
+            const uint64_t m = __ballot(bits != 0u);
+            return (uint32_t)m | (uint32_t)(m >> 32);
+        };
+        auto present_results = [&](int i, bool rows) __attribute__((always_inline)) {
+            uint32_t bits = 0, found = 0;
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g)
+                if ((rows ? g / NB : g % NB) == i) bits |= zero[g];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint64_t m = __ballot((bits >> v) & 1u);
+                found |= ((uint32_t)m != 0u ? 1u : 0u) << in_block(v, 0) | ((m >> 32) != 0u ? 1u : 0u) << in_block(v, 1);
+            }
+            return found;
+        };
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            uint32_t rows = SWAP ? present_lanes(mb, true) : present_results(mb, true), all_zero = 0;
+#pragma clang loop unroll(disable)
+            while (rows != 0u) {
+                const int r = __builtin_ctz(rows);
+                rows &= rows - 1u;
+                const uint32_t rowoff = (uint32_t)(krow0 + mb * 32 + r) * (uint32_t)p.wsRow * 4u;
+                bool found = false;
+#pragma clang loop unroll(disable)
+                for (int k0 = 0; k0 < p.CRS && !found; k0 += 512) {
+                    float a[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int k = k0 + e * 64 + lane;
+                        a[e] = load_w(k < p.CRS, rowoff, decode((uint32_t)k));
+                    }
+                    bool some = false;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) some = some || a[e] != 0.f;
+                    found = __any(some);
+                }
+                all_zero |= found ? 0u : 1u << r;
+            }
+            if (SWAP) strike_lanes(mb, all_zero, true);
+            else strike_results(mb, all_zero, true);
+        }
+        // (a lane on column l32 of block `half`, then of the two blocks after)
+        static_assert(NB % 2 == 0, "two blocks of columns at a time");
+#pragma unroll
+        for (int nb = 0; nb < NB; nb += 2) {
+            const uint32_t c0 = SWAP ? present_results(nb, false) : present_lanes(nb, false), c1 = SWAP ? present_results(nb + 1, false) : present_lanes(nb + 1, false);
+            bool open = (((half ? c1 : c0) >> l32) & 1u) != 0u;
+            const bool asked = open;
+            const int j = col0 + (nb + half) * 32 + l32;
+            const Window w = window(j < p.NPQ ? j : p.NPQ - 1);
+#pragma clang loop unroll(disable)
+            for (int rs = 0; rs < p.RS && __any(open); ++rs) {   // tap by tap
+                const uint32_t tr = magic_div((uint32_t)rs, p.mS), ts = (uint32_t)rs - tr * (uint32_t)p.S;
+                const bool inside = (uint32_t)(w.h0 + (int)tr) < (uint32_t)p.H && (uint32_t)(w.w0 + (int)ts) < (uint32_t)p.W;
+                const uint32_t at = w.base + (tr * (uint32_t)p.xsH + ts * (uint32_t)p.xsW) * 4u;
+#pragma clang loop unroll(disable)
+                for (int c = 0; c < p.C && __any(open); c += 32) {
+                    float b[32];
+                    const uint32_t from = open && inside ? at + (uint32_t)c * (uint32_t)p.xsC * 4u : kOutOfRange;
+#pragma unroll
+                    for (int e = 0; e < 32; ++e)   // (beyond the last channel: the last again)
+                        b[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, from, (uint32_t)(c + e < p.C ? e : p.C - 1 - c) * (uint32_t)p.xsC * 4u, 0));
+                    bool some = false;
+#pragma unroll
+                    for (int e = 0; e < 32; ++e) some = some || b[e] != 0.f;
+                    open = open && !some;
+                }
+            }
+            const uint64_t m = __ballot(asked && open);   // (still open: all of it is zero)
+            if (SWAP) {
+                strike_results(nb, (uint32_t)m, false);
+                strike_results(nb + 1, (uint32_t)(m >> 32), false);
+            } else {
+                strike_lanes(nb, (uint32_t)m, false);
+                strike_lanes(nb + 1, (uint32_t)(m >> 32), false);
+            }
+        }
+    };
+    auto sums = [&](const int (&which)[4], const int (&from)[4], float (&s)[4]) __attribute__((always_inline)) {
+        uint32_t rowoff[4];
+        Window w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int g = which[i] >> 4, r = in_block(which[i] & 15, from[i] >> 5), l = from[i] & 31;
+            rowoff[i] = (uint32_t)(krow0 + g / NB * 32 + (SWAP ? l : r)) * (uint32_t)p.wsRow * 4u;
+            w[i] = window(col0 + g % NB * 32 + (SWAP ? r : l));
+            s[i] = 0.f;
+        }
+#pragma clang loop unroll(disable)
+        for (int k0 = 0; k0 < p.CRS; k0 += 192) {
+            float a[3][4], b[3][4];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int k = k0 + e * 64 + lane;
+                const Index x = decode((uint32_t)k);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a[e][i] = load_w(k < p.CRS, rowoff[i], x);
+                    b[e][i] = load_x(k < p.CRS, w[i], x);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = __builtin_fmaf(a[e][i], b[e][i], s[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = wave_sum(s[i]);
+    };
+    if (!mend_results<MB * NB>(limit, zeros_too, lane, get, set, counts, zeros, sums)) halves_in_fp32<SWAP, MB, NB>(p, total, krow0, col0, half, l32);
+#pragma unroll
+    for (int g = 0; g < MB * NB; ++g) blocks[g] = total[g / NB][g % NB];
+}
+#endif
 
 template <class Cfg>
 __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelParams p) {
@@ -317,8 +734,11 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             *reinterpret_cast<u32x4 *>(dst) = bh;
             *reinterpret_cast<u32x4 *>(dst + Cfg::B_PART) = bm;
         };
-        uint32_t small_b = 0;   // smallest magnitude of what is in registers (this wavefront's)
-        uint32_t lossy_a = 0, lossy_b = 0;   // operands of the tile that lose something: all of the filter's, this wavefront's
+        uint32_t small_b = 0;   // smallest magnitude of what is in registers (this lane's, as in HalvesSeen)
+        // Products of one result that this wavefront's lost operands could touch, counted from above (a lane with a small one may have as many as it
+        // holds; a block has 144 indices per group).
+        uint32_t lossy_b = 0, far_a = 0, far_b = 0;
+        float off_a = 0.f, off_b = 0.f;   // 2^22 times what a sum may be off by for lost operands of the filter, for any of the patch
         auto look_at_patch = [&](auto set_c, int parity) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
             HalvesSeen seen;
@@ -328,18 +748,17 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
 #pragma unroll
                     for (int e = 0; e < 8; e += 2) look_at(seen, b_reg[set][i][e], b_reg[set][i][e + 1]);
             });
-            small_b = publish_largest(lds + Cfg::SLOT_B + parity * 16 + mw * 4, seen, lane);
+            publish_largest(lds + Cfg::SLOT_B + parity * 16 + mw * 4, seen, lane);
+            small_b = seen.smallest;
         };
-        auto scale_patch = [&](auto set_c, int parity) __attribute__((always_inline)) {
-            constexpr int set = decltype(set_c)::value;
+        auto scale_patch = [&](int parity) __attribute__((always_inline)) {
             sb = read_scale(lds + Cfg::SLOT_B + parity * 16);
-            if (small_b < 2u * sb.below - 1u)
-                static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value;
-                    if (3 * i + mw < held[0])
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) lossy_b += count_lossy(b_reg[set][i][e], sb.below);
-                });
+            const uint64_t small = lanes_under(small_b, sb.below);
+            if (small != 0u) {
+                const uint32_t n = (uint32_t)__popcll(small) * (8u * ITEMS), most = 144u * (uint32_t)groups;
+                lossy_b += n < most ? n : most;   // (far below 2^31: the split filter has fewer chunks)
+                if (lanes_under(small_b, far_below(sb.below)) != 0u) far_b = kFarBelow;
+            }
         };
 
         // where the chunk being written and the block being requested are
@@ -360,13 +779,21 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         auto publish_scale = [&](bool tile_begins) __attribute__((always_inline)) {   // the chunk's, for the multipliers
             if (mw == 0) {
                 const uint64_t t = table[entry];   // HalvesChunk
-                lossy_a = (tile_begins ? 0u : lossy_a) + (uint32_t)(t >> 32);
-                if (lane == 0)
-                    *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_C + (n_chunk & 1u) * 4u) = (uint32_t)(127 - (int)(uint32_t)t - e_patch) << 23;
+                const uint32_t n = (uint32_t)(t >> 32), c = (uint32_t)(127 - (int)(uint32_t)t - e_patch) << 23;
+                const float c14 = __builtin_bit_cast(float, c) * 0x1p-14f;   // (2^-36 * 2^22)
+                off_a = __builtin_fmaf((float)((n & 255u) << 15), c14, tile_begins ? 0.f : off_a);
+                off_b = __builtin_fmaf((float)(n >> 8 & 0x7FFFFFu), c14, tile_begins ? 0.f : off_b);
+                far_a = (tile_begins ? 0u : far_a) | (n & kFarBelow);
+                if (lane == 0) *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_C + (n_chunk & 1u) * 4u) = c;
             }
         };
         auto publish_lossy = [&]() __attribute__((always_inline)) {   // the tile's
-            if (lane == 0) *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + ((it & 1) * 4 + mw) * 4) = lossy_a + lossy_b;
+            uint8_t *const slot = lds + Cfg::SLOT_N + (it & 1) * 32;
+            if (lane == 0) {
+                *reinterpret_cast<uint32_t *>(slot + mw * 4) = lossy_b | far_a | far_b;
+                if (mw == 0) *reinterpret_cast<float *>(slot + 12) = off_b;
+                if (mw == 0) *reinterpret_cast<float *>(slot + 16) = off_a;
+            }
         };
         auto next_chunk = [&]() __attribute__((always_inline)) {
             ++n_chunk;
@@ -393,8 +820,8 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
                     if (block_end && cb == nch - 1) publish_lossy();
                 }
                 if constexpr (j == 1 && block_end) {
-                    if (cb == nch - 1) lossy_b = 0;   // (from here on the next tile's)
-                    scale_patch(Blk{}, (n_block + 1) & 1);
+                    if (cb == nch - 1) lossy_b = far_b = 0;   // (from here on the next tile's)
+                    scale_patch((n_block + 1) & 1);
                 }
                 if constexpr (j > 0 && block_end)
                     static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
@@ -422,8 +849,8 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         // after the next, the next one's magnitudes taken.
         auto whole_chunk = [&](auto par_c) __attribute__((always_inline)) {
             constexpr int par = decltype(par_c)::value;
-            if (cb == 0) lossy_b = 0;
-            scale_patch(par_c, par);
+            if (cb == 0) lossy_b = far_b = 0;
+            scale_patch(par);
             e_patch = sb.e;
             publish_scale(cb == 0);
             if (cb == nch - 1) publish_lossy();
@@ -449,7 +876,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         };
         if (lane == 0 && mw == 0)   // (the unused fourth wavefront's)
             for (int i = 0; i < 2; ++i)
-                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_B + i * 16 + 12) = *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + i * 16 + 12) = 0u;
+                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_B + i * 16 + 12) = 0u;
         setup_patch(tile_number(0));
         request_patch(S0{}, 0);
         if constexpr (SETS == 2) request_patch(std::integral_constant<int, 1>{}, 1);
@@ -465,7 +892,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             split_barrier();
             return;
         }
-        scale_patch(S0{}, 0);
+        scale_patch(0);
         e_patch = sb.e;
         static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) { if (3 * decltype(ic)::value + mw < held[0]) convert_b(S0{}, decltype(ic)::value, 0); });
         if constexpr (SETS == 2) held[0] = held[1];
@@ -601,16 +1028,19 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
     columns(tile_number(0), 0, fb);
     int s0;
     int off0 = tap_position(0, &s0);
+    auto first_fragments = [&]() __attribute__((always_inline)) {   // of the next chunk
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        ah[0][mb] = read(fa + mb * 512);
-        am[mb] = read(fa + mb * 512 + Cfg::A_PART);
-    }
+        for (int mb = 0; mb < MB; ++mb) {
+            ah[0][mb] = read(fa + mb * 512);
+            am[mb] = read(fa + mb * 512 + Cfg::A_PART);
+        }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        bm[nb] = read(fb[nb] + off0 + Cfg::B_PART);
-        if (nb < NB - 1) bh[nb] = read(fb[nb] + off0);
-    }
+        for (int nb = 0; nb < NB; ++nb) {
+            bm[nb] = read(fb[nb] + off0 + Cfg::B_PART);
+            if (nb < NB - 1) bh[nb] = read(fb[nb] + off0);
+        }
+    };
+    first_fragments();
     for (int it = 0;; ++it) {
         const int tile = tile_number(it);
         if (tile >= tiles_total) break;
@@ -655,13 +1085,38 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) total[mb][nb][v] = __builtin_fmaf(acc[mb][nb][v], c_before, total[mb][nb][v]);
-        const u32x4 lossy = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
-        const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lossy[0] + lossy[1] + lossy[2] + lossy[3]));
-        const float off_by = (float)count * 8.f * __builtin_bit_cast(float, c_largest);   // count * 2^-36 * 2^15 * 2^24 * c
+        // What a sum may be off by, times 2^22: each lost operand of the patch by 2^-36 times one of the filter's - as many as were counted, below 2^15
+        // each, or all of the row's -, each of the filter's by 2^-36 * 2^15; scaled.
+        const u32x4 lossy = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 32);
+        const uint32_t count = (lossy[0] & ~kFarBelow) + (lossy[1] & ~kFarBelow) + (lossy[2] & ~kFarBelow);
+        const bool zeros_too = __builtin_amdgcn_readfirstlane((int)((lossy[0] | lossy[1] | lossy[2]) & kFarBelow)) != 0;
+        const uint32_t all_bits = lossy[3];   // (a bit cast of the vector's element itself takes element 0)
+        const float counted = (float)count * 2.f * __builtin_bit_cast(float, c_largest), all = __builtin_bit_cast(float, all_bits);
+        float off_by = *reinterpret_cast<const float *>(lds + Cfg::SLOT_N + (it & 1) * 32 + 16) + (count == 0u ? 0.f : (counted < all ? counted : all));
+        off_by = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, off_by)));
         ConvKernelParams pt = p;
         pt.NPQ = n_end;
-        if (__any(outside_split_range<MB, NB>(total, count != 0 ? __builtin_bit_cast(uint32_t, off_by) : 0u)))
-            sums_in_fp32<Cfg::SWAP, MB, NB>(pt, total, krow0, col0, 0, p.CRS, half, l32);
+        // (rows beyond the last one are zero and would always be asked about: they count as large)
+        const bool ragged = zeros_too && krow0 + Cfg::TM > p.K;
+        if (__builtin_expect(ragged, 0)) {
+            const int rows = p.K - krow0 - (Cfg::SWAP ? l32 : half * 4);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        total[mb][nb][v] = mb * 32 + (Cfg::SWAP ? 0 : v / 4 * 8 + v % 4) < rows ? total[mb][nb][v] : 3e38f;
+        }
+        if (__builtin_expect(__any(outside_halves_range<MB, NB>(total, off_by, zeros_too)), 0)) {
+            f32x16 blocks[MB * NB];
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g) blocks[g] = total[g / NB][g % NB];
+            halves_mend<Cfg::SWAP, MB, NB>((uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), blocks, off_by, zeros_too, n_end, krow0, col0);
+#pragma unroll
+            for (int g = 0; g < MB * NB; ++g) total[g / NB][g % NB] = blocks[g];
+            first_fragments();   // (again: not held across the call)
+        }
         const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.y_bytes, kBufferWord3);
         store_tile<Cfg::SWAP, MB, NB>(pt, ybuf, total, bvec, krow0, col0, half, l32);
     }

@@ -9,7 +9,7 @@ __global__ __launch_bounds__(512) void igconv_split_filter_kernel(const float *w
                                                                   uint32_t row_stride, uint32_t channel_stride, uint32_t w_bytes) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64, CPT = BM / 32;
-    __shared__ __attribute__((aligned(16))) uint32_t slots[8], counts[8];
+    __shared__ __attribute__((aligned(16))) uint32_t slots[8], counts[8], sums[8];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = blockIdx.x, cb = chunk / groups, g = chunk - cb * groups;
     const int row = tid / (16 / CPT), sub = tid % (16 / CPT);
@@ -47,7 +47,20 @@ __global__ __launch_bounds__(512) void igconv_split_filter_kernel(const float *w
     for (int e = 0; e < CPT; ++e)
 #pragma unroll
         for (int t = 0; t < 9; ++t) lossy += count_lossy(x[e][t], sc.below);
-    if (lane == 0) counts[wave] = lossy;
+    float sum = 0.f;   // of the row's magnitudes: eight neighbouring threads have it
+#pragma unroll
+    for (int e = 0; e < CPT; ++e)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) sum += __builtin_fabsf(x[e][t]) * sc.s;
+    static_assert(16 / CPT == 8, "threads of a row");
+#pragma unroll
+    for (int d = 4; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    const uint32_t row_sum = wave_largest(__builtin_bit_cast(uint32_t, sum));   // (not negative: ordered like its bits)
+    if (lanes_under(seen.smallest, far_below(sc.below)) != 0u) lossy |= kFarBelow;
+    if (lane == 0) {
+        counts[wave] = lossy;
+        sums[wave] = row_sum;
+    }
     uint8_t *const dst = out + ((size_t)blockIdx.y * gridDim.x + (size_t)chunk) * (9 * BM * 64) + (sub * CPT / 8) * (BM * 16) + row * 16 + sub * CPT % 8 * 2;
     using u32xq = uint32_t __attribute__((ext_vector_type(CPT / 2)));
 #pragma unroll
@@ -64,9 +77,15 @@ __global__ __launch_bounds__(512) void igconv_split_filter_kernel(const float *w
     }
     __syncthreads();
     if (tid == 0) {
-        uint32_t n = 0;
-        for (int i = 0; i < 8; ++i) n += counts[i];
-        table[(size_t)blockIdx.y * gridDim.x + (size_t)chunk] = HalvesChunk{sc.e, n};
+        uint32_t n = 0, far = 0, most = 0;
+        for (int i = 0; i < 8; ++i) {
+            n += counts[i] & ~kFarBelow;
+            far |= counts[i] & kFarBelow;
+            most = most > sums[i] ? most : sums[i];
+        }
+        const float bound = __builtin_bit_cast(float, most) + 2.f;   // (rounded up; infinities and NaN, whose sums are multiplied again anyway: the largest)
+        const uint32_t row_most = bound < 144.f * 32768.f ? (uint32_t)bound : 144u * 32768u;
+        table[(size_t)blockIdx.y * gridDim.x + (size_t)chunk] = HalvesChunk{sc.e, (n < 144u ? n : 144u) | row_most << 8 | far};
     }
 #endif
 }
