@@ -28,10 +28,13 @@
 // the chunk itself is split and written.
 //
 // Exponents.  As in the forward kernel an operand is scaled by a power of two, here kept from chunk to chunk of a range while the
-// chunk's largest magnitude, scaled, stays within [2^6, 2^15) (it is put into [2^13, 2^14) when it does not; the sums so far are then
-// multiplied by the ratio).  Operands below 2^-13 after scaling lose up to 2^-36 and are counted: a sum of a range with n of them
-// is off by less than n * 2^-36 * 2^15 * 2^-(e + e'), e + e' the smallest of the range.  A wavefront with a sum below 2^24 times that, or that is not
-// finite, or not zero but below 2^-100, or in a range whose exponents moved by more than 40, multiplies its blocks again with the fp32 instruction.
+// chunk's largest magnitude, scaled, stays within [2^13, 2^15) (it is put into [2^13, 2^14) when it does not; the sums so far are then
+// multiplied by the ratio, which the multipliers have time for), and at most 2^40 finer than that of the range's largest chunk.  Operands below 2^-13
+// after scaling lose up to 2^-36; the movers count the lanes that have some, and with them, per chunk, what a sum may be off by.  Results below 2^22 times that, not
+// finite, or not zero but below 2^-100 are multiplied again as in the forward kernel (wgrad_halves_mend), zeros where an operand was below 2^-19.
+// us, 128x64x56x56 -> 64, 3x3 (scaled to [2^6, 2^15), every range with such an operand multiplied again -> this): normal 154 -> 154; one gradient of 1e-11
+// 791 -> 175 with a map of zeros; log-normal gradients, sigma 2 820 -> 162, with maps of zeros 825 -> 161, 2.5 880 -> 185 and 222, 3 875 -> 215 and 258;
+// images whose gradients differ by up to 10^12 787 -> 222.
 #ifndef IGCONV_KERNEL_WGRAD_F32H_HPP_
 #define IGCONV_KERNEL_WGRAD_F32H_HPP_
 
@@ -55,14 +58,11 @@ struct WgradHalvesConfig {
     static constexpr int POS = TABLE + 2 * TABLE_BYTES;        // [chunk % 4][pixel]: distance of its window in the patch
     static constexpr int SLOT_MAX = POS + 4 * BK * 4;          // largest magnitudes [parity][dy, x][wavefront]
     static constexpr int SLOT_E = SLOT_MAX + 64;               // e + e' [parity of the chunk]
-    static constexpr int SLOT_N = SLOT_E + 16;                 // operands that lost something [parity of the range][wavefront]
-    static constexpr int SLOT_LOW = SLOT_N + 32;               // smallest e + e' [parity of the range]
-    static constexpr int LDS_BYTES = SLOT_LOW + 16;
+    static constexpr int SLOT_N = SLOT_E + 16;                 // what a sum may be off by [parity of the range][wavefront]; sign: kFarBelow
+    static constexpr int LDS_BYTES = SLOT_N + 32;
     static constexpr int A_ITEMS = BK / 16 * 2 / 4, B_ITEMS = PIX / 16 * 2 / 4, ITEMS = A_ITEMS + B_ITEMS;   // of 16 pixels x 32 rows, per moving wavefront
     static_assert(LDS_BYTES <= 160 * 1024 && A_STAGE + A_PART + A_BLOCK + 256 < 65536 && B_STAGE + B_PART + 32 < 65536, "LDS budget, offsets of the LDS instructions");
 };
-
-constexpr uint32_t kWildExponents = 1u << 30;
 
 // Row (channel) that stands at position `at` (of 0..31) of the block beginning at `first`: eights beyond the last
 // whole one are the last eight again; *ours: not one that an earlier position has.
@@ -117,6 +117,187 @@ __device__ __forceinline__ void wgrad_halves_in_fp32(const ConvKernelParams &p, 
                 for (int mb = 0; mb < 2; ++mb) acc[t][mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mb], b[t], acc[t][mb], 0, 0, 0);
         }
 }
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// One bit per lane of a half wavefront, set in either of the two.
+__device__ __forceinline__ uint32_t nonzero_lanes(uint32_t v) {
+    const uint64_t m = __ballot(v != 0u);
+    return (uint32_t)m | (uint32_t)(m >> 32);
+}
+// A wavefront's blocks of a range: where they are.
+struct WgradMend {
+    int m0, c0, tap_h, tap_w, j_begin, j_end, part;
+    bool live;        // (not one that fills up a pair of units)
+    bool zeros_too;   // (mend_results)
+};
+
+// As halves_mend of the forward kernel: the sums that are out of range or that something lost could have touched, one by one or all.
+__device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, f32x16 *blocks, float limit, WgradMend where) {
+    ConvKernelParams p = *(KernelArguments *)(uintptr_t)uniform64(arguments);
+    auto uniform = [](auto &v) __attribute__((always_inline)) { v = __builtin_bit_cast(std::remove_reference_t<decltype(v)>, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
+    uniform(limit);
+    uniform(where.m0); uniform(where.c0); uniform(where.tap_h); uniform(where.tap_w); uniform(where.j_begin); uniform(where.j_end); uniform(where.part);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    f32x16 acc[3][2];
+#pragma unroll
+    for (int g = 0; g < 6; ++g) acc[g / 2][g % 2] = blocks[g];
+    auto get = [&](auto gc, auto vc) __attribute__((always_inline)) {
+        const float a = acc[decltype(gc)::value / 2][decltype(gc)::value % 2][decltype(vc)::value];
+        return a;
+    };
+    auto set = [&](auto gc, auto vc, float a) __attribute__((always_inline)) { acc[decltype(gc)::value / 2][decltype(gc)::value % 2][decltype(vc)::value] = a; };
+    auto in_block = [](int v, int h) { return v / 4 * 8 + v % 4 + h * 4; };   // row of a block
+    auto counts = [&](auto, auto) { return where.live; };
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.w), 0, p.w_bytes, kBufferWord3);
+    // a lane's output pixel: its offset in dy, of its window in x; the window's place
+    struct Pixel { uint32_t ao, xo; bool live, row; uint32_t w; };
+    auto pixel = [&](int j) __attribute__((always_inline)) {
+        const uint32_t n = magic_div((uint32_t)j, p.mRS), rem = (uint32_t)j - n * (uint32_t)p.RS, pp = magic_div(rem, p.mS), qq = rem - pp * (uint32_t)p.S;
+        const uint32_t h = pp * (uint32_t)p.redMulH + (uint32_t)where.tap_h;
+        Pixel x;
+        x.live = j < where.j_end;
+        x.row = x.live && h < (uint32_t)p.H;
+        x.w = qq + (uint32_t)where.tap_w;
+        x.ao = (n * (uint32_t)p.wsRed + pp * (uint32_t)p.wsTapR + qq * (uint32_t)p.wsTapS) * 4u;
+        x.xo = (n * (uint32_t)p.xsC + h * (uint32_t)p.xsH + x.w * (uint32_t)p.xsW) * 4u;
+        return x;
+    };
+    auto load_dy = [&](const Pixel &x, uint32_t rowoff) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wbuf, x.live ? rowoff + x.ao : kOutOfRange, 0, 0));
+    };
+    auto load_x = [&](const Pixel &x, uint32_t coloff, int t) __attribute__((always_inline)) {
+        const bool ok = x.row && x.w + (uint32_t)t < (uint32_t)p.W;
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, ok ? coloff + x.xo + (uint32_t)(t * p.xsW) * 4u : kOutOfRange, 0, 0));
+    };
+    auto rowoff_of = [&](int mb, int r) __attribute__((always_inline)) {
+        bool ours;
+        return (uint32_t)wgrad_row(where.m0 + mb * 32, r, p.K, &ours) * (uint32_t)p.wsRow * 4u;
+    };
+    auto coloff_of = [&](int c) __attribute__((always_inline)) {
+        bool ours;
+        return (uint32_t)wgrad_row(where.c0, c, p.NPQ, &ours) * (uint32_t)p.xsN * 4u;
+    };
+    const int j_first = where.j_begin + where.part * 64 + lane;
+    // Maps, then channels, of zeros: the lanes along the pixels, as far as the first operand that is not zero.
+    auto zeros = [&](uint32_t (&zero)[6]) __attribute__((always_inline)) {
+        uint64_t rows = 0, all_zero = 0;   // (bit 32 mb + r)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            const uint32_t asked = zero[mb] | zero[2 + mb] | zero[4 + mb];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint64_t m = __ballot((asked >> v) & 1u);
+                rows |= (uint64_t)(((uint32_t)m != 0u ? 1u : 0u) << in_block(v, 0) | ((m >> 32) != 0u ? 1u : 0u) << in_block(v, 1)) << (32 * mb);
+            }
+        }
+#pragma clang loop unroll(disable)
+        while (rows != 0u) {   // four at a time (fewer left: the last again)
+            uint32_t rowoff[4], found = 0;
+            int r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                r[i] = rows != 0u ? __builtin_ctzll(rows) : r[i > 0 ? i - 1 : 0];
+                rows &= rows - 1u;
+                rowoff[i] = rowoff_of(r[i] >> 5, r[i] & 31);
+            }
+#pragma clang loop unroll(disable)
+            for (int j = j_first; __any(j < where.j_end) && found != 15u; j += 768) {
+                float a[6][4];
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+                    const Pixel x = pixel(j + e * 128);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) a[e][i] = load_dy(x, rowoff[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    bool some = false;
+#pragma unroll
+                    for (int e = 0; e < 6; ++e) some = some || a[e][i] != 0.f;
+                    found |= __any(some) ? 1u << i : 0u;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) all_zero |= ((found >> i) & 1u) != 0u ? 0u : (uint64_t)1 << r[i];
+        }
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bits |= (((uint32_t)(all_zero >> (32 * mb)) >> in_block(v, half)) & 1u) << v;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) zero[t * 2 + mb] &= ~bits;
+        }
+        uint32_t channels = nonzero_lanes(zero[0] | zero[1] | zero[2] | zero[3] | zero[4] | zero[5]), some_in[3] = {~0u, ~0u, ~0u};
+#pragma clang loop unroll(disable)
+        while (channels != 0u) {   // two at a time, three taps
+            const int c0 = __builtin_ctz(channels);
+            channels &= channels - 1u;
+            const int c1 = channels != 0u ? __builtin_ctz(channels) : c0;
+            channels &= channels - 1u;
+            const uint32_t coloff[2] = {coloff_of(c0), coloff_of(c1)};
+            uint32_t found = 0;
+#pragma clang loop unroll(disable)
+            for (int j = j_first; __any(j < where.j_end) && found != 63u; j += 512) {
+                float b[4][6];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const Pixel x = pixel(j + e * 128);
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) b[e][i] = load_x(x, coloff[i / 3], i % 3);
+                }
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    bool some = false;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) some = some || b[e][i] != 0.f;
+                    found |= __any(some) ? 1u << i : 0u;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) some_in[i % 3] &= ((found >> i) & 1u) != 0u ? ~0u : ~(1u << (i < 3 ? c0 : c1));
+        }
+#pragma unroll
+        for (int g = 0; g < 6; ++g) zero[g] = ((some_in[g / 2] >> l32) & 1u) != 0u ? zero[g] : 0u;
+    };
+    auto sums = [&](const int (&which)[4], const int (&from)[4], float (&s)[4]) __attribute__((always_inline)) {
+        uint32_t rowoff[4], coloff[4];
+        int tap[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int g = which[i] >> 4;
+            rowoff[i] = rowoff_of(g % 2, in_block(which[i] & 15, from[i] >> 5));
+            coloff[i] = coloff_of(from[i] & 31);
+            tap[i] = g / 2;
+            s[i] = 0.f;
+        }
+#pragma clang loop unroll(disable)
+        for (int j = j_first; __any(j < where.j_end); j += 512) {
+            float a[4][4], b[4][4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const Pixel x = pixel(j + e * 128);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a[e][i] = load_dy(x, rowoff[i]);
+                    b[e][i] = load_x(x, coloff[i], tap[i]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = __builtin_fmaf(a[e][i], b[e][i], s[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = wave_sum(s[i]);
+    };
+    if (!mend_results<6>(limit, __builtin_amdgcn_readfirstlane((int)where.zeros_too) != 0, lane, get, set, counts, zeros, sums))
+        wgrad_halves_in_fp32(p, acc, where.m0, where.c0, where.tap_h, where.tap_w, where.j_begin, where.j_end, where.part, half, l32);
+#pragma unroll
+    for (int g = 0; g < 6; ++g) blocks[g] = acc[g / 2][g % 2];
+}
+#endif
 
 // p.Wp: pixels of a row of the patch (output columns and two), p.HpWp: output rows; p.PQ: blocks of 32 channels;
 // p.tilesN: pairs of units; otherwise as for the kernels by tap.
@@ -325,7 +506,7 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
 
         // ---- magnitudes and scales
         HalvesSeen seen_a, seen_b;          // of the next chunk's operands
-        uint32_t small_a = 0, small_b = 0;  // this thread's smallest ones of this chunk
+        uint32_t small_a = 0, small_b = 0;  // this lane's smallest ones of this chunk
         auto look = [&](auto set_c, auto ic, int q) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value, i = decltype(ic)::value;
             look_at(i < Cfg::A_ITEMS ? seen_a : seen_b, reg[set][i][2 * q], reg[set][i][2 * q + 1]);
@@ -349,7 +530,8 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
         int it = 0, c = 0;                       // range and chunk being written
         int ea = 0, eb = 0, e_low = 0, e_high = 0;
         bool set_a = false, set_b = false, begun = false;
-        uint32_t lossy = 0;
+        float off_by = 0.f;      // 2^22 times what a sum of the range may be off by for this wavefront's operands that lost something
+        uint32_t far = 0;        // kFarBelow: one of them far below the others
         HalvesScale sa = {}, sb = {};
         // an exponent out of bounds?  (zeros say nothing)
         auto largest_of = [&](const uint8_t *slots) __attribute__((always_inline)) {
@@ -357,7 +539,7 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             const uint32_t s0 = s[0] > s[1] ? s[0] : s[1], s1 = s[2] > s[3] ? s[2] : s[3];
             return (uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 > s1 ? s0 : s1));
         };
-        auto fits = [](uint32_t largest, int e, bool set) { return largest == 0 || (set && (uint32_t)((int)(largest >> 23) - 133 + e) <= 8u); };
+        auto fits = [](uint32_t largest, int e, bool set) { return largest == 0 || (set && (uint32_t)((int)(largest >> 23) - 140 + e) <= 1u); };
         auto choose = [](uint32_t largest, int &e, bool &set) {
             const int w = 140 - (int)(largest >> 23);
             e = w < -60 ? -60 : (w > 60 ? 60 : w);
@@ -371,19 +553,25 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             r.below = (uint32_t)(114 - e) << 23;
             return r;
         };
-        auto scales = [&](auto set_c, int parity, int ng) __attribute__((always_inline)) {
-            constexpr int set = decltype(set_c)::value;
+        auto scales = [&](int parity) __attribute__((always_inline)) {
             const uint32_t la = largest_of(lds + Cfg::SLOT_MAX + parity * 32), lb = largest_of(lds + Cfg::SLOT_MAX + parity * 32 + 16);
             const bool first = c == 0;
             if (first || !fits(la, ea, set_a) || !fits(lb, eb, set_b)) {
                 if (first) {
                     set_a = set_b = begun = false;
-                    lossy = 0;
+                    off_by = 0.f;
+                    far = 0;
                 }
                 if (!fits(la, ea, set_a)) choose(la, ea, set_a);
                 if (!fits(lb, eb, set_b)) choose(lb, eb, set_b);
-                const int e = ea + eb;
                 if (set_a && set_b) {   // (before that all products are zero)
+                    // A chunk far below the range's largest gets no finer unit than 2^-40 of that one's: sums multiplied up by more could leave the float range.
+                    // Those multiplied down by more than 2^-70 could lose something.
+                    const int over = begun && ea + eb > e_low + 40 ? ea + eb - (e_low + 40) : 0, of_a = over < ea + 100 ? over : ea + 100;
+                    ea -= of_a;
+                    eb -= over - of_a;
+                    const int e = ea + eb;
+                    if (begun && e_high - e > 70) off_by += __builtin_ldexpf(2.f, -e);
                     e_low = !begun || e < e_low ? e : e_low;
                     e_high = !begun || e > e_high ? e : e_high;
                     begun = true;
@@ -391,19 +579,19 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
                 sa = scale_of(ea);
                 sb = scale_of(eb);
             }
-            if (__any(small_a < 2u * sa.below - 1u || small_b < 2u * sb.below - 1u))
-                static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value;
-                    if (held(ic, ng))
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) lossy += count_lossy(reg[set][i][q], i < Cfg::A_ITEMS ? sa.below : sb.below);
-                });
-            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = ea + eb;
-            if (c == per - 1 && lane == 0) {
-                if (lossy >= kWildExponents) lossy = kWildExponents;
-                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = begun && e_high - e_low > 40 ? kWildExponents : lossy;
-                *reinterpret_cast<int *>(lds + Cfg::SLOT_LOW + (it & 1) * 4) = begun ? e_low : 0;
+            // Of the 64 pixels that a result's sum takes from the chunk (half of it) this wavefront has 16 of dy, one per lane and map, and up to 64 of the
+            // patch, five per lane and channel at most: as many products may a lost operand have touched, each by 2^-36 of the other operand's largest.
+            const uint64_t under_a = lanes_under(small_a, sa.below), under_b = lanes_under(small_b, sb.below);
+            if ((under_a | under_b) != 0u) {
+                const int na = __popcll(under_a), nb = Cfg::B_ITEMS * __popcll(under_b);
+                // (none times infinity would be NaN)
+                if (na != 0) off_by += (float)(na < 16 ? na : 16) * __builtin_ldexpf(__builtin_bit_cast(float, lb), -ea - 14);   // (times 2^22)
+                if ((lanes_under(small_a, far_below(sa.below)) | lanes_under(small_b, far_below(sb.below))) != 0u) far = kFarBelow;
+                if (nb != 0) off_by += (float)(nb < 64 ? nb : 64) * __builtin_ldexpf(__builtin_bit_cast(float, la), -eb - 14);
             }
+            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = ea + eb;
+            if (c == per - 1 && lane == 0)
+                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = __builtin_bit_cast(uint32_t, off_by) | far;
         };
         u32x4 part_h, part_m;
         auto convert = [&](auto set_c, auto ic, int q) __attribute__((always_inline)) {
@@ -437,7 +625,7 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             span[0] = span[1];
             span[1] = span[2];
             span[2] = write_table(d, par ^ 1);
-            scales(par_c, par, ng);
+            scales(par);
             __builtin_amdgcn_sched_barrier(0);
             // (an item's loads among the splitting of the next one: eight together wait for the other moving wavefronts')
             static_for<ITEMS + 1>([&](auto ic) __attribute__((always_inline)) {
@@ -577,13 +765,16 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
     read_positions(pos_now, 0);
     take_positions();
     e_read = *reinterpret_cast<const int *>(lds + Cfg::SLOT_E);
+    auto first_fragments = [&](int stage) __attribute__((always_inline)) {   // of a range
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-        am[mb] = read_a(0, 0, 1, mb);
-        ah[0][mb] = read_a(0, 0, 0, mb);
-    }
-    bh[0] = read_b(0, 0, 0);
-    bm[0] = read_b(0, 1, 0);
+        for (int mb = 0; mb < 2; ++mb) {
+            am[mb] = read_a(stage, 0, 1, mb);
+            ah[0][mb] = read_a(stage, 0, 0, mb);
+        }
+        bh[0] = read_b(stage, 0, 0);
+        bm[0] = read_b(stage, 1, 0);
+    };
+    first_fragments(0);
     for (int it = 0; it < ntiles; ++it) {
         const Tile tile = tile_of(tile_number(it));
         const Unit unit = unit_of(tile.u0 + wn);
@@ -622,19 +813,32 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[t][mb][v] = __builtin_ldexpf(__builtin_fmaf(low[t][mb][v], 0x1p-11f, acc[t][mb][v]), -e_sum);
-        const u32x4 counts = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
-        const int e_low = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int *>(lds + Cfg::SLOT_LOW + (it & 1) * 4));
-        uint32_t lossy = 0;
+        const u32x4 slots = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
+        float off_by = 0.f;
+        uint32_t far = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lossy = lossy + counts[i] < kWildExponents ? lossy + counts[i] : kWildExponents;
-        lossy = (uint32_t)__builtin_amdgcn_readfirstlane((int)lossy);
-        // (sums of operands scaled up by 2^60 and more in all may have left the float range on the way back)
-        uint32_t inexact = lossy == 0 ? 0u : __builtin_bit_cast(uint32_t, __builtin_ldexpf((float)lossy, 3 - e_low));
-        if (e_low > 60 && inexact == 0) inexact = __builtin_bit_cast(uint32_t, 0x1p-100f);
-        if (lossy >= kWildExponents) inexact = 0x7F800000u;
-        if (__any(outside_split_range<3, 2>(acc, inexact))) {
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t slot = slots[i];
+            off_by += __builtin_bit_cast(float, slot & ~kFarBelow);
+            far |= slot & kFarBelow;
+        }
+        const bool zeros_too = __builtin_amdgcn_readfirstlane((int)far) != 0;
+        if (__builtin_expect(__any(outside_halves_range<3, 2>(acc, off_by, zeros_too)), 0)) {
             const long long jb = (long long)tile.split * per * BK, je = jb + (long long)per * BK;
-            wgrad_halves_in_fp32(p, acc, tile.m0, unit.c0, unit.tap_h, unit.tap_w, jb < p.CRS ? (int)jb : p.CRS, je < p.CRS ? (int)je : p.CRS, ph, half, l32);
+            WgradMend m;
+            m.m0 = tile.m0; m.c0 = unit.c0; m.tap_h = unit.tap_h; m.tap_w = unit.tap_w;
+            m.j_begin = jb < p.CRS ? (int)jb : p.CRS;
+            m.j_end = je < p.CRS ? (int)je : p.CRS;
+            m.part = ph;
+            m.live = unit.live;
+            m.zeros_too = zeros_too;
+            f32x16 blocks[6];
+#pragma unroll
+            for (int g = 0; g < 6; ++g) blocks[g] = acc[g / 2][g % 2];
+            wgrad_halves_mend((uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), blocks, off_by, m);
+#pragma unroll
+            for (int g = 0; g < 6; ++g) acc[g / 2][g % 2] = blocks[g];
+            first_fragments(0);   // (again: not held across the call)
         }
         float *const sums = reinterpret_cast<float *>(lds + Cfg::SUMS) + wn * (8 * 64) + lane;
         static_for<Cfg::SUM_ROUNDS>([&](auto rc) __attribute__((always_inline)) {

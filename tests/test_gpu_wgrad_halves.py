@@ -6,6 +6,7 @@ import pytest
 import paper_1410_0759_amd as ig
 from oracle import conv_oracle as oc
 import workloads as wl
+from tests.test_gpu_halves import _microseconds
 from tests.test_gpu_split import SMALL, _check, _planted, _same, _scaled
 
 pytestmark = pytest.mark.gpu
@@ -147,3 +148,56 @@ def test_tensors_of_any_order(order, run):
     print(order, flush=True)
     want = run(gu, x, dy, (3, 3), (1, 1), (1, 1), layout="NHWC" if order[-1] == "c" else "NCHW")
     assert np.array_equal(run(gu, cut, placed(dy), (3, 3), (1, 1), (1, 1), layout=None), want)
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("kind", ["log-normal", "log-normal, maps of zeros", "image scales", "one gradient", "falling", "rising"])
+@pytest.mark.parametrize("prob", [PROBLEMS[0], PROBLEMS[2], PROBLEMS[5]])
+def test_sums_looked_at_again(prob, kind, layout, run):
+    """Results that operands with something lost could have touched, a few of a range or all; ranges whose chunks differ by more than sums can
+    be multiplied up or down."""
+    gu = _gpu()
+    *dims, pad, stride = prob
+    rng = np.random.default_rng(71)
+    x, dy = _problem(72, *prob)
+    dy = dy.astype(np.float64)
+    n = np.arange(dims[0])
+    if kind.startswith("log-normal"):
+        dy = np.sign(dy) * np.exp(3.0 * rng.standard_normal(size=dy.shape))
+    elif kind == "image scales":
+        dy = dy * 10.0 ** (-4.0 * (n % 4))[:, None, None, None]
+    elif kind == "one gradient":
+        dy[0, 0, 0, 0] = 1e-14
+    else:
+        dy = dy * 2.0 ** (-33.0 * (n if kind == "falling" else n[::-1]) / len(n) * 3)[:, None, None, None]
+    if kind.endswith("maps of zeros"):
+        dy[:, 1::6], x[:, 2::5] = 0, 0
+    dy = dy.astype(np.float32)
+    for mode, workspace in ((0, "full"), (1, "none")):
+        print(prob, kind, layout, mode, workspace, flush=True)
+        got = run(gu, x, dy, dims[5:], pad, stride, mode, layout, workspace)
+        want, mag = (oc.conv_backward_filter(a, b, dims[5:], pad=pad, stride=stride, mode=mode) for a, b in ((x, dy), (np.abs(x), np.abs(dy))))
+        _check(got, want, mag, dy.size // dims[4], (prob, kind, layout, mode))
+
+
+@pytest.mark.parametrize("kind", ["one gradient, a map of zeros", "log-normal gradients, maps of zeros", "image scales"])
+def test_a_few_small_operands_cost_little(kind):
+    """128x64x56x56 -> 64, 3x3.  (Multiplying every range that holds a small operand again took 5.2, 5.3 and 5.2 times as long as without; now
+    1.2, 1.0 and 1.6.)"""
+    gu = _gpu()
+    rng = np.random.default_rng(73)
+    x = np.maximum(rng.standard_normal(size=(128, 64, 56, 56), dtype=np.float32), 0)
+    dy = rng.standard_normal(size=x.shape, dtype=np.float32)
+    times = []
+    for small in (False, True):
+        if small and kind == "one gradient, a map of zeros":
+            dy[:, 3, 5, 5], dy[:, 9] = 1e-11, 0
+        elif small and kind == "image scales":
+            dy *= (np.float32(10) ** (np.arange(128) * 5 % 13 * -1.0).astype(np.float32))[:, None, None, None]
+        elif small:
+            dy = np.copysign(np.exp(2 * rng.standard_normal(size=dy.shape, dtype=np.float32)), dy)
+            dy[:, 5::16], x[:, 5::16] = 0, 0
+        g = gu.GpuBackwardFilter(x, dy, (3, 3), (1, 1), (1, 1), 1, "f32", "full")
+        times.append(_microseconds(lambda: g.launch(1.0, 0.0)))
+    print(kind, times, flush=True)
+    assert times[1] <= 2.2 * times[0], times
