@@ -163,8 +163,11 @@ igcStatus igcGetConvolutionForwardWorkspaceSize(igcHandle_t handle,
  * filter other than 1x1 or nine taps, enough channels) when no cut is chosen: the query reports the
  * filter's size in bytes, and with a workspace of that size (16-byte aligned) the
  * filter is first rewritten there with the channel index innermost, which makes a step's
- * filter reads contiguous; the sums and their order, hence the result's bits, are the same as
- * without the workspace (a smaller one is ignored).
+ * filter reads contiguous; float sums and their order, hence the result's bits, are the same as
+ * without the workspace (a smaller one is ignored).  bfloat16 problems with x's channels innermost run on another
+ * kernel over the rewritten filter, and so do, which the query does not report, those with nine taps under a stride
+ * (and others whose windows lie too far apart to be staged) with more tiles than compute units: the same products, summed in
+ * another order.
  * A third use, for float problems with a zero border and so few channels that the library would test
  * every gathered element against the window (the generic gather): the query reports the size of x
  * with its border written out, N*C*(H+2*pad_h)*(W+2*pad_w)*4 bytes; with such a workspace (16-byte
@@ -172,8 +175,10 @@ igcStatus igcGetConvolutionForwardWorkspaceSize(igcHandle_t handle,
  * 5x5 filters over up to four channels need no copy: the workspace is then left alone).
  * A fourth use, which the query does not report: float problems with nine taps or more, C*R*S >= 432 and enough tiles run up
  * to several times faster with any workspace (16-byte aligned) that holds the filter written as pairs of 16-bit numbers,
- * ceil(K/64) * ceil(C/16) * ceil(R*S/9) * 36872 bytes, for instance the one lent to the same layer's backward filter pass; the sums
- * then round otherwise (no further from the exact ones).  Backward data with unit strides: the same with C and K exchanged. */
+ * ceil(K/64) * ceil(C/16) * ceil(R*S/9) * 36872 bytes, less than 2 GiB, for instance the one lent to the same layer's backward filter pass.
+ * The sums then round otherwise: every product may be off by 2^-21 of it, the sums of the products round less.  Results over operands that differ
+ * in their low bits are no further from the exact ones than without; over constants they may be off by 2^-21 of the sum of
+ * the products' magnitudes.  Backward data with unit strides: the same with C and K exchanged. */
 igcStatus igcGetConvolutionForwardOptionalWorkspaceSize(igcHandle_t handle,
                                                         igcTensorDescriptor_t xDesc,
                                                         igcFilterDescriptor_t wDesc,
@@ -289,7 +294,8 @@ igcStatus igcConvolutionBackwardData(igcHandle_t handle, const void *alpha,
  *    a single range, because that kernel keeps its results in another order than dw's),
  *    down to a single range that writes dw directly - same result up to summation order,
  *    less parallelism.
- *    Float layers whose filter rows have three taps and more, at unit horizontal stride, may be cut finer with more than the query reports.
+ *    Float layers whose filter rows have three taps and more, at unit horizontal stride, may be cut finer with more than the query reports; their products
+ *    may be off by 2^-21, as those of the fourth use of igcGetConvolutionForwardOptionalWorkspaceSize.
  *  - dw and workSpace must not overlap x, dy or each other.
  *  - NOT_SUPPORTED also when H + 2*pad_h or W + 2*pad_w exceeds 2^14.
  *  - Other errors as for igcConvolutionForward; igcSetKernelOverride does not apply. */

@@ -1,5 +1,5 @@
 // fp32 backward filter on the 16-bit matrix pipes: dw = dy . D_m^T with every float operand as two binary16 parts
-// (igconv_kernel_f32h.hpp: what the parts hold, why three products make one of floats), unit horizontal stride, rows of three taps and more.
+// (igconv_kernel_f32h.hpp: what the parts hold, what three products leave out of one of floats), unit horizontal stride, rows of three taps and more.
 // Rows are feature maps k of dy, 64 per tile; columns come in units of (32 channels, three neighbouring taps of a filter row),
 // two units per tile; the reduction runs over output pixels (n,p,q) in chunks of 128 and is cut into ranges, one
 // (tile, range) after another per workgroup (igconv_kernel_wgrad.hpp).

@@ -71,10 +71,12 @@ def test_forward(prob, layout):
         want = oc.conv_forward(x, w, pad=pad, stride=stride, mode=mode)
         y0 = rng.uniform(-1, 1, size=want.shape).astype(np.float32)
         print(prob, layout, mode, flush=True)
-        # one byte less: another route, whose sums round otherwise
+        # a little less: another route, whose sums round otherwise (or the one without any, whose order of sums the room can change too)
         plain = _forward(gu, x, w, pad, stride, mode, layout, 0)
+        short = _forward(gu, x, w, pad, stride, mode, layout, _bytes(K, C, R * S) - 16)
         got = _forward(gu, x, w, pad, stride, mode, layout, _bytes(K, C, R * S))
-        assert not np.array_equal(got, plain), "the route under test did not run"
+        assert not np.array_equal(got, plain) and not np.array_equal(got, short), "the route under test did not run"
+        assert np.abs(short - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
         assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
         # (as exact as the route without the workspace, which holds three parts of an operand: 1.25 allows for few results)
         assert np.linalg.norm(got - want) <= 1.25 * np.linalg.norm(plain - want)
@@ -122,8 +124,10 @@ def test_backward_data(prob, layout):
         old = dx0 if beta else None
         want = oc.conv_backward_data(dy, w, (H, W), pad=pad, mode=mode, alpha=alpha, beta=beta, dx_old=old)
         plain = _backward_data(gu, dy, w, (H, W), pad, mode, layout, 0, alpha, beta, old)
+        short = _backward_data(gu, dy, w, (H, W), pad, mode, layout, _bytes(C, K, R * S) - 16, alpha, beta, old)
         got = _backward_data(gu, dy, w, (H, W), pad, mode, layout, _bytes(C, K, R * S), alpha, beta, old)
-        assert not np.array_equal(got, plain), "the route under test did not run"
+        assert not np.array_equal(got, plain) and not np.array_equal(got, short), "the route under test did not run"
+        _same(short, want, (prob, layout, mode))
         _same(got, want, (prob, layout, mode))
         assert np.linalg.norm(got - want) <= 1.25 * np.linalg.norm(plain - want)
 
@@ -264,3 +268,24 @@ def test_a_few_small_operands_cost_little(kind):
             times.append(_microseconds(lambda: g.launch(1.0, 0.0)))
     print(kind, times, flush=True)
     assert times[1] <= 2.2 * times[0], times
+
+
+# Operands that all have the same low bits: each of a sum's products loses on the same side.  A unit of an operand's last place is 2^-23 of it at most,
+# the product left out 2^-22: 2^-21 of the sum of magnitudes.  The growing sum is rounded, by 2^-24 of it, at nine additions per chunk (five times the
+# chunk's sum in all) and one of each chunk; three more for the small products, the scale and the result.
+SAME_BITS = [1 + 2.0 ** -11, 1 + 3001 * 2.0 ** -23, 1 / 3, 0.1, 2.0 ** 14 - 2.0 ** -9]
+
+
+@pytest.mark.parametrize("value", SAME_BITS)
+@pytest.mark.parametrize("prob", PLANTED)
+def test_operands_with_the_same_low_bits(prob, value):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad = prob
+    x, w = (np.full(shape, value, np.float32) for shape in ((N, C, H, W), (K, C, R, S)))
+    x[:, 1::2] *= 4     # (a power of two: the same bits)
+    for sign in (1, -1):
+        print(prob, value, sign, flush=True)
+        got = _forward(gu, sign * x, w, pad, (1, 1), 1, "NCHW", _bytes(K, C, R * S))
+        want = oc.conv_forward(sign * x, w, pad=pad, mode=1)
+        chunks = -(-C // 16) * -(-(R * S) // 9)
+        assert (np.abs(got - want) <= (2.0 ** -21 + (8 + chunks / 2) * 2.0 ** -24) * np.abs(want)).all()

@@ -6,7 +6,7 @@ import pytest
 import paper_1410_0759_amd as ig
 from oracle import conv_oracle as oc
 import workloads as wl
-from tests.test_gpu_halves import _microseconds
+from tests.test_gpu_halves import SAME_BITS, _microseconds
 from tests.test_gpu_split import SMALL, _check, _planted, _same, _scaled
 
 pytestmark = pytest.mark.gpu
@@ -201,3 +201,18 @@ def test_a_few_small_operands_cost_little(kind):
         times.append(_microseconds(lambda: g.launch(1.0, 0.0)))
     print(kind, times, flush=True)
     assert times[1] <= 2.2 * times[0], times
+
+
+@pytest.mark.parametrize("value", SAME_BITS)
+@pytest.mark.parametrize("prob", PLANTED)
+def test_operands_with_the_same_low_bits(prob, value, run):
+    """As in the forward pass: 2^-21 of the sum of magnitudes, and 2^-24 of the growing sum per addition of sixteen pixels' products; the two halves',
+    the small products', the scale's and the parts' (of up to 24 ranges on eight compute units, half of the sum on average)."""
+    gu = _gpu()
+    *dims, pad, stride = prob
+    x, dy = _problem(74, *prob)
+    x[:], dy[:] = np.float32(value), np.float32(value)
+    print(prob, value, flush=True)
+    got = run(gu, x, dy, dims[5:], pad, stride)
+    want = oc.conv_backward_filter(x, dy, dims[5:], pad=pad, stride=stride, mode=1)
+    assert (np.abs(got - want) <= (2.0 ** -21 + (dy.size / dims[4] / 32 + 16) * 2.0 ** -24) * np.abs(want)).all()
