@@ -34,9 +34,9 @@
 // [row block][chunk][tap][part][half of the channels][row][8 channels], and each chunk's exponent and count).
 //
 // Measured, us and error against 64 bits, 128 images unless said, three bfloat16 parts -> this with the filter's split: 64x56x56 -> 64, 3x3
-// 151 -> 106, 1.3e-7 -> 1.1e-7 (backward data 147 -> 107); 384x13x13 -> 256, 3x3 200 -> 144, 3.4e-7 -> 1.6e-7 (168 -> 117); 96x64x64 -> 128,
-// 9x9, 32 images 1228 -> 566, 5.5e-7 -> 2.1e-7 (1670 -> 720); 96x27x27 -> 256, 5x5 653 -> 318 (765 -> 384); 64x224x224 -> 64, 3x3, 4
-// images 118 -> 80.  What bounds it: with many taps the matrix pipes at the clocks that power leaves (350 TFLOP/s); with nine the
+// 160 -> 117, 1.3e-7 -> 1.1e-7 (backward data 149 -> 111); 384x13x13 -> 256, 3x3 203 -> 143, 3.4e-7 -> 1.6e-7 (163 -> 117); 96x64x64 -> 128,
+// 9x9, 32 images 1206 -> 569, 5.5e-7 -> 2.1e-7 (1621 -> 723); 96x27x27 -> 256, 5x5 647 -> 320 (750 -> 386); 64x224x224 -> 64, 3x3, 4
+// images 124 -> 83.  What bounds it: with many taps the matrix pipes at the clocks that power leaves (350 TFLOP/s); with nine the
 // requests and the splitting of the patch (the first layer without them 87 us, with neither MFMAs nor their waits 77) and 17 us of epilogues.
 // (The filter split by the movers as well, in each tile, from registers: 137 us where this took 121, the 9x9 layer 1230; a barrier per
 // step instead of per chunk: 121 instead of 110; 128 x 128 tiles level.)
@@ -276,7 +276,7 @@ struct HalvesPatchConfig {
     static constexpr int BLOCKS = PIX / 64;               // of 64 pixels
     static constexpr int ITEMS = (2 * BLOCKS + MOVERS - 1) / MOVERS;   // (block, half of the channels) per moving wavefront
     static_assert(WM * WN == 4 && BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "four wavefronts of 32x32 blocks");
-    static_assert((BM == 64 || BM == 128) && PIX % 64 == 0 && COPIES < 64 && !(WHOLE && SETS == 1), "shares of the moving wavefronts");
+    static_assert(BM == 64 && PIX % 64 == 0 && COPIES < 64 && !(WHOLE && SETS == 1), "shares of the moving wavefronts");
     static_assert(LDS_BYTES <= 160 * 1024 && B_PART < 65536, "LDS budget, offsets of the LDS instructions");
 };
 

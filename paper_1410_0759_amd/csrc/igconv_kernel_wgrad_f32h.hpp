@@ -8,8 +8,9 @@
 // and split once for every tap.  Here the pixels of x that a chunk's three taps read - 128 and two more per output row - are split
 // once into LDS, 136 elements of splitting per 12288 products; one tap more is a read from LDS at the next pixel.
 //
-// Measured, us, three bfloat16 parts or fp32 instruction -> this, 128 images: 64x56x56 -> 64, 3x3 301 -> 154 (error against 64 bits 1.1e-6 -> 3.3e-7),
-// channels innermost 787 -> 132; 384x13x13 -> 256, 3x3 287 -> 227 (4.4e-7 -> 3.9e-7); 96x64x64 -> 128, 9x9, 32 images 1459 -> 777 (1.2e-6 -> 8.2e-7).
+// Measured, us, three bfloat16 parts or fp32 instruction -> this, 128 images: 64x56x56 -> 64, 3x3 256 -> 135 (error against 64 bits 1.1e-6 -> 3.3e-7),
+// channels innermost 784 -> 128; 384x13x13 -> 256, 3x3 234 -> 198 (4.4e-7 -> 3.9e-7); 96x27x27 -> 256, 5x5 822 -> 546; 96x64x64 -> 128, 9x9, 32 images 1419 -> 768
+// (1.2e-6 -> 8.2e-7).
 // What bounds it: instruction issue of the moving wavefronts, one per SIMD, about 750 instructions of 5.3 cycles per chunk (binary16
 // fused multiply-adds take 9.3) where the MFMAs take 2304: 9400 cycles in all at 64x56x56; without its loads 106 us, without its MFMAs 132.
 // Chunks of 64 pixels took 214 us, an item's eight loads together instead of among the splitting of the next one 822 (9x9),

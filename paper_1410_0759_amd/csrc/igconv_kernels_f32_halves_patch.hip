@@ -8,7 +8,7 @@ namespace igc {
 __global__ __launch_bounds__(512) void igconv_split_filter_kernel(const float *w, uint8_t *out, HalvesChunk *table, int K, int C, int taps, int groups,
                                                                   uint32_t row_stride, uint32_t channel_stride, uint32_t w_bytes) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int BM = 64, CPT = BM / 32;
+    constexpr int BM = 64, CPT = 2;   // rows of a workgroup, channels of a thread
     __shared__ __attribute__((aligned(16))) uint32_t slots[8], counts[8], sums[8];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = blockIdx.x, cb = chunk / groups, g = chunk - cb * groups;
@@ -62,18 +62,12 @@ __global__ __launch_bounds__(512) void igconv_split_filter_kernel(const float *w
         sums[wave] = row_sum;
     }
     uint8_t *const dst = out + ((size_t)blockIdx.y * gridDim.x + (size_t)chunk) * (9 * BM * 64) + (sub * CPT / 8) * (BM * 16) + row * 16 + sub * CPT % 8 * 2;
-    using u32xq = uint32_t __attribute__((ext_vector_type(CPT / 2)));
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-        u32xq h, m;
-#pragma unroll
-        for (int q = 0; q < CPT / 2; ++q) {
-            uint32_t hq, mq;
-            halves_pair(x[2 * q][t], x[2 * q + 1][t], sc, hq, mq);
-            h[q] = hq; m[q] = mq;
-        }
-        *reinterpret_cast<u32xq *>(dst + t * (BM * 64)) = h;
-        *reinterpret_cast<u32xq *>(dst + t * (BM * 64) + BM * 32) = m;
+        uint32_t h, m;
+        halves_pair(x[0][t], x[1][t], sc, h, m);
+        *reinterpret_cast<uint32_t *>(dst + t * (BM * 64)) = h;
+        *reinterpret_cast<uint32_t *>(dst + t * (BM * 64) + BM * 32) = m;
     }
     __syncthreads();
     if (tid == 0) {
