@@ -17,12 +17,12 @@
 // the third accumulator.  No range is assumed and none is kept from chunk to chunk.  What leaves it: an operand below 2^-13 after scaling
 // (below 2^-28 of its chunk's largest) loses up to 2^-36.  The movers note each lane's smallest operand that is not zero; from the lanes that have such
 // operands, and from the largest sum of magnitudes of a filter row, follows what a sum of the tile may be off by (off_by).  Results below 2^22 times that,
-// not finite, or not zero but below 2^-100 are multiplied again with fp32 multiply-adds, one by one or - more than 96 of a wavefront's 4096 -
-// together (halves_mend).  Zeros are asked about only where an operand was below 2^-19, and pass where their whole filter row or window is zero.
+// not finite, or not zero but below 2^-100 are multiplied again (halves_mend): with fp32 multiply-adds, one by one; more than 24 of a wavefront's 4096
+// with an exponent for each column; and what that leaves one by one, or, more than 24 again, all with the fp32 instruction.  Zeros are asked about only where an operand was below 2^-19, and pass where their whole filter row or window is zero.
 // us, 128x64x56x56 -> 64, 3x3, backward data (every tile with such an operand multiplied again -> this): log-normal gradients, sigma 2 130 -> 128, 2.5
 // 291 -> 137, 3 733 -> 150, with maps of zeros 739 -> 150; normal ones 134 -> 131.  -> 70 maps, one weight of 1e-12: 1152 -> 195, without it 207 -> 193.
-// What still costs: tiles over images whose gradients differ by 10^6 and more (384x13x13 -> 256: 868 -> 789, 123 where they are alike), windows of
-// zeros beside an operand far below the others (1286 -> 415, 150 without it).
+// What still costs: tiles over images whose gradients differ, 384x13x13 -> 256, by 10^4 833 -> 281, by 10^6 845 -> 463 (alike 126); windows of
+// zeros beside an operand far below the others (1286 -> 420, 150 without it).
 //
 // The reduction is ordered (16 channels, group of nine taps, tap, channel).  A tile's whole range of pixels of the
 // zero-extended image goes to LDS once per 16 channels, and all R*S taps read their operands from it at shifted
@@ -178,13 +178,11 @@ struct HalvesChunk {
 
 // The results that operands with something lost could have touched, multiplied again one by one: four at a time, the wavefront's lanes along
 // their reduction.  get(g, v), set(g, v, s): result v of the lane's block g; counts(g, v): whether it is stored;
-// sums(which, from, s): the sums of result which[i] (16 g + v) of lane from[i].  limit: see the callers.  Results that are zero are, where
-// they are asked about, handed to zeros(bits) first, which strikes out those whose zero is right.  False, and nothing done, when there
-// are more than kMendMost left (then the blocks are cheaper as a whole).
-constexpr int kMendMost = 96;
-template <int G, class Get, class Set, class Counts, class Zeros, class Sums>
-__device__ __forceinline__ bool mend_results(float limit, bool zeros_too, int lane, Get get, Set set, Counts counts, Zeros zeros, Sums sums) {
-    const float least = limit > 0x1p-100f ? limit : 0x1p-100f;
+// sums(which, from, s): the sums of result which[i] (16 g + v) of lane from[i].  limit(g, v): see the callers.  Results that are zero are, where
+// they are asked about (asked(g): a bit each), handed to zeros(bits) first, which strikes out those whose zero is right.  False, and nothing done, when there
+// are more than MOST left (then the blocks are cheaper as a whole).
+template <int G, int MOST, class Limit, class Asked, class Get, class Set, class Counts, class Zeros, class Sums>
+__device__ __forceinline__ bool mend_results(Limit limit, Asked asked, int lane, Get get, Set set, Counts counts, Zeros zeros, Sums sums) {
     uint32_t bad[G], zero[G];   // one bit per result
     uint32_t any_zero = 0;
     int left = 0;
@@ -201,18 +199,20 @@ __device__ __forceinline__ bool mend_results(float limit, bool zeros_too, int la
             constexpr int v = decltype(vc)::value;
             const float a = __builtin_fabsf(get(gc, vc));
             const uint32_t bit = counts(gc, vc) ? 1u << v : 0u;
+            const float least = limit(gc, vc);
             zero[g] |= a == 0.f ? bit : 0u;
-            bad[g] |= a >= least && a < __builtin_inff() ? 0u : bit;   // (NaN: bad)
+            bad[g] |= a >= (least > 0x1p-100f ? least : 0x1p-100f) && a < __builtin_inff() ? 0u : bit;   // (NaN: bad)
         });
         bad[g] &= ~zero[g];
-        if (zeros_too) any_zero |= zero[g];
+        zero[g] &= asked(gc);
+        any_zero |= zero[g];
     });
     left = count(bad);
-    if (left > kMendMost) return false;
+    if (left > MOST) return false;
     if (__any(any_zero != 0u)) {
         zeros(zero);
         left += count(zero);
-        if (left > kMendMost) return false;
+        if (left > MOST) return false;
 #pragma unroll
         for (int g = 0; g < G; ++g) bad[g] |= zero[g];
     }
@@ -380,9 +380,139 @@ __device__ __forceinline__ void halves_in_fp32(const ConvKernelParams &p, f32x16
     }
 }
 
-// The sums of a tile's results that are out of range or that something lost could have touched, with fp32 multiply-adds, one by one or - many of them -
-// all blocks of the wavefront.  limit: 2^22 times what a sum may be off by.  A sum of zero is right where its whole row or window of operands is zero.
+// x0, x1 as two pairs of binary16 numbers, each lane with a scale of its own.
+__device__ __forceinline__ void halves_pair_lanes(float x0, float x1, const HalvesScale &sc, uint32_t &h, uint32_t &m) {
+    const float t0 = x0 * sc.t, t1 = x1 * sc.t;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(x0), "v"(sc.s));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(h) : "v"(x1), "v"(sc.s));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(m) : "v"(h), "s"(-2048.f), "v"(t0));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(m) : "v"(h), "s"(-2048.f), "v"(t1));
+}
+
+// All sums of a wavefront's blocks over the split filter again, every column of the gathered operand - read from global memory - with
+// an exponent of its own for three taps of 16 channels: columns of images that are small beside others of the tile lose nothing then.  limit: 2^22 times what
+// the sums of this lane's column of each block may be off by; far: a bit per block as kFarBelow.
+template <bool SWAP, int MB, int NB>
+__device__ __forceinline__ void halves_by_columns(const ConvKernelParams &p, f32x16 (&total)[MB][NB], float (&limit)[NB], uint32_t *far, int krow0, int col0,
+                                                  int half, int l32) {
+    constexpr int BM = 64;
+    static_assert(MB == 2, "a wavefront has a whole row block");
+    const int groups = (p.RS + 8) / 9, nch = (p.C + 15) / 16, chunks = groups * nch, row_block = krow0 / BM;
+    const uint32_t filter_bytes = (uint32_t)p.tilesM * (uint32_t)chunks * (9u * BM * 64u);   // (below 2^31: see gather_mode_ok)
+    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.halves), 0, filter_bytes, kBufferWord3);
+    using ConstantChunk = const __attribute__((address_space(4))) uint64_t;
+    ConstantChunk *const table = (ConstantChunk *)(uintptr_t)(static_cast<const char *>(p.halves) + filter_bytes) + (size_t)row_block * (size_t)chunks;
+    const bool rev = (p.flip != 0) != (p.wsTapS < 0);   // (see the kernel)
+    const uint32_t lane_at = (uint32_t)(half * (BM * 16) + l32 * 16);
+    static_for<NB>([&](auto nbc) __attribute__((always_inline)) {
+        constexpr int nb = decltype(nbc)::value;
+        const int j = col0 + nb * 32 + l32;
+        const uint32_t jj = j < p.NPQ ? (uint32_t)j : 0u, n = magic_div(jj, p.mPQ), rem = jj - n * (uint32_t)p.PQ, pp = magic_div(rem, p.mQ), qq = rem - pp * (uint32_t)p.Q;
+        const int h0 = j < p.NPQ ? (int)pp * p.u - p.pad_h : -(1 << 20), w0 = (int)qq * p.v - p.pad_w;
+        const uint32_t base = (n * (uint32_t)p.xsN + (uint32_t)((int)pp * p.u - p.pad_h) * (uint32_t)p.xsH + (uint32_t)w0 * (uint32_t)p.xsW) * 4u;
+        f32x16 sum[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[mb][v] = 0.f;
+        float off = 0.f;
+        bool far_off = false;
+        // three taps of a chunk at a time: their patch operands and the first block's rows are requested while the ones before are multiplied
+        const int thirds = chunks * 3;
+        float x[3][8];
+        auto request_x = [&](int at3) __attribute__((always_inline)) {
+            const int chunk = at3 / 3, cb = chunk / groups, first = halves_first_tap(chunk - cb * groups, p.RS) + (at3 - chunk * 3) * 3;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const int at = rev ? p.RS - 1 - (first + t) : first + t;
+                const uint32_t tr = magic_div((uint32_t)at, p.mS), ts = (uint32_t)at - tr * (uint32_t)p.S;
+                const bool ok = at3 < thirds && (uint32_t)(h0 + (int)tr) < (uint32_t)p.H && (uint32_t)(w0 + (int)ts) < (uint32_t)p.W;
+                const uint32_t from = base + (tr * (uint32_t)p.xsH + ts * (uint32_t)p.xsW) * 4u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {   // (beyond the last channel, where the filter is zero, nothing)
+                    const int c = cb * 16 + half * 8 + e;
+                    x[t][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, ok && c < p.C ? from + (uint32_t)c * (uint32_t)p.xsC * 4u : kOutOfRange, 0, 0));
+                }
+            }
+        };
+        u32x4 a[2][3][2];   // [block of rows][tap][part]
+        auto request_a = [&](int at3, auto mbc) __attribute__((always_inline)) {   // (past the last one: beyond the row block, or zero)
+            constexpr int mb = decltype(mbc)::value;
+            const uint32_t from = ((uint32_t)(row_block * chunks) * 3u + (uint32_t)at3) * (3u * BM * 64u) + mb * 512u;
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int part = 0; part < 2; ++part)
+                    a[mb][t][part] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane_at + (t * (BM * 64u) + part * (BM * 32u)), from, 0));
+        };
+        request_x(0);
+        request_a(0, std::integral_constant<int, 0>{});
+#pragma clang loop unroll(disable)
+        for (int at3 = 0; at3 < thirds; ++at3) {
+            HalvesSeen seen;
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) look_at(seen, x[t][e], x[t][e + 1]);
+            // (the other half wavefront has the column's other eight channels)
+            const uint32_t here = __builtin_bit_cast(uint32_t, seen.largest), there = (uint32_t)__shfl_xor((int)here, 32), least = (uint32_t)__shfl_xor((int)seen.smallest, 32);
+            const HalvesScale sc = halves_scale(here > there ? here : there);
+            const uint32_t smallest = seen.smallest < least ? seen.smallest : least;
+            u32x4 bh[3], bm[3];
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t h, m;
+                    halves_pair_lanes(x[t][2 * q], x[t][2 * q + 1], sc, h, m);
+                    bh[t][q] = h; bm[t][q] = m;
+                }
+            // (requests return in order: the second block's rows before the next patch operands)
+            request_a(at3, std::integral_constant<int, 1>{});
+            __builtin_amdgcn_sched_barrier(0);
+            request_x(at3 + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint64_t entry = table[at3 / 3];   // HalvesChunk
+            const uint32_t lossy = (uint32_t)(entry >> 32);
+            const float c = __builtin_bit_cast(float, (uint32_t)(127 - (int)(uint32_t)entry - sc.e) << 23), c14 = c * 0x1p-14f;
+            off = __builtin_fmaf((float)((lossy & 255u) << 15), c14, off);
+            if (smallest < 2u * sc.below - 1u) off = __builtin_fmaf((float)(lossy >> 8 & 0x7FFFFFu), c14, off);
+            far_off = far_off || (lossy & kFarBelow) != 0u || smallest < 2u * far_below(sc.below) - 1u;
+            static_for<MB>([&](auto mbc) __attribute__((always_inline)) {
+                constexpr int mb = decltype(mbc)::value;
+                f32x16 acc = {}, low = {};
+                auto product = [&](u32x4 rows, u32x4 column, f32x16 &to) __attribute__((always_inline)) {
+                    const f16x8 fa = __builtin_bit_cast(f16x8, rows), fb = __builtin_bit_cast(f16x8, column);
+                    if constexpr (SWAP) to = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb, fa, to, 0, 0, 0);
+                    else to = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa, fb, to, 0, 0, 0);
+                };
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    product(a[mb][t][0], bm[t], low);
+                    product(a[mb][t][1], bh[t], low);
+                    product(a[mb][t][0], bh[t], acc);
+                }
+                if constexpr (mb == 0) request_a(at3 + 1, std::integral_constant<int, 0>{});
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float cv = SWAP ? __shfl(c, v / 4 * 8 + v % 4 + half * 4) : c;
+                    sum[mb][v] = __builtin_fmaf(__builtin_fmaf(low[v], 0x1p-11f, acc[v]), cv, sum[mb][v]);
+                }
+            });
+        }
+        limit[nb] = off;
+        *far |= far_off ? 1u << nb : 0u;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) total[mb][nb] = sum[mb];
+    });
+}
+
+// The sums of a tile's results that are out of range or that something lost could have touched, one by one or - many of them -
+// all blocks of the wavefront (see the head of the file).  limit: 2^22 times what a sum may be off by.  A sum of zero is right where its whole row or window of operands is zero.
 // n_end: first column beyond the tile's.  A call: inlined, its registers spilled in the tiles that need none of it (64x56x56 -> 64, channels innermost 120 -> 131 us).
+constexpr int kForwardMost = 24;   // 384x13x13 -> 256, backward data: four results 13 us, all of a wavefront's by columns 95, with the fp32 instruction 330
 using KernelArguments = const __attribute__((address_space(4))) ConvKernelParams;
 template <bool SWAP, int MB, int NB>
 __device__ __attribute__((noinline)) void halves_mend(uint64_t arguments, f32x16 *blocks, float limit, bool zeros_too, int n_end, int krow0, int col0) {
@@ -567,7 +697,32 @@ __device__ __attribute__((noinline)) void halves_mend(uint64_t arguments, f32x16
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] = wave_sum(s[i]);
     };
-    if (!mend_results<MB * NB>(limit, zeros_too, lane, get, set, counts, zeros, sums)) halves_in_fp32<SWAP, MB, NB>(p, total, krow0, col0, half, l32);
+    bool done = mend_results<MB * NB, kForwardMost>([&](auto, auto) { return limit; }, [&](auto) { return zeros_too ? 0xFFFFu : 0u; }, lane, get, set, counts, zeros, sums);
+    int infinite = 0;   // or NaN: no exponent helps
+    static_for<MB * NB>([&](auto gc) __attribute__((always_inline)) {
+        static_for<16>([&](auto vc) __attribute__((always_inline)) { infinite += __builtin_fabsf(get(gc, vc)) < __builtin_inff() ? 0 : 1; });
+    });
+    if (!done && wave_sum(infinite) <= kForwardMost) {
+        float limits[NB];
+        uint32_t far = 0;
+        halves_by_columns<SWAP, MB, NB>(p, total, limits, &far, krow0, col0, half, l32);
+        // (SWAP: a lane's results have columns of their own)
+        auto limit_of = [&](auto gc, auto vc) __attribute__((always_inline)) {
+            const float own = limits[decltype(gc)::value % NB];
+            return SWAP ? __shfl(own, in_block(decltype(vc)::value, half)) : own;
+        };
+        auto asked = [&](auto gc) __attribute__((always_inline)) {
+            const bool own = (far >> (decltype(gc)::value % NB) & 1u) != 0u;
+            if (!SWAP) return own ? 0xFFFFu : 0u;
+            const uint32_t columns = (uint32_t)__ballot(own);
+            uint32_t bits = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bits |= ((columns >> in_block(v, half)) & 1u) << v;
+            return bits;
+        };
+        done = mend_results<MB * NB, kForwardMost>(limit_of, asked, lane, get, set, counts, zeros, sums);
+    }
+    if (!done) halves_in_fp32<SWAP, MB, NB>(p, total, krow0, col0, half, l32);
 #pragma unroll
     for (int g = 0; g < MB * NB; ++g) blocks[g] = total[g / NB][g % NB];
 }

@@ -270,6 +270,23 @@ def test_a_few_small_operands_cost_little(kind):
     assert times[1] <= 2.2 * times[0], times
 
 
+def test_images_of_unequal_gradients():
+    """128x384x13x13 -> 256, 3x3, backward data, tiles over three images: every other one's gradients 10^4 times smaller.  (6.5 times as long as
+    without where every such tile was multiplied again with the fp32 instruction; now 2.2.)"""
+    gu = _gpu()
+    rng = np.random.default_rng(64)
+    dy = rng.standard_normal(size=(128, 256, 13, 13), dtype=np.float32)
+    w = rng.standard_normal(size=(256, 384, 3, 3), dtype=np.float32) * np.float32(0.02)
+    times = []
+    for small in (False, True):
+        if small:
+            dy[1::2] *= np.float32(1e-4)
+        g = gu.GpuBackwardData(dy, w, (13, 13), (1, 1), (1, 1), 1, "f32", "NCHW", _bytes(384, 256, 9))
+        times.append(_microseconds(lambda: g.launch(1.0, 0.0)))
+    print(times, flush=True)
+    assert times[1] <= 3.5 * times[0], times
+
+
 # Operands that all have the same low bits: each of a sum's products loses on the same side.  A unit of an operand's last place is 2^-23 of it at most,
 # the product left out 2^-22: 2^-21 of the sum of magnitudes.  The growing sum is rounded, by 2^-24 of it, at nine additions per chunk (five times the
 # chunk's sum in all) and one of each chunk; three more for the small products, the scale and the result.
