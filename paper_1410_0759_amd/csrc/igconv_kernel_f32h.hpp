@@ -18,7 +18,8 @@
 // (below 2^-28 of its chunk's largest) loses up to 2^-36.  The movers note each lane's smallest operand that is not zero; from the lanes that have such
 // operands, and from the largest sum of magnitudes of a filter row, follows what a sum of the tile may be off by (off_by).  Results below 2^22 times that,
 // not finite, or not zero but below 2^-100 are multiplied again (halves_mend): with fp32 multiply-adds, one by one; more than 24 of a wavefront's 4096
-// with an exponent for each column; and what that leaves one by one, or, more than 24 again, all with the fp32 instruction.  Zeros are asked about only where an operand was below 2^-19, and pass where their whole filter row or window is zero.
+// with an exponent for each column; and what that leaves one by one, or, more than 24 again, all with the fp32 instruction.  Zeros are asked about
+// only where an operand was below 2^-19, and pass where their whole filter row or window is zero.
 // us, 128x64x56x56 -> 64, 3x3, backward data (every tile with such an operand multiplied again -> this): log-normal gradients, sigma 2 130 -> 128, 2.5
 // 291 -> 137, 3 733 -> 150, with maps of zeros 739 -> 150; normal ones 134 -> 131.  -> 70 maps, one weight of 1e-12: 1152 -> 195, without it 207 -> 193.
 // What still costs: tiles over images whose gradients differ, 384x13x13 -> 256, by 10^4 833 -> 281, by 10^6 845 -> 463 (alike 126); windows of
@@ -151,6 +152,7 @@ __device__ __forceinline__ bool outside_halves_range(const f32x16 (&sums)[MB][NB
     const uint32_t least = __builtin_bit_cast(uint32_t, 0x1p-100f) << 1, other = __builtin_bit_cast(uint32_t, limit) << 1;
     return nan != 0.f || small < (least > other ? least : other);
 }
+
 // A sum over the wavefront, the same in every lane.
 template <class T>
 __device__ __forceinline__ T wave_sum(T s) {
@@ -252,9 +254,11 @@ __device__ __forceinline__ bool mend_results(Limit limit, Asked asked, int lane,
     }
     return true;
 }
+
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
 }
+
 // NHWC: channel-fastest x (16-byte loads of channels) and y (lanes along output channels in the epilogue).
 // SETS: patches in registers, 2 (nine taps: a chunk is a block) or 1 (more).  WHOLE: one barrier per chunk, where two stages of
 // a chunk's filter fit (nine taps).

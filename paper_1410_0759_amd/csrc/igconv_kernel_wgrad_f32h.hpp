@@ -32,7 +32,8 @@
 // chunk's largest magnitude, scaled, stays within [2^13, 2^15) (it is put into [2^13, 2^14) when it does not; the sums so far are then
 // multiplied by the ratio, which the multipliers have time for), and at most 2^40 finer than that of the range's largest chunk.  Operands below 2^-13
 // after scaling lose up to 2^-36; the movers count the lanes that have some, and with them, per chunk, what a sum may be off by.  Results below 2^22 times that, not
-// finite, or not zero but below 2^-100 are multiplied again as in the forward kernel (wgrad_halves_mend), zeros where an operand was below 2^-19.
+// finite, or not zero but below 2^-100 are multiplied again one by one, more than 96 of a wavefront's 6144 all with the fp32 instruction (wgrad_halves_mend);
+// zeros as in the forward kernel.
 // us, 128x64x56x56 -> 64, 3x3 (scaled to [2^6, 2^15), every range with such an operand multiplied again -> this): normal 154 -> 154; one gradient of 1e-11
 // 791 -> 175 with a map of zeros; log-normal gradients, sigma 2 820 -> 162, with maps of zeros 825 -> 161, 2.5 880 -> 185 and 222, 3 875 -> 215 and 258;
 // images whose gradients differ by up to 10^12 787 -> 222.
