@@ -281,7 +281,11 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         return tile_times * st * 1000.0 *
                (2.75 * ki.BM + (ki.gmode == 5 ? 1.0 : 1.5) * ki.BN + ki.BM * ki.BN / 256.0);
     }
-    // (any filter over channel vectors: as the 1x1 kernel, a step of two units of 32 channels)
+    // (Any filter over channel vectors.  Measured per step of 32 channels of a tap with the chip full, us: 64 x 128 0.17, 128 x 128 0.27,
+    // 128 x 256 - one workgroup per compute unit instead of two, two thirds of the bytes per result - 0.44: 256 -> 128x28x28, 5x5, 128
+    // images 237, 220 and 174 us.  The large one not below one and a half tiles per compute unit: nothing covers its start and its
+    // epilogue then: 128x56x56 -> 256, 3x3 stride 2, 32 images, 196 tiles 40 us, 128 x 128 30; 192 -> 320x27x27, 5x5, 12 images 64 and 51.)
+    if (ki.variant == 6 && ki.BN == 256 && tiles * 2 < cus * 3) return 1e300;
     if (ki.variant == 6) return tile_times * (steps + 2.0) * 500.0 * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0);
     if (is_halves(ki)) {
         // Operands as two binary16 parts (igconv_kernel_f32h.hpp), counted like variant 5, and about 6 us for splitting the filter.

@@ -131,3 +131,41 @@ def test_forward_nine_taps(prob, layout):
                 g.ws.result()   # (guard bands)
             assert gu.rel_err(res[-1], np.maximum(0.5 * want - 1.5 * y0 + bias[None, :, None, None], 0.0)) <= gu.BOUND["bf16"]
         assert np.array_equal(res[0], res[1]) and not np.array_equal(res[0], res[2]), "the route under test did not run"
+
+
+@pytest.mark.parametrize("layout", ["NHWC", "NCHW"])     # of dx
+@pytest.mark.parametrize("prob", [
+    # the 128 x 256 tile (the handle is told of 8 compute units), several tiles per workgroup
+    (40, 130, 30, 31, 72, 5, 5, (2, 2), (1, 1)),      # ragged rows and columns, a ragged last unit of channels
+    (33, 256, 17, 16, 32, 3, 2, (1, 1), (1, 1)),      # one unit per tap: six steps per tile, fewer than the stages of the ring
+    (64, 128, 16, 16, 8, 2, 1, (0, 0), (1, 1)),       # two steps per tile
+])
+def test_backward_data_large_tiles(prob, layout):
+    import torch
+    import paper_1410_0759_amd as ig
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    rng = np.random.default_rng(7)
+    P, Q = oc.output_dim(H, R, stride[0], pad[0]), oc.output_dim(W, S, stride[1], pad[1])
+    dy, w = wl.with_layout(_rnd(rng, (N, K, P, Q)), "NHWC"), _rnd(rng, (K, C, R, S), (K * R * S) ** -0.5)
+    want = oc.conv_backward_data(dy, w, (H, W), pad=pad, stride=stride)
+    t = lambda a, lay: torch.from_numpy(np.ascontiguousarray(a)).to("cuda") if lay == "NCHW" else \
+        torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1))).to("cuda").permute(0, 3, 1, 2)
+    dyt, wt = t(dy, "NHWC").to(torch.bfloat16), t(w, "NCHW").to(torch.bfloat16)
+    res = []
+    for cus in (8, 256):
+        h = ig.Handle()
+        h.set_stream(torch.cuda.current_stream().cuda_stream)
+        ig.set_compute_units(h, cus)
+        dx = t(np.full((N, C, H, W), np.nan, np.float32), layout)
+        wd = ig.FilterDescriptor().set(ig.IGC_DATA_BFLOAT16, K, C, R, S)
+        cd = ig.ConvolutionDescriptor().set(pad[0], pad[1], stride[0], stride[1], ig.IGC_CROSS_CORRELATION)
+        dyd, dxd = ig.tensor_descriptor_for(dyt), ig.tensor_descriptor_for(dx)
+        n = ig.get_backward_data_workspace_size(h, wd, dyd, cd, dxd)
+        assert n == w.size * 2
+        ws = torch.empty(n // 4 + 4, device="cuda")
+        print(prob, layout, cus, flush=True)
+        ig.check(ig.convolution_backward_data(h, 1.0, wd, wt.data_ptr(), dyd, dyt.data_ptr(), cd, 0.0, dxd, dx.data_ptr(), ws.data_ptr(), n))
+        res.append(dx.cpu().numpy())
+        assert gu.rel_err(res[-1], want) <= gu.BOUND["bf16"]
+    assert np.array_equal(res[0], res[1])      # (the same order of the sums in every tile)
