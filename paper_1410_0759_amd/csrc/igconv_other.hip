@@ -96,10 +96,10 @@ __device__ __forceinline__ void offsets_of(const View &v, uint32_t idx, uint32_t
 
 // ---- host side ---------------------------------------------------------------------------
 template <class Kernel, class Args>
-igcStatus launch(Kernel kernel, const char *what, const Args &args, uint32_t blocks, void *stream, size_t lds_bytes = 0) {
+igcStatus launch(Kernel kernel, const char *what, const Args &args, uint32_t blocks, void *stream, size_t lds_bytes = 0, int threads = 256) {
     Args copy = args;
     void *argv[] = {&copy};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(blocks), dim3(256), argv, lds_bytes,
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(blocks), dim3(threads), argv, lds_bytes,
                                          static_cast<hipStream_t>(stream));
     if (e != hipSuccess && std::getenv("IGCONV_DEBUG"))
         std::fprintf(stderr, "igconv: launch of %s failed: %s\n", what, hipGetErrorString(e));
@@ -133,6 +133,10 @@ __device__ __forceinline__ wide_t rload_wide(__amdgpu_buffer_rsrc_t buf, uint32_
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(wide_t, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(buf, off4, 0, 0));
 }
+__device__ __forceinline__ void rstore_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4, wide_t v) {
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), buf, off4, 0, 0);
+}
 __device__ __forceinline__ real_t rexp(real_t x) { return __expf(x); }
 __device__ __forceinline__ real_t rmax(real_t a, real_t b) { return fmaxf(a, b); }
 #include "igconv_other_impl.inc"
@@ -155,6 +159,10 @@ typedef double wide_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ wide_t rload_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4) {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(wide_t, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(buf, off4 >= 0x80000000u ? 0x80000000u : off4 * 2u, 0, 0));
+}
+__device__ __forceinline__ void rstore_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4, wide_t v) {
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), buf, off4 >= 0x80000000u ? 0x80000000u : off4 * 2u, 0, 0);
 }
 __device__ __forceinline__ real_t rexp(real_t x) { return exp(x); }
 __device__ __forceinline__ real_t rmax(real_t a, real_t b) { return fmax(a, b); }

@@ -253,3 +253,43 @@ def test_backward_bias():
     z[2, 129, 6, 8] = 7.0
     got = gu.run_backward_bias(wl.with_layout(z, "NHWC"))
     assert got[129] == 7.0 and np.count_nonzero(got) == 1
+
+
+@pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
+@pytest.mark.parametrize("shape, win, pad", [
+    # stride 2, 512 planes and more: the kernel that walks down rows of 2 x 2 cells
+    ((8, 64, 55, 55), 3, 0), ((4, 128, 9, 127), 3, 1), ((4, 130, 70, 128), 2, 1), ((2, 256, 40, 126), 3, 2), ((8, 65, 1, 1), 2, 1),
+    ((8, 64, 2, 3), 3, 2), ((16, 32, 7, 6), 3, 1), ((2, 64, 112, 112), 3, 0), ((2, 64, 75, 117), 3, 1), ((8, 64, 33, 31), 2, 0), ((4, 129, 34, 20), 3, 0), ((8, 64, 10, 12), 3, 0)])
+def test_pooling_backward_cells(shape, win, pad, mode):
+    """Against the oracle, and bit for bit against the kernels for rows with a pitch, infinities and NaN included."""
+    import torch
+    import paper_1410_0759_amd as ig
+    gu = _gpu()
+    x = np.maximum(rnd(51, *shape), 0)          # (many equal zeros)
+    N, C, H, W = shape
+    P, Q = po.pooling_output_dim(H, win, pad, 2), po.pooling_output_dim(W, win, pad, 2)
+    dy = rnd(52, N, C, P, Q)
+    old = rnd(53, *shape)
+    print(shape, win, pad, mode, flush=True)
+    close(gu.run_pooling_backward(mode, x, dy, (win, win), (pad, pad), (2, 2)), po.pooling_backward(mode, x, dy, (win, win), (pad, pad), (2, 2)))
+    close(gu.run_pooling_backward(mode, x, dy, (win, win), (pad, pad), (2, 2), 0.5, -1.0, old),
+          po.pooling_backward(mode, x, dy, (win, win), (pad, pad), (2, 2), 0.5, -1.0, old))
+    rng = np.random.default_rng(54)
+    for value in (np.nan, np.inf, -np.inf):
+        x[rng.uniform(size=shape) < 0.3] = value
+    x[:, ::3] = -np.inf
+    x[:, 1::7] = np.nan
+    h = ig.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    pd = ig.PoolingDescriptor().set(ig.IGC_POOLING_MAX if mode == 0 else ig.IGC_POOLING_AVERAGE, win, win, pad, pad, 2, 2)
+    dyt = torch.from_numpy(dy).cuda()
+    d = ig.tensor_descriptor_for
+    got = []
+    for pitch in (0, 1):
+        xt = torch.zeros(N, C, H, W + pitch, device="cuda")[..., :W]
+        dx = torch.zeros(N, C, H, W + pitch, device="cuda")[..., :W]
+        xt.copy_(torch.from_numpy(x))
+        dx.copy_(torch.from_numpy(old))
+        ig.check(ig.pooling_backward(h, pd, 1.5, d(dyt), dyt.data_ptr(), d(xt), xt.data_ptr(), 0.25, d(dx), dx.data_ptr()))
+        got.append(dx.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
