@@ -748,7 +748,9 @@ struct BackwardFilterProblem {
     // channel-vector kernels (gather mode 10): a part of the workspace holds [tap][row position][column position],
     // rows and columns padded to whole tiles; 0 for the other kernels, whose parts are copies of dw
     long long pos_rows = 0, pos_cols = 0;
-    long long part_elems() const { return pos_rows ? pos_rows * pos_cols * (out_elems / (pr.kp.K * (long long)pr.kp.NPQ)) : out_elems; }
+    int image_chunks = 0;   // (variant 10) ConvKernelParams::imageTiles
+    bool rows_parts = false;   // (variant 10) parts in the order of the accumulators
+    long long part_elems() const { return rows_parts ? tiles * (long long)WgradRowsPart::kTileElems : pos_rows ? pos_rows * pos_cols * (out_elems / (pr.kp.K * (long long)pr.kp.NPQ)) : out_elems; }
 };
 
 static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDescriptor_t dy,
@@ -856,7 +858,7 @@ static igcStatus validate_backward_filter(igcTensorDescriptor_t x, igcTensorDesc
     for (int attempt = 0; attempt < 2 && id < 0; ++attempt) {
         for (int i = 0; i < list.count; ++i) {
             const KernelInfo &ki = *list.info[i];
-            if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn || ki.variant == 9) continue;   // (variant 9: halves_backward_filter)
+            if (ki.gmode != want_mode || ki.BM != want_bm || ki.BN != want_bn || ki.variant >= 9) continue;   // (variants 9 and 10: halves_backward_filter)
             if (ki.variant == 4 && prefer_fp32(ki.BM, ki.BN)) continue;
             id = list.id[i];   // (the split kernels come last)
         }
@@ -1038,6 +1040,25 @@ static void backward_filter_split(const igcContext *h, const BackwardFilterProbl
     const long long cus = h->computeUnits;
     const KernelInfo *ki = kernel_info(b.kernel_id);
     const long long per_cu = ki && ki->f64 ? 4 : (ki && ki->gmode != 10 ? workgroups_per_cu(*ki) : 2);
+    if (ki && ki->variant == 10) {
+        // One workgroup per compute unit, chunks of about 3.3 us; two chunks' time per range for its start and end, a part's bytes by 10 MB
+        // for its pass of the ordered sum.  As for the kernels below finer ranges even out the rounds: 128x96x64x64 -> 128, 9x9, 54 tiles of 3136
+        // chunks: 4 ranges in one round of 216 workgroups 784 chunks, 14 in three rounds 690.
+        const double part_bytes = (double)b.part_elems() * 4.0;
+        const long long hi = std::max<long long>(1, std::min({(long long)((double)IGC_NOALLOC_SCRATCH_BYTES / part_bytes), b.ksteps / 2, max_parts}));
+        double best = 0.0;
+        *splits = 0;
+        for (long long s = 1; s <= hi; ++s) {
+            const long long per = ((b.ksteps + s - 1) / s + 1) & ~1ll, used = (b.ksteps + per - 1) / per;
+            const double cost = (double)((b.tiles * used + cus - 1) / cus) * ((double)per + 2.0) + (double)used * part_bytes / 10e6;
+            if (*splits == 0 || cost < best * 0.98) {
+                best = cost;
+                *splits = (int)used;
+                *steps_per_split = (int)per;
+            }
+        }
+        return;
+    }
     long long want = std::max<long long>(1, (per_cu * cus) / b.tiles);
     want = std::min(want, std::max<long long>(1, b.ksteps / (ki && ki->variant == 9 ? 2 : 8)));
     want = std::min(want, std::max<long long>(1, max_parts));
@@ -1075,8 +1096,8 @@ static void backward_filter_split(const igcContext *h, const BackwardFilterProbl
 }
 
 // Float operands as two binary16 parts (igconv_kernel_wgrad_f32h.hpp), where that kernel can run, is the faster one and loses
-// no precision: `b`, whose workspace the query has reported, becomes its problem.  max_parts: ranges there is room for.
-static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b, long long max_parts) {
+// no precision: `b`, whose workspace the query has reported, becomes its problem.  room_bytes: of the workspace, which starts on a 16-byte boundary if `aligned`.
+static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b, long long room_bytes, bool aligned) {
     const KernelInfo &old = *kernel_info(b->kernel_id);
     const ConvKernelParams &k = b->pr.kp;
     if (old.gmode != 8 || old.bf16 || old.f64) return;
@@ -1087,20 +1108,25 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
     if (S < 3 || k.redMulW != 1 || k.K < 8 || C < 8 || Q < 9 || (k.xsN == 1) != (k.wsRow == 1)) return;
     const bool innermost = k.xsN == 1;
     const KernelList &list = kernels_of(false, false, true);
-    BackwardFilterProblem n = *b;
-    n.kernel_id = -1;
-    for (int i = 0; i < list.count; ++i)
-        if (list.info[i]->variant == 9 && list.info[i]->swap == innermost) n.kernel_id = list.id[i];
-    if (n.kernel_id < 0) return;
-    const KernelInfo &ki = *kernel_info(n.kernel_id);
-    ConvKernelParams &kn = n.pr.kp;
-    kn.PQ = (C + 31) / 32;
-    kn.Wp = Q + 2;
-    kn.HpWp = P;
-    if (!magic_for((uint32_t)kn.PQ, &kn.mPQ) || !magic_for((uint32_t)kn.Wp, &kn.mWp) || !magic_for((uint32_t)kn.HpWp, &kn.mHpWp)) return;
-    n.ksteps = (k.CRS + ki.BK - 1) / ki.BK;
-    n.tiles_n = ((long long)k.R * ((S + 2) / 3) * kn.PQ + 1) / 2;
-    n.tiles = (long long)((k.K + ki.BM - 1) / ki.BM) * n.tiles_n;
+    const long long max_parts = std::max<long long>(1, room_bytes / (4 * b->part_elems()));
+    auto problem_of = [&](int variant, int patch_rows, BackwardFilterProblem *n) {
+        *n = *b;
+        n->kernel_id = -1;
+        for (int i = 0; i < list.count; ++i)
+            if (list.info[i]->variant == variant && list.info[i]->swap == innermost) n->kernel_id = list.id[i];
+        if (n->kernel_id < 0) return false;
+        ConvKernelParams &kn = n->pr.kp;
+        kn.PQ = (C + 31) / 32;
+        kn.Wp = Q + 2;
+        kn.HpWp = patch_rows;
+        if (!magic_for((uint32_t)kn.PQ, &kn.mPQ) || !magic_for((uint32_t)kn.Wp, &kn.mWp) || !magic_for((uint32_t)kn.HpWp, &kn.mHpWp)) return false;
+        n->ksteps = (k.CRS + kernel_info(n->kernel_id)->BK - 1) / kernel_info(n->kernel_id)->BK;
+        return true;
+    };
+    BackwardFilterProblem n;
+    if (!problem_of(9, P, &n)) return;
+    n.tiles_n = ((long long)k.R * ((S + 2) / 3) * n.pr.kp.PQ + 1) / 2;
+    n.tiles = (long long)((k.K + 63) / 64) * n.tiles_n;
     int splits, per, splits_old, per_old;
     backward_filter_split(h, n, max_parts, &splits, &per);
     backward_filter_split(h, *b, max_parts, &splits_old, &per_old);
@@ -1109,7 +1135,8 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
     // and small products' own.  Short reductions therefore stay (2x320x27x27 -> 112, 3x3: 1.1e-7, here 1.3e-7).
     const bool split = old.variant == 4;
     const double chain_old = 32.0 * per_old, chain = 64.0 * per;   // (two halves of a chunk's pixels apart)
-    if ((split ? 34.8 : 317.0) * chain_old < 22500.0 + 38.4 * chain) return;
+    const double longest = ((split ? 34.8 : 317.0) * chain_old - 22500.0) / 38.4;   // chain here that loses no more than there
+    bool found = chain <= longest;
     // Time, us.  Here 3.0 per chunk, NCHW or channels innermost, and 21 for start, end and the parts' sum.  The others: steps at
     // 195 to 143 TFLOP/s of the chip in tiles of split operands, 110 of fp32 ones, half of that or less with channels innermost.  Model and measured
     // times of those layers (others -> here): 28x32x64x64 -> 112, 3x3 128 -> 69, measured 137 -> 80; 20x384x15x15 -> 160, 5x5 179 -> 129,
@@ -1120,8 +1147,45 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
     double rate = split ? (old.BM * old.BN >= 96 * 128 ? 6.6e5 : 5.6e5) : 4.3e5;   // flop per us and compute unit
     if (innermost) rate *= 0.5;
     const double us_old = 6.0 + std::ceil(wgs_old / (cus * resident)) * (per_old + 3.0) * resident * old.BM * old.BN * 64.0 / rate;
-    const double us = 21.0 + std::ceil((double)n.tiles * splits / cus) * per * 3.0;
-    if (us < us_old) *b = n;
+    double us = 21.0 + std::ceil((double)n.tiles * splits / cus) * per * 3.0;
+    found = found && us < us_old;
+    if (!found) us = us_old;
+    // Three filter rows at unit strides (igconv_kernel_wgrad_f32h_rows.hpp), where a chunk's pixels fit its patch, those of two images or of one.
+    if (k.R >= 3 && k.redMulH == 1) {
+        BackwardFilterProblem r;
+        auto span = [&](int images) {   // of 128 pixels in `images` images at most, and the rest of the last window
+            const int rows = (127 + Q - 1) / Q;
+            return 127 + 2 * rows + 2 * (Q + 2) * (images - 1) + 2 * (Q + 2) + 3;
+        };
+        const bool any = span(1 + (127 + k.RS - 1) / k.RS) <= kWgradRowsPatch;
+        if ((any || span(1) <= kWgradRowsPatch) && problem_of(10, P + 2, &r) && (long long)r.out_elems * 8 < kMaxBytes) {
+            if (!any) {
+                r.image_chunks = (k.RS + 127) / 128;
+                r.ksteps = (long long)r.image_chunks * (k.CRS / k.RS);
+            }
+            r.tiles_n = (long long)((k.R + 2) / 3) * ((S + 2) / 3) * r.pr.kp.PQ;
+            r.tiles = (long long)((k.K + 63) / 64) * r.tiles_n;
+            r.rows_parts = true;
+            int splits_r, per_r;
+            backward_filter_split(h, r, aligned ? std::max<long long>(1, room_bytes / (4 * r.part_elems())) : 1, &splits_r, &per_r);
+            // Chains of no more pixels than in the kernel that would run instead, or than lose as much there.
+            const double chain_r = found ? chain : longest;
+            const int per_chain = (int)std::min((double)per_r, chain_r / 128.0) & ~1;
+            if (per_chain >= 2) {
+                r.pr.kp.stepsPerChain = per_chain;
+                const int pieces = (per_r + per_chain - 1) / per_chain;
+                // 3.3 us per chunk, two chunks per chain of sums for its start and end, 18 for the rest.  Measured, us, the kernel before and here: 64x256x14x14 ->
+                // 256, 3x3 104 and 71; 2x512x28x28 -> 512 77 and 61; 11x24x40x40 -> 200, 9x9 151 and 98; 20x384x15x15 -> 160, 5x5 130 and 100;
+                // 8x64x56x56 -> 64, 3x3 36 and 30; 28x32x56x56 -> 112 41 and 41; 16x32x28x28 -> 64 18.7 and 22.9.
+                const double us_r = 18.0 + std::ceil((double)r.tiles * splits_r / cus) * (per_r + 2.0 * pieces) * 3.3;
+                if (us_r < us) {
+                    found = true;
+                    n = r;
+                }
+            }
+        }
+    }
+    if (found) *b = n;
 }
 
 }  // namespace igc
@@ -1795,6 +1859,13 @@ igcStatus igcGetConvolutionBackwardFilterWorkspaceSize(igcHandle_t handle, igcTe
     backward_filter_split(handle, b, 1 << 20, &splits, &per);
     // (the channel-vector kernels want their workspace even for a single range: see the entry point)
     *sizeInBytes = splits > 1 || b.pos_rows ? (size_t)splits * b.part_elems() * (b.pr.f64 ? 8 : 4) : 0;
+    // The kernels of three filter rows per tile have fewer, larger tiles and want more ranges of them.
+    BackwardFilterProblem rows = b;
+    halves_backward_filter(handle, &rows, IGC_NOALLOC_SCRATCH_BYTES, true);
+    if (kernel_info(rows.kernel_id)->variant == 10) {
+        backward_filter_split(handle, rows, 1 << 20, &splits, &per);
+        if (splits > 1) *sizeInBytes = std::max(*sizeInBytes, (size_t)(splits * rows.part_elems() * 4));
+    }
     return IGC_STATUS_SUCCESS;
 }
 
@@ -1809,11 +1880,12 @@ igcStatus igcConvolutionBackwardFilter(igcHandle_t handle, const void *alpha, ig
     const bool f64 = b.pr.f64;
     const int es = b.pr.bf16 ? 2 : (f64 ? 8 : 4), out_es = f64 ? 8 : 4;
     if ((uintptr_t)x % es || (uintptr_t)dy % es || (uintptr_t)dw % out_es || (uintptr_t)workSpace % out_es) return IGC_STATUS_BAD_PARAM;
+    halves_backward_filter(handle, &b, workSpace ? (long long)std::min<size_t>(workSpaceSizeInBytes, (size_t)LLONG_MAX) : 0, (uintptr_t)workSpace % 16 == 0);
     const size_t part_bytes = (size_t)b.part_elems() * out_es;
     int splits, per;
-    const long long room = workSpace ? (long long)(workSpaceSizeInBytes / part_bytes) : 0;
-    halves_backward_filter(handle, &b, std::max<long long>(1, room));
+    const long long room = workSpace && ((uintptr_t)workSpace % 16 == 0 || !b.rows_parts) ? (long long)(workSpaceSizeInBytes / part_bytes) : 0;
     backward_filter_split(handle, b, room, &splits, &per);
+    b.rows_parts = b.rows_parts && splits > 1;
     // Channel-vector kernels: with room for at least one part the results go to the workspace in accumulator
     // order (coalesced) and the summing kernel moves them to dw; writing dw's layout from the tile is slow.
     const bool positions = b.pos_rows != 0 && room >= 1;
@@ -1822,6 +1894,7 @@ igcStatus igcConvolutionBackwardFilter(igcHandle_t handle, const void *alpha, ig
     st = fill_plan(handle, b.kernel_id, &b.pr, &plan);
     if (st != IGC_STATUS_SUCCESS) return st;
     k.tilesN = (int)b.tiles_n;
+    k.imageTiles = b.image_chunks;
     const float a = f64 ? 0.f : *static_cast<const float *>(alpha), bt = f64 ? 0.f : *static_cast<const float *>(beta);
     const double a64 = f64 ? *static_cast<const double *>(alpha) : 0.0, bt64 = f64 ? *static_cast<const double *>(beta) : 0.0;
     k.x = x;
@@ -1838,6 +1911,10 @@ igcStatus igcConvolutionBackwardFilter(igcHandle_t handle, const void *alpha, ig
         k.beta = 0.f; k.beta64 = 0.0;
         if (positions) {
             k.ysN = 1; k.ysP = (int)b.pos_rows; k.ysK = (int)b.pos_cols;
+            k.y_bytes = (uint32_t)part_bytes;
+        }
+        if (b.rows_parts) {
+            k.ysN = 1;
             k.y_bytes = (uint32_t)part_bytes;
         }
     } else {
@@ -1861,6 +1938,11 @@ igcStatus igcConvolutionBackwardFilter(igcHandle_t handle, const void *alpha, ig
                                  handle->stream) != 0)
             return IGC_STATUS_EXECUTION_FAILED;
         return IGC_STATUS_SUCCESS;
+    }
+    if (b.rows_parts) {
+        const WgradRowsPart part{k.K, k.NPQ, k.R, k.Q, k.PQ, k.tilesM, (int)b.tiles, k.flip};
+        return launch_sum_rows(static_cast<const float *>(workSpace), static_cast<float *>(dw), part, splits, a, bt, handle->stream) == 0
+                   ? IGC_STATUS_SUCCESS : IGC_STATUS_EXECUTION_FAILED;
     }
     if (splits > 1 && !f64 && launch_sum_parts(static_cast<const float *>(workSpace), static_cast<float *>(dw), b.out_elems, splits,
                                                b.out_elems, a, bt, handle->stream) != 0)

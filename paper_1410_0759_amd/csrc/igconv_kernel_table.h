@@ -36,6 +36,7 @@ struct KernelInfo {
                       // 6: channel vectors of a filter rewritten with the channel index innermost (gather mode 1, bf16)
                       // 7: float operands as two binary16 parts, the gathered side from a staged image patch, nine taps (gather mode 3); 8: more taps
                       // 9: backward filter, float operands as two binary16 parts, three taps of a filter row per tile (gather mode 8)
+                      // 10: the same with three filter rows by three taps per tile
                       // 5: the same as 4 for nine taps, the gathered side from a staged image patch (gather mode 3)
     bool f64 = false; // double precision in and out (alpha64 / beta64 of the parameters apply)
     int patchPixels = 512;  // gather mode 5, variants 5, 7 and 8: pixels of the zero-extended image a tile's staged patch can hold
@@ -91,6 +92,13 @@ int launch_phase_scatter(const float *y, float *dx, int N, int C, int H, int W, 
 // position] (KP x CP positions per tap, tiles of BM x BN): see igconv_kernel_wgrad_bf16c.hpp.
 int launch_sum_positions(const float *parts, float *out, uint32_t n, int count, uint32_t stride, float alpha, float beta, int C,
                          int RS, int BM, int BN, int KP, int CP, void *stream);
+// The same for the backward-filter kernels of variant 10, whose parts are stored as [tile][filter row][tap][block of maps][registers / 4][lane]
+// [four maps] (igconv_kernel_wgrad_f32h_rows.hpp): out = alpha * sum + beta * out, K x C x R x S.
+struct WgradRowsPart {
+    static constexpr int kTileElems = 64 * 288;
+    int K, C, R, S, cblocks, tilesM, tiles, flip;
+};
+int launch_sum_rows(const float *parts, float *out, const WgradRowsPart &part, int count, float alpha, float beta, void *stream);
 int launch_sum_parts_f64(const double *parts, double *out, uint32_t n, int count, uint32_t stride, double alpha, double beta,
                          void *stream);
 

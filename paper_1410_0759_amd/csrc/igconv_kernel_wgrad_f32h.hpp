@@ -74,9 +74,9 @@ __device__ __forceinline__ int wgrad_row(int first, int at, int count, bool *our
     return from + (at & 7);
 }
 
-// A wavefront's blocks over its share of the output pixels [j_begin, j_end) with the fp32 instruction straight from global memory.
+// A wavefront's blocks over its share of the output pixels [j_begin, j_end) - 64 of every `apart` - with the fp32 instruction straight from global memory.
 __device__ __forceinline__ void wgrad_halves_in_fp32(const ConvKernelParams &p, f32x16 (&acc)[3][2], int m0, int c0, int tap_h, int tap_w, int j_begin,
-                                                     int j_end, int part, int half, int l32) {
+                                                     int j_end, int part, int apart, int half, int l32) {
     const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
     const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.w), 0, p.w_bytes, kBufferWord3);
     bool ours;
@@ -91,7 +91,7 @@ __device__ __forceinline__ void wgrad_halves_in_fp32(const ConvKernelParams &p, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][mb][v] = 0.f;
 #pragma clang loop unroll(disable)
-    for (int jb = j_begin + part * 64; jb < j_end; jb += 128)
+    for (int jb = j_begin + part * 64; jb < j_end; jb += apart)
 #pragma clang loop unroll(disable)
         for (int i = 0; i < 64; i += 2) {
             const uint32_t j = (uint32_t)(jb + i + half);
@@ -128,7 +128,7 @@ __device__ __forceinline__ uint32_t nonzero_lanes(uint32_t v) {
 }
 // A wavefront's blocks of a range: where they are.
 struct WgradMend {
-    int m0, c0, tap_h, tap_w, j_begin, j_end, part;
+    int m0, c0, tap_h, tap_w, j_begin, j_end, part, apart;   // (its share: 64 of every `apart` pixels, from part * 64 on)
     bool live;        // (not one that fills up a pair of units)
     bool zeros_too;   // (mend_results)
 };
@@ -138,7 +138,7 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
     ConvKernelParams p = *(KernelArguments *)(uintptr_t)uniform64(arguments);
     auto uniform = [](auto &v) __attribute__((always_inline)) { v = __builtin_bit_cast(std::remove_reference_t<decltype(v)>, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
     uniform(limit);
-    uniform(where.m0); uniform(where.c0); uniform(where.tap_h); uniform(where.tap_w); uniform(where.j_begin); uniform(where.j_end); uniform(where.part);
+    uniform(where.m0); uniform(where.c0); uniform(where.tap_h); uniform(where.tap_w); uniform(where.j_begin); uniform(where.j_end); uniform(where.part); uniform(where.apart);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     f32x16 acc[3][2];
 #pragma unroll
@@ -204,11 +204,11 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
                 rowoff[i] = rowoff_of(r[i] >> 5, r[i] & 31);
             }
 #pragma clang loop unroll(disable)
-            for (int j = j_first; __any(j < where.j_end) && found != 15u; j += 768) {
+            for (int j = j_first; __any(j < where.j_end) && found != 15u; j += 6 * where.apart) {
                 float a[6][4];
 #pragma unroll
                 for (int e = 0; e < 6; ++e) {
-                    const Pixel x = pixel(j + e * 128);
+                    const Pixel x = pixel(j + e * where.apart);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) a[e][i] = load_dy(x, rowoff[i]);
                 }
@@ -241,11 +241,11 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
             const uint32_t coloff[2] = {coloff_of(c0), coloff_of(c1)};
             uint32_t found = 0;
 #pragma clang loop unroll(disable)
-            for (int j = j_first; __any(j < where.j_end) && found != 63u; j += 512) {
+            for (int j = j_first; __any(j < where.j_end) && found != 63u; j += 4 * where.apart) {
                 float b[4][6];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const Pixel x = pixel(j + e * 128);
+                    const Pixel x = pixel(j + e * where.apart);
 #pragma unroll
                     for (int i = 0; i < 6; ++i) b[e][i] = load_x(x, coloff[i / 3], i % 3);
                 }
@@ -275,11 +275,11 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
             s[i] = 0.f;
         }
 #pragma clang loop unroll(disable)
-        for (int j = j_first; __any(j < where.j_end); j += 512) {
+        for (int j = j_first; __any(j < where.j_end); j += 4 * where.apart) {
             float a[4][4], b[4][4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const Pixel x = pixel(j + e * 128);
+                const Pixel x = pixel(j + e * where.apart);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     a[e][i] = load_dy(x, rowoff[i]);
@@ -297,7 +297,7 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
     const bool zeros_too = __builtin_amdgcn_readfirstlane((int)where.zeros_too) != 0;
     // (64x56x56 -> 64: four results 13 us, a range's blocks 700)
     if (!mend_results<6, 96>([&](auto, auto) { return limit; }, [&](auto) { return zeros_too ? 0xFFFFu : 0u; }, lane, get, set, counts, zeros, sums))
-        wgrad_halves_in_fp32(p, acc, where.m0, where.c0, where.tap_h, where.tap_w, where.j_begin, where.j_end, where.part, half, l32);
+        wgrad_halves_in_fp32(p, acc, where.m0, where.c0, where.tap_h, where.tap_w, where.j_begin, where.j_end, where.part, where.apart, half, l32);
 #pragma unroll
     for (int g = 0; g < 6; ++g) blocks[g] = acc[g / 2][g % 2];
 }
@@ -834,6 +834,7 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             m.j_begin = jb < p.CRS ? (int)jb : p.CRS;
             m.j_end = je < p.CRS ? (int)je : p.CRS;
             m.part = ph;
+            m.apart = BK;
             m.live = unit.live;
             m.zeros_too = zeros_too;
             f32x16 blocks[6];

@@ -35,6 +35,8 @@ constexpr uint32_t few_channels_map_offset(int map, int K, uint32_t map_bytes) {
 // The kernels that feed the MFMAs straight from global memory (igconv_kernel_f32d.hpp): entries of their LDS table of
 // tap offsets (one per reduction index), and how many steps ahead their requests run (as many register sets).
 constexpr int kDirectTableEntries = 16384;
+// Pixels of x that a chunk of output pixels may span in the backward-filter kernels of three filter rows per tile (variant 10).
+constexpr int kWgradRowsPatch = 256;
 constexpr int direct_depth(int bk, bool staged_rows = false) { return staged_rows ? 4 : (bk >= 32 ? 2 : 3); }   // (bk: reduction indices per step)
 
 struct ConvKernelParams {
@@ -74,7 +76,8 @@ struct ConvKernelParams {
     int32_t Wp, HpWp;
     Magic mWp, mHpWp;
     const void *halves = nullptr;   // (variants 7 and 8) the split filter, then its table (igconv_kernel_f32h.hpp)
-    int32_t imageTiles = 0;   // (variants 7 and 8) column tiles of each image where no tile spans two; 0: columns cut regardless of images
+    int32_t imageTiles = 0;   // (variants 7 and 8) column tiles - (variant 10) chunks of pixels - of each image where none spans two; 0: cut regardless of images
+    int32_t stepsPerChain = 0;   // (variant 10) chunks that one chain of sums takes, an even number (igconv_kernel_wgrad_f32h_rows.hpp)
 };
 
 // Several problems of one kernel in one launch (the stride phases of backward data): workgroup b belongs to problem i with

@@ -216,3 +216,55 @@ def test_operands_with_the_same_low_bits(prob, value, run):
     got = run(gu, x, dy, dims[5:], pad, stride)
     want = oc.conv_backward_filter(x, dy, dims[5:], pad=pad, stride=stride, mode=1)
     assert (np.abs(got - want) <= (2.0 ** -21 + (dy.size / dims[4] / 32 + 16) * 2.0 ** -24) * np.abs(want)).all()
+
+
+ROWS = [
+    # N, C, H, W, K, R, S, pad, stride: three filter rows and taps per tile
+    (10, 40, 20, 57, 70, 3, 3, (1, 1), (1, 1)),      # long rows: chunks keep to one image
+    (12, 33, 21, 13, 45, 5, 4, (2, 1), (1, 1)),      # five rows and four taps: the second three share one and two
+    (30, 25, 18, 23, 8, 7, 7, (3, 3), (1, 1)),       # eight maps, the last eight channels again; three groups of rows and of taps
+    (40, 64, 9, 9, 130, 3, 3, (1, 1), (1, 1)),       # shortest rows, two images and more per chunk; ragged third block of maps
+    (1, 32, 150, 58, 64, 6, 3, (0, 1), (1, 1)),      # one image
+    (64, 40, 6, 11, 24, 3, 5, (1, 2), (1, 1)),       # images of 66 pixels
+]
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("prob", ROWS)
+def test_three_filter_rows(prob, layout, monkeypatch, capfd):
+    """With room for every range, for two, for none, and a workspace off the 16-byte boundary; several tiles and chains of sums per workgroup."""
+    import torch
+    gu = _gpu()
+    *dims, pad, stride = prob
+    N, C, H, W, K, R, S = dims
+    x, dy = _problem(61, *prob)
+    rng = np.random.default_rng(62)
+    old = rng.uniform(-1, 1, size=(K, C, R, S)).astype(np.float32)
+    h = ig.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    ig.set_compute_units(h, 8)
+    put = lambda a: torch.from_numpy(a).cuda() if layout == "NCHW" else torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1))).cuda().permute(0, 3, 1, 2)
+    xt, dyt = put(x), put(dy)
+    xd, dyd = ig.tensor_descriptor_for(xt), ig.tensor_descriptor_for(dyt)
+    wd = ig.FilterDescriptor().set(ig.IGC_DATA_FLOAT, K, C, R, S)
+    monkeypatch.setenv("IGCONV_DEBUG", "1")
+    for mode in (ig.IGC_CONVOLUTION, ig.IGC_CROSS_CORRELATION):
+        cd = ig.ConvolutionDescriptor().set(*pad, *stride, mode)
+        full = ig.get_backward_filter_workspace_size(h, xd, dyd, cd, wd)
+        tiles = -(-K // 64) * -(-C // 32) * -(-R // 3) * -(-S // 3)
+        for room, offset, alpha, beta in ((full, 0, 0.5, -1.5), (2 * tiles * 18432 * 4, 0, 1.0, 0.0), (0, 0, 0.5, -1.5), (full, 4, 1.0, 0.0)):
+            ws = torch.full((full // 4 + tiles * 18432 * 2 + 8,), float("nan"), device="cuda")
+            dw = torch.from_numpy(old if beta else np.full_like(old, np.nan)).cuda()
+            capfd.readouterr()
+            ig.check(ig.convolution_backward_filter(h, alpha, xd, xt.data_ptr(), dyd, dyt.data_ptr(), cd, beta, wd, dw.data_ptr(),
+                                                    ws.data_ptr() + offset if room else 0, room))
+            torch.cuda.synchronize()
+            err = capfd.readouterr().err
+            print(prob, layout, mode, room, offset, err, flush=True)
+            assert "three filter rows" in err or room != full or offset, err      # (with less room another kernel may be chosen)
+            assert torch.isnan(ws[(room + offset + 3) // 4:]).all()       # (nothing beyond the room lent)
+            want = oc.conv_backward_filter(x, dy, (R, S), pad=pad, stride=stride, mode=mode, alpha=alpha, beta=beta, dw_old=old if beta else None)
+            got = dw.cpu().numpy()
+            assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
+            if beta == 0.0:
+                assert np.linalg.norm(got - want) <= (1.5e-7 + 1.3e-8 * (dy.size / K) ** 0.5) * np.linalg.norm(want)
