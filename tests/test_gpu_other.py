@@ -257,9 +257,10 @@ def test_backward_bias():
 
 @pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
 @pytest.mark.parametrize("shape, win, pad", [
-    # stride 2, 512 planes and more: the kernel that walks down rows of 2 x 2 cells
-    ((8, 64, 55, 55), 3, 0), ((4, 128, 9, 127), 3, 1), ((4, 130, 70, 128), 2, 1), ((2, 256, 40, 126), 3, 2), ((8, 65, 1, 1), 2, 1),
-    ((8, 64, 2, 3), 3, 2), ((16, 32, 7, 6), 3, 1), ((2, 64, 112, 112), 3, 0), ((2, 64, 75, 117), 3, 1), ((8, 64, 33, 31), 2, 0), ((4, 129, 34, 20), 3, 0), ((8, 64, 10, 12), 3, 0)])
+    # stride 2, 4096 planes or (more than 48 rows) 512 strips and more: the kernel that walks down rows of 2 x 2 cells
+    ((8, 64, 55, 55), 3, 0), ((32, 130, 9, 127), 3, 1), ((4, 130, 70, 128), 2, 1), ((32, 130, 12, 126), 3, 2), ((64, 65, 1, 1), 2, 1),
+    ((64, 64, 2, 3), 3, 2), ((32, 129, 7, 6), 3, 1), ((2, 64, 112, 112), 3, 0), ((2, 64, 75, 117), 3, 1), ((32, 128, 13, 31), 2, 0),
+    ((8, 129, 66, 20), 3, 0), ((64, 64, 10, 12), 3, 0)])
 def test_pooling_backward_cells(shape, win, pad, mode):
     """Against the oracle, and bit for bit against the kernels for rows with a pitch, infinities and NaN included."""
     import torch
