@@ -862,23 +862,38 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
                 b_voff[i] = ok ? (n * (uint32_t)p.xsN + h * (uint32_t)p.xsH + w * (uint32_t)p.xsW) * 4u : kOutOfRange;
             }
         };
-        // request item i of the patch of block cb
-        auto request_b = [&](auto set_c, int i, uint32_t cb) __attribute__((always_inline)) {
-            constexpr int set = decltype(set_c)::value;
-            const uint32_t c = cb * 16u + (uint32_t)((3 * i + mw) % 2 * 8);
-            // (beyond the last channel, where the filter is zero, the last one again - channel-fastest: the last four)
-            auto channel = [&](uint32_t k, uint32_t last) { return k < last ? k : last; };
-            if constexpr (Cfg::NHWC) {
+        // Offsets of the channels that the even (odd) items of block cb have: one set for all of them, worked out when their turn comes.
+        // (Per load they took three scalar instructions and, kept for both halves, moves out of spilled registers, 350 of 1150 instructions per chunk:
+        // 384x13x13 -> 256, 128 images, 143 -> 134 us, 64x56x56 -> 64, 3x3, backward data 110.5 -> 109.5.  Channel-fastest, two loads per item, that gains nothing.)
+        struct Channels { uint32_t off[8]; };
+        auto channels_of = [&](uint32_t cb, int odd) __attribute__((always_inline)) {
+            Channels r = {};
+            if constexpr (!Cfg::NHWC) {
+                const uint32_t c = cb * 16u + (uint32_t)((odd + mw) % 2 * 8);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xbuf, b_voff[i], channel(c + (uint32_t)e * 4u, (uint32_t)p.C - 4u) * 4u, 0));
+                for (int e = 0; e < 8; ++e) {   // (beyond the last channel, where the filter is zero, the last one again)
+                    const uint32_t k = c + (uint32_t)e < (uint32_t)p.C - 1u ? c + (uint32_t)e : (uint32_t)p.C - 1u;
+                    r.off[e] = k * (uint32_t)p.xsC * 4u;
+                }
+            }
+            return r;
+        };
+        // request item i of the patch of block cb
+        auto request_b = [&](auto set_c, int i, uint32_t cb, const Channels &ch) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            if constexpr (Cfg::NHWC) {
+                const uint32_t c = cb * 16u + (uint32_t)((3 * i + mw) % 2 * 8);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {   // (beyond the last channel the last four again)
+                    const uint32_t k = c + (uint32_t)e * 4u < (uint32_t)p.C - 4u ? c + (uint32_t)e * 4u : (uint32_t)p.C - 4u;
+                    const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xbuf, b_voff[i], k * 4u, 0));
 #pragma unroll
                     for (int q = 0; q < 4; ++q) b_reg[set][i][e * 4 + q] = v[q];
                 }
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    b_reg[set][i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, b_voff[i], channel(c + (uint32_t)e, (uint32_t)p.C - 1u) * (uint32_t)p.xsC * 4u, 0));
+                    b_reg[set][i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xbuf, b_voff[i], ch.off[e], 0));
             }
         };
         // split item i and write it into the stage at byte offset `stage`
@@ -927,6 +942,18 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         // where the chunk being written and the block being requested are
         int it = 0, cb = 0, g = 0;
         int b_it = 0, b_cb = 0;
+        // f(item, its channels): the even items, then the odd ones; channel-fastest, where two items in a row read the same pixels' lines, as they come
+        auto in_order = [&](auto f) __attribute__((always_inline)) {
+            if constexpr (Cfg::NHWC) {
+                static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) { f(ic, Channels{}); });
+            } else {
+                static_for<2>([&](auto oc) __attribute__((always_inline)) {
+                    constexpr int odd = decltype(oc)::value;
+                    const Channels ch = channels_of((uint32_t)b_cb, odd);
+                    static_for<(ITEMS + 1 - odd) / 2>([&](auto ic) __attribute__((always_inline)) { f(std::integral_constant<int, decltype(ic)::value * 2 + odd>{}, ch); });
+                });
+            }
+        };
         // (past the last tile the last one's operands are requested again; nothing of them is multiplied)
         auto next_block = [&]() {
             if (++b_cb == nch) {
@@ -986,15 +1013,17 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
                     if (cb == nch - 1) lossy_b = far_b = 0;   // (from here on the next tile's)
                     scale_patch((n_block + 1) & 1);
                 }
-                if constexpr (j > 0 && block_end)
+                if constexpr (j > 0 && block_end) {
+                    const Channels ch = channels_of((uint32_t)b_cb, j - 1);
                     static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
                         constexpr int i = decltype(ic)::value;
                         if constexpr (i % 2 == j - 1) {
                             if (3 * i + mw < held[0]) convert_b(Blk{}, i, Cfg::B_STAGE - stage);
-                            request_b(Blk{}, i, (uint32_t)b_cb);
+                            request_b(Blk{}, i, (uint32_t)b_cb, ch);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     });
+                }
                 if constexpr (j == 0 && block_end) look_at_patch(Blk{}, (n_block + 1) & 1);
                 split_barrier();
             });
@@ -1017,10 +1046,10 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             e_patch = sb.e;
             publish_scale(cb == 0);
             if (cb == nch - 1) publish_lossy();
-            static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) {
+            in_order([&](auto ic, const Channels &ch) __attribute__((always_inline)) {
                 constexpr int i = decltype(ic)::value;
                 if (3 * i + mw < held[0]) convert_b(par_c, i, par * Cfg::B_STAGE);
-                request_b(par_c, i, (uint32_t)b_cb);
+                request_b(par_c, i, (uint32_t)b_cb, ch);
                 __builtin_amdgcn_sched_barrier(0);
             });
             held[0] = held[SETS - 1];
@@ -1034,7 +1063,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         using S0 = std::integral_constant<int, 0>;
         auto request_patch = [&](auto set_c, int h) __attribute__((always_inline)) {
             held[h] = items;
-            static_for<ITEMS>([&](auto ic) __attribute__((always_inline)) { request_b(set_c, decltype(ic)::value, (uint32_t)b_cb); });
+            in_order([&](auto ic, const Channels &ch) __attribute__((always_inline)) { request_b(set_c, decltype(ic)::value, (uint32_t)b_cb, ch); });
             next_block();
         };
         if (lane == 0 && mw == 0)   // (the unused fourth wavefront's)
