@@ -9,11 +9,11 @@
 //    (a tensor packed N,H,W,C whose C divides a workgroup's round of 16-byte loads is read as one run of elements, 16
 //    bytes per thread and load);
 //  * any other layout: a workgroup takes one feature map and a range of the N*(H*W) positions, threads along the
-//    flattened (h,w) index (consecutive addresses when w has unit stride).
+//    flattened (h,w) index (consecutive addresses when w has unit stride), on 16 bytes each where the maps are runs.
 // Every thread adds in double, whatever dy's type (float, bfloat16 or double): a map of 400 000 pixels would otherwise
 // lose the digits the parity bound asks for.  The threads' sums are added through LDS in a fixed order.  With a lent
 // workspace the positions are cut into ranges across workgroups, one double per (range, feature map), and a second
-// kernel adds the ranges in order; without, one workgroup per (group of) feature map(s) does it all.  Deterministic
+// kernel adds the ranges in order; without, or where that is no slower (in_one_piece), one workgroup per (group of) feature map(s) does it all.  Deterministic
 // either way; nothing is allocated.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -36,7 +36,8 @@ struct BiasGradArgs {
     uint32_t HW, positions;       // H*W, N*H*W
     Magic mHW, mW;
     uint32_t runs;                // 1 when a feature map is one run of H*W elements (w-stride 1, h-stride W)
-    uint32_t HWv;                 // H*W in 16-byte vectors (feature maps stored as runs: the vector form below)
+    // feature maps stored as runs, the vector form below: 16-byte vectors of a run, what it has beyond them, vectors of a map and of a range
+    uint32_t HWv, tail, vectors, perv;
     Magic mHWv;
     uint32_t sN, sC, sH, sW;      // element strides of dy
     uint32_t per;                 // positions per range
@@ -189,25 +190,26 @@ __global__ __launch_bounds__(256) void bias_grad_map_kernel(const BiasGradArgs a
     if (threadIdx.x == 0) finish<OUT>(a, c, range, sums[0]);
 }
 
-// feature maps stored as runs (w-stride 1, h-stride W), H*W and the strides of n and c whole 16-byte vectors, dy on a
-// 16-byte boundary: as above with a thread on 16 bytes of its feature map at a time - one division per 16 bytes
-// instead of two per element, eight loads requested before they are added
-template <class T, class OUT>
-__global__ __launch_bounds__(256) void bias_grad_map_vectors_kernel(const BiasGradArgs a) {
+// feature maps stored as runs (w-stride 1, h-stride W) that begin on 4-byte boundaries, all a 16-byte load asks for: as above with a thread on
+// 16 bytes of its feature map at a time - one division per 16 bytes instead of two per element, eight loads requested before they
+// are added.  What is left of each run goes one by one, in the map's last range.  (64x96x55x55, whose maps are no whole vectors,
+// element by element: 17.1 us, so 15.0 and in one piece 13.5.)  A range has 256 threads, a map in one piece 1024.
+template <class T, class OUT, int THREADS>
+__global__ __launch_bounds__(THREADS) void bias_grad_map_vectors_kernel(const BiasGradArgs a) {
     constexpr int V = Pack<T>::V;
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    __shared__ double sums[256];
+    __shared__ double sums[THREADS];
     const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.dy), 0, a.dy_bytes, 0x00020000u);
     const int c = (int)blockIdx.x, range = (int)blockIdx.y;
-    const uint32_t perv = a.per / (uint32_t)V, total = a.positions / (uint32_t)V;   // (the host made `per` a multiple of V)
-    const uint32_t begin = (uint32_t)range * perv, end = begin + perv < total ? begin + perv : total;
+    const uint32_t total = a.vectors;
+    const uint32_t begin = (uint32_t)range * a.perv, end = begin + a.perv < total ? begin + a.perv : total;
     const uint32_t cbase = (uint32_t)c * a.sC;
     double sum = 0.0;
-    for (uint32_t i0 = begin + threadIdx.x; i0 < end; i0 += 8u * 256u) {
+    for (uint32_t i0 = begin + threadIdx.x; i0 < end; i0 += 8u * THREADS) {
         u32x4_t q[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint32_t i = i0 + (uint32_t)j * 256u;
+            const uint32_t i = i0 + (uint32_t)j * THREADS;
             const uint32_t n = mdiv(i, a.mHWv), rem = i - n * a.HWv;
             const uint32_t off = (n * a.sN + cbase + rem * (uint32_t)V) * (uint32_t)sizeof(T);
             q[j] = __builtin_amdgcn_raw_buffer_load_b128(buf, i < end ? off : 0x80000000u, 0, 0);   // (past the end: zeros)
@@ -237,9 +239,16 @@ __global__ __launch_bounds__(256) void bias_grad_map_vectors_kernel(const BiasGr
             }
         }
     }
+    if (a.tail != 0u && range == a.ranges - 1) {
+        const uint32_t left = a.positions / a.HW * a.tail;
+        for (uint32_t i = threadIdx.x; i < left; i += THREADS) {
+            const uint32_t n = i / a.tail;
+            sum += load_as_double<T>(buf, n * a.sN + cbase + a.HW - a.tail + (i - n * a.tail));
+        }
+    }
     sums[threadIdx.x] = sum;
     __syncthreads();
-    for (int width = 128; width > 0; width >>= 1) {   // (a fixed tree: the same order every time)
+    for (int width = THREADS / 2; width > 0; width >>= 1) {   // (a fixed tree: the same order every time)
         if ((int)threadIdx.x < width) sums[threadIdx.x] += sums[threadIdx.x + width];
         __syncthreads();
     }
@@ -275,10 +284,19 @@ struct BiasGradPlan {
     BiasGradArgs a;
     bool packed;     // dy is one run of positions * C elements and the workgroup's round holds whole multiples of C
     bool channels;   // dy has unit channel stride
-    bool vectors;    // feature maps are runs of whole 16-byte vectors
+    bool vectors;    // feature maps are runs, each from a 4-byte boundary on, long or of whole 16-byte vectors
     bool f64;
     igcDataType in;
 };
+
+// A map in one piece, one workgroup of 1024 threads each, and no second launch?  Measured, us, ranges and their sum -> one piece: 128x256x13x13 8.4 -> 4.5,
+// 64x96x55x55 15.0 -> 13.5, 64x256x28x28 11.5 -> 9.4 (bfloat16 7.1 -> 4.5), 8x64x56x56 6.9 -> 4.2, 128x128x56x56 32.1 -> 29.9; where few maps leave
+// compute units idle 18.5 -> 20.9 (128x64x56x56), 6.8 -> 10.6 (64x32x56x56), 11.4 -> 12.0 (double, 32x64x56x56).  A workgroup reads 65 to 85 KB per
+// us, the chip up to 7 MB from the last-level cache; the second launch costs 4.5 us.
+bool in_one_piece(const igcContext *h, const BiasGradArgs &a, long long elem) {
+    const long long map = (long long)a.positions * elem, rounds = (a.C + h->computeUnits - 1) / h->computeUnits;
+    return (double)(map * rounds) / 60e3 <= 4.5 + (double)map * a.C / 7e6;
+}
 
 igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcTensorDescriptor_t dbDesc, BiasGradPlan *pl) {
     if (!dyDesc || !dbDesc) return IGC_STATUS_BAD_PARAM;
@@ -308,10 +326,13 @@ igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcT
     pl->packed = pl->channels && a.C % per16 == 0 && a.C / per16 <= 256 && dyDesc->stride[3] == a.C &&
                  dyDesc->stride[2] == (long long)a.W * a.C && dyDesc->stride[0] == (long long)a.HW * a.C;
     a.runs = dyDesc->stride[3] == 1 && dyDesc->stride[2] == a.W ? 1u : 0u;
-    pl->vectors = !pl->channels && dyDesc->stride[3] == 1 && dyDesc->stride[2] == a.W && a.HW % per16 == 0 &&
-                  dyDesc->stride[0] % per16 == 0 && dyDesc->stride[1] % per16 == 0;
+    // (short runs with something left over stay element by element: 64x512x7x7 3.9 us, with vectors 4.3)
+    pl->vectors = !pl->channels && a.runs != 0u && (a.HW % (uint32_t)per16 == 0 || a.HW >= 128u) &&
+                  (dyDesc->dtype != IGC_DATA_BFLOAT16 || (dyDesc->stride[0] % 2 == 0 && dyDesc->stride[1] % 2 == 0));
     if (pl->vectors) {
         a.HWv = a.HW / (uint32_t)per16;
+        a.tail = a.HW % (uint32_t)per16;
+        a.vectors = (uint32_t)dyDesc->dim[0] * a.HWv;
         if (!magic_for(a.HWv, &a.mHWv)) return IGC_STATUS_NOT_SUPPORTED;
     }
     pl->f64 = f64;
@@ -328,8 +349,13 @@ igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcT
     ranges = std::max<long long>(1, std::min<long long>(ranges, kMaxRanges));
     a.ranges = (int)ranges;
     a.per = (uint32_t)((positions + ranges - 1) / ranges);
-    if (pl->vectors) a.per = (a.per + (uint32_t)per16 - 1u) / (uint32_t)per16 * (uint32_t)per16;   // (whole vectors per range)
     a.ranges = (int)((positions + a.per - 1) / a.per);
+    if (pl->vectors) {
+        if (in_one_piece(h, a, elem_size(dyDesc->dtype))) a.ranges = 1;
+        a.perv = (a.vectors + (uint32_t)a.ranges - 1u) / (uint32_t)a.ranges;
+        a.ranges = (int)((a.vectors + a.perv - 1u) / a.perv);
+        a.per = (uint32_t)((positions + a.ranges - 1) / a.ranges);   // (should dy not be on such a boundary)
+    }
     return IGC_STATUS_SUCCESS;
 }
 
@@ -340,13 +366,14 @@ int launch_bias_grad(const BiasGradPlan &pl, hipStream_t stream) {
     void *argv[] = {&a};
     // (the packed form wants dy itself on a 16-byte boundary)
     const bool packed = pl.packed && (uintptr_t)a.dy % 16 == 0;
-    const bool vectors = pl.vectors && (uintptr_t)a.dy % 16 == 0;
+    const bool vectors = pl.vectors && (uintptr_t)a.dy % 4 == 0, whole = vectors && a.ranges == 1 && a.vectors > 8u * 256u;   // (that much 256 threads request at once)
     const void *kernel = packed ? reinterpret_cast<const void *>(&bias_grad_packed_kernel<T, OUT>)
                                 : (pl.channels ? reinterpret_cast<const void *>(&bias_grad_channels_kernel<T, OUT>)
-                                               : (vectors ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT>)
+                                               : (whole ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, 1024>)
+                                                  : vectors ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, 256>)
                                                           : reinterpret_cast<const void *>(&bias_grad_map_kernel<T, OUT>)));
     const dim3 grid = packed ? dim3(a.ranges) : dim3(pl.channels ? (a.C + 63) / 64 : a.C, a.ranges);
-    if (hipLaunchKernel(kernel, grid, dim3(256), argv, 0, stream) != hipSuccess) return 1;
+    if (hipLaunchKernel(kernel, grid, dim3(whole ? 1024 : 256), argv, 0, stream) != hipSuccess) return 1;
     if (a.ranges > 1) {
         const double *parts = a.parts;
         int ranges = a.ranges, C = a.C;
@@ -395,6 +422,7 @@ igcStatus igcConvolutionBackwardBias(igcHandle_t handle, const void *alpha, igcT
     if (a.ranges > 1 && (!workSpace || (uintptr_t)workSpace % 8 != 0 || workSpaceSizeInBytes < need)) {
         a.ranges = 1;
         a.per = a.positions;
+        a.perv = a.vectors;
     }
     a.parts = static_cast<double *>(workSpace);
     hipStream_t stream = static_cast<hipStream_t>(handle->stream);

@@ -255,6 +255,23 @@ def test_backward_bias():
     assert got[129] == 7.0 and np.count_nonzero(got) == 1
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f64"])
+@pytest.mark.parametrize("shape", [
+    # maps as runs of which 16-byte vectors leave something: in one piece (2240 vectors of float: 1024 threads; 2048 and fewer: 256), in ranges, runs short of 128 and not
+    (40, 300, 15, 15), (64, 8, 8, 16), (65, 8, 8, 16), (64, 2, 82, 41), (3000, 5, 1, 7), (33, 70, 1, 127), (33, 70, 3, 43), (1, 1, 1, 129), (16, 3, 180, 181),
+], ids=str)
+def test_backward_bias_runs(shape, dtype):
+    """Feature maps as runs of any length, whole and every second one of a larger tensor (odd strides), with the workspace and without."""
+    gu = _gpu()
+    big = rnd(sum(shape), shape[0], 2 * shape[1], *shape[2:], lo=-1.0, hi=1.0)
+    big = wl.round_to_bf16(big) if dtype == "bf16" else (big.astype(np.float64) if dtype == "f64" else big)
+    for dy in (np.ascontiguousarray(big[:, ::2]), big[:, 1::2]):
+        print("backward bias", dtype, shape, dy.strides, flush=True)
+        want = po.bias_backward(np.ascontiguousarray(dy))
+        for workspace in ("full", "none"):
+            close(gu.run_backward_bias(dy, dtype=dtype, workspace=workspace), want)
+
+
 @pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
 @pytest.mark.parametrize("shape, win, pad", [
     # stride 2, 4096 planes or (more than 48 rows) 512 strips and more: the kernel that walks down rows of 2 x 2 cells
