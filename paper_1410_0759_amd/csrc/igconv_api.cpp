@@ -317,8 +317,10 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
         // tiles, teams and cut reductions win there.  96x27x27 -> 256, 5x5, 16 images: 128 rows on 184 units 101 us, 64 rows on
         // all twice 124; 64x32x32 -> 128, 9x9, 24 images, 216 tiles of 64 rows: 138, fp32 teams 191; 144 tiles (128x32x32 ->
         // 128, 16 images): 271, fp32 cut 213.  Not offered either for short reductions whose filter cannot be read by 16-byte loads (3x227x227 -> 96,
-        // 11x11, stride 4, 64 images: 107 us at best against 112, with other tiles 125 and 175).
-        if ((ki.BM == 128 ? tiles * 2 < cus : tiles * 3 < cus * 2) || (!ki.veca && steps < 16)) return 1e300;
+        // 11x11, stride 4, 64 images: 107 us at best against 112, with other tiles 125 and 175) - but for a filter whose rows lie next to each
+        // other, backward data of 1x1 layers, from one whole step on: 64x256x14x14 -> 256 29.5 -> 23.4 us, 128x384x13x13 -> 256 56.3 -> 48.6, channels innermost
+        // 75.2 -> 68.7, 37x101x29x31 -> 77 24.3 -> 18.6, 128x96x27x27 -> 32 21.7 -> 20.4.
+        if ((ki.BM == 128 ? tiles * 2 < cus : tiles * 3 < cus * 2) || (!ki.veca && steps < 16 && (k.wsRow != 1 || k.CRS < ki.BK))) return 1e300;
         // At most 32 rows, where the fp32 kernels have a tile of 32: a seventh more, which prefers that tile and not the fp32 kernels
         // with 64 rows.  Measured, split and fp32 kernel of 32 rows: 170x37x37 -> 9, 11x11 630 and 438; 290x120x120 -> 12, 3x3 83 and 62;
         // 82x26x26 -> 10, 7x7, border 219 and 189; of 64 rows: 69x118x83 -> 22, 7x7, border 202 and 260.

@@ -83,6 +83,26 @@ def test_backward_data_phases(prob):
 
 
 @pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, stride, pad: K = 32 and more in three parts (with tiles enough), 31 and fewer with the fp32 instruction
+    (40, 100, 31, 33, 31, 1, 0), (40, 100, 31, 33, 32, 1, 0), (40, 70, 31, 33, 33, 1, 0), (12, 300, 29, 31, 77, 1, 1), (24, 260, 41, 43, 65, 2, 0), (9, 40, 5, 7, 100, 1, 0),
+], ids=str)
+def test_backward_data_of_one_tap(prob, layout):
+    gu = _gpu()
+    N, C, H, W, K, u, pad = prob
+    rng = np.random.default_rng(54)
+    P, Q = oc.output_dim(H, 1, u, pad), oc.output_dim(W, 1, u, pad)
+    dy = wl.with_layout(rng.uniform(-1, 1, size=(N, K, P, Q)).astype(np.float32), layout)
+    w = rng.uniform(-1, 1, size=(K, C, 1, 1)).astype(np.float32)
+    dx0 = rng.uniform(-1, 1, size=(N, C, H, W)).astype(np.float32)
+    for alpha, beta in ((1.0, 0.0), (0.5, -1.5)):
+        print(prob, layout, alpha, beta, flush=True)
+        want = oc.conv_backward_data(dy, w, (H, W), pad=(pad, pad), stride=(u, u), mode=1, alpha=alpha, beta=beta, dx_old=dx0 if beta else None)
+        got = gu.run_backward_data(dy, w, (H, W), (pad, pad), (u, u), 1, alpha, beta, dx0 if beta else None)
+        assert gu.rel_err(got, want) <= gu.BOUND["f32"]
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
 @pytest.mark.parametrize("C", [756, 1200])      # 16 and 24 steps per wavefront
 def test_short_reduction_with_a_workspace(C, layout):
     gu = _gpu()
