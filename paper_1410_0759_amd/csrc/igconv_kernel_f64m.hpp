@@ -21,7 +21,10 @@
 //    of a step orders LDS traffic alone, and every piece of side work sits between two MFMAs
 //    (the order is pinned, as in igconv_kernel.hpp);
 //  * workgroups are persistent and walk the tiles of their XCD's range; the first loads of
-//    the next tile are issued during the last two steps of the current one.
+//    the next tile are issued during the last two steps of the current one;
+//  * a compute unit's time is its number of tiles: where at most half of the units would have one more than the others,
+//    those tiles (p.halvedPerXcd per XCD, the last ones) go as two halves of 32 columns, a block of 16 per
+//    wavefront instead of two - the loads of a step for half of its MFMAs, on a unit's idle quarter.
 //
 // Tile BM x BN x 16, 256 threads = 2 x 2 wavefronts, each with (BM/32) x (BN/32) blocks of
 // 16 x 16.  LDS rows are [row][k], 16 doubles plus 16 bytes: lane (l16, lq) of a wavefront
@@ -50,7 +53,7 @@ struct F64mConfig {
     static constexpr int CG = BN / 64, KPARTS = 4 / CG, KPT = BK / KPARTS;
     // waves per SIMD the registers must allow: four workgroups of the small tile per compute unit, two of the others
     static constexpr int MIN_WAVES = BM * BN <= 64 * 64 ? 4 : 2;
-    static_assert(BM % 32 == 0 && (BN == 64 || BN == 128), "tile shapes");
+    static_assert(BM % 32 == 0 && BN == 64, "tile shapes");
     static_assert(LDS_BYTES * MIN_WAVES <= 160 * 1024, "LDS budget");
 };
 
@@ -75,13 +78,17 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
     const int wg_xcd = (int)(blockIdx.x % 8u), wg_local = (int)(blockIdx.x / 8u);
     const int tiles_mn = p.tilesM * p.tilesN;
     const int tiles_total = tiles_mn * p.splits;
-    auto tile_number = [&](int i) {
-        const int local = wg_local + i * p.wgsPerXcd;
-        const int t = wg_xcd * p.tilesPerXcd + local;
-        return local < p.tilesPerXcd && t < tiles_total ? t : tiles_total;
+    // work item: four times the tile, and 0 (all of it), 1 or 2 (its left or right half); none: 4 * tiles_total
+    const int whole_tiles = p.tilesPerXcd - p.halvedPerXcd;
+    auto work_number = [&](int i) {
+        const int local = wg_local + i * p.wgsPerXcd, past = local - whole_tiles;
+        const int t = wg_xcd * p.tilesPerXcd + (past < 0 ? local : whole_tiles + past / 2);
+        const bool some = past < 2 * p.halvedPerXcd && t < tiles_total;
+        return some ? t * 4 + (past < 0 ? 0 : 1 + past % 2) : tiles_total * 4;
     };
-    if (tile_number(0) >= tiles_total) return;
+    if (work_number(0) >= tiles_total * 4) return;
     int m0 = 0, n0 = 0, split = 0, t_begin = 0;
+    bool halved = false;
 
     const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.x), 0, p.x_bytes, kBufferWord3);
     const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.w), 0, p.w_bytes, kBufferWord3);
@@ -98,7 +105,7 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
     for (int r = 0; r < p.R; ++r) ms_row_bits |= 1ull << (r * p.S);
     auto setup_column = [&]() {
         const int j = n0 + jl;
-        const bool cv = j < p.NPQ;
+        const bool cv = j < p.NPQ && !(halved && jl >= BN / 2);
         const uint32_t jj = cv ? (uint32_t)j : 0u;
         const uint32_t n = magic_div(jj, p.mPQ);
         const uint32_t rem = jj - n * (uint32_t)p.PQ;
@@ -137,14 +144,16 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
                 a_voff[ps] = (uint32_t)(row < p.K ? row : 0) * (uint32_t)p.wsRow * ES;
         }
     };
-    auto setup_tile = [&](int tile) {
+    auto setup_tile = [&](int work) {
+        int tile = work >> 2;
+        halved = (work & 3) != 0;
         if (p.splits > 1) {
             split = tile / tiles_mn;
             tile -= split * tiles_mn;
             t_begin = split * p.stepsPerSplit;
         }
         m0 = (tile % p.tilesM) * BM;
-        n0 = (tile / p.tilesM) * BN;
+        n0 = (tile / p.tilesM) * BN + ((work & 3) == 2 ? BN / 2 : 0);
         setup_column();
         setup_rows();
     };
@@ -267,17 +276,20 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
     const int wm = wave % Cfg::WM;
     const int wn = wave / Cfg::WM;
     f64x4m acc[MB][NB];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f64x4m{0.0, 0.0, 0.0, 0.0};
+            for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f64x4m{0.0, 0.0, 0.0, 0.0};
+    };
 
     constexpr int G = 2;                    // k-groups of 8 per step
     constexpr int MPG = 2 * MB * NB;        // MFMAs per group
     constexpr int NM = G * MPG, SB = NM - MPG;
     u32x4 fragA[2][MB], fragB[2][NB];
     const int fa_off = (wm * Cfg::TM + l16) * LD + lq * 2;
-    const int fb_off = (wn * Cfg::TN + l16) * LD + lq * 2;
+    // (columns of a wavefront: TN, of half a tile TN / 2)
+    int fb_off = (wn * Cfg::TN + l16) * LD + lq * 2;
     auto read_frags = [&](int buf, int g, int fs) {
         const double *const A = ldsA + buf * Cfg::A_ELEMS + fa_off + g * 8;
         const double *const B = ldsB + buf * Cfg::B_ELEMS + fb_off + g * 8;
@@ -302,7 +314,8 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
     // item per MFMA, and step t+1, requested a step earlier into the other set, is written to the other stage in the
     // slots just before the barrier, which sits before the last k-group; after it the first fragments of step t+1
     // are read.  Steps beyond the last read zeros, so no step is special.
-    auto step = [&](auto parity, int k2) __attribute__((always_inline)) {
+    auto step = [&](auto parity, auto half_c, int k2) __attribute__((always_inline)) {
+        constexpr bool half = decltype(half_c)::value;   // (the first half of the blocks of columns alone)
         constexpr int cur = decltype(parity)::value, nxt = cur ^ 1;
         static_for<NM>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
@@ -322,63 +335,74 @@ __global__ __launch_bounds__(256, Cfg::MIN_WAVES) void igconv_f64m_kernel(const 
                 constexpr int w0 = (q * NW + WS - 1) / WS, w1 = ((q + 1) * NW + WS - 1) / WS;
                 static_for<w1 - w0>([&](auto ic) { write_item(w0 + decltype(ic)::value, nxt, nxt); });
             }
-            mfma(fs, j);
+            if constexpr (!half || j % NB < NB / 2) mfma(fs, j);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
     const int nsteps = p.stepsPerSplit;   // (even; the host rounds an odd number of steps up)
-    setup_tile(tile_number(0));
-    static_for<NL>([&](auto ic) { load_item(decltype(ic)::value, 0, t_begin); });
-    static_for<NL>([&](auto ic) { load_item(decltype(ic)::value, 1, t_begin + 1); });
-    static_for<NW>([&](auto ic) { write_item(decltype(ic)::value, 0, 0); });
-    lds_barrier();
-    read_frags(0, 0, 0);
-    // (enter the loop with no load outstanding: otherwise the compiler, merging this path with the loop's back
-    // edge, waits for every load at the top of each step)
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __builtin_amdgcn_sched_barrier(0);
     const double alpha = p.alpha64, beta = p.beta64;
-    for (int it = 1;; ++it) {
-        for (int t = 2; t < nsteps; t += 2) {
-            step(std::integral_constant<int, 0>{}, t_begin + t);
-            step(std::integral_constant<int, 1>{}, t_begin + t + 1);
+    int it = 0, work = work_number(0);
+    // the tiles of one kind, whole or halved (which come last), from `work` on
+    auto run = [&](auto half_c) __attribute__((always_inline)) {
+        constexpr bool half = decltype(half_c)::value;
+        if constexpr (half) fb_off = (wn * (Cfg::TN / 2) + l16) * LD + lq * 2;
+        setup_tile(work);
+        static_for<NL>([&](auto ic) { load_item(decltype(ic)::value, 0, t_begin); });
+        static_for<NL>([&](auto ic) { load_item(decltype(ic)::value, 1, t_begin + 1); });
+        static_for<NW>([&](auto ic) { write_item(decltype(ic)::value, 0, 0); });
+        lds_barrier();
+        read_frags(0, 0, 0);
+        // (enter the loop with no load outstanding: otherwise the compiler, merging this path with the loop's back
+        // edge, waits for every load at the top of each step)
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        clear();
+        for (;;) {
+            for (int t = 2; t < nsteps; t += 2) {
+                step(std::integral_constant<int, 0>{}, half_c, t_begin + t);
+                step(std::integral_constant<int, 1>{}, half_c, t_begin + t + 1);
+            }
+            // the last two steps of this tile request the first two of the workgroup's next tile (of "no tile", whose
+            // columns lie beyond the end, after the last one; of its first half tile in vain, run(true) begins anew)
+            const int out_m0 = m0, out_n0 = n0, out_split = split;
+            const int next = work_number(++it);
+            setup_tile(next);
+            step(std::integral_constant<int, 0>{}, half_c, t_begin);
+            step(std::integral_constant<int, 1>{}, half_c, t_begin + 1);
+            // epilogue: value v of block (mb, nb) in lane (l16, lq) is row 4*v + lq, column l16 of the block
+            const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(
+                static_cast<char *>(p.y) + (size_t)out_split * p.ySplitBytes, 0, p.y_bytes, kBufferWord3);
+            static_for<half ? NB / 2 : NB>([&](auto nbc) __attribute__((always_inline)) {
+                constexpr int nb = decltype(nbc)::value;
+                const int col = out_n0 + wn * (half ? Cfg::TN / 2 : Cfg::TN) + nb * 16 + l16;
+                const bool cv = col < p.NPQ;
+                const uint32_t cc = cv ? (uint32_t)col : 0u;
+                const uint32_t j0 = magic_div(cc, p.mPQ), rem = cc - j0 * (uint32_t)p.PQ;
+                const uint32_t j1 = magic_div(rem, p.mQ), j2 = rem - j1 * (uint32_t)p.Q;
+                const uint32_t ycol = j0 * (uint32_t)p.ysN + j1 * (uint32_t)p.ysP + j2 * (uint32_t)p.ysQ;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = out_m0 + wm * Cfg::TM + mb * 16 + 4 * v + lq;
+                        const uint32_t off = cv && row < p.K ? (ycol + (uint32_t)row * (uint32_t)p.ysK) * ES : kOutOfRange;
+                        double r = alpha * acc[mb][nb][v];
+                        if (beta != 0.0) r += beta * __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ybuf, off, 0, 0));
+                        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), ybuf, off, 0, 0);
+                    }
+            });
+            work = next;
+            if (next >= tiles_total * 4 || halved != half) break;
+            clear();
         }
-        // the last two steps of this tile request the first two of the workgroup's next tile (of "no tile", whose
-        // columns lie beyond the end, after the last one)
-        const int out_m0 = m0, out_n0 = n0, out_split = split;
-        const int next = tile_number(it);
-        setup_tile(next);
-        step(std::integral_constant<int, 0>{}, t_begin);
-        step(std::integral_constant<int, 1>{}, t_begin + 1);
-        // epilogue: value v of block (mb, nb) in lane (l16, lq) is row 4*v + lq, column l16 of the block
-        const __amdgpu_buffer_rsrc_t ybuf = __builtin_amdgcn_make_buffer_rsrc(
-            static_cast<char *>(p.y) + (size_t)out_split * p.ySplitBytes, 0, p.y_bytes, kBufferWord3);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int col = out_n0 + wn * Cfg::TN + nb * 16 + l16;
-            const bool cv = col < p.NPQ;
-            const uint32_t cc = cv ? (uint32_t)col : 0u;
-            const uint32_t j0 = magic_div(cc, p.mPQ), rem = cc - j0 * (uint32_t)p.PQ;
-            const uint32_t j1 = magic_div(rem, p.mQ), j2 = rem - j1 * (uint32_t)p.Q;
-            const uint32_t ycol = j0 * (uint32_t)p.ysN + j1 * (uint32_t)p.ysP + j2 * (uint32_t)p.ysQ;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = out_m0 + wm * Cfg::TM + mb * 16 + 4 * v + lq;
-                    const uint32_t off = cv && row < p.K ? (ycol + (uint32_t)row * (uint32_t)p.ysK) * ES : kOutOfRange;
-                    double r = alpha * acc[mb][nb][v];
-                    if (beta != 0.0) r += beta * __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ybuf, off, 0, 0));
-                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), ybuf, off, 0, 0);
-                }
-        }
-        if (next >= tiles_total) break;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f64x4m{0.0, 0.0, 0.0, 0.0};
+    };
+    if (work % 4 == 0) {
+        run(std::false_type{});
+        if (work >= tiles_total * 4) return;
+        lds_barrier();
     }
+    run(std::true_type{});
 #endif
 }
 
