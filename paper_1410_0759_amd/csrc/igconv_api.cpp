@@ -530,11 +530,12 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
         k.tail_step = k.ksteps - 1;
     k.wgsPerXcd = workgroups_per_xcd(h, ki, k.tilesPerXcd);
     k.halvedPerXcd = 0;
-    // Double precision: the tiles that would make one more on at most half of the compute units go as two halves of their columns (igconv_kernel_f64m.hpp).
-    // us, whole tiles -> this: 64x56x56 -> 64, 3x3, 32 images (six tiles per unit and four left per 32 units) forward 129.6 -> 124.6, backward data 137.5 -> 133,
+    // The tiles that would make one more on at most half of the compute units go as two halves of their columns: double precision
+    // (igconv_kernel_f64m.hpp) and float with more than nine taps (igconv_kernel_f32h.hpp, with what it measured).
+    // us, whole tiles -> this, double: 64x56x56 -> 64, 3x3, 32 images (six tiles per unit and four left per 32 units) forward 129.6 -> 124.6, backward data 137.5 -> 133,
     // 64 images 239 -> 232, 64x28x28, 64 images 79 -> 73; fewer tiles than units: 64x30x30 -> 64, 9 images 25.6 -> 19.6, 256x14x14 -> 256, 2 images 87 -> 62,
     // 96x27x27 -> 256, 5x5, 3 images, backward data 259 -> 191.  With more left than half of the units some would have two halves: level.
-    if (ki.f64 && ki.gmode == 14) {
+    if ((ki.f64 && ki.gmode == 14) || ki.variant == 8) {
         const int cus = std::max(1, h->computeUnits / kXcds), left = k.tilesPerXcd % cus;
         if (left * 2 <= cus) k.halvedPerXcd = left;
         k.wgsPerXcd = workgroups_per_xcd(h, ki, k.tilesPerXcd + k.halvedPerXcd);

@@ -50,6 +50,9 @@
 //     every other item (steps 1 and 2), requesting the same item of the block after (nine taps: of the one after that, so
 //     that its loads have four steps to arrive);
 //   multipliers run one step behind: they pass the barrier that ends step q + 1 in the middle of step q's last tap.
+// Where at most half of the compute units would have a tile more than the others, those tiles go as two halves of 128 columns (more than
+// nine taps), a block of 32 columns per wavefront instead of two: 96x64x64 -> 128, 9x9, 32 images (784 tiles on 256 units) 570 -> 533 us, channels
+// innermost 571 -> 537; 48x40x40 -> 60, 5x5, 100 images level.  (Nine taps: a chunk of half a tile takes nearly as long, 64x56x56 -> 64 with tanh 120 -> 124.)
 // LDS: filter [stage][tap of 3][part][half][row][8 channels], patch [stage][part][half][pixel][8 channels]: a fragment is
 // 32 neighbouring 16-byte pieces per half wavefront, and a tap a distance the same for all lanes.
 #ifndef IGCONV_KERNEL_F32H_HPP_
@@ -266,6 +269,7 @@ template <int BM_, int BN_, int WM_, int WN_, int PIX_, bool NHWC_, int SETS_, b
 struct HalvesPatchConfig {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, PIX = PIX_, SETS = SETS_;
     static constexpr bool NHWC = NHWC_, SWAP = NHWC_, WHOLE = WHOLE_;
+    static constexpr bool HALVES = SETS == 1;   // the last tiles may go as halves
     static constexpr int THREADS = 512, BK = 144, MOVERS = 3;
     static constexpr int A_PLANE = BM * 16, A_PART = 2 * A_PLANE, A_TAP = 2 * A_PART, A_STAGE = (WHOLE ? 9 : 3) * A_TAP;
     static constexpr int B_PLANE = PIX * 16, B_PART = 2 * B_PLANE, B_STAGE = 2 * B_PART;
@@ -748,18 +752,29 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
     // persistent workgroups, tiles numbered in contiguous ranges per XCD (see igconv_kernel.hpp)
     const int wg_xcd = (int)(blockIdx.x % 8u), wg_local = (int)(blockIdx.x / 8u);
     const int tiles_total = p.tilesM * p.tilesN;
-    auto tile_number = [&](int i) {
+    // Work item: the tile; with HALVES four times the tile, and 0 - all of it -, 1 or 2 - its left or right half.  (The last p.halvedPerXcd tiles of an
+    // XCD's range, which would be one more for some of the compute units, go as halves: see the head of the file.)
+    constexpr int PARTS = Cfg::HALVES ? 4 : 1;
+    const int none = Cfg::HALVES ? tiles_total * 4 : tiles_total;
+    auto work_number = [&](int i) {
         const int local = wg_local + i * p.wgsPerXcd;
-        const int t = wg_xcd * p.tilesPerXcd + local;
-        return local < p.tilesPerXcd && t < tiles_total ? t : tiles_total;
+        if constexpr (Cfg::HALVES) {
+            const int whole_tiles = p.tilesPerXcd - p.halvedPerXcd, past = local - whole_tiles;
+            const int t = wg_xcd * p.tilesPerXcd + (past < 0 ? local : whole_tiles + past / 2);
+            return past < 2 * p.halvedPerXcd && t < tiles_total ? t * 4 + (past < 0 ? 0 : 1 + past % 2) : none;
+        } else {
+            const int t = wg_xcd * p.tilesPerXcd + local;
+            return local < p.tilesPerXcd && t < tiles_total ? t : tiles_total;
+        }
     };
-    if (tile_number(0) >= tiles_total) return;
+    if (work_number(0) >= none) return;
     const int groups = (p.RS + 8) / 9;            // of nine taps
     const int nch = (p.C + 15) / 16;              // blocks of 16 channels; the split filter is zero beyond the last channel
     auto first_tap = [&](int g) { return halves_first_tap(g, p.RS); };
-    // columns of a tile: [first, end); where an image's pixels are tiled by themselves its last tile is cut short
-    auto tile_columns = [&](int tile, int *first, int *end) {
-        const int tn = tile / p.tilesM;
+    // columns of a work item: [first, end); where an image's pixels are tiled by themselves its last tile is cut short.  (A right half with none:
+    // the last column, of which nothing is stored.)
+    auto work_columns = [&](int work, int *first, int *end) {
+        const int tn = work / PARTS / p.tilesM, part = work % PARTS;
         if (p.imageTiles == 0) {
             *first = tn * BN;
             *end = p.NPQ;
@@ -768,6 +783,13 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             *first = image * p.PQ + (tn - image * p.imageTiles) * BN;
             *end = (image + 1) * p.PQ;
         }
+        bool some = true;
+        if (part == 1) *end = *end < *first + BN / 2 ? *end : *first + BN / 2;
+        if (part == 2) {
+            some = *first + BN / 2 < *end;
+            *first = some ? *first + BN / 2 : *end - 1;
+        }
+        return some;
     };
     // first pixel of column j's window as a flat index into the zero-extended images
     auto window_start = [&](uint32_t j) {
@@ -780,7 +802,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
 
     const int chunks = nch * groups;
     int rem = 0;
-    for (int i = 0; tile_number(i) < tiles_total; ++i) rem += chunks;   // chunks of all tiles of this workgroup
+    for (int i = 0; work_number(i) < none; ++i) rem += chunks;   // chunks of all tiles of this workgroup
 
     if (wave == 4) {
         // ================================ filter ================================
@@ -789,7 +811,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         const uint32_t voff = (uint32_t)lane * 16u;
         constexpr int STEPS = Cfg::WHOLE ? 1 : 3;
         int it = 0, left = chunks * STEPS;   // of the step to be requested: tile, steps of it that are left
-        uint32_t from = (uint32_t)(tile_number(0) % p.tilesM) * block_bytes;
+        uint32_t from = (uint32_t)(work_number(0) / PARTS % p.tilesM) * block_bytes;
         auto request = [&](auto stage_c) __attribute__((always_inline)) {
             uint8_t *const dst = lds + decltype(stage_c)::value * Cfg::A_STAGE;
 #pragma unroll
@@ -798,8 +820,8 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
             from += Cfg::A_STAGE;
             if (--left == 0) {   // (past the last tile: its first steps again; nothing of them is multiplied)
                 left = chunks * STEPS;
-                const int next = tile_number(++it);
-                from = next < tiles_total ? (uint32_t)(next % p.tilesM) * block_bytes : 0u;
+                const int next = work_number(++it);
+                from = next < none ? (uint32_t)(next / PARTS % p.tilesM) * block_bytes : 0u;
             }
         };
         if constexpr (Cfg::WHOLE) {
@@ -842,9 +864,9 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         float b_reg[SETS][ITEMS][8];
         int items = 0, held[SETS];   // items of the block to be requested, of those in registers, next one first
 
-        auto setup_patch = [&](int tile) {
+        auto setup_patch = [&](int work) {
             int n0, n_end;
-            tile_columns(tile, &n0, &n_end);
+            work_columns(work, &n0, &n_end);
             const uint32_t g_first = __builtin_amdgcn_readfirstlane(window_start((uint32_t)n0));
             const int j_last = n0 + BN - 1 < n_end ? n0 + BN - 1 : n_end - 1;
             const uint32_t g_end = __builtin_amdgcn_readfirstlane(window_start((uint32_t)j_last)) +
@@ -958,14 +980,14 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         auto next_block = [&]() {
             if (++b_cb == nch) {
                 b_cb = 0;
-                if (tile_number(++b_it) < tiles_total) setup_patch(tile_number(b_it));
+                if (work_number(++b_it) < none) setup_patch(work_number(b_it));
             }
         };
         int e_patch;                 // exponent of the block being multiplied
         int stage = 0;               // byte offset of its patch's stage
         uint32_t n_chunk = 0;        // chunks so far
         int n_block = 0;             // blocks so far
-        uint32_t entry = (uint32_t)(tile_number(0) % p.tilesM) * (uint32_t)chunks;   // this chunk's in the table
+        uint32_t entry = (uint32_t)(work_number(0) / PARTS % p.tilesM) * (uint32_t)chunks;   // this chunk's in the table
         auto publish_scale = [&](bool tile_begins) __attribute__((always_inline)) {   // the chunk's, for the multipliers
             if (mw == 0) {
                 const uint64_t t = table[entry];   // HalvesChunk
@@ -992,8 +1014,8 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
                 g = 0;
                 if (++cb == nch) {
                     cb = 0;
-                    const int next = tile_number(++it);
-                    entry = next < tiles_total ? (uint32_t)(next % p.tilesM) * (uint32_t)chunks : 0u;
+                    const int next = work_number(++it);
+                    entry = next < none ? (uint32_t)(next / PARTS % p.tilesM) * (uint32_t)chunks : 0u;
                 }
             }
         };
@@ -1069,7 +1091,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         if (lane == 0 && mw == 0)   // (the unused fourth wavefront's)
             for (int i = 0; i < 2; ++i)
                 *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_B + i * 16 + 12) = 0u;
-        setup_patch(tile_number(0));
+        setup_patch(work_number(0));
         request_patch(S0{}, 0);
         if constexpr (SETS == 2) request_patch(std::integral_constant<int, 1>{}, 1);
         look_at_patch(S0{}, 0);
@@ -1125,13 +1147,14 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         const int o = (int)r * p.Wp + *s;
         return (rev ? (p.R - 1) * p.Wp + p.S - 1 - o : o) * 16;
     };
-    auto columns = [&](int tile, int stage_offset, int (&f)[NB]) {
+    auto columns = [&](int work, int stage_offset, int (&f)[NB]) {
         int n0, n_end;
-        tile_columns(tile, &n0, &n_end);
+        work_columns(work, &n0, &n_end);
         const uint32_t g_first = __builtin_amdgcn_readfirstlane(window_start((uint32_t)n0));
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int j = n0 + wn * Cfg::TN + nb * 32 + l32;
+            int j = n0 + wn * Cfg::TN + nb * 32 + l32;
+            if constexpr (Cfg::HALVES) j -= work % PARTS != 0 ? wn * (Cfg::TN / 2) : 0;   // (the second half of its blocks is not read)
             // columns past the end are never stored; let them read the last column's window
             const uint32_t rel = window_start((uint32_t)(j < n_end ? j : n_end - 1)) - g_first;
             f[nb] = Cfg::B_BASE + stage_offset + half * Cfg::B_PLANE + (int)rel * 16;
@@ -1214,10 +1237,70 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) ah[0][mb] = ah[1][mb];
     };
+    // The same of half a tile: one block of columns per wavefront, the other's registers of bh for the next tap's.
+    auto half_chunk = [&](int off, int s, int off_next) __attribute__((always_inline)) {
+        static_assert(NB == 2 && MB == 2, "one block of columns, registers for two");
+        uint32_t c_bits = 0;
+        static_for<9>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value, set = t & 1;
+            constexpr bool last = t % 3 == 2;
+            const int a_next = fa + (t == 8 ? a_other : (t + 1) * Cfg::A_TAP);
+            const bool wrap = s + 1 == p.S;
+            const int off_after = t == 8 ? off_next : off + (wrap ? to_row : in_row);
+            s = wrap ? 0 : s + 1;
+            const int f = t == 8 ? fb_next[0] : fb[0];
+            if constexpr (t == 1) c_bits = *reinterpret_cast<const uint32_t *>(lds + Cfg::SLOT_C + (n_chunk & 1u) * 4u);
+            static_for<6>([&](auto sc) __attribute__((always_inline)) {
+                constexpr int i = decltype(sc)::value, prod = i / 2, mb = i % 2;
+                if constexpr ((Cfg::WHOLE ? t == 8 : last) && i == 2) split_barrier();
+                // the next tap's fragments: bm after product 0, ah and bh any time, am after product 1
+                if constexpr (i == 2) {
+                    bh[set ^ 1] = read(f + off_after);
+                    bm[0] = read(f + off_after + Cfg::B_PART);
+                }
+                if constexpr (i == 3) {
+                    ah[set ^ 1][0] = read(a_next);
+                    ah[set ^ 1][1] = read(a_next + 512);
+                }
+                if constexpr (i >= 4) am[mb] = read(a_next + mb * 512 + Cfg::A_PART);
+                const f16x8 a = __builtin_bit_cast(f16x8, prod == 1 ? am[mb] : ah[set][mb]);
+                const f16x8 b = __builtin_bit_cast(f16x8, prod == 0 ? bm[0] : bh[set]);
+                f32x16 &sum = prod == 2 ? acc[mb][0] : low[mb][0];
+                const f32x16 zero = {};
+                constexpr bool fresh = t == 0 && prod != 1;
+                if constexpr (Cfg::SWAP) sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a, fresh ? zero : sum, 0, 0, 0);
+                else sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, fresh ? zero : sum, 0, 0, 0);
+                if constexpr (t == 0 && i < 4)
+#pragma unroll
+                    for (int v = 0; v < 8; ++v)
+                        total[i / 2][0][i % 2 * 8 + v] = __builtin_fmaf(acc[i / 2][0][i % 2 * 8 + v], c_before, total[i / 2][0][i % 2 * 8 + v]);
+                if constexpr (t == 8 && i >= 4) {
+                    const float c_low = c_cur * 0x1p-11f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) total[mb][0][v] = __builtin_fmaf(low[mb][0][v], c_low, total[mb][0][v]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (t == 4) {
+                c_bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)c_bits);
+                c_cur = __builtin_bit_cast(float, c_bits);
+                c_largest = c_largest > c_bits ? c_largest : c_bits;
+            }
+            off = off_after;
+        });
+        fa += a_other;
+        a_other = -a_other;
+        // (the next chunk's first fragments sit in set 1)
+        c_before = c_cur;
+        ++n_chunk;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) ah[0][mb] = ah[1][mb];
+        bh[0] = bh[1];
+    };
     __builtin_amdgcn_s_setprio(2);   // the MFMA stream goes first where both kinds of wavefront want to issue
     split_barrier();
     split_barrier();
-    columns(tile_number(0), 0, fb);
+    columns(work_number(0), 0, fb);
     int s0;
     int off0 = tap_position(0, &s0);
     auto first_fragments = [&]() __attribute__((always_inline)) {   // of the next chunk
@@ -1234,11 +1317,18 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
     };
     first_fragments();
     for (int it = 0;; ++it) {
-        const int tile = tile_number(it);
-        if (tile >= tiles_total) break;
+        const int work = work_number(it);
+        if (work >= none) break;
+        const bool half_tile = Cfg::HALVES && work % PARTS != 0;
         int n0, n_end;
-        tile_columns(tile, &n0, &n_end);
-        const int krow0 = (tile % p.tilesM) * BM + wm * Cfg::TM, col0 = n0 + wn * Cfg::TN;
+        [[maybe_unused]] const bool some = work_columns(work, &n0, &n_end);
+        const int krow0 = (work / PARTS % p.tilesM) * BM + wm * Cfg::TM;
+        int col0 = n0 + wn * Cfg::TN;
+        if constexpr (Cfg::HALVES)
+            if (half_tile) {
+                col0 -= wn * (Cfg::TN / 2);
+                n_end = !some ? 0 : (n_end < col0 + Cfg::TN / 2 ? n_end : col0 + Cfg::TN / 2);   // (the wavefront's)
+            }
         float bvec[MB];
         load_bias<MB>(p, krow0, l32, bvec);
 #pragma unroll
@@ -1248,29 +1338,33 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[mb][nb][v] = total[mb][nb][v] = 0.f;
         c_largest = 0;
-        const int next = tile_number(it + 1);
-        for (int c = 0; c < nch; ++c)
-            for (int g = 0; g < groups; ++g) {
-                int s_next;
-                const int off_next = tap_position(g + 1 < groups ? g + 1 : 0, &s_next);
-                if (g + 1 < groups) {
+        const int next = work_number(it + 1);
+        auto multiply = [&](auto one) __attribute__((always_inline)) {   // (a loop for each kind of chunk)
+            for (int c = 0; c < nch; ++c)
+                for (int g = 0; g < groups; ++g) {
+                    int s_next;
+                    const int off_next = tap_position(g + 1 < groups ? g + 1 : 0, &s_next);
+                    if (g + 1 < groups) {
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb];
-                } else {
-                    if (c + 1 < nch) {
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb] + b_other;
+                        for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb];
                     } else {
-                        columns(next < tiles_total ? next : tile, b_other < 0 ? 0 : Cfg::B_STAGE, fb_next);
-                    }
-                    b_other = -b_other;
-                }
-                chunk(off0, s0, off_next);
-                off0 = off_next;
-                s0 = s_next;
+                        if (c + 1 < nch) {
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) fb[nb] = fb_next[nb];
-            }
+                            for (int nb = 0; nb < NB; ++nb) fb_next[nb] = fb[nb] + b_other;
+                        } else {
+                            columns(next < none ? next : work, b_other < 0 ? 0 : Cfg::B_STAGE, fb_next);
+                        }
+                        b_other = -b_other;
+                    }
+                    one(off0, s0, off_next);
+                    off0 = off_next;
+                    s0 = s_next;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) fb[nb] = fb_next[nb];
+                }
+        };
+        if (Cfg::HALVES && half_tile) multiply([&](int off, int tap, int next_off) __attribute__((always_inline)) { half_chunk(off, tap, next_off); });
+        else multiply([&](int off, int tap, int next_off) __attribute__((always_inline)) { chunk(off, tap, next_off); });
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -1299,6 +1393,12 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
                         total[mb][nb][v] = mb * 32 + (Cfg::SWAP ? 0 : v / 4 * 8 + v % 4) < rows ? total[mb][nb][v] : 3e38f;
+        }
+        if (Cfg::HALVES && half_tile) {   // (the other blocks count as large, and are not stored)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) total[mb][NB - 1][v] = 3e38f;
         }
         if (__builtin_expect(__any(outside_halves_range<MB, NB>(total, off_by, zeros_too)), 0)) {
             f32x16 blocks[MB * NB];

@@ -77,7 +77,7 @@ struct ConvKernelParams {
     Magic mWp, mHpWp;
     const void *halves = nullptr;   // (variants 7 and 8) the split filter, then its table (igconv_kernel_f32h.hpp)
     int32_t imageTiles = 0;   // (variants 7 and 8) column tiles - (variant 10) chunks of pixels - of each image where none spans two; 0: cut regardless of images
-    int32_t halvedPerXcd = 0;    // (double precision, pipelined) the last tiles of an XCD's range that go as two halves of their columns (igconv_kernel_f64m.hpp)
+    int32_t halvedPerXcd = 0;    // (variants 7 and 8; double precision, pipelined) the last tiles of an XCD's range that go as two halves of their columns
     int32_t stepsPerChain = 0;   // (variant 10) chunks that one chain of sums takes, an even number (igconv_kernel_wgrad_f32h_rows.hpp)
 };
 

@@ -37,9 +37,9 @@ def _forward(gu, x, w, pad, stride, mode, layout, lent, alpha=1.0, beta=0.0, y0=
     return got
 
 
-def _backward_data(gu, dy, w, hw, pad, mode, layout, lent, alpha=1.0, beta=0.0, dx0=None):
+def _backward_data(gu, dy, w, hw, pad, mode, layout, lent, alpha=1.0, beta=0.0, dx0=None, units=8):
     g = gu.GpuBackwardData(wl.with_layout(dy, layout), w, hw, pad, (1, 1), mode, "f32", layout, lent or "none")
-    ig.set_compute_units(g.handle, 8)
+    ig.set_compute_units(g.handle, units)
     if dx0 is not None:
         g.out.prefill(old=dx0)
     else:
@@ -130,6 +130,42 @@ def test_backward_data(prob, layout):
         _same(short, want, (prob, layout, mode))
         _same(got, want, (prob, layout, mode))
         assert np.linalg.norm(got - want) <= 1.25 * np.linalg.norm(plain - want)
+
+
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+@pytest.mark.parametrize("prob", [
+    # N, C, H, W, K, R, S, pad: tiles for sixteen units, two per XCD; the last of an odd number goes as halves
+    (4, 36, 15, 16, 96, 5, 5, (2, 2)),       # 8 tiles of 256 columns, all as halves
+    (7, 32, 20, 64, 40, 9, 9, (0, 0)),       # 21, three to an image
+    (17, 48, 1, 107, 60, 1, 11, (0, 5)),     # 8, the last one of 27 columns: nothing in its right half
+    (18, 64, 12, 9, 130, 7, 2, (3, 1)),      # 24: two whole ones, then halves
+], ids=str)
+def test_halved_tiles(prob, layout):
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad = prob
+    rng = np.random.default_rng(50)
+    for kind in (None, "inf", "nan", "tiny", "zeros"):
+        x, w = wl.random_problem(51, N, C, H, W, K, R, S)
+        if kind == "zeros":      # sums of zero beside operands far below the others
+            x[:, 3::7], w[1::6], x[:, :, : H // 2] = 0, 0, 0
+            x[:, 1, -1, -1] = 1e-14
+        elif kind:
+            x, other = _planted(x, kind, rng)
+            w = w * other
+        want = oc.conv_forward(x, w, pad=pad, mode=1)
+        y0 = rng.uniform(-1, 1, size=want.shape).astype(np.float32)
+        beta = -1.5 if kind is None else 0.0
+        print(prob, layout, kind, flush=True)
+        whole, got = (_forward(gu, x, w, pad, (1, 1), 1, layout, _bytes(K, C, R * S), 1.0, beta, y0, units=u) for u in (8, 16))
+        _same(got, want + beta * y0 if beta else want, (prob, layout, kind))
+        # (the products, their order and the exponents of the filter are the same; the patch's may differ)
+        if kind is None:
+            assert np.linalg.norm(got - want - beta * y0) <= 1.25 * np.linalg.norm(whole - want - beta * y0)
+    wt = np.ascontiguousarray(w.transpose(1, 0, 2, 3)) if R == S else None
+    if wt is not None:   # (the exchanged layer: as many rows and, but for the border, columns)
+        dy = rng.uniform(-1, 1, size=(N, C, H + 2 * pad[0] - R + 1, W + 2 * pad[1] - S + 1)).astype(np.float32)
+        dx = _backward_data(gu, dy, wt, (H, W), pad, 1, layout, _bytes(K, C, R * S), units=16)
+        _same(dx, oc.conv_backward_data(dy, wt, (H, W), pad=pad, mode=1), (prob, layout, "data"))
 
 
 PLANTED = [(12, 48, 14, 13, 70, 3, 3, (1, 1)), (4, 32, 15, 16, 70, 5, 5, (2, 2))]
