@@ -529,7 +529,6 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
     if ((ki.gmode == 0 || ki.gmode == 2 || ki.gmode == 7 || ki.gmode == 11 || ki.gmode == 13 || ki.gmode == 14) && k.CRS % ki.BK != 0)
         k.tail_step = k.ksteps - 1;
     k.wgsPerXcd = workgroups_per_xcd(h, ki, k.tilesPerXcd);
-    k.halvedPerXcd = 0;
     // The tiles that would make one more on at most half of the compute units go as two halves of their columns: double precision
     // (igconv_kernel_f64m.hpp) and float with more than nine taps (igconv_kernel_f32h.hpp, with what it measured).
     // us, whole tiles -> this, double: 64x56x56 -> 64, 3x3, 32 images (six tiles per unit and four left per 32 units) forward 129.6 -> 124.6, backward data 137.5 -> 133,
@@ -537,7 +536,7 @@ static igcStatus fill_plan(const igcContext *h, int id, Problem *pr, igcConvolut
     // 96x27x27 -> 256, 5x5, 3 images, backward data 259 -> 191.  With more left than half of the units some would have two halves: level.
     if ((ki.f64 && ki.gmode == 14) || ki.variant == 8) {
         const int cus = std::max(1, h->computeUnits / kXcds), left = k.tilesPerXcd % cus;
-        if (left * 2 <= cus) k.halvedPerXcd = left;
+        k.halvedPerXcd = left * 2 <= cus ? left : 0;
         k.wgsPerXcd = workgroups_per_xcd(h, ki, k.tilesPerXcd + k.halvedPerXcd);
     }
     k.splits = 1;

@@ -77,8 +77,10 @@ struct ConvKernelParams {
     Magic mWp, mHpWp;
     const void *halves = nullptr;   // (variants 7 and 8) the split filter, then its table (igconv_kernel_f32h.hpp)
     int32_t imageTiles = 0;   // (variants 7 and 8) column tiles - (variant 10) chunks of pixels - of each image where none spans two; 0: cut regardless of images
-    int32_t halvedPerXcd = 0;    // (variants 7 and 8; double precision, pipelined) the last tiles of an XCD's range that go as two halves of their columns
-    int32_t stepsPerChain = 0;   // (variant 10) chunks that one chain of sums takes, an even number (igconv_kernel_wgrad_f32h_rows.hpp)
+    union {   // (the arguments of a launch stay five cache lines)
+        int32_t halvedPerXcd = 0;   // (variant 8; double precision, pipelined) the last tiles of an XCD's range that go as two halves of their columns
+        int32_t stepsPerChain;      // (variant 10) chunks that one chain of sums takes, an even number (igconv_kernel_wgrad_f32h_rows.hpp)
+    };
 };
 
 // Several problems of one kernel in one launch (the stride phases of backward data): workgroup b belongs to problem i with
