@@ -154,6 +154,32 @@ int main() {
         REQUIRE(igc::choose(h, pr, true, true, &id) == IGC_STATUS_SUCCESS);
         REQUIRE(igc::is_halves(*igc::kernel_info(id)) == r.taken);
     }
+    // Backward filter, float: two binary16 parts of three filter rows per tile stand in for those of one row alone, never for the kernels that hold 24
+    // bits of an operand; the query reports room for them where they run with it.  (kernel: variant with the room asked for, and with 64 MB more)
+    struct { int N, C, H, W, K, R, S, pad, kernel, with_more; bool innermost; } const filters[] = {
+        {23, 320, 14, 14, 144, 5, 5, 2, 4, 4, false}, {28, 64, 28, 28, 384, 3, 3, 0, 4, 4, false}, {24, 114, 37, 37, 50, 9, 9, 0, 4, 4, false},
+        {13, 336, 18, 18, 112, 9, 9, 4, 4, 4, false}, {64, 256, 14, 14, 256, 3, 3, 1, 4, 4, false}, {34, 91, 45, 45, 11, 3, 3, 0, 4, 4, false},
+        {89, 50, 16, 16, 11, 3, 3, 1, 0, 0, false}, {19, 312, 16, 16, 55, 3, 3, 1, 0, 0, false},
+        {128, 64, 56, 56, 64, 3, 3, 1, 10, 10, false}, {128, 384, 13, 13, 256, 3, 3, 1, 10, 10, false}, {128, 96, 64, 64, 128, 9, 9, 0, 10, 10, false},
+        {128, 64, 56, 56, 64, 3, 3, 1, 10, 10, true}};
+    for (it = 0; it < 12; ++it) {
+        const auto &r = filters[it];
+        const int P = r.H + 2 * r.pad - r.R + 1, Q = r.W + 2 * r.pad - r.S + 1;
+        auto set = [&](igcTensorDescriptor_t d, long long cc, long long hh, long long ww) {
+            return igcSetTensor4dDescriptor(d, IGC_DATA_FLOAT, r.N, (int)cc, (int)hh, (int)ww, cc * hh * ww, r.innermost ? 1 : hh * ww, r.innermost ? ww * cc : ww, r.innermost ? cc : 1);
+        };
+        REQUIRE(set(x, r.C, r.H, r.W) == IGC_STATUS_SUCCESS && set(y, r.K, P, Q) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetFilter4dDescriptor(w, IGC_DATA_FLOAT, r.K, r.C, r.R, r.S) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetConvolution2dDescriptor(c, r.pad, r.pad, 1, 1, IGC_CROSS_CORRELATION) == IGC_STATUS_SUCCESS);
+        size_t asked = 0;
+        REQUIRE(igcGetConvolutionBackwardFilterWorkspaceSize(h, x, y, c, w, &asked) == IGC_STATUS_SUCCESS && asked <= (size_t)IGC_NOALLOC_SCRATCH_BYTES);
+        for (size_t more : {(size_t)0, (size_t)64 << 20}) {
+            igc::BackwardFilterProblem b;
+            REQUIRE(igc::validate_backward_filter(x, y, c, w, &b) == IGC_STATUS_SUCCESS);
+            igc::halves_backward_filter(h, &b, (long long)(asked + more), true);
+            REQUIRE(igc::kernel_info(b.kernel_id)->variant == (more ? r.with_more : r.kernel));
+        }
+    }
     it = -3;
     REQUIRE(igcDestroyTensorDescriptor(x) == IGC_STATUS_SUCCESS && igcDestroyTensorDescriptor(y) == IGC_STATUS_SUCCESS &&
             igcDestroyTensorDescriptor(dx) == IGC_STATUS_SUCCESS && igcDestroyFilterDescriptor(w) == IGC_STATUS_SUCCESS &&

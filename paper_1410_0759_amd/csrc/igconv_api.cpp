@@ -1108,8 +1108,9 @@ static void backward_filter_split(const igcContext *h, const BackwardFilterProbl
 }
 
 // Float operands as two binary16 parts (igconv_kernel_wgrad_f32h.hpp), where that kernel can run, is the faster one and loses
-// no precision: `b`, whose workspace the query has reported, becomes its problem.  room_bytes: of the workspace, which starts on a 16-byte boundary if `aligned`.
-static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b, long long room_bytes, bool aligned) {
+// no precision: `b`, whose workspace the query has reported, becomes its problem.  room_bytes: of the workspace, which starts on a 16-byte boundary if `aligned`;
+// rows_bytes: what the kernels of three filter rows may count on instead.
+static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b, long long room_bytes, bool aligned, long long rows_bytes = 0) {
     const KernelInfo &old = *kernel_info(b->kernel_id);
     const ConvKernelParams &k = b->pr.kp;
     if (old.gmode != 8 || old.bf16 || old.f64) return;
@@ -1147,8 +1148,7 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
     // and small products' own.  Short reductions therefore stay (2x320x27x27 -> 112, 3x3: 1.1e-7, here 1.3e-7).
     const bool split = old.variant == 4;
     const double chain_old = 32.0 * per_old, chain = 64.0 * per;   // (two halves of a chunk's pixels apart)
-    const double longest = ((split ? 34.8 : 317.0) * chain_old - 22500.0) / 38.4;   // chain here that loses no more than there
-    bool found = chain <= longest;
+    if ((split ? 34.8 : 317.0) * chain_old < 22500.0 + 38.4 * chain) return;
     // Time, us.  Here 3.0 per chunk, NCHW or channels innermost, and 21 for start, end and the parts' sum.  The others: steps at
     // 195 to 143 TFLOP/s of the chip in tiles of split operands, 110 of fp32 ones, half of that or less with channels innermost.  Model and measured
     // times of those layers (others -> here): 28x32x64x64 -> 112, 3x3 128 -> 69, measured 137 -> 80; 20x384x15x15 -> 160, 5x5 179 -> 129,
@@ -1159,10 +1159,11 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
     double rate = split ? (old.BM * old.BN >= 96 * 128 ? 6.6e5 : 5.6e5) : 4.3e5;   // flop per us and compute unit
     if (innermost) rate *= 0.5;
     const double us_old = 6.0 + std::ceil(wgs_old / (cus * resident)) * (per_old + 3.0) * resident * old.BM * old.BN * 64.0 / rate;
-    double us = 21.0 + std::ceil((double)n.tiles * splits / cus) * per * 3.0;
-    found = found && us < us_old;
-    if (!found) us = us_old;
-    // Three filter rows at unit strides (igconv_kernel_wgrad_f32h_rows.hpp), where a chunk's pixels fit its patch, those of two images or of one.
+    const double us = 21.0 + std::ceil((double)n.tiles * splits / cus) * per * 3.0;
+    if (us >= us_old) return;
+    *b = n;
+    // In its place, with the same operands and chains of sums no longer - not in place of the others, whose operands keep 24 bits: random ones lose no more here, but
+    // ones alike in their low bits up to 2^-21 -, three filter rows at unit strides (igconv_kernel_wgrad_f32h_rows.hpp), where a chunk's pixels fit its patch, those of two images or of one.
     if (k.R >= 3 && k.redMulH == 1) {
         BackwardFilterProblem r;
         auto span = [&](int images) {   // of 128 pixels in `images` images at most, and the rest of the last window
@@ -1179,25 +1180,19 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
             r.tiles = (long long)((k.K + 63) / 64) * r.tiles_n;
             r.rows_parts = true;
             int splits_r, per_r;
-            backward_filter_split(h, r, aligned ? std::max<long long>(1, room_bytes / (4 * r.part_elems())) : 1, &splits_r, &per_r);
-            // Chains of no more pixels than in the kernel that would run instead, or than lose as much there.
-            const double chain_r = found ? chain : longest;
-            const int per_chain = (int)std::min((double)per_r, chain_r / 128.0) & ~1;
+            backward_filter_split(h, r, aligned ? std::max<long long>(1, std::max(room_bytes, rows_bytes) / (4 * r.part_elems())) : 1, &splits_r, &per_r);
+            const int per_chain = std::min(per_r, per / 2) & ~1;   // chunks of 128 pixels (here all of them in one chain)
             if (per_chain >= 2) {
                 r.pr.kp.stepsPerChain = per_chain;
                 const int pieces = (per_r + per_chain - 1) / per_chain;
-                // 3.3 us per chunk, two chunks per chain of sums for its start and end, 18 for the rest.  Measured, us, the kernel before and here: 64x256x14x14 ->
-                // 256, 3x3 104 and 71; 2x512x28x28 -> 512 77 and 61; 11x24x40x40 -> 200, 9x9 151 and 98; 20x384x15x15 -> 160, 5x5 130 and 100;
-                // 8x64x56x56 -> 64, 3x3 36 and 30; 28x32x56x56 -> 112 41 and 41; 16x32x28x28 -> 64 18.7 and 22.9.
+                // 3.3 us per chunk, two chunks per chain of sums for its start and end, 18 for the rest.  Measured, us, the kernel before and here: 2x512x28x28 -> 512,
+                // 3x3 77 and 61; 11x24x40x40 -> 200, 9x9 151 and 98; 20x384x15x15 -> 160, 5x5 130 and 100; 8x64x56x56 -> 64, 3x3 36 and 30; 28x32x56x56 -> 112
+                // 41 and 41; 16x32x28x28 -> 64 18.7 and 22.9.
                 const double us_r = 18.0 + std::ceil((double)r.tiles * splits_r / cus) * (per_r + 2.0 * pieces) * 3.3;
-                if (us_r < us) {
-                    found = true;
-                    n = r;
-                }
+                if (us_r < us) *b = r;
             }
         }
     }
-    if (found) *b = n;
 }
 
 }  // namespace igc
@@ -1871,12 +1866,14 @@ igcStatus igcGetConvolutionBackwardFilterWorkspaceSize(igcHandle_t handle, igcTe
     backward_filter_split(handle, b, 1 << 20, &splits, &per);
     // (the channel-vector kernels want their workspace even for a single range: see the entry point)
     *sizeInBytes = splits > 1 || b.pos_rows ? (size_t)splits * b.part_elems() * (b.pr.f64 ? 8 : 4) : 0;
-    // The kernels of three filter rows per tile have fewer, larger tiles and want more ranges of them.
+    // The kernels of three filter rows per tile have fewer, larger tiles and want more ranges of them: room for those where they run without and with it.
     BackwardFilterProblem rows = b;
-    halves_backward_filter(handle, &rows, IGC_NOALLOC_SCRATCH_BYTES, true);
+    halves_backward_filter(handle, &rows, (long long)*sizeInBytes, true, IGC_NOALLOC_SCRATCH_BYTES);
     if (kernel_info(rows.kernel_id)->variant == 10) {
         backward_filter_split(handle, rows, 1 << 20, &splits, &per);
-        if (splits > 1) *sizeInBytes = std::max(*sizeInBytes, (size_t)(splits * rows.part_elems() * 4));
+        const size_t more = splits > 1 ? (size_t)(splits * rows.part_elems() * 4) : 0;
+        halves_backward_filter(handle, &b, (long long)more, true);
+        if (more > *sizeInBytes && kernel_info(b.kernel_id)->variant == 10) *sizeInBytes = more;
     }
     return IGC_STATUS_SUCCESS;
 }

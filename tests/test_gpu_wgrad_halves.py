@@ -268,3 +268,24 @@ def test_three_filter_rows(prob, layout, monkeypatch, capfd):
             assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
             if beta == 0.0:
                 assert np.linalg.norm(got - want) <= (1.5e-7 + 1.3e-8 * (dy.size / K) ** 0.5) * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("prob", [
+    # with three bfloat16 parts, with the fp32 instruction
+    (34, 91, 45, 45, 11, 3, 3, (0, 0), (1, 1)), (89, 50, 16, 16, 11, 3, 3, (1, 1), (1, 1)),
+], ids=str)
+def test_products_of_24_bits_where_three_rows_would_be_faster(prob):
+    """One gradient that is not zero: every result is one product, rounded (2^-24) after what three parts leave out (2^-25).  Two binary16 parts leave up to 2^-22."""
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad, stride = prob
+    x, dy = _problem(75, *prob)
+    n, p, q = N // 2, H // 2, W // 2
+    one = dy[n, :, p, q].astype(np.float64)
+    dy[:] = 0
+    dy[n, :, p, q] = one
+    g = gu.GpuBackwardFilter(x, dy, (R, S), pad, stride, 1, "f32", "full")
+    g.out.prefill(value=float("nan"))
+    print(prob, g.asked, flush=True)
+    g.launch(1.0, 0.0)
+    want = one[:, None, None, None] * x[n][:, p - pad[0]:p - pad[0] + R, q - pad[1]:q - pad[1] + S].astype(np.float64)
+    assert np.abs(g.out.result() / want - 1).max() <= 2.0 ** -23
