@@ -786,6 +786,7 @@ __global__ __launch_bounds__(512, 2) void igconv_f32h_kernel(const ConvKernelPar
         bool some = true;
         if (part == 1) *end = *end < *first + BN / 2 ? *end : *first + BN / 2;
         if (part == 2) {
+            *end = *end < *first + BN ? *end : *first + BN;
             some = *first + BN / 2 < *end;
             *first = some ? *first + BN / 2 : *end - 1;
         }

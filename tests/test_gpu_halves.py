@@ -168,6 +168,21 @@ def test_halved_tiles(prob, layout):
         _same(dx, oc.conv_backward_data(dy, wt, (H, W), pad=pad, mode=1), (prob, layout, "data"))
 
 
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+def test_a_half_tile_reads_its_own_columns(layout):
+    """What other tiles' pixels hold changes no bit of a tile's results: they are not among those whose largest sets its scale.  24 tiles of 256 output
+    pixels, all as halves; a pixel of x that no window of the first tile has, but some of the 128 after it."""
+    gu = _gpu()
+    N, C, H, W, K, R, S, pad = 8, 32, 20, 64, 40, 9, 9, (0, 0)
+    x, w = wl.random_problem(76, N, C, H, W, K, R, S)
+    large = x.copy()
+    large[0, :, 13, 20] = 3e5
+    print(layout, flush=True)
+    got = [_forward(gu, a, w, pad, (1, 1), 1, layout, _bytes(K, C, R * S), units=48).transpose(1, 0, 2, 3).reshape(K, -1) for a in (x, large)]
+    assert np.array_equal(got[0][:, :256], got[1][:, :256])
+    assert np.abs(got[1][:, 256:384]).max() > 1e3 * np.abs(got[0]).max()
+
+
 PLANTED = [(12, 48, 14, 13, 70, 3, 3, (1, 1)), (4, 32, 15, 16, 70, 5, 5, (2, 2))]
 
 
