@@ -284,7 +284,8 @@ struct BiasGradPlan {
     BiasGradArgs a;
     bool packed;     // dy is one run of positions * C elements and the workgroup's round holds whole multiples of C
     bool channels;   // dy has unit channel stride
-    bool vectors;    // feature maps are runs, each from a 4-byte boundary on, long or of whole 16-byte vectors
+    bool vectors;    // feature maps are runs, long or of whole 16-byte vectors, each from a 4-byte boundary on if dy is on one
+    bool one_piece;  // then better without ranges
     bool f64;
     igcDataType in;
 };
@@ -350,12 +351,7 @@ igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcT
     a.ranges = (int)ranges;
     a.per = (uint32_t)((positions + ranges - 1) / ranges);
     a.ranges = (int)((positions + a.per - 1) / a.per);
-    if (pl->vectors) {
-        if (in_one_piece(h, a, elem_size(dyDesc->dtype))) a.ranges = 1;
-        a.perv = (a.vectors + (uint32_t)a.ranges - 1u) / (uint32_t)a.ranges;
-        a.ranges = (int)((a.vectors + a.perv - 1u) / a.perv);
-        a.per = (uint32_t)((positions + a.ranges - 1) / a.ranges);   // (should dy not be on such a boundary)
-    }
+    pl->one_piece = pl->vectors && in_one_piece(h, a, elem_size(dyDesc->dtype));
     return IGC_STATUS_SUCCESS;
 }
 
@@ -366,7 +362,7 @@ int launch_bias_grad(const BiasGradPlan &pl, hipStream_t stream) {
     void *argv[] = {&a};
     // (the packed form wants dy itself on a 16-byte boundary)
     const bool packed = pl.packed && (uintptr_t)a.dy % 16 == 0;
-    const bool vectors = pl.vectors && (uintptr_t)a.dy % 4 == 0, whole = vectors && a.ranges == 1 && a.vectors > 8u * 256u;   // (that much 256 threads request at once)
+    const bool vectors = pl.vectors, whole = vectors && a.ranges == 1 && a.vectors > 8u * 256u;   // (that much 256 threads request at once)
     const void *kernel = packed ? reinterpret_cast<const void *>(&bias_grad_packed_kernel<T, OUT>)
                                 : (pl.channels ? reinterpret_cast<const void *>(&bias_grad_channels_kernel<T, OUT>)
                                                : (whole ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, 1024>)
@@ -417,12 +413,16 @@ igcStatus igcConvolutionBackwardBias(igcHandle_t handle, const void *alpha, igcT
     a.db = db;
     a.alpha = pl.f64 ? *static_cast<const double *>(alpha) : (double)*static_cast<const float *>(alpha);
     a.beta = pl.f64 ? *static_cast<const double *>(beta) : (double)*static_cast<const float *>(beta);
+    // (the query, which does not see dy, reports the room that maps on no such boundary use)
+    pl.vectors = pl.vectors && (uintptr_t)dy % 4 == 0;
+    if (pl.vectors && pl.one_piece) a.ranges = 1;
     // without room for the ranges' sums (or with a misaligned one): one range
     const size_t need = (size_t)a.ranges * a.C * sizeof(double);
-    if (a.ranges > 1 && (!workSpace || (uintptr_t)workSpace % 8 != 0 || workSpaceSizeInBytes < need)) {
-        a.ranges = 1;
-        a.per = a.positions;
-        a.perv = a.vectors;
+    if (a.ranges > 1 && (!workSpace || (uintptr_t)workSpace % 8 != 0 || workSpaceSizeInBytes < need)) a.ranges = 1;
+    if (a.ranges == 1) a.per = a.positions;
+    if (pl.vectors) {
+        a.perv = (a.vectors + (uint32_t)a.ranges - 1u) / (uint32_t)a.ranges;
+        a.ranges = (int)((a.vectors + a.perv - 1u) / a.perv);
     }
     a.parts = static_cast<double *>(workSpace);
     hipStream_t stream = static_cast<hipStream_t>(handle->stream);

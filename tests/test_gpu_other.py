@@ -272,6 +272,34 @@ def test_backward_bias_runs(shape, dtype):
             close(gu.run_backward_bias(dy, dtype=dtype, workspace=workspace), want)
 
 
+def _bias_gradients(dtype, shape, start):
+    """db of dy whose first element is `start` elements into its buffer, with the workspace asked for, and microseconds."""
+    import torch
+    import paper_1410_0759_amd as ig
+    from tests.test_gpu_halves import _microseconds
+    _gpu()
+    N, C, H, W = shape
+    flat = torch.randn(N * C * H * W + start, device="cuda").to(dtype)
+    dy = flat[start:].view(shape)
+    db, h = torch.empty(C, device="cuda"), ig.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    dyd, dbd = ig.tensor_descriptor_for(dy), ig.TensorDescriptor().set(ig.IGC_DATA_FLOAT, 1, C, 1, 1, (C, 1, 1, 1))
+    n = ig.get_backward_bias_workspace_size(h, dyd, dbd)
+    ws = torch.empty(n // 4 + 4, device="cuda")
+    us = _microseconds(lambda: ig.check(ig.convolution_backward_bias(h, 1.0, dyd, dy.data_ptr(), 0.0, dbd, db.data_ptr(), ws.data_ptr(), n)))
+    want = dy.double().sum((0, 2, 3))
+    assert ((db.double() - want).abs() <= 2.0 ** -23 * want.abs() + 1e-9).all()
+    return us
+
+
+def test_backward_bias_between_boundaries():
+    """bfloat16 maps that no 16-byte load may read.  (In one piece, one workgroup per map, they took 5 to 6 times as long as where it may; now 1.3.)"""
+    import torch
+    on, between = (_bias_gradients(torch.bfloat16, (128, 128, 56, 56), start) for start in (0, 1))
+    print(on, between, flush=True)
+    assert between <= 2.5 * on
+
+
 @pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
 @pytest.mark.parametrize("shape, win, pad", [
     # stride 2, 4096 planes or (more than 48 rows) 512 strips and more: the kernel that walks down rows of 2 x 2 cells

@@ -344,6 +344,8 @@ def test_backward_bias_is_validated_and_planned_before_any_gpu_call():
     big = ig.get_backward_bias_workspace_size(h, dy, db)
     assert big > 0 and big % (64 * 8) == 0 and big <= 1024 * 64 * 8          # whole ranges of 64 doubles, at most 1024 of them
     assert ig.get_backward_bias_workspace_size(h, t(2, 3, 5, 7), t(1, 3, 1, 1)) == 0
+    # (maps of bfloat16 that 16-byte loads take in one piece: room for the ranges all the same, dy may start between two of their 4-byte boundaries)
+    assert ig.get_backward_bias_workspace_size(h, t(128, 128, 56, 56, dt=1), t(1, 128, 1, 1)) > 0
     nhwc = t(128, 64, 56, 56, st=(56 * 56 * 64, 1, 56 * 64, 64))
     assert ig.get_backward_bias_workspace_size(h, nhwc, db) > 0
     ig.set_compute_units(h, 64)                                               # fewer compute units, fewer ranges
