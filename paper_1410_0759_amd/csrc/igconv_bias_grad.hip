@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "igconv_desc.h"
 #include "igconv_params.h"
 
@@ -36,8 +38,9 @@ struct BiasGradArgs {
     uint32_t HW, positions;       // H*W, N*H*W
     Magic mHW, mW;
     uint32_t runs;                // 1 when a feature map is one run of H*W elements (w-stride 1, h-stride W)
-    // feature maps stored as runs, the vector form below: 16-byte vectors of a run, what it has beyond them, vectors of a map and of a range
-    uint32_t HWv, tail, vectors, perv;
+    // feature maps stored as runs, the vector form below: 16-byte vectors of a run, dwords of the last one that the one before it has, vectors of
+    // a map and of a range
+    uint32_t HWv, drop, vectors, perv;
     Magic mHWv;
     uint32_t sN, sC, sH, sW;      // element strides of dy
     uint32_t per;                 // positions per range
@@ -192,9 +195,11 @@ __global__ __launch_bounds__(256) void bias_grad_map_kernel(const BiasGradArgs a
 
 // feature maps stored as runs (w-stride 1, h-stride W) that begin on 4-byte boundaries, all a 16-byte load asks for: as above with a thread on
 // 16 bytes of its feature map at a time - one division per 16 bytes instead of two per element, eight loads requested before they
-// are added.  What is left of each run goes one by one, in the map's last range.  (64x96x55x55, whose maps are no whole vectors,
-// element by element: 17.1 us, so 15.0 and in one piece 13.5.)  A range has 256 threads, a map in one piece 1024.
-template <class T, class OUT, int THREADS>
+// are added.  The last 16 bytes of a run that is no whole number of them overlap those before and count from their dword `drop` on.
+// (64x96x55x55, element by element: 16.9 us, so, in one piece, 13.8.  What is left of the runs loaded apart, by the last range: 20000x4x9x15 91 us,
+// element by element 14, so 12.2.)  A range has 256 threads, a map in one piece 1024.
+// OVERLAP: such runs.
+template <class T, class OUT, int THREADS, bool OVERLAP>
 __global__ __launch_bounds__(THREADS) void bias_grad_map_vectors_kernel(const BiasGradArgs a) {
     constexpr int V = Pack<T>::V;
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -204,20 +209,25 @@ __global__ __launch_bounds__(THREADS) void bias_grad_map_vectors_kernel(const Bi
     const uint32_t total = a.vectors;
     const uint32_t begin = (uint32_t)range * a.perv, end = begin + a.perv < total ? begin + a.perv : total;
     const uint32_t cbase = (uint32_t)c * a.sC;
+    const bool drop1 = a.drop > 1u, drop2 = a.drop > 2u;
     double sum = 0.0;
     for (uint32_t i0 = begin + threadIdx.x; i0 < end; i0 += 8u * THREADS) {
         u32x4_t q[8];
+        bool last[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t i = i0 + (uint32_t)j * THREADS;
             const uint32_t n = mdiv(i, a.mHWv), rem = i - n * a.HWv;
-            const uint32_t off = (n * a.sN + cbase + rem * (uint32_t)V) * (uint32_t)sizeof(T);
+            last[j] = OVERLAP && rem * (uint32_t)V > a.HW - (uint32_t)V;
+            const uint32_t at = OVERLAP ? min(rem * (uint32_t)V, a.HW - (uint32_t)V) : rem * (uint32_t)V;
+            const uint32_t off = (n * a.sN + cbase + at) * (uint32_t)sizeof(T);
             q[j] = __builtin_amdgcn_raw_buffer_load_b128(buf, i < end ? off : 0x80000000u, 0, 0);   // (past the end: zeros)
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint32_t q0 = q[j].x, q1 = q[j].y, q2 = q[j].z, q3 = q[j].w;   // (by name: see the packed kernel)
+            // (by name: see the packed kernel)
+            const uint32_t q0 = last[j] ? 0u : q[j].x, q1 = last[j] && drop1 ? 0u : q[j].y, q2 = last[j] && drop2 ? 0u : q[j].z, q3 = q[j].w;
             if constexpr (V == 4) {
                 sum += (double)__builtin_bit_cast(float, q0);
                 sum += (double)__builtin_bit_cast(float, q1);
@@ -237,13 +247,6 @@ __global__ __launch_bounds__(THREADS) void bias_grad_map_vectors_kernel(const Bi
                 sum += __builtin_bit_cast(double, u32x2_t{q0, q1});
                 sum += __builtin_bit_cast(double, u32x2_t{q2, q3});
             }
-        }
-    }
-    if (a.tail != 0u && range == a.ranges - 1) {
-        const uint32_t left = a.positions / a.HW * a.tail;
-        for (uint32_t i = threadIdx.x; i < left; i += THREADS) {
-            const uint32_t n = i / a.tail;
-            sum += load_as_double<T>(buf, n * a.sN + cbase + a.HW - a.tail + (i - n * a.tail));
         }
     }
     sums[threadIdx.x] = sum;
@@ -329,10 +332,10 @@ igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcT
     a.runs = dyDesc->stride[3] == 1 && dyDesc->stride[2] == a.W ? 1u : 0u;
     // (short runs with something left over stay element by element: 64x512x7x7 3.9 us, with vectors 4.3)
     pl->vectors = !pl->channels && a.runs != 0u && (a.HW % (uint32_t)per16 == 0 || a.HW >= 128u) &&
-                  (dyDesc->dtype != IGC_DATA_BFLOAT16 || (dyDesc->stride[0] % 2 == 0 && dyDesc->stride[1] % 2 == 0));
+                  (dyDesc->dtype != IGC_DATA_BFLOAT16 || (a.HW % 2u == 0 && dyDesc->stride[0] % 2 == 0 && dyDesc->stride[1] % 2 == 0));
     if (pl->vectors) {
-        a.HWv = a.HW / (uint32_t)per16;
-        a.tail = a.HW % (uint32_t)per16;
+        a.HWv = (a.HW + (uint32_t)per16 - 1u) / (uint32_t)per16;
+        a.drop = (a.HWv * (uint32_t)per16 - a.HW) * (uint32_t)elem_size(dyDesc->dtype) / 4u;
         a.vectors = (uint32_t)dyDesc->dim[0] * a.HWv;
         if (!magic_for(a.HWv, &a.mHWv)) return IGC_STATUS_NOT_SUPPORTED;
     }
@@ -363,10 +366,15 @@ int launch_bias_grad(const BiasGradPlan &pl, hipStream_t stream) {
     // (the packed form wants dy itself on a 16-byte boundary)
     const bool packed = pl.packed && (uintptr_t)a.dy % 16 == 0;
     const bool vectors = pl.vectors, whole = vectors && a.ranges == 1 && a.vectors > 8u * 256u;   // (that much 256 threads request at once)
+    auto by_threads = [&](auto threads) {
+        constexpr int n = decltype(threads)::value;
+        return a.drop != 0u ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, n, true>)
+                            : reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, n, false>);
+    };
     const void *kernel = packed ? reinterpret_cast<const void *>(&bias_grad_packed_kernel<T, OUT>)
                                 : (pl.channels ? reinterpret_cast<const void *>(&bias_grad_channels_kernel<T, OUT>)
-                                               : (whole ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, 1024>)
-                                                  : vectors ? reinterpret_cast<const void *>(&bias_grad_map_vectors_kernel<T, OUT, 256>)
+                                               : (whole ? by_threads(std::integral_constant<int, 1024>{})
+                                                  : vectors ? by_threads(std::integral_constant<int, 256>{})
                                                           : reinterpret_cast<const void *>(&bias_grad_map_kernel<T, OUT>)));
     const dim3 grid = packed ? dim3(a.ranges) : dim3(pl.channels ? (a.C + 63) / 64 : a.C, a.ranges);
     if (hipLaunchKernel(kernel, grid, dim3(whole ? 1024 : 256), argv, 0, stream) != hipSuccess) return 1;

@@ -300,6 +300,17 @@ def test_backward_bias_between_boundaries():
     assert between <= 2.5 * on
 
 
+@pytest.mark.parametrize("shape", [(20000, 4, 9, 15), (30000, 3, 11, 13)], ids=str)
+def test_backward_bias_of_many_short_runs(shape):
+    """Runs that 16-byte vectors do not divide, against runs an element longer that they do.  (With what is left of all of them in one range 7 to 9
+    times as long; now as long.)"""
+    import torch
+    N, C, H, W = shape
+    ragged, whole = _bias_gradients(torch.float32, shape, 0), _bias_gradients(torch.float32, (N, C, 1, H * W + 1), 0)
+    print(shape, ragged, whole, flush=True)
+    assert ragged <= 2.0 * whole
+
+
 @pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
 @pytest.mark.parametrize("shape, win, pad", [
     # stride 2, 4096 planes or (more than 48 rows) 512 strips and more: the kernel that walks down rows of 2 x 2 cells
