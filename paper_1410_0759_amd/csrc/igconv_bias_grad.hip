@@ -296,10 +296,12 @@ struct BiasGradPlan {
 // A map in one piece, one workgroup of 1024 threads each, and no second launch?  Measured, us, ranges and their sum -> one piece: 128x256x13x13 8.4 -> 4.5,
 // 64x96x55x55 15.0 -> 13.5, 64x256x28x28 11.5 -> 9.4 (bfloat16 7.1 -> 4.5), 8x64x56x56 6.9 -> 4.2, 128x128x56x56 32.1 -> 29.9; where few maps leave
 // compute units idle 18.5 -> 20.9 (128x64x56x56), 6.8 -> 10.6 (64x32x56x56), 11.4 -> 12.0 (double, 32x64x56x56).  A workgroup reads 65 to 85 KB per
-// us, the chip up to 7 MB from the last-level cache; the second launch costs 4.5 us.
+// us, the chip up to 7 MB from the last-level cache; the second launch costs 4.5 us.  Of tensors beyond that cache a workgroup reads 42 KB, the chip
+// 6 MB: 512x128x56x56 136 -> 152, 64x128x128x128 89 -> 97, 2048x257x13x13 70 -> 86; but 2048x256x13x13 68 -> 65, 128x192x56x56 48.5 -> 45.
 bool in_one_piece(const igcContext *h, const BiasGradArgs &a, long long elem) {
     const long long map = (long long)a.positions * elem, rounds = (a.C + h->computeUnits - 1) / h->computeUnits;
-    return (double)(map * rounds) / 60e3 <= 4.5 + (double)map * a.C / 7e6;
+    const bool beyond = map * a.C > 256ll << 20;
+    return (double)(map * rounds) / (beyond ? 42e3 : 60e3) <= 4.5 + (double)map * a.C / (beyond ? 6e6 : 7e6);
 }
 
 igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcTensorDescriptor_t dbDesc, BiasGradPlan *pl) {
