@@ -180,6 +180,20 @@ int main() {
             REQUIRE(igc::kernel_info(b.kernel_id)->variant == (more ? r.with_more : r.kernel));
         }
     }
+    // ... and only where they count the pixels of the images with their borders in 31 bits (an image and its gradients, repeated by a stride of zero)
+    for (it = 0; it < 2; ++it) {
+        const int N = it ? 9200000 : 8000000;
+        REQUIRE(igcSetTensor4dDescriptor(x, IGC_DATA_FLOAT, N, 128, 2, 58, 0, 116, 58, 1) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetTensor4dDescriptor(y, IGC_DATA_FLOAT, N, 512, 2, 58, 0, 116, 58, 1) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetFilter4dDescriptor(w, IGC_DATA_FLOAT, 512, 128, 3, 3) == IGC_STATUS_SUCCESS);
+        REQUIRE(igcSetConvolution2dDescriptor(c, 1, 1, 1, 1, IGC_CROSS_CORRELATION) == IGC_STATUS_SUCCESS);
+        igc::BackwardFilterProblem b;
+        REQUIRE(igc::validate_backward_filter(x, y, c, w, &b) == IGC_STATUS_SUCCESS);
+        igc::halves_backward_filter(h, &b, (long long)64 << 20, true);
+        const igc::KernelInfo &ki = *igc::kernel_info(b.kernel_id);
+        REQUIRE(ki.variant == (it ? 9 : 10));
+        REQUIRE((long long)N * b.pr.kp.HpWp * b.pr.kp.Wp < (1ll << 31));
+    }
     it = -3;
     REQUIRE(igcDestroyTensorDescriptor(x) == IGC_STATUS_SUCCESS && igcDestroyTensorDescriptor(y) == IGC_STATUS_SUCCESS &&
             igcDestroyTensorDescriptor(dx) == IGC_STATUS_SUCCESS && igcDestroyFilterDescriptor(w) == IGC_STATUS_SUCCESS &&

@@ -1132,6 +1132,7 @@ static void halves_backward_filter(const igcContext *h, BackwardFilterProblem *b
         kn.PQ = (C + 31) / 32;
         kn.Wp = Q + 2;
         kn.HpWp = patch_rows;
+        if ((long long)(k.CRS / k.RS) * patch_rows * (Q + 2) >= (1ll << 31)) return false;   // (the images' pixels, divided by multiply and shift)
         if (!magic_for((uint32_t)kn.PQ, &kn.mPQ) || !magic_for((uint32_t)kn.Wp, &kn.mWp) || !magic_for((uint32_t)kn.HpWp, &kn.mHpWp)) return false;
         n->ksteps = (k.CRS + kernel_info(n->kernel_id)->BK - 1) / kernel_info(n->kernel_id)->BK;
         return true;
