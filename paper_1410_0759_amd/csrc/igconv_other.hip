@@ -133,13 +133,15 @@ __device__ __forceinline__ wide_t rload_wide(__amdgpu_buffer_rsrc_t buf, uint32_
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(wide_t, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(buf, off4, 0, 0));
 }
-__device__ __forceinline__ void rstore_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4, wide_t v) {
+[[maybe_unused]] __device__ __forceinline__ void rstore_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4, wide_t v) {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), buf, off4, 0, 0);
 }
 __device__ __forceinline__ real_t rexp(real_t x) { return __expf(x); }
 __device__ __forceinline__ real_t rmax(real_t a, real_t b) { return fmaxf(a, b); }
+#define IGC_REAL_IS_FLOAT
 #include "igconv_other_impl.inc"
+#undef IGC_REAL_IS_FLOAT
 }  // namespace f32
 
 namespace f64 {
@@ -159,10 +161,6 @@ typedef double wide_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ wide_t rload_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4) {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(wide_t, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(buf, off4 >= 0x80000000u ? 0x80000000u : off4 * 2u, 0, 0));
-}
-__device__ __forceinline__ void rstore_wide(__amdgpu_buffer_rsrc_t buf, uint32_t off4, wide_t v) {
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), buf, off4 >= 0x80000000u ? 0x80000000u : off4 * 2u, 0, 0);
 }
 __device__ __forceinline__ real_t rexp(real_t x) { return exp(x); }
 __device__ __forceinline__ real_t rmax(real_t a, real_t b) { return fmax(a, b); }
