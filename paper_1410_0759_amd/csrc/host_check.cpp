@@ -194,6 +194,83 @@ int main() {
         REQUIRE(ki.variant == (it ? 9 : 10));
         REQUIRE((long long)N * b.pr.kp.HpWp * b.pr.kp.Wp < (1ll << 31));
     }
+    // Which kernels the layers of tests take that compare results alone.  (halved: tiles of an XCD's range that go as two halves)
+    auto set_layer = [&](igcDataType in, bool innermost, int N, int C, int H, int W, int K, int R, int S, int pad_h, int pad_w, int stride) {
+        const int P = (H + 2 * pad_h - R) / stride + 1, Q = (W + 2 * pad_w - S) / stride + 1;
+        const igcDataType out = in == IGC_DATA_BFLOAT16 ? IGC_DATA_FLOAT : in;
+        auto set = [&](igcTensorDescriptor_t d, igcDataType dt, bool last, long long cc, long long hh, long long ww) {
+            return igcSetTensor4dDescriptor(d, dt, N, (int)cc, (int)hh, (int)ww, cc * hh * ww, last ? 1 : hh * ww, last ? ww * cc : ww, last ? cc : 1) == IGC_STATUS_SUCCESS;
+        };
+        // (16-bit gradients have their channels innermost)
+        return set(x, in, innermost, C, H, W) && set(dx, out, innermost, C, H, W) && set(y, in, innermost || in == IGC_DATA_BFLOAT16, K, P, Q) &&
+               igcSetFilter4dDescriptor(w, in, K, C, R, S) == IGC_STATUS_SUCCESS &&
+               igcSetConvolution2dDescriptor(c, pad_h, pad_w, stride, stride, IGC_CROSS_CORRELATION) == IGC_STATUS_SUCCESS;
+    };
+    auto forward_kernel = [&](size_t halves_room, const igc::KernelInfo **ki) {   // tiles that go as halves
+        igc::Problem pr;
+        int id = -1;
+        igcConvolutionForwardPlan plan;
+        if (igc::validate(x, w, c, y, &pr) != IGC_STATUS_SUCCESS) return -1;
+        pr.halves_room = halves_room;
+        if (igc::choose(h, pr, true, true, &id) != IGC_STATUS_SUCCESS || igc::fill_plan(h, id, &pr, &plan) != IGC_STATUS_SUCCESS) return -1;
+        *ki = igc::kernel_info(id);
+        return (int)pr.kp.halvedPerXcd;
+    };
+    auto data_kernel = [&](bool filter_inner, size_t halves_room, const igc::KernelInfo **ki) {   // (of the phases that meet a tap: one kernel)
+        igc::BackwardDataProblem b;
+        std::vector<igc::PhaseLaunch> launches;
+        if (igc::validate_backward_data(w, y, c, dx, &b) != IGC_STATUS_SUCCESS ||
+            igc::plan_backward_data_phases(h, b, &launches, filter_inner, true, halves_room) != IGC_STATUS_SUCCESS) return -1;
+        int halved = -1;
+        for (const igc::PhaseLaunch &l : launches)
+            if (!l.pr.zero_steps) {
+                if (halved >= 0 && *ki != igc::kernel_info(l.id)) return -1;
+                *ki = igc::kernel_info(l.id);
+                halved = (int)l.pr.kp.halvedPerXcd;
+            }
+        return halved;
+    };
+    const igc::KernelInfo *ki = nullptr;
+    for (it = 0; it < 12; ++it) {   // bfloat16 backward data: tiles of 128 x 256 on 8 compute units, smaller ones on 256 (test_backward_data_large_tiles)
+        const int large[3][9] = {{40, 130, 30, 31, 72, 5, 5, 2, 2}, {33, 256, 17, 16, 32, 3, 2, 1, 1}, {64, 128, 16, 16, 8, 2, 1, 0, 0}};
+        const int *r = large[it / 4];
+        REQUIRE(igcSetComputeUnits(h, it & 1 ? 256 : 8) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_BFLOAT16, (it & 2) != 0, r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], r[8], 1));
+        REQUIRE(data_kernel(true, 0, &ki) >= 0);
+        REQUIRE(ki->variant == 6 && ki->BN == (it & 1 ? 128 : 256));
+    }
+    for (it = 0; it < 24; ++it) {   // double precision, forward and backward data (test_halved_tiles_f64)
+        const int tiles[6][6] = {{3, 2, 75, 75, 10, 1}, {3, 2, 78, 78, 65, 8}, {5, 2, 70, 70, 64, 16}, {5, 2, 71, 71, 64, 0}, {15, 1, 66, 67, 9, 2}, {1, 3, 16, 97, 33, 4}};
+        const int *r = tiles[it / 4];
+        const bool data = it & 2;
+        REQUIRE(igcSetComputeUnits(h, 256) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_DOUBLE, it & 1, r[0], r[data ? 4 : 1], r[2], r[3], r[data ? 1 : 4], 3, 3, 1, 1, 1));
+        REQUIRE((data ? data_kernel(false, 0, &ki) : forward_kernel(0, &ki)) == r[5]);
+        REQUIRE(ki->f64 && ki->gmode == 14);
+    }
+    for (it = 0; it < 32; ++it) {   // float with more than nine taps, and the exchanged layer's backward data: one such tile on 16 compute units (test_halved_tiles)
+        const int tiles[4][9] = {{4, 64, 15, 16, 96, 5, 5, 2, 2}, {7, 32, 20, 64, 40, 9, 9, 0, 0}, {17, 64, 1, 107, 60, 1, 21, 0, 10}, {16, 64, 12, 9, 130, 7, 2, 3, 1}};
+        const int *r = tiles[it / 8];
+        const bool data = it & 4;
+        if (data && r[5] != r[6]) continue;
+        REQUIRE(igcSetComputeUnits(h, it & 1 ? 16 : 8) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_FLOAT, (it & 2) != 0, r[0], r[data ? 4 : 1], r[2], r[3], r[data ? 1 : 4], r[5], r[6], r[7], r[8], 1));
+        REQUIRE((data ? data_kernel(false, (size_t)1 << 26, &ki) : forward_kernel((size_t)1 << 26, &ki)) == (it & 1));
+        REQUIRE(ki->variant == 8);
+    }
+    for (it = 0; it < 2; ++it) {    // the same, three on 48 (test_a_half_tile_reads_its_own_columns)
+        REQUIRE(igcSetComputeUnits(h, 48) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_FLOAT, it, 8, 32, 20, 64, 40, 9, 9, 0, 0, 1));
+        REQUIRE(forward_kernel((size_t)1 << 26, &ki) == 3 && ki->variant == 8);
+    }
+    for (it = 0; it < 12; ++it) {   // float, one tap, backward data: three parts from 32 maps on, where tiles are enough (test_backward_data_of_one_tap)
+        const int taps[6][8] = {{40, 100, 31, 33, 31, 1, 0, 0}, {40, 100, 31, 33, 32, 1, 0, 4}, {40, 70, 31, 33, 33, 1, 0, 4},
+                                {12, 300, 29, 31, 77, 1, 1, 4}, {24, 260, 41, 43, 65, 2, 0, 4}, {9, 40, 5, 7, 100, 1, 0, 0}};
+        const int *r = taps[it / 2];
+        REQUIRE(igcSetComputeUnits(h, 256) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_FLOAT, it & 1, r[0], r[1], r[2], r[3], r[4], 1, 1, r[6], r[6], r[5]));
+        REQUIRE(data_kernel(false, 0, &ki) >= 0 && ki->variant == r[7]);
+    }
     it = -3;
     REQUIRE(igcDestroyTensorDescriptor(x) == IGC_STATUS_SUCCESS && igcDestroyTensorDescriptor(y) == IGC_STATUS_SUCCESS &&
             igcDestroyTensorDescriptor(dx) == IGC_STATUS_SUCCESS && igcDestroyFilterDescriptor(w) == IGC_STATUS_SUCCESS &&

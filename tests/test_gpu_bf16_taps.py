@@ -141,6 +141,7 @@ def test_forward_nine_taps(prob, layout):
     (64, 128, 16, 16, 8, 2, 1, (0, 0), (1, 1)),       # two steps per tile
 ])
 def test_backward_data_large_tiles(prob, layout):
+    """(csrc/host_check.cpp requires that these layers take the large tile with 8 compute units, a smaller one with 256.)"""
     import torch
     import paper_1410_0759_amd as ig
     gu = _gpu()

@@ -88,6 +88,7 @@ def test_backward_data_phases(prob):
     (40, 100, 31, 33, 31, 1, 0), (40, 100, 31, 33, 32, 1, 0), (40, 70, 31, 33, 33, 1, 0), (12, 300, 29, 31, 77, 1, 1), (24, 260, 41, 43, 65, 2, 0), (9, 40, 5, 7, 100, 1, 0),
 ], ids=str)
 def test_backward_data_of_one_tap(prob, layout):
+    """(csrc/host_check.cpp requires that these layers run with the kernels named.)"""
     gu = _gpu()
     N, C, H, W, K, u, pad = prob
     rng = np.random.default_rng(54)

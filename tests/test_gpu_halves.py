@@ -135,12 +135,13 @@ def test_backward_data(prob, layout):
 @pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
 @pytest.mark.parametrize("prob", [
     # N, C, H, W, K, R, S, pad: tiles for sixteen units, two per XCD; the last of an odd number goes as halves
-    (4, 36, 15, 16, 96, 5, 5, (2, 2)),       # 8 tiles of 256 columns, all as halves
+    (4, 64, 15, 16, 96, 5, 5, (2, 2)),       # 8 tiles of 256 columns, all as halves
     (7, 32, 20, 64, 40, 9, 9, (0, 0)),       # 21, three to an image
-    (17, 48, 1, 107, 60, 1, 11, (0, 5)),     # 8, the last one of 27 columns: nothing in its right half
-    (18, 64, 12, 9, 130, 7, 2, (3, 1)),      # 24: two whole ones, then halves
+    (17, 64, 1, 107, 60, 1, 21, (0, 10)),    # 8, the last one of 27 columns: nothing in its right half
+    (16, 64, 12, 9, 130, 7, 2, (3, 1)),      # 24: two whole ones, then halves
 ], ids=str)
 def test_halved_tiles(prob, layout):
+    """(csrc/host_check.cpp requires that these layers take this route.)"""
     gu = _gpu()
     N, C, H, W, K, R, S, pad = prob
     rng = np.random.default_rng(50)

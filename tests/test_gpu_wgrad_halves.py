@@ -28,7 +28,7 @@ def _problem(seed, N, C, H, W, K, R, S, pad, stride):
 
 @pytest.fixture
 def run(monkeypatch, capfd):
-    def call(gu, x, dy, rs, pad, stride, mode=1, layout="NCHW", workspace="full", alpha=1.0, beta=0.0, old=None, units=8):
+    def call(gu, x, dy, rs, pad, stride, mode=1, layout="NCHW", workspace="full", alpha=1.0, beta=0.0, old=None, units=8, kernel="wgrad halves"):
         g = gu.GpuBackwardFilter(wl.with_layout(x, layout) if layout else x, wl.with_layout(dy, layout) if layout else dy, rs, pad, stride, mode, "f32", workspace)
         if units:
             ig.set_compute_units(g.handle, units)
@@ -39,7 +39,7 @@ def run(monkeypatch, capfd):
         monkeypatch.setenv("IGCONV_DEBUG", "1")
         capfd.readouterr()
         g.launch(alpha, beta)
-        assert "wgrad halves" in capfd.readouterr().err, "the route under test did not run"
+        assert kernel in capfd.readouterr().err, "the route under test did not run"
         g.ws.result()   # (guard bands)
         return g.out.result()
     return call
@@ -268,6 +268,38 @@ def test_three_filter_rows(prob, layout, monkeypatch, capfd):
             assert np.abs(got - want).max() <= gu.BOUND["f32"] * np.abs(want).max()
             if beta == 0.0:
                 assert np.linalg.norm(got - want) <= (1.5e-7 + 1.3e-8 * (dy.size / K) ** 0.5) * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny", "images", "drift", "wide range", "mostly zero"])
+@pytest.mark.parametrize("prob", ROWS[:4:3])
+def test_three_filter_rows_outside_the_range(prob, kind, run):
+    """Values that one exponent does not hold, in either operand: chunks of one image and of several."""
+    gu = _gpu()
+    *dims, pad, stride = prob
+    rng = np.random.default_rng(77)
+    for operand in (0, 1):
+        a = list(_problem(78, *prob))
+        if kind == "images":      # exponents that leave what a range may span, up and down
+            for n in range(dims[0]):
+                a[operand][n], a[1 - operand][n] = _scaled(a[operand][n], 60 - 30 * (n % 5)), _scaled(a[1 - operand][n], 10 * (n % 3) - 60)
+        elif kind == "drift":       # sums scaled again from image to image
+            for n in range(dims[0]):
+                a[operand][n] = _scaled(a[operand][n], (n * 5) % 17)
+        elif kind == "wide range":
+            a[operand] = np.ldexp(a[operand].astype(np.float64), rng.integers(-60, 1, size=a[operand].shape)).astype(np.float32)
+        elif kind == "mostly zero":
+            a[operand] *= rng.random(size=a[operand].shape) < 0.02
+            a[operand][0], a[operand][1, 1, -1, -1] = 0, 1e-14
+        else:
+            a[operand], other = _planted(a[operand], kind, rng)
+            a[1 - operand] = a[1 - operand] * other
+        print(prob, kind, operand, flush=True)
+        got = run(gu, a[0], a[1], dims[5:], pad, stride, workspace=8 << 20, kernel="three filter rows")
+        want = oc.conv_backward_filter(a[0], a[1], dims[5:], pad=pad, stride=stride, mode=1)
+        _same(got, want, (prob, kind, operand))
+        if kind in ("images", "drift", "wide range", "mostly zero"):
+            magnitude = oc.conv_backward_filter(np.abs(a[0]), np.abs(a[1]), dims[5:], pad=pad, stride=stride, mode=1)
+            _check(got, want, magnitude, a[1].size // dims[4], (prob, kind, operand))
 
 
 @pytest.mark.parametrize("prob", [
