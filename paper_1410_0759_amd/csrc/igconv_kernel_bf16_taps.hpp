@@ -10,8 +10,8 @@
 // What bounds it: what L2 delivers in pieces of 64 bytes, about 12 TB/s over the chip (128-byte pieces: 16 TB/s, but they need
 // another order of the sums); the MFMAs of a 128 x 128 tile's step take 256 cycles, its 16 KB three times that.  Hence
 // the 128 x 256 tile for problems that fill the chip with it, and moving and multiplying wavefronts apart with a ring of stages
-// in LDS - the one being read, the others complete or on their way: 64 KB per workgroup of the smaller tiles (two per compute
-// unit), 120 KB of the large one.  Persistent workgroups; the movers run on across the tile boundary, so that the next
+// in LDS - the one being read, the others complete or on their way: 80 KB per workgroup of the 128 x 128 tile and 72 of the
+// 64 x 128 one, two of which share a compute unit's 160, 144 KB of the large one.  Persistent workgroups; the movers run on across the tile boundary, so that the next
 // tile's first stages arrive while the finished tile is stored.
 // Measured against the form before (steps of two units, requested two steps ahead into registers and written to LDS from
 // there; branches around its loads made every step wait for those just issued), us with the filter's rewriting:
