@@ -232,12 +232,22 @@ int main() {
     };
     const igc::KernelInfo *ki = nullptr;
     for (it = 0; it < 12; ++it) {   // bfloat16 backward data: tiles of 128 x 256 on 8 compute units, smaller ones on 256 (test_backward_data_large_tiles)
-        const int large[3][9] = {{40, 130, 30, 31, 72, 5, 5, 2, 2}, {33, 256, 17, 16, 32, 3, 2, 1, 1}, {64, 128, 16, 16, 8, 2, 1, 0, 0}};
+        const int large[3][10] = {{40, 130, 30, 31, 72, 5, 5, 2, 2, 1}, {33, 256, 17, 16, 160, 3, 2, 1, 1, 1}, {16, 250, 32, 30, 520, 3, 3, 1, 1, 2}};
         const int *r = large[it / 4];
         REQUIRE(igcSetComputeUnits(h, it & 1 ? 256 : 8) == IGC_STATUS_SUCCESS);
-        REQUIRE(set_layer(IGC_DATA_BFLOAT16, (it & 2) != 0, r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], r[8], 1));
+        REQUIRE(set_layer(IGC_DATA_BFLOAT16, (it & 2) != 0, r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], r[8], r[9]));
         REQUIRE(data_kernel(true, 0, &ki) >= 0);
         REQUIRE(ki->variant == 6 && ki->BN == (it & 1 ? 128 : 256));
+    }
+    for (it = 0; it < 6; ++it) {    // ... and not where a tile has few steps, alone or in one launch with other phases
+        const int shorts[6][11] = {{41, 96, 56, 57, 256, 2, 2, 1, 1, 2, 128}, {68, 448, 32, 33, 64, 3, 3, 1, 1, 2, 128}, {66, 320, 28, 28, 208, 2, 2, 1, 1, 2, 128},
+                                   {84, 416, 28, 28, 32, 3, 4, 1, 2, 1, 128}, {34, 224, 44, 44, 384, 2, 2, 0, 0, 2, 128},
+                                   {128, 128, 28, 28, 256, 5, 5, 2, 2, 1, 256}};
+        const int *r = shorts[it];
+        REQUIRE(igcSetComputeUnits(h, 256) == IGC_STATUS_SUCCESS);
+        REQUIRE(set_layer(IGC_DATA_BFLOAT16, true, r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7], r[8], r[9]));
+        REQUIRE(data_kernel(true, 0, &ki) >= 0 && ki->variant == 6);
+        REQUIRE(ki->BN == r[10]);
     }
     for (it = 0; it < 24; ++it) {   // double precision, forward and backward data (test_halved_tiles_f64)
         const int tiles[6][6] = {{3, 2, 75, 75, 10, 1}, {3, 2, 78, 78, 65, 8}, {5, 2, 70, 70, 64, 16}, {5, 2, 71, 71, 64, 0}, {15, 1, 66, 67, 9, 2}, {1, 3, 16, 97, 33, 4}};

@@ -245,6 +245,15 @@ static size_t halves_bytes(const KernelInfo &ki, const ConvKernelParams &k) {
     return (size_t)((k.K + ki.BM - 1) / ki.BM) * (size_t)kernel_steps(ki, k) * ((size_t)(9 * ki.BM * 64) + 8);
 }
 
+// A tile of the kernels over channel vectors of both operands (variant 6), in the units of plan_cost / 500.  Its start and epilogue count as two steps of a 128 x 128 tile;
+// as four of a 64 x 128 one, whose steps are shorter, and as six of a 128 x 256 one, alone on its compute unit: nothing covers them.  Backward data, counted
+// as two everywhere -> so, us: 41x96x56x57 -> 256, 2x2 stride 2 (8 steps) 36 -> 27, 68x448x32x33 -> 64, 3x3 stride 2 (8, 4, 4 and 2) 46 -> 36, 84x416x28x28 ->
+// 32, 3x4 (12) 50 -> 41; 644 layers of 13 to 500 us 2 % less on average.
+static double taps_tile_cost(const KernelInfo &ki, double steps) {
+    const double ends = ki.BN == 256 ? 6.0 : (ki.BM == 64 ? 4.0 : 2.0);
+    return (steps + ends) * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0);
+}
+
 static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKernelParams &k) {
     const long long cus = h->computeUnits;
     const long long tm = (k.K + ki.BM - 1) / ki.BM;
@@ -286,7 +295,7 @@ static double plan_cost(const igcContext *h, const KernelInfo &ki, const ConvKer
     // images 237, 220 and 174 us.  The large one not below one and a half tiles per compute unit: nothing covers its start and its
     // epilogue then: 128x56x56 -> 256, 3x3 stride 2, 32 images, 196 tiles 40 us, 128 x 128 30; 192 -> 320x27x27, 5x5, 12 images 64 and 51.)
     if (ki.variant == 6 && ki.BN == 256 && tiles * 2 < cus * 3) return 1e300;
-    if (ki.variant == 6) return tile_times * (steps + 2.0) * 500.0 * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0);
+    if (ki.variant == 6) return tile_times * 500.0 * taps_tile_cost(ki, (double)steps);
     if (is_halves(ki)) {
         // Operands as two binary16 parts (igconv_kernel_f32h.hpp), counted like variant 5, and about 6 us for splitting the filter.
         // Measured per step in the units of the line below: 29 with nine taps, 39 where its patch is wide, 24 with more taps.
@@ -952,9 +961,8 @@ static int joint_kernel(const igcContext *h, const std::vector<PhaseLaunch> &lau
                 break;
             }
             const long long t = (long long)((k.K + ki.BM - 1) / ki.BM) * ((k.NPQ + ki.BN - 1) / ki.BN);
-            const double steps = (double)kernel_steps(ki, k) + 2.0;
-            const double c = ki.variant == 6 ? steps * (1.0 * ki.BM + 1.0 * ki.BN + ki.BM * ki.BN / 64.0)
-                                             : steps * (0.70 * ki.BM + 25.0);
+            const double steps = (double)kernel_steps(ki, k);
+            const double c = ki.variant == 6 ? taps_tile_cost(ki, steps) : (steps + 2.0) * (0.70 * ki.BM + 25.0);
             tiles += t;
             work += (double)t * c;
             longest = std::max(longest, c);

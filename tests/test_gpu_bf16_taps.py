@@ -137,8 +137,8 @@ def test_forward_nine_taps(prob, layout):
 @pytest.mark.parametrize("prob", [
     # the 128 x 256 tile (the handle is told of 8 compute units), several tiles per workgroup
     (40, 130, 30, 31, 72, 5, 5, (2, 2), (1, 1)),      # ragged rows and columns, a ragged last unit of channels
-    (33, 256, 17, 16, 32, 3, 2, (1, 1), (1, 1)),      # one unit per tap: six steps per tile, fewer than the stages of the ring
-    (64, 128, 16, 16, 8, 2, 1, (0, 0), (1, 1)),       # two steps per tile
+    (33, 256, 17, 16, 160, 3, 2, (1, 1), (1, 1)),     # thirty steps per tile
+    (16, 250, 32, 30, 520, 3, 3, (1, 1), (2, 2)),      # four stride phases, the last of one tap, in one launch
 ])
 def test_backward_data_large_tiles(prob, layout):
     """(csrc/host_check.cpp requires that these layers take the large tile with 8 compute units, a smaller one with 256.)"""
