@@ -298,10 +298,12 @@ struct BiasGradPlan {
 // compute units idle 18.5 -> 20.9 (128x64x56x56), 6.8 -> 10.6 (64x32x56x56), 11.4 -> 12.0 (double, 32x64x56x56).  A workgroup reads 65 to 85 KB per
 // us, the chip up to 7 MB from the last-level cache; the second launch costs 4.5 us.  Of tensors beyond that cache a workgroup reads 42 KB, the chip
 // 6 MB: 512x128x56x56 136 -> 152, 64x128x128x128 89 -> 97, 2048x257x13x13 70 -> 86; but 2048x256x13x13 68 -> 65, 128x192x56x56 48.5 -> 45.
+// Of more maps than compute units some share one, each read more slowly: 0.4 on top (double, 100x289x69x71 191 -> 241, 443x312x20x21 80 -> 93;
+// 77x269x52x52 35 -> 40; one piece stays better for 128x384x13x13, 10.1 -> 9.3, and 64x512x28x28, 19.4 -> 17.3).
 bool in_one_piece(const igcContext *h, const BiasGradArgs &a, long long elem) {
     const long long map = (long long)a.positions * elem, rounds = (a.C + h->computeUnits - 1) / h->computeUnits;
     const bool beyond = map * a.C > 256ll << 20;
-    return (double)(map * rounds) / (beyond ? 42e3 : 60e3) <= 4.5 + (double)map * a.C / (beyond ? 6e6 : 7e6);
+    return (double)(map * rounds) * (rounds > 1 ? 1.4 : 1.0) / (beyond ? 42e3 : 60e3) <= 4.5 + (double)map * a.C / (beyond ? 6e6 : 7e6);
 }
 
 igcStatus plan_bias_grad(const igcContext *h, igcTensorDescriptor_t dyDesc, igcTensorDescriptor_t dbDesc, BiasGradPlan *pl) {

@@ -281,9 +281,10 @@ def _bias_gradients(dtype, shape, start):
     N, C, H, W = shape
     flat = torch.randn(N * C * H * W + start, device="cuda").to(dtype)
     dy = flat[start:].view(shape)
-    db, h = torch.empty(C, device="cuda"), ig.Handle()
+    double = dtype == torch.float64
+    db, h = torch.empty(C, device="cuda", dtype=torch.float64 if double else torch.float32), ig.Handle()
     h.set_stream(torch.cuda.current_stream().cuda_stream)
-    dyd, dbd = ig.tensor_descriptor_for(dy), ig.TensorDescriptor().set(ig.IGC_DATA_FLOAT, 1, C, 1, 1, (C, 1, 1, 1))
+    dyd, dbd = ig.tensor_descriptor_for(dy), ig.TensorDescriptor().set(ig.IGC_DATA_DOUBLE if double else ig.IGC_DATA_FLOAT, 1, C, 1, 1, (C, 1, 1, 1))
     n = ig.get_backward_bias_workspace_size(h, dyd, dbd)
     ws = torch.empty(n // 4 + 4, device="cuda")
     us = _microseconds(lambda: ig.check(ig.convolution_backward_bias(h, 1.0, dyd, dy.data_ptr(), 0.0, dbd, db.data_ptr(), ws.data_ptr(), n)))
@@ -311,13 +312,15 @@ def test_backward_bias_of_many_short_runs(shape):
     assert ragged <= 2.0 * whole
 
 
-def test_backward_bias_of_a_map_more_than_units():
-    """A tensor beyond the last-level cache whose maps are one more than the compute units.  (One piece per map: 1.3 times as long as with one map
-    less; now 1.01, in ranges.)"""
+@pytest.mark.parametrize("dtype, shape, maps", [("float32", (2048, 13, 13), 257), ("float64", (100, 69, 71), 289)])
+def test_backward_bias_of_more_maps_than_units(dtype, shape, maps):
+    """A tensor beyond the last-level cache with a few more maps than compute units.  (One piece per map: each 1.3 times as long as of as many maps as
+    units; now, in ranges, 1.01.)"""
     import torch
-    one_more, even = (_bias_gradients(torch.float32, (2048, C, 13, 13), 0) for C in (257, 256))
-    print(one_more, even, flush=True)
-    assert one_more <= 1.18 * even
+    N, H, W = shape
+    more, even = (_bias_gradients(getattr(torch, dtype), (N, C, H, W), 0) / C for C in (maps, 256))
+    print(dtype, more, even, flush=True)
+    assert more <= 1.18 * even
 
 
 @pytest.mark.parametrize("mode", [0, 1], ids=["max", "average"])
