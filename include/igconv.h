@@ -290,8 +290,8 @@ igcStatus igcConvolutionBackwardData(igcHandle_t handle, const void *alpha,
  *    reports the size that lets the reduction be cut as finely as the library would like.
  *    Any smaller size is accepted, NULL / 0 included: the reduction is then cut into as
  *    many ranges as fit (a part is K*C*R*S results; for bfloat16 x and dy with unit channel
- *    strides, and at unit strides for float filters of three rows and columns and more, K and C may be rounded up to
- *    the kernel's tiles; with bfloat16 the workspace is used even for
+ *    strides K and C may be rounded up to the kernel's tiles, and at unit strides for float filters of three rows and columns
+ *    and more K to 64, C to 32 and R and S to multiples of three: 5x5 counts 36 taps; with bfloat16 the workspace is used even for
  *    a single range, because that kernel keeps its results in another order than dw's),
  *    down to a single range that writes dw directly - same result up to summation order,
  *    less parallelism.

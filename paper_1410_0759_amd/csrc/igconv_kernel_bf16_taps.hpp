@@ -7,9 +7,9 @@
 // place, with the same 16-index groups per MFMA: the same bits with and without the rewritten filter.  A step is one unit,
 // 32 channels of one tap: 64 bytes of every row of the tile.
 //
-// What bounds it: what L2 delivers in pieces of 64 bytes, about 12 TB/s over the chip (128-byte pieces: 16 TB/s, but they need
-// another order of the sums); the MFMAs of a 128 x 128 tile's step take 256 cycles, its 16 KB three times that.  Hence
-// the 128 x 256 tile for problems that fill the chip with it, and moving and multiplying wavefronts apart with a ring of stages
+// What bounds it: pieces of 64 bytes from L2 (128-byte ones need another order of the sums) - 10 TB/s over the chip with the 128 x 256 tile at 256 -> 128x28x28,
+// 5x5, 96 % of them hits, MFMAs busy for 60 % of the cycles; a 128 x 128 tile's step of 256 cycles of MFMAs asks for 16 KB, half as much again per product.  Hence
+// the 128 x 256 tile for problems that fill the chip with it and have enough steps, and moving and multiplying wavefronts apart with a ring of stages
 // in LDS - the one being read, the others complete or on their way: 80 KB per workgroup of the 128 x 128 tile and 72 of the
 // 64 x 128 one, two of which share a compute unit's 160, 144 KB of the large one.  Persistent workgroups; the movers run on across the tile boundary, so that the next
 // tile's first stages arrive while the finished tile is stored.

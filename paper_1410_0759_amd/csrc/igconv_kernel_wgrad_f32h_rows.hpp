@@ -17,8 +17,8 @@
 // Measured, us, that kernel -> this, 128 images: 64x56x56 -> 64, 3x3 152 -> 123 (error against 64 bits 3.4e-7 -> 3.1e-7 in a training step), channels
 // innermost 137 -> 122; 384x13x13 -> 256, 3x3 198 -> 140 (4.1e-7 -> 3.8e-7); 96x27x27 -> 256, 5x5 550 -> 494; 96x64x64 -> 128, 9x9 3050 -> 2300 (350
 // TFLOP/s; 1.7e-6 -> 1.1e-6).
-// What bounds it: the moving wavefronts' instructions still, about 880 per chunk, beside the MFMAs (4608 cycles of about 7900 per chunk): without the
-// multiplying wavefronts' work 77 % of the time, without the loads 85 %.  With the decoding in the movers, five of them, 1400 instructions and
+// What bounds it: the moving wavefronts' instructions still, about 880 per chunk, beside the MFMAs (4608 of about 6150 cycles per chunk at 9x9), and the
+// clock that is left, 1.6 GHz (2340 us, of zeros 1850): without the multiplying wavefronts' work 70 to 75 % of the time, without the loads 74 (9x9) to 88 %.  With the decoding in the movers, five of them, 1400 instructions and
 // 2650 us (9x9); parts stored in dw's order 30 us more at 64x56x56.
 #ifndef IGCONV_KERNEL_WGRAD_F32H_ROWS_HPP_
 #define IGCONV_KERNEL_WGRAD_F32H_ROWS_HPP_
