@@ -301,6 +301,90 @@ __device__ __attribute__((noinline)) void wgrad_halves_mend(uint64_t arguments, 
 #pragma unroll
     for (int g = 0; g < 6; ++g) blocks[g] = acc[g / 2][g % 2];
 }
+
+// What a moving wavefront of the filter kernels knows of its operands: the exponents of dy (a) and of the patch (b) that the chunk being written is split
+// by, and what a sum may be off by for what they lost.
+struct WgradScales {
+    int ea = 0, eb = 0, e_low = 0, e_high = 0;
+    bool set_a = false, set_b = false, begun = false;
+    float off_by = 0.f;      // 2^22 times what a sum of the chain may be off by for this wavefront's operands that lost something
+    uint32_t far = 0;        // kFarBelow: one of them far below the others
+    HalvesScale sa = {}, sb = {};
+
+    // the largest magnitude of all moving wavefronts
+    static __device__ __forceinline__ uint32_t largest_of(const uint8_t *slots) {
+        const u32x4 s = *reinterpret_cast<const u32x4 *>(slots);
+        const uint32_t s0 = s[0] > s[1] ? s[0] : s[1], s1 = s[2] > s[3] ? s[2] : s[3];
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 > s1 ? s0 : s1));
+    }
+    // an exponent out of bounds?  (zeros say nothing)
+    static __device__ __forceinline__ bool fits(uint32_t largest, int e, bool set) { return largest == 0 || (set && (uint32_t)((int)(largest >> 23) - 140 + e) <= 1u); }
+    static __device__ __forceinline__ void choose(uint32_t largest, int &e, bool &set) {
+        const int w = 140 - (int)(largest >> 23);
+        e = w < -60 ? -60 : (w > 60 ? 60 : w);
+        set = true;
+    }
+    static __device__ __forceinline__ HalvesScale scale_of(int e) {
+        HalvesScale r;
+        r.e = e;
+        r.s = __builtin_bit_cast(float, (uint32_t)(127 + e) << 23);
+        r.t = __builtin_bit_cast(float, (uint32_t)(138 + e) << 23);
+        r.below = (uint32_t)(114 - e) << 23;
+        return r;
+    }
+    // The next chunk, of a new chain of sums if `first`.  slots: the wavefronts' largest magnitudes of dy, then of the patch; small_a, small_b: this lane's
+    // smallest ones.  A lost operand may have touched as many of a result's products as the lane's pixels are: A_LANE of dy, B_LANE of the patch, for all
+    // lanes not more than A_MOST and 64; each by 2^-36 of the other operand's largest.
+    template <int A_LANE, int A_MOST, int B_LANE>
+    __device__ __forceinline__ void next(const uint8_t *slots, bool first, uint32_t small_a, uint32_t small_b) {
+        const uint32_t la = largest_of(slots), lb = largest_of(slots + 16);
+        if (first || !fits(la, ea, set_a) || !fits(lb, eb, set_b)) {
+            if (first) {
+                set_a = set_b = begun = false;
+                off_by = 0.f;
+                far = 0;
+            }
+            if (!fits(la, ea, set_a)) choose(la, ea, set_a);
+            if (!fits(lb, eb, set_b)) choose(lb, eb, set_b);
+            if (set_a && set_b) {   // (before that all products are zero)
+                // A chunk far below the range's largest gets no finer unit than 2^-40 of that one's: sums multiplied up by more could leave the float range.
+                // Those multiplied down by more than 2^-70 could lose something.
+                const int over = begun && ea + eb > e_low + 40 ? ea + eb - (e_low + 40) : 0, of_a = over < ea + 100 ? over : ea + 100;
+                ea -= of_a;
+                eb -= over - of_a;
+                const int e = ea + eb;
+                if (begun && e_high - e > 70) off_by += __builtin_ldexpf(2.f, -e);
+                e_low = !begun || e < e_low ? e : e_low;
+                e_high = !begun || e > e_high ? e : e_high;
+                begun = true;
+            }
+            sa = scale_of(ea);
+            sb = scale_of(eb);
+        }
+        const uint64_t under_a = lanes_under(small_a, sa.below), under_b = lanes_under(small_b, sb.below);
+        if ((under_a | under_b) != 0u) {
+            const int na = A_LANE * __popcll(under_a), nb = B_LANE * __popcll(under_b);
+            // (none times infinity would be NaN)
+            if (na != 0) off_by += (float)(na < A_MOST ? na : A_MOST) * __builtin_ldexpf(__builtin_bit_cast(float, lb), -ea - 14);   // (times 2^22)
+            if ((lanes_under(small_a, far_below(sa.below)) | lanes_under(small_b, far_below(sb.below))) != 0u) far = kFarBelow;
+            if (nb != 0) off_by += (float)(nb < 64 ? nb : 64) * __builtin_ldexpf(__builtin_bit_cast(float, la), -eb - 14);
+        }
+    }
+};
+// What a sum of a chain may be off by, of all moving wavefronts; zeros_too: sums of zero are in question as well.
+__device__ __forceinline__ float wgrad_off_by(const uint8_t *slots, bool *zeros_too) {
+    const u32x4 s = *reinterpret_cast<const u32x4 *>(slots);
+    float off_by = 0.f;
+    uint32_t far = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t slot = s[i];
+        off_by += __builtin_bit_cast(float, slot & ~kFarBelow);
+        far |= slot & kFarBelow;
+    }
+    *zeros_too = __builtin_amdgcn_readfirstlane((int)far) != 0;
+    return off_by;
+}
 #endif
 
 // p.Wp: pixels of a row of the patch (output columns and two), p.HpWp: output rows; p.PQ: blocks of 32 channels;
@@ -532,76 +616,20 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             seen_b = HalvesSeen{};
         };
         int it = 0, c = 0;                       // range and chunk being written
-        int ea = 0, eb = 0, e_low = 0, e_high = 0;
-        bool set_a = false, set_b = false, begun = false;
-        float off_by = 0.f;      // 2^22 times what a sum of the range may be off by for this wavefront's operands that lost something
-        uint32_t far = 0;        // kFarBelow: one of them far below the others
-        HalvesScale sa = {}, sb = {};
-        // an exponent out of bounds?  (zeros say nothing)
-        auto largest_of = [&](const uint8_t *slots) __attribute__((always_inline)) {
-            const u32x4 s = *reinterpret_cast<const u32x4 *>(slots);
-            const uint32_t s0 = s[0] > s[1] ? s[0] : s[1], s1 = s[2] > s[3] ? s[2] : s[3];
-            return (uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 > s1 ? s0 : s1));
-        };
-        auto fits = [](uint32_t largest, int e, bool set) { return largest == 0 || (set && (uint32_t)((int)(largest >> 23) - 140 + e) <= 1u); };
-        auto choose = [](uint32_t largest, int &e, bool &set) {
-            const int w = 140 - (int)(largest >> 23);
-            e = w < -60 ? -60 : (w > 60 ? 60 : w);
-            set = true;
-        };
-        auto scale_of = [&](int e) {
-            HalvesScale r;
-            r.e = e;
-            r.s = __builtin_bit_cast(float, (uint32_t)(127 + e) << 23);
-            r.t = __builtin_bit_cast(float, (uint32_t)(138 + e) << 23);
-            r.below = (uint32_t)(114 - e) << 23;
-            return r;
-        };
+        WgradScales scale;
         auto scales = [&](int parity) __attribute__((always_inline)) {
-            const uint32_t la = largest_of(lds + Cfg::SLOT_MAX + parity * 32), lb = largest_of(lds + Cfg::SLOT_MAX + parity * 32 + 16);
-            const bool first = c == 0;
-            if (first || !fits(la, ea, set_a) || !fits(lb, eb, set_b)) {
-                if (first) {
-                    set_a = set_b = begun = false;
-                    off_by = 0.f;
-                    far = 0;
-                }
-                if (!fits(la, ea, set_a)) choose(la, ea, set_a);
-                if (!fits(lb, eb, set_b)) choose(lb, eb, set_b);
-                if (set_a && set_b) {   // (before that all products are zero)
-                    // A chunk far below the range's largest gets no finer unit than 2^-40 of that one's: sums multiplied up by more could leave the float range.
-                    // Those multiplied down by more than 2^-70 could lose something.
-                    const int over = begun && ea + eb > e_low + 40 ? ea + eb - (e_low + 40) : 0, of_a = over < ea + 100 ? over : ea + 100;
-                    ea -= of_a;
-                    eb -= over - of_a;
-                    const int e = ea + eb;
-                    if (begun && e_high - e > 70) off_by += __builtin_ldexpf(2.f, -e);
-                    e_low = !begun || e < e_low ? e : e_low;
-                    e_high = !begun || e > e_high ? e : e_high;
-                    begun = true;
-                }
-                sa = scale_of(ea);
-                sb = scale_of(eb);
-            }
-            // Of the 64 pixels that a result's sum takes from the chunk (half of it) this wavefront has 16 of dy, one per lane and map, and up to 64 of the
-            // patch, five per lane and channel at most: as many products may a lost operand have touched, each by 2^-36 of the other operand's largest.
-            const uint64_t under_a = lanes_under(small_a, sa.below), under_b = lanes_under(small_b, sb.below);
-            if ((under_a | under_b) != 0u) {
-                const int na = __popcll(under_a), nb = Cfg::B_ITEMS * __popcll(under_b);
-                // (none times infinity would be NaN)
-                if (na != 0) off_by += (float)(na < 16 ? na : 16) * __builtin_ldexpf(__builtin_bit_cast(float, lb), -ea - 14);   // (times 2^22)
-                if ((lanes_under(small_a, far_below(sa.below)) | lanes_under(small_b, far_below(sb.below))) != 0u) far = kFarBelow;
-                if (nb != 0) off_by += (float)(nb < 64 ? nb : 64) * __builtin_ldexpf(__builtin_bit_cast(float, la), -eb - 14);
-            }
-            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = ea + eb;
+            // (of the 64 pixels that a result's sum takes from the chunk - half of it - this wavefront has 16 of dy, one per lane and map, and up to 64 of the
+            // patch, five per lane and channel at most)
+            scale.next<1, 16, Cfg::B_ITEMS>(lds + Cfg::SLOT_MAX + parity * 32, c == 0, small_a, small_b);
+            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = scale.ea + scale.eb;
             if (c == per - 1 && lane == 0)
-                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = __builtin_bit_cast(uint32_t, off_by) | far;
+                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = __builtin_bit_cast(uint32_t, scale.off_by) | scale.far;
         };
         u32x4 part_h, part_m;
         auto convert = [&](auto set_c, auto ic, int q) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value, i = decltype(ic)::value;
             uint32_t h, m;
-            halves_pair(reg[set][i][2 * q], reg[set][i][2 * q + 1], i < Cfg::A_ITEMS ? sa : sb, h, m);
+            halves_pair(reg[set][i][2 * q], reg[set][i][2 * q + 1], i < Cfg::A_ITEMS ? scale.sa : scale.sb, h, m);
             part_h[q] = h; part_m[q] = m;
         };
         auto write_item = [&](auto ic, int parity) __attribute__((always_inline)) {
@@ -817,16 +845,8 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_kernel(const ConvKer
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[t][mb][v] = __builtin_ldexpf(__builtin_fmaf(low[t][mb][v], 0x1p-11f, acc[t][mb][v]), -e_sum);
-        const u32x4 slots = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
-        float off_by = 0.f;
-        uint32_t far = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t slot = slots[i];
-            off_by += __builtin_bit_cast(float, slot & ~kFarBelow);
-            far |= slot & kFarBelow;
-        }
-        const bool zeros_too = __builtin_amdgcn_readfirstlane((int)far) != 0;
+        bool zeros_too;
+        const float off_by = wgrad_off_by(lds + Cfg::SLOT_N + (it & 1) * 16, &zeros_too);
         if (__builtin_expect(__any(outside_halves_range<3, 2>(acc, off_by, zeros_too)), 0)) {
             const long long jb = (long long)tile.split * per * BK, je = jb + (long long)per * BK;
             WgradMend m;

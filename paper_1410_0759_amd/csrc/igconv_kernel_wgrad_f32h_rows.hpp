@@ -300,77 +300,21 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_rows_kernel(const Co
             seen_b = HalvesSeen{};
         };
         int it = 0, c = 0;                       // piece and chunk of it being written
-        int ea = 0, eb = 0, e_low = 0, e_high = 0;
-        bool set_a = false, set_b = false, begun = false;
-        float off_by = 0.f;      // 2^22 times what a sum of the piece may be off by for this wavefront's operands that lost something
-        uint32_t far = 0;        // kFarBelow: one of them far below the others
-        HalvesScale sa = {}, sb = {};
+        WgradScales scale;
         int steps_now = steps_of(0);             // chunks of the piece being written
-        // an exponent out of bounds?  (zeros say nothing)
-        auto largest_of = [&](const uint8_t *slots) __attribute__((always_inline)) {
-            const u32x4 s = *reinterpret_cast<const u32x4 *>(slots);
-            const uint32_t s0 = s[0] > s[1] ? s[0] : s[1], s1 = s[2] > s[3] ? s[2] : s[3];
-            return (uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 > s1 ? s0 : s1));
-        };
-        auto fits = [](uint32_t largest, int e, bool set) { return largest == 0 || (set && (uint32_t)((int)(largest >> 23) - 140 + e) <= 1u); };
-        auto choose = [](uint32_t largest, int &e, bool &set) {
-            const int w = 140 - (int)(largest >> 23);
-            e = w < -60 ? -60 : (w > 60 ? 60 : w);
-            set = true;
-        };
-        auto scale_of = [&](int e) {
-            HalvesScale r;
-            r.e = e;
-            r.s = __builtin_bit_cast(float, (uint32_t)(127 + e) << 23);
-            r.t = __builtin_bit_cast(float, (uint32_t)(138 + e) << 23);
-            r.below = (uint32_t)(114 - e) << 23;
-            return r;
-        };
         auto scales = [&](int parity) __attribute__((always_inline)) {
-            const uint32_t la = largest_of(lds + Cfg::SLOT_MAX + parity * 32), lb = largest_of(lds + Cfg::SLOT_MAX + parity * 32 + 16);
-            const bool first = c == 0;
-            if (first || !fits(la, ea, set_a) || !fits(lb, eb, set_b)) {
-                if (first) {
-                    set_a = set_b = begun = false;
-                    off_by = 0.f;
-                    far = 0;
-                }
-                if (!fits(la, ea, set_a)) choose(la, ea, set_a);
-                if (!fits(lb, eb, set_b)) choose(lb, eb, set_b);
-                if (set_a && set_b) {   // (before that all products are zero)
-                    // A chunk far below the range's largest gets no finer unit than 2^-40 of that one's: sums multiplied up by more could leave the float range.
-                    // Those multiplied down by more than 2^-70 could lose something.
-                    const int over = begun && ea + eb > e_low + 40 ? ea + eb - (e_low + 40) : 0, of_a = over < ea + 100 ? over : ea + 100;
-                    ea -= of_a;
-                    eb -= over - of_a;
-                    const int e = ea + eb;
-                    if (begun && e_high - e > 70) off_by += __builtin_ldexpf(2.f, -e);
-                    e_low = !begun || e < e_low ? e : e_low;
-                    e_high = !begun || e > e_high ? e : e_high;
-                    begun = true;
-                }
-                sa = scale_of(ea);
-                sb = scale_of(eb);
-            }
-            // Of the 128 pixels that a result's sum takes from the chunk this wavefront has at most 32 of dy, two per lane and map, and 64 of the
-            // patch, four per lane and channel: as many products may a lost operand have touched, each by 2^-36 of the other operand's largest.
-            const uint64_t under_a = lanes_under(small_a, sa.below), under_b = lanes_under(small_b, sb.below);
-            if ((under_a | under_b) != 0u) {
-                const int na = 2 * __popcll(under_a), nb = Cfg::B_ITEMS * __popcll(under_b);
-                // (none times infinity would be NaN)
-                if (na != 0) off_by += (float)(na < 32 ? na : 32) * __builtin_ldexpf(__builtin_bit_cast(float, lb), -ea - 14);   // (times 2^22)
-                if ((lanes_under(small_a, far_below(sa.below)) | lanes_under(small_b, far_below(sb.below))) != 0u) far = kFarBelow;
-                if (nb != 0) off_by += (float)(nb < 64 ? nb : 64) * __builtin_ldexpf(__builtin_bit_cast(float, la), -eb - 14);
-            }
-            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = ea + eb;
+            // (of the 128 pixels that a result's sum takes from the chunk this wavefront has at most 32 of dy, two per lane and map, and 64 of the
+            // patch, four per lane and channel)
+            scale.next<2, 32, Cfg::B_ITEMS>(lds + Cfg::SLOT_MAX + parity * 32, c == 0, small_a, small_b);
+            if (mw == 0 && lane == 0) *reinterpret_cast<int *>(lds + Cfg::SLOT_E + parity * 4) = scale.ea + scale.eb;
             if (c == steps_now - 1 && lane == 0)
-                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = __builtin_bit_cast(uint32_t, off_by) | far;
+                *reinterpret_cast<uint32_t *>(lds + Cfg::SLOT_N + (it & 1) * 16 + mw * 4) = __builtin_bit_cast(uint32_t, scale.off_by) | scale.far;
         };
         u32x4 part_h, part_m;
         auto convert = [&](auto set_c, auto ic, int q) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value, i = decltype(ic)::value;
             uint32_t h, m;
-            halves_pair(reg[set][i][2 * q], reg[set][i][2 * q + 1], i < Cfg::A_ITEMS ? sa : sb, h, m);
+            halves_pair(reg[set][i][2 * q], reg[set][i][2 * q + 1], i < Cfg::A_ITEMS ? scale.sa : scale.sb, h, m);
             part_h[q] = h; part_m[q] = m;
         };
         auto write_item = [&](auto ic, int parity) __attribute__((always_inline)) {
@@ -573,16 +517,8 @@ __global__ __launch_bounds__(512, 2) void igconv_wgrad_f32h_rows_kernel(const Co
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[t][mb][v] = __builtin_ldexpf(__builtin_fmaf(low[t][mb][v], 0x1p-11f, acc[t][mb][v]), -e_sum);
-        const u32x4 slots = *reinterpret_cast<const u32x4 *>(lds + Cfg::SLOT_N + (it & 1) * 16);
-        float off_by = 0.f;
-        uint32_t far = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t slot = slots[i];
-            off_by += __builtin_bit_cast(float, slot & ~kFarBelow);
-            far |= slot & kFarBelow;
-        }
-        const bool zeros_too = __builtin_amdgcn_readfirstlane((int)far) != 0;
+        bool zeros_too;
+        const float off_by = wgrad_off_by(lds + Cfg::SLOT_N + (it & 1) * 16, &zeros_too);
         if (__builtin_expect(__any(outside_halves_range<3, 2>(acc, off_by, zeros_too)), 0)) {
             auto first_pixel = [&](int chunk) {
                 const long long j = p.imageTiles ? (long long)(chunk / p.imageTiles) * p.RS + chunk % p.imageTiles * BK : (long long)chunk * BK;
